@@ -99,6 +99,24 @@ class Problem:
     def batch(self) -> int:
         return len(self.seqlen)
 
+    # The C struct of a Problem is kept between calls: building it costs 5 us (8 us for a batch of 8), as much as a
+    # decoding step's two launches.  Assigning a field drops it, and the sequences, which can change in place, are
+    # compared by value (0.5 us).
+    def __setattr__(self, name, value):
+        self.__dict__["_packed"] = None
+        object.__setattr__(self, name, value)
+
+    def __getstate__(self):
+        return {k: v for k, v in self.__dict__.items() if k != "_packed"}
+
+    def _c(self):
+        now = (tuple(self.seqlen), tuple(self.n_keep), tuple(self.kv_base), tuple(self.out_base))
+        kept = self.__dict__.get("_packed")
+        if kept is None or kept[0] != now:
+            cp = self.as_c()
+            kept = self.__dict__["_packed"] = (now, cp, C.byref(cp))
+        return kept[2]
+
     def as_c(self):
         B = self.batch
         keep = {
@@ -176,13 +194,18 @@ def load_library(path: Optional[str] = None):
 
 
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+def _bytes(t: Optional[torch.Tensor]) -> int:
+    return 0 if t is None else t.nbytes
 
 
 def _stream(stream):
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return C.c_void_p(stream.cuda_stream)
+        # the handle itself: building a torch.cuda.Stream object around it takes 2.7 us
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream
 
 
 def _check(rc: int, where: str):
@@ -195,28 +218,28 @@ def chunkkv_status_string(status: int) -> str:
 
 
 def chunkkv_workspace_bytes(prob: Problem, n_layers: int = 1, reuse: int = 1) -> int:
-    return int(load_library().chunkkv_workspace_bytes(C.byref(prob.as_c()), n_layers, reuse))
+    return int(load_library().chunkkv_workspace_bytes(prob._c(), n_layers, reuse))
 
 
 def chunkkv_score(prob: Problem, q_obs, k, chunk_scores, token_importance, workspace, stream=None) -> None:
-    cp = prob.as_c()
-    _check(load_library().chunkkv_score(C.byref(cp), _ptr(q_obs), _ptr(k), _ptr(chunk_scores),
+    cp = prob._c()
+    _check(load_library().chunkkv_score(cp, _ptr(q_obs), _ptr(k), _ptr(chunk_scores),
                                         _ptr(token_importance), _ptr(workspace),
-                                        0 if workspace is None else workspace.numel() * workspace.element_size(),
+                                        _bytes(workspace),
                                         _stream(stream)), "chunkkv_score")
 
 
 def chunkkv_chunk_topk(prob: Problem, chunk_scores, sel_chunk, sel_len, sel_count, workspace=None, stream=None) -> None:
-    cp = prob.as_c()
-    _check(load_library().chunkkv_chunk_topk(C.byref(cp), _ptr(chunk_scores), _ptr(sel_chunk), _ptr(sel_len),
+    cp = prob._c()
+    _check(load_library().chunkkv_chunk_topk(cp, _ptr(chunk_scores), _ptr(sel_chunk), _ptr(sel_len),
                                              _ptr(sel_count), _ptr(workspace),
-                                             0 if workspace is None else workspace.numel() * workspace.element_size(),
+                                             _bytes(workspace),
                                              _stream(stream)), "chunkkv_chunk_topk")
 
 
 def chunkkv_compact(prob: Problem, k, v, sel_chunk, sel_len, sel_count, k_out, v_out, stream=None) -> None:
-    cp = prob.as_c()
-    _check(load_library().chunkkv_compact(C.byref(cp), _ptr(k), _ptr(v), _ptr(sel_chunk), _ptr(sel_len),
+    cp = prob._c()
+    _check(load_library().chunkkv_compact(cp, _ptr(k), _ptr(v), _ptr(sel_chunk), _ptr(sel_len),
                                           _ptr(sel_count), _ptr(k_out), _ptr(v_out), _stream(stream)),
            "chunkkv_compact")
 
@@ -224,23 +247,23 @@ def chunkkv_compact(prob: Problem, k, v, sel_chunk, sel_len, sel_count, k_out, v
 def chunkkv_compress_stack(prob: Problem, reuse: int, q_obs: Sequence, k: Sequence, v: Sequence, k_out: Sequence,
                            v_out: Sequence, sel_chunk, sel_len, sel_count, workspace, stream=None) -> None:
     n = len(k)
-    cp = prob.as_c()
+    cp = prob._c()
 
     def table(ts):
         return (C.c_void_p * n)(*[None if t is None else t.data_ptr() for t in ts])
 
     _check(load_library().chunkkv_compress_stack(
-        C.byref(cp), n, reuse, table(q_obs), table(k), table(v), table(k_out), table(v_out), _ptr(sel_chunk),
+        cp, n, reuse, table(q_obs), table(k), table(v), table(k_out), table(v_out), _ptr(sel_chunk),
         _ptr(sel_len), _ptr(sel_count), _ptr(workspace),
-        0 if workspace is None else workspace.numel() * workspace.element_size(), _stream(stream)),
+        _bytes(workspace), _stream(stream)),
         "chunkkv_compress_stack")
 
 
 def chunkkv_score_lse(prob: Problem, q_obs, k, lse, chunk_scores, token_importance, workspace, stream=None) -> None:
-    cp = prob.as_c()
-    _check(load_library().chunkkv_score_lse(C.byref(cp), _ptr(q_obs), _ptr(k), _ptr(lse), _ptr(chunk_scores),
+    cp = prob._c()
+    _check(load_library().chunkkv_score_lse(cp, _ptr(q_obs), _ptr(k), _ptr(lse), _ptr(chunk_scores),
                                             _ptr(token_importance), _ptr(workspace),
-                                            0 if workspace is None else workspace.numel() * workspace.element_size(),
+                                            _bytes(workspace),
                                             _stream(stream)), "chunkkv_score_lse")
 
 
@@ -248,25 +271,25 @@ def chunkkv_compress_stack_lse(prob: Problem, reuse: int, q_obs: Sequence, k: Se
                                k_out: Sequence, v_out: Sequence, sel_chunk, sel_len, sel_count, workspace,
                                stream=None) -> None:
     n = len(k)
-    cp = prob.as_c()
+    cp = prob._c()
 
     def table(ts):
         return (C.c_void_p * n)(*[None if t is None else t.data_ptr() for t in ts])
 
     _check(load_library().chunkkv_compress_stack_lse(
-        C.byref(cp), n, reuse, table(q_obs), table(k), table(v), table(lse), table(k_out), table(v_out),
+        cp, n, reuse, table(q_obs), table(k), table(v), table(lse), table(k_out), table(v_out),
         _ptr(sel_chunk), _ptr(sel_len), _ptr(sel_count), _ptr(workspace),
-        0 if workspace is None else workspace.numel() * workspace.element_size(), _stream(stream)),
+        _bytes(workspace), _stream(stream)),
         "chunkkv_compress_stack_lse")
 
 
 def chunkkv_compress_layer(prob: Problem, layer: int, reuse: int, q_obs, lse, k, v, k_out, v_out, sel_chunk, sel_len,
                            sel_count, workspace, stream=None) -> None:
-    cp = prob.as_c()
+    cp = prob._c()
     _check(load_library().chunkkv_compress_layer(
-        C.byref(cp), layer, reuse, _ptr(q_obs), _ptr(lse), _ptr(k), _ptr(v), _ptr(k_out), _ptr(v_out),
+        cp, layer, reuse, _ptr(q_obs), _ptr(lse), _ptr(k), _ptr(v), _ptr(k_out), _ptr(v_out),
         _ptr(sel_chunk), _ptr(sel_len), _ptr(sel_count), _ptr(workspace),
-        0 if workspace is None else workspace.numel() * workspace.element_size(), _stream(stream)),
+        _bytes(workspace), _stream(stream)),
         "chunkkv_compress_layer")
 
 
@@ -275,7 +298,7 @@ def _chunk_table(chunk_per_group):
 
 
 def chunkkv_workspace_bytes_hybrid(prob: Problem, n_layers: int, reuse: int, chunk_per_group) -> int:
-    return int(load_library().chunkkv_workspace_bytes_hybrid(C.byref(prob.as_c()), n_layers, reuse,
+    return int(load_library().chunkkv_workspace_bytes_hybrid(prob._c(), n_layers, reuse,
                                                              _chunk_table(chunk_per_group)))
 
 
@@ -283,52 +306,52 @@ def chunkkv_compress_stack_hybrid(prob: Problem, reuse: int, chunk_per_group, q_
                                   v: Sequence, lse, k_out: Sequence, v_out: Sequence, sel_chunk, sel_len, sel_count,
                                   workspace, stream=None) -> None:
     n = len(k)
-    cp = prob.as_c()
+    cp = prob._c()
 
     def table(ts):
         return None if ts is None else (C.c_void_p * n)(*[None if t is None else t.data_ptr() for t in ts])
 
     _check(load_library().chunkkv_compress_stack_hybrid(
-        C.byref(cp), n, reuse, _chunk_table(chunk_per_group), table(q_obs), table(k), table(v), table(lse),
+        cp, n, reuse, _chunk_table(chunk_per_group), table(q_obs), table(k), table(v), table(lse),
         table(k_out), table(v_out), _ptr(sel_chunk), _ptr(sel_len), _ptr(sel_count), _ptr(workspace),
-        0 if workspace is None else workspace.numel() * workspace.element_size(), _stream(stream)),
+        _bytes(workspace), _stream(stream)),
         "chunkkv_compress_stack_hybrid")
 
 
 def chunkkv_jaccard(prob: Problem, n_groups: int, sel_chunk, sel_len, sel_count, jaccard, stream=None) -> None:
-    cp = prob.as_c()
-    _check(load_library().chunkkv_jaccard(C.byref(cp), n_groups, _ptr(sel_chunk), _ptr(sel_len), _ptr(sel_count),
+    cp = prob._c()
+    _check(load_library().chunkkv_jaccard(cp, n_groups, _ptr(sel_chunk), _ptr(sel_len), _ptr(sel_count),
                                           _ptr(jaccard), _stream(stream)), "chunkkv_jaccard")
 
 
 def chunkkv_quality_workspace_bytes(prob: Problem) -> int:
-    return int(load_library().chunkkv_quality_workspace_bytes(C.byref(prob.as_c())))
+    return int(load_library().chunkkv_quality_workspace_bytes(prob._c()))
 
 
 def chunkkv_quality_metrics(prob: Problem, kv_len, q, k, v, k_out, v_out, l1_loss, attn_cos, workspace, stream=None) -> None:
-    cp = prob.as_c()
+    cp = prob._c()
     _check(load_library().chunkkv_quality_metrics(
-        C.byref(cp), _ptr(kv_len), _ptr(q), _ptr(k), _ptr(v), _ptr(k_out), _ptr(v_out), _ptr(l1_loss), _ptr(attn_cos),
-        _ptr(workspace), 0 if workspace is None else workspace.numel() * workspace.element_size(), _stream(stream)),
+        cp, _ptr(kv_len), _ptr(q), _ptr(k), _ptr(v), _ptr(k_out), _ptr(v_out), _ptr(l1_loss), _ptr(attn_cos),
+        _ptr(workspace), _bytes(workspace), _stream(stream)),
         "chunkkv_quality_metrics")
 
 
 def chunkkv_decode_workspace_bytes(prob: Problem, compacted: bool = True) -> int:
-    return int(load_library().chunkkv_decode_workspace_bytes(C.byref(prob.as_c()), 1 if compacted else 0))
+    return int(load_library().chunkkv_decode_workspace_bytes(prob._c(), 1 if compacted else 0))
 
 
 def chunkkv_decode_attention(prob: Problem, compacted: bool, kv_len, q, k, v, out, lse, workspace, stream=None) -> None:
-    cp = prob.as_c()
+    cp = prob._c()
     _check(load_library().chunkkv_decode_attention(
-        C.byref(cp), 1 if compacted else 0, _ptr(kv_len), _ptr(q), _ptr(k), _ptr(v), _ptr(out), _ptr(lse),
-        _ptr(workspace), 0 if workspace is None else workspace.numel() * workspace.element_size(), _stream(stream)),
+        cp, 1 if compacted else 0, _ptr(kv_len), _ptr(q), _ptr(k), _ptr(v), _ptr(out), _ptr(lse),
+        _ptr(workspace), _bytes(workspace), _stream(stream)),
         "chunkkv_decode_attention")
 
 
 def chunkkv_decode_attention_static(prob: Problem, compacted: bool, kv_len, q, k, v, out, lse, stream=None) -> None:
-    cp = prob.as_c()
+    cp = prob._c()
     _check(load_library().chunkkv_decode_attention_static(
-        C.byref(cp), 1 if compacted else 0, _ptr(kv_len), _ptr(q), _ptr(k), _ptr(v), _ptr(out), _ptr(lse),
+        cp, 1 if compacted else 0, _ptr(kv_len), _ptr(q), _ptr(k), _ptr(v), _ptr(out), _ptr(lse),
         _stream(stream)), "chunkkv_decode_attention_static")
 
 
