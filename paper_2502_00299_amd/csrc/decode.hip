@@ -124,16 +124,18 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(DecodeArgs a) {
   const int b = a.batch0 + bl;
 
   // tokens of this (sequence, kv-head): the capacity of the cache, or the caller's count clamped to it
-  const int cap = pick(a.n_tok, bl);
+  const int cap = CKV_ARG(DecodeArgs, n_tok, bl);
   int n = cap;
   if (a.kv_len != nullptr) {
     n = a.kv_len[(int64_t)b * a.n_kv_heads + h];
     n = n < 0 ? 0 : (n > cap ? cap : n);
   }
-  const int r0 = split * a.rows_per_split;
-  const int r1 = r0 + a.rows_per_split < n ? r0 + a.rows_per_split : n;
+  const int rps = CKV_ARG(DecodeArgs, rows_per_split, bl);
+  const int r0 = split * rps;
+  const int r1 = r0 + rps < n ? r0 + rps : n;
+  if (r0 >= n && split > 0) return;   // the merge knows how many ranges hold rows
 
-  const int64_t head_off = (pick(a.base, bl) + (int64_t)h * a.stride_head) * ESZ;
+  const int64_t head_off = (CKV_ARG(DecodeArgs, base, bl) + (int64_t)h * a.stride_head) * ESZ;
   const char *kbase = (const char *)a.k + head_off + seg * 16;
   const char *vbase = (const char *)a.v + head_off + seg * 16;
   const int64_t tok = a.stride_tok * ESZ;
@@ -340,78 +342,106 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(DecodeArgs a) {
   }
 }
 
-// out = sum_s o_s 2^(m_s - M) / sum_s l_s 2^(m_s - M) over the key ranges of one query head.
-// grid: x = query head of the batch slice; 256 threads: a thread owns four consecutive output elements
-// and every kCombineGroups-th key range; the groups are folded through LDS in group order, so the
-// summation order is fixed.
+// out = sum_s o_s 2^(m_s - M) / sum_s l_s 2^(m_s - M) over the key ranges of one query head that hold rows.
+// grid: x = query head, y = sequence of the slice; 256 threads: a thread owns four consecutive output elements and
+// every NG-th key range.  Bound by latency, so the (m, l) pairs and the partial rows are loaded together (one round
+// trip) and merged online; the groups are folded through LDS in group order, so the summation order is fixed.
 constexpr int kCombineThreads = 256;
 template <int HD>
 __global__ __launch_bounds__(kCombineThreads) void decode_combine_kernel(DecodeArgs a) {
   constexpr int TPR = HD / 4;                     // threads per partial row
   constexpr int NG = kCombineThreads / TPR;       // key-range groups
-  const int64_t head = (int64_t)a.batch0 * a.n_q_heads + blockIdx.x;
+  constexpr int UN = 4;
+  const int bl = blockIdx.y, hq = blockIdx.x, b = a.batch0 + bl;
+  const int64_t head = (int64_t)b * a.n_q_heads + hq;
+  int n = CKV_ARG(DecodeArgs, n_tok, bl);
+  if (a.kv_len != nullptr) {
+    const int x = a.kv_len[(int64_t)b * a.n_kv_heads + hq / (a.n_q_heads / a.n_kv_heads)];
+    n = x < 0 ? 0 : (x > n ? n : x);
+  }
+  const int rps = CKV_ARG(DecodeArgs, rows_per_split, bl);
+  const int used = n > 0 ? (n + rps - 1) / rps : 1;
   const float2 *ml = a.part_ml + head * a.n_split;
   const int t = threadIdx.x, col = t % TPR, grp = t / TPR;
-  __shared__ float s_red[kCombineThreads / 64];
-  __shared__ float s_acc[NG][HD + 1];
-  // maximum over the key ranges
-  float M = kDecodeNegBig;
-  for (int s = t; s < a.n_split; s += kCombineThreads) M = fmaxf(M, ml[s].x);
-  for (int o = 32; o > 0; o >>= 1) M = fmaxf(M, __shfl_xor(M, o));
-  if ((t & 63) == 0) s_red[t >> 6] = M;
-  __syncthreads();
-  M = fmaxf(fmaxf(s_red[0], s_red[1]), fmaxf(s_red[2], s_red[3]));
-  // weighted sums of this thread's key ranges
+  __shared__ float s_acc[NG][HD + 2];
   const float *po = a.part_o + head * a.n_split * HD + col * 4;
-  float acc[4] = {0.f, 0.f, 0.f, 0.f}, lsum = 0.f;
-#pragma unroll 4
-  for (int s = grp; s < a.n_split; s += NG) {
-    const float2 p = ml[s];
-    const float f = __builtin_amdgcn_exp2f(p.x - M);
-    const float4 o4 = *(const float4 *)(po + (int64_t)s * HD);
-    lsum += p.y * f;
-    acc[0] += o4.x * f; acc[1] += o4.y * f; acc[2] += o4.z * f; acc[3] += o4.w * f;
+  float acc[4] = {0.f, 0.f, 0.f, 0.f}, m = kDecodeNegBig, lsum = 0.f;
+  for (int s0 = grp; s0 < used; s0 += UN * NG) {
+    float2 p[UN];
+    float4 o4[UN];
+#pragma unroll
+    for (int u = 0; u < UN; ++u) {
+      const int s = s0 + u * NG < used ? s0 + u * NG : s0;
+      p[u] = ml[s];
+      o4[u] = *(const float4 *)(po + (int64_t)s * HD);
+    }
+    float mm = m;
+#pragma unroll
+    for (int u = 0; u < UN; ++u) mm = fmaxf(mm, p[u].x);
+    const float f0 = __builtin_amdgcn_exp2f(m - mm);
+    lsum *= f0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc[e] *= f0;
+#pragma unroll
+    for (int u = 0; u < UN; ++u) {
+      const float f = s0 + u * NG < used ? __builtin_amdgcn_exp2f(p[u].x - mm) : 0.f;
+      lsum += p[u].y * f;
+      acc[0] += o4[u].x * f; acc[1] += o4[u].y * f; acc[2] += o4[u].z * f; acc[3] += o4[u].w * f;
+    }
+    m = mm;
   }
 #pragma unroll
   for (int e = 0; e < 4; ++e) s_acc[grp][col * 4 + e] = acc[e];
-  if (col == 0) s_acc[grp][HD] = lsum;
+  if (col == 0) { s_acc[grp][HD] = lsum; s_acc[grp][HD + 1] = m; }
   __syncthreads();
   if (t < HD) {
-    float v = 0.f, Lsum = 0.f;
+    float M = s_acc[0][HD + 1];
 #pragma unroll
-    for (int g2 = 0; g2 < NG; ++g2) { v += s_acc[g2][t]; Lsum += s_acc[g2][HD]; }
-    a.out[head * HD + t] = Lsum > 0.f ? v / Lsum : 0.f;
+    for (int g2 = 1; g2 < NG; ++g2) M = fmaxf(M, s_acc[g2][HD + 1]);
+    float v = 0.f, L = 0.f;
+#pragma unroll
+    for (int g2 = 0; g2 < NG; ++g2) {
+      const float f = __builtin_amdgcn_exp2f(s_acc[g2][HD + 1] - M);
+      v += s_acc[g2][t] * f;
+      L += s_acc[g2][HD] * f;
+    }
+    a.out[head * HD + t] = L > 0.f ? v / L : 0.f;
     if (a.lse != nullptr && t == 0)
-      a.lse[head] = Lsum > 0.f ? (M + __builtin_log2f(Lsum)) * 0.6931471805599453f : -__builtin_inff();
+      a.lse[head] = L > 0.f ? (M + __builtin_log2f(L)) * 0.6931471805599453f : -__builtin_inff();
   }
 }
 
+// fp32 caches; for 16-bit caches only strides beyond the matrix-core kernel's offsets come here, one head at a time
 template <int DT, int HD>
-int launch_decode_hd(const DecodeArgs &a, int batch_slice, int g, hipStream_t s) {
-  const int G = decode_heads_per_wg(DT, g);
+int launch_decode_valu(const DecodeArgs &a, int batch_slice, int g, hipStream_t s) {
+  const int G = DT == CHUNKKV_F32 ? decode_heads_per_wg(DT, g) : 1;
   const dim3 grid(a.n_split, batch_slice * a.n_kv_heads, (g + G - 1) / G);
-  if (grid.x == 0 || grid.y == 0) return CHUNKKV_OK;
   if (G == 1) hipLaunchKernelGGL((decode_kernel<DT, HD, 1>), grid, dim3(kThreads), 0, s, a);
-  else if (G == 2) hipLaunchKernelGGL((decode_kernel<DT, HD, 2>), grid, dim3(kThreads), 0, s, a);
-  else if (G == 4) hipLaunchKernelGGL((decode_kernel<DT, HD, 4>), grid, dim3(kThreads), 0, s, a);
-  else if constexpr (DT != CHUNKKV_F32) hipLaunchKernelGGL((decode_kernel<DT, HD, 8>), grid, dim3(kThreads), 0, s, a);
-  else return CHUNKKV_ERR_UNSUPPORTED;
-  if (hipGetLastError() != hipSuccess) return CHUNKKV_ERR_LAUNCH;
-  hipLaunchKernelGGL((decode_combine_kernel<HD>), dim3(batch_slice * a.n_q_heads), dim3(kCombineThreads), 0, s, a);
+  else if constexpr (DT == CHUNKKV_F32) {
+    if (G == 2) hipLaunchKernelGGL((decode_kernel<DT, HD, 2>), grid, dim3(kThreads), 0, s, a);
+    else hipLaunchKernelGGL((decode_kernel<DT, HD, 4>), grid, dim3(kThreads), 0, s, a);
+  }
   return hipGetLastError() == hipSuccess ? CHUNKKV_OK : CHUNKKV_ERR_LAUNCH;
 }
 
-int launch_decode(int dtype, int head_dim, const DecodeArgs &a, int batch_slice, hipStream_t s) {
+template <int HD>
+int launch_decode_hd(int dtype, bool matrix_cores, const DecodeArgs &a, int batch_slice, hipStream_t s) {
   const int g = a.n_q_heads / a.n_kv_heads;
-  if (head_dim == 128) {
-    if (dtype == CHUNKKV_BF16) return launch_decode_hd<CHUNKKV_BF16, 128>(a, batch_slice, g, s);
-    if (dtype == CHUNKKV_F16) return launch_decode_hd<CHUNKKV_F16, 128>(a, batch_slice, g, s);
-    if (dtype == CHUNKKV_F32) return launch_decode_hd<CHUNKKV_F32, 128>(a, batch_slice, g, s);
-  } else if (head_dim == 64) {
-    if (dtype == CHUNKKV_BF16) return launch_decode_hd<CHUNKKV_BF16, 64>(a, batch_slice, g, s);
-    if (dtype == CHUNKKV_F16) return launch_decode_hd<CHUNKKV_F16, 64>(a, batch_slice, g, s);
-    if (dtype == CHUNKKV_F32) return launch_decode_hd<CHUNKKV_F32, 64>(a, batch_slice, g, s);
-  }
+  int rc;
+  if (matrix_cores) rc = launch_decode_mfma(dtype, HD, a, batch_slice, s);
+  else if (dtype == CHUNKKV_BF16) rc = launch_decode_valu<CHUNKKV_BF16, HD>(a, batch_slice, g, s);
+  else if (dtype == CHUNKKV_F16) rc = launch_decode_valu<CHUNKKV_F16, HD>(a, batch_slice, g, s);
+  else rc = launch_decode_valu<CHUNKKV_F32, HD>(a, batch_slice, g, s);
+  if (rc) return rc;
+  if (matrix_cores && a.n_split == 1) return CHUNKKV_OK;   // the range kernel wrote the outputs
+  hipLaunchKernelGGL((decode_combine_kernel<HD>), dim3(a.n_q_heads, batch_slice), dim3(kCombineThreads), 0, s, a);
+  return hipGetLastError() == hipSuccess ? CHUNKKV_OK : CHUNKKV_ERR_LAUNCH;
+}
+
+int launch_decode(int dtype, int head_dim, bool matrix_cores, const DecodeArgs &a, int batch_slice, hipStream_t s) {
+  if (a.n_split == 0 || batch_slice * a.n_kv_heads == 0) return CHUNKKV_OK;
+  if (head_dim == 128) return launch_decode_hd<128>(dtype, matrix_cores, a, batch_slice, s);
+  if (head_dim == 64) return launch_decode_hd<64>(dtype, matrix_cores, a, batch_slice, s);
   return CHUNKKV_ERR_UNSUPPORTED;
 }
 

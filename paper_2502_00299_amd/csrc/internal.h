@@ -1,7 +1,10 @@
 // Internal declarations shared by the translation units of libchunkkv (not part of the ABI).
 #pragma once
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
+
+#include <type_traits>
 
 #include "chunkkv.h"
 
@@ -93,11 +96,12 @@ struct DecodeArgs {
   float *part_o;              // [batch_total * Hq][n_split][d]
   const int32_t *kv_len;      // [batch_total][Hkv] tokens to attend to, or null (= n_tok)
   int32_t n_tok[kMaxBatchPerLaunch];  // tokens the cache of a sequence holds per head
+  int32_t rows_per_split[kMaxBatchPerLaunch];  // rows of one key range of the sequence
   int64_t base[kMaxBatchPerLaunch];   // element offset of the sequence in k / v
   int64_t stride_head, stride_tok;
-  int32_t batch0, n_q_heads, n_kv_heads;
+  int32_t batch0, n_q_heads, n_kv_heads, group;   // group: query heads per kv-head
   float scale_log2e;
-  int32_t n_split, rows_per_split;
+  int32_t n_split;            // pitch of the partial results; 1: every head is one range and no merge follows
 };
 
 // Absolute mass of one layer's cache (quality.hip): sum of |K| + |V| over blocks of rows of every (sequence, kv-head).
@@ -118,10 +122,11 @@ struct QualityFinishArgs {
   int32_t n_q_heads, n_kv_heads, blocks_full, blocks_kept;
 };
 
-// query heads of one kv-head that a decode workgroup serves: 1, 2, 4 or 8 (fp32 caches: at most 4, registers)
+// Query heads of one kv-head that a decode workgroup serves.  16-bit caches (matrix cores): 4 or 8; 5..7 heads are one
+// padded batch of 8, not two passes over K and V.  fp32 caches (vector ALU): 1, 2 or 4 (registers).
 inline int decode_heads_per_wg(int dtype, int g) {
-  const int G = g > 4 ? 8 : (g > 2 ? 4 : g);  // 5..7 heads: one padded batch of 8, not two passes over K and V
-  return dtype == CHUNKKV_F32 && G > 4 ? 4 : G;
+  if (dtype != CHUNKKV_F32) return g > 4 ? 8 : 4;
+  return g > 2 ? 4 : g;
 }
 
 // Reads element i of a small table that travels as a kernel argument.  A chain of selects on the
@@ -134,6 +139,15 @@ __device__ __forceinline__ T pick(const T (&arr)[N], int i) {
   for (int j = 1; j < N; ++j) r = (i == j) ? arr[j] : r;
   return r;
 }
+
+// Element i of a table inside a kernel's argument struct (the kernel's only parameter): one scalar load from the
+// argument segment, where a chain of selects would load the whole table first.
+template <typename T>
+__device__ __forceinline__ T kernarg_at(size_t offset, int i) {
+  typedef __attribute__((address_space(4))) const char *arg_ptr;
+  return *(__attribute__((address_space(4))) const T *)((arg_ptr)__builtin_amdgcn_kernarg_segment_ptr() + offset + (size_t)i * sizeof(T));
+}
+#define CKV_ARG(STRUCT, FIELD, I) kernarg_at<std::remove_cv_t<std::remove_extent_t<decltype(STRUCT::FIELD)>>>(offsetof(STRUCT, FIELD), (I))
 
 // Single-pass scoring: periods (160 keys) one workgroup walks, for a sequence of n_periods periods.  A function
 // of the sequence alone (about 32 ranges per sequence and kv-head, at least 8 periods each), so the key ranges,
@@ -167,7 +181,8 @@ int launch_lse_refs(const LseArgs &a, int n_leaders_slice, int batch_slice, hipS
 int launch_single_scores(const ScoreArgs &a, int n_leaders_slice, int batch_slice, hipStream_t s);
 bool single_pass_ok(int dtype, int head_dim, int rows, int chunk);
 int launch_topk(const TopkArgs &a, int n_groups, int batch_slice, hipStream_t s);
-int launch_decode(int dtype, int head_dim, const DecodeArgs &a, int batch_slice, hipStream_t s);
+int launch_decode_mfma(int dtype, int head_dim, const DecodeArgs &a, int batch_slice, hipStream_t s);
+int launch_decode(int dtype, int head_dim, bool matrix_cores, const DecodeArgs &a, int batch_slice, hipStream_t s);
 int abs_sum_blocks(int n_tok_max);
 int launch_abs_sum(int dtype, const AbsSumArgs &a, int batch_slice, hipStream_t s);
 int launch_quality_finish(const QualityFinishArgs &a, int batch, hipStream_t s);

@@ -1,0 +1,93 @@
+"""Decode attention of 16-bit caches where its matrix-core kernel can go wrong: the edges of a 32-row step, of the
+one-range and the many-range forms and of a range, padded head batches, the parts a weight is cut into, and strides
+its 32-bit offsets cannot hold."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import chunkkv_oracle as orc
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+# fp32 accumulation of 128 products, an exponential and n weighted rows: a few 2^-24 of the logits' size (up to about
+# 100 before scaling, 1e-6 of a weight) and about sqrt(n) 2^-24 of the row for the sums; 20 times that
+TOL = 2e-5
+
+
+def bits(t):
+    t = t.cpu().contiguous()
+    return t.view(torch.int16).numpy().view(np.uint16) if t.dtype == torch.bfloat16 else t.numpy()
+
+
+def run(lib, dtype, n, hq, hkv, d, k, v, q, kv_len=None, stride_tok=None, scale=0.0):
+    """Compacted-cache call over k, v [hkv][n][d] (strided copies when stride_tok is given)."""
+    stride_tok = stride_tok or d
+    stride_head = n * stride_tok if stride_tok == d else d
+    prob = lib.Problem(hq, hkv, d, 1, 1, {torch.bfloat16: lib.BF16, torch.float16: lib.F16}[dtype], [n], [n - 1], [0], n * d, d,
+                       [0], stride_head, stride_tok, softmax_scale=scale)
+    kk, vv = k, v
+    if stride_tok != d:
+        kk, vv = (torch.zeros((n - 1) * stride_tok + hkv * d, dtype=dtype, device=DEV) for _ in range(2))
+        for src, dst in ((k, kk), (v, vv)):
+            torch.as_strided(dst, (hkv, n, d), (stride_head, stride_tok, 1)).copy_(src)
+    out = torch.full((1, hq, d), 7.0, dtype=torch.float32, device=DEV)
+    lse = torch.full((1, hq), 7.0, dtype=torch.float32, device=DEV)
+    ws = torch.empty(lib.chunkkv_decode_workspace_bytes(prob, True), dtype=torch.uint8, device=DEV)
+    lib.chunkkv_decode_attention(prob, True, kv_len, q, kk, vv, out, lse, ws)
+    torch.cuda.synchronize()
+    return out[0].cpu().numpy(), lse[0].cpu().numpy()
+
+
+def check(out, lse, q, k, v, n, scale=None):
+    hq, hkv = q.shape[0], k.shape[0]
+    g = hq // hkv
+    for h in range(hkv):
+        o_ref, l_ref = orc.decode_attention(bits(q[h * g:(h + 1) * g]), bits(k[h:h + 1, :n]), bits(v[h:h + 1, :n]), scale)
+        err = np.abs(out[h * g:(h + 1) * g] - o_ref).max(axis=1) / np.abs(o_ref).max(axis=1)
+        assert err.max() <= TOL, (h, err)
+        assert np.abs(lse[h * g:(h + 1) * g] - l_ref).max() <= TOL * 10
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
+@pytest.mark.parametrize("n,hq,hkv,d", [(1, 4, 1, 128), (31, 8, 2, 64), (33, 7, 1, 128), (255, 3, 3, 128), (256, 8, 1, 64), (257, 4, 1, 128),
+                                        (257, 10, 2, 64), (1025, 8, 1, 128), (5000, 9, 1, 128), (4097, 36, 9, 64), (20011, 8, 2, 128)])
+def test_edges(lib, dtype, n, hq, hkv, d):
+    gen = torch.Generator(device=DEV).manual_seed(n)
+    q, k, v = (torch.randn(s, generator=gen, device=DEV).mul_(a).to(dtype) for s, a in (((hq, d), 2.0), ((hkv, n, d), 1.0), ((hkv, n, d), 1.0)))
+    print(f"n={n} hq={hq} hkv={hkv} d={d} {dtype}", flush=True)
+    out, lse = run(lib, dtype, n, hq, hkv, d, k, v, q)
+    check(out, lse, q, k, v, n)
+    if n > 40:   # fewer tokens than the cache holds: the rows behind them must not count
+        m = n - 37
+        out, lse = run(lib, dtype, n, hq, hkv, d, k, v, q, kv_len=torch.full((1, hkv), m, dtype=torch.int32, device=DEV))
+        check(out, lse, q, k, v, m)
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
+@pytest.mark.parametrize("peak", [0, 300, 599])
+def test_one_token_far_above_many(lib, dtype, peak):
+    """One token 25 nats above 599 equal ones, wherever it comes: the others' weights (1.4e-11) stay in the sums."""
+    n, d, hq = 600, 128, 4
+    u = torch.zeros(d, device=DEV)
+    u[5] = 1.0
+    k = torch.zeros((1, n, d), device=DEV)
+    k[0, peak] = 25.0 * u
+    q = u.repeat(hq, 1)
+    v = torch.zeros((1, n, d), device=DEV)
+    v[0, :, 1] = 30000.0
+    v[0, peak] = 0.0
+    v[0, peak, 2] = 1.0
+    q, k, v = q.to(dtype), k.to(dtype), v.to(dtype)
+    out, lse = run(lib, dtype, n, hq, 1, d, k, v, q, scale=1.0)
+    p = np.exp(-25.0) / (1.0 + 599 * np.exp(-25.0))
+    want = 599 * p * float(v[0, (peak + 1) % n, 1].float())
+    assert np.abs(out[:, 1] / want - 1).max() <= 1e-5 and np.abs(out[:, 2] - 1).max() <= 1e-6
+    assert np.abs(lse - 25.0).max() <= 1e-5
+
+
+def test_strides_past_32_bit_offsets(lib):
+    n, d, hq, hkv = 3, 128, 8, 2
+    gen = torch.Generator(device=DEV).manual_seed(3)
+    q, k, v = (torch.randn(s, generator=gen, device=DEV).to(torch.bfloat16) for s in ((hq, d), (hkv, n, d), (hkv, n, d)))
+    out, lse = run(lib, torch.bfloat16, n, hq, hkv, d, k, v, q, stride_tok=(1 << 22) + 64)   # 259 rows of 8 MB: past 2^31
+    check(out, lse, q, k, v, n)
