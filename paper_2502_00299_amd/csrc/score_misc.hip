@@ -143,31 +143,53 @@ int launch_chunk_sums(const ScoreArgs &a, int n_leaders_slice, int batch_slice, 
 //   ref_r = m_r + log2(sum_r), merged from the (reference, sum) pairs the key ranges left for row r
 //           (pairs merge associatively; always in the same order: range by range);
 //   score[chunk] = sum over rows of E[chunk][row] * exp2(m[chunk][row] - ref[row]).
-// A workgroup of 256 threads merges the statistics of its problem (one row per thread) and then takes
-// kPeriodsPerGroup consecutive periods.  Per period the scoring kernel left, for each lane half h and each
-// group of eight consecutive chunks of that half, rows_pad pieces of 16 + 4 bytes (eight sums as 20-bit floats:
-// 8 exponent and 12 mantissa bits; chunk size 20 has four chunks per half: pieces of 12 bytes, four 24-bit
-// floats), and rows_pad references (one per row).  A wavefront takes one (period, half, group) at a time: its
-// lanes walk the rows (consecutive lanes read consecutive pieces), weigh, and the sums are reduced over the
-// lanes in a fixed order.  The chunk of (half h, position s) is 2 s + h of the period's 2 S chunks.  Rows past
-// the real ones are skipped: nothing was written for them.
+// A workgroup of 256 threads merges the statistics of its problem (one row per thread, eight ranges' pairs in flight)
+// and then takes `periods_per_wg` consecutive periods.  Per period the scoring kernel left, for each lane half h and
+// each group of eight consecutive chunks of that half, rows_pad pieces of 16 + 4 bytes (eight sums as 20-bit floats:
+// 8 exponent and 12 mantissa bits; chunk size 20 has four chunks per half: pieces of 12 bytes, four 24-bit floats), and
+// rows_pad references (one per row).  A wavefront takes one (period, half, group) at a time: its lanes walk the rows
+// (consecutive lanes read consecutive pieces, all pieces of a task in flight), weigh, and the sums are reduced over
+// the lanes in a fixed order, halving the values a lane holds with every step (10 shuffles for eight sums instead of
+// 48).  The chunk of (half h, position s) is 2 s + h of the period's 2 S chunks.  Rows past the real ones are skipped:
+// nothing was written for them.
+// Bound by HBM over a stack; over a single layer by how many workgroups share it: one layer of 20011 tokens, c = 5, took
+// 98 us with 32 periods per workgroup (32 workgroups); the launcher now cuts it finer.
 // grid: x = period group, y = (sequence, kv-head), z = leader.
-constexpr int kPeriodsPerGroup = 32;
 constexpr int kSinglePeriod = 160, kSingleHalf = 80;   // as in the single-pass scoring kernel
+constexpr int kScoresTargetWgs = 2048, kScoresMaxPeriods = 32;
 
-__global__ __launch_bounds__(256) void single_scores_kernel(ScoreArgs a) {
-  typedef float f32x4 __attribute__((ext_vector_type(4)));
+// Sum over the 64 lanes of N (4 or 8) values per lane; lane l returns the total of value (l >> (6 - log2 N)).
+template <int N>
+__device__ __forceinline__ float wave_sum_scatter(float (&v)[N]) {
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int n = N / 2, o = 32; n >= 1; n /= 2, o /= 2) {
+    const bool upper = (lane & o) != 0;
+#pragma unroll
+    for (int i = 0; i < n; ++i) {
+      const float keep = upper ? v[n + i] : v[i], send = upper ? v[i] : v[n + i];
+      v[i] = keep + __shfl_xor(send, o);
+    }
+  }
+  float x = v[0];
+#pragma unroll
+  for (int o = 32 / N; o >= 1; o /= 2) x += __shfl_xor(x, o);
+  return x;
+}
+
+template <int S, int RB>   // chunks per lane half and period; 64-row blocks of rows_pad
+__global__ __launch_bounds__(256) void single_scores_kernel(ScoreArgs a, int periods_per_wg) {
   typedef unsigned int u32x3 __attribute__((ext_vector_type(3)));
   typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int bl = blockIdx.y / a.n_kv_heads, h = blockIdx.y % a.n_kv_heads, z = blockIdx.z;
   const int64_t problem = ((int64_t)(a.leader0 + z) * a.batch_total + (a.batch0 + bl)) * a.n_kv_heads + h;
-  const int L = pick(a.seq.seqlen, bl), P = L - a.window, c = a.chunk;
-  const int C = (P + c - 1) / c, S = kSingleHalf / c;
+  const int L = CKV_ARG(ScoreArgs, seq.seqlen, bl), P = L - a.window, c = kSingleHalf / S;
+  const int C = (P + c - 1) / c;
   const int np = (P + kSinglePeriod - 1) / kSinglePeriod;   // periods that hold prefix keys
-  const int p0 = blockIdx.x * kPeriodsPerGroup;
+  const int p0 = blockIdx.x * periods_per_wg;
   if (p0 >= np) return;
-  const int p1 = p0 + kPeriodsPerGroup < np ? p0 + kPeriodsPerGroup : np;
+  const int p1 = p0 + periods_per_wg < np ? p0 + periods_per_wg : np;
   const int nrows = (a.n_q_heads / a.n_kv_heads) * a.window;
   __shared__ float s_ref[256];
 
@@ -178,99 +200,109 @@ __global__ __launch_bounds__(256) void single_scores_kernel(ScoreArgs a) {
     float m = -1.0e30f, l = 0.f;
     if (tid < nrows) {
       const float2 *ps = a.part_stats + problem * a.max_split * a.rows_pad + tid;
-      for (int s = 0; s < nsplit; ++s) {
-        const float2 x = ps[(int64_t)s * a.rows_pad];
-        const float mm = fmaxf(m, x.x);
-        l = l * exp2f(m - mm) + x.y * exp2f(x.x - mm);
+      for (int s0 = 0; s0 < nsplit; s0 += 8) {
+        float2 x[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) x[i] = ps[(int64_t)(s0 + i < nsplit ? s0 + i : nsplit - 1) * a.rows_pad];
+        float mm = m;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) mm = fmaxf(mm, x[i].x);
+        l *= exp2f(m - mm);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) l += s0 + i < nsplit ? x[i].y * exp2f(x[i].x - mm) : 0.f;
         m = mm;
       }
     }
     s_ref[tid] = tid < nrows ? m + log2f(l) : 3.0e38f;
   }
   __syncthreads();
+  float ref[RB];
+#pragma unroll
+  for (int i = 0; i < RB; ++i) ref[i] = s_ref[64 * i + lane];   // 3e38 past the real rows: weight 0
 
   // ---- chunk scores
+  constexpr int G8 = S / 8, NV = S == 4 ? 4 : 8, combos = S == 4 ? 2 : 2 * G8;   // values and tasks per period
+  constexpr int kRowBytes = S == 4 ? 24 : combos * 20;                           // E bytes per period and row
   const int64_t prow = (int64_t)a.rows_pad;
   const float *m_problem = a.m_period + problem * a.n_periods * prow;
-  if (S == 4) {
-    // [lane half][rows_pad] x 12 bytes: four sums as the upper three bytes of their fp32
-    const char *e_problem = (const char *)a.e_buf + problem * a.n_periods * prow * 24;
-    for (int task = wave; task < (p1 - p0) * 2; task += 4) {
-      const int period = p0 + task / 2, hh = task % 2;
-      const char *src = e_problem + ((int64_t)period * 2 + hh) * prow * 12;
-      const float *mp = m_problem + (int64_t)period * prow;
-      f32x4 v = {0.f, 0.f, 0.f, 0.f};
-      for (int row = lane; row < nrows; row += 64) {
-        const float wgt = exp2f(mp[row] - s_ref[row]);
-        const u32x3 d = __builtin_nontemporal_load((const u32x3 *)(src + row * 12));
-        const f32x4 x = {__uint_as_float(d.x << 8), __uint_as_float(__builtin_amdgcn_alignbit(d.y, d.x, 24) << 8),
-                         __uint_as_float(__builtin_amdgcn_alignbit(d.z, d.y, 16) << 8), __uint_as_float(d.z & 0xFFFFFF00u)};
-        v += x * wgt;
-      }
+  const char *e_problem = (const char *)a.e_buf + problem * a.n_periods * prow * kRowBytes;
+  float *scores = a.chunk_scores + problem * a.score_cap;
+  for (int task = wave; task < (p1 - p0) * combos; task += 4) {
+    const int period = p0 + task / combos, combo = task % combos;   // combo = half * G8 + group
+    const int hh = S == 4 ? combo : combo / G8, g8 = S == 4 ? 0 : combo % G8;
+    const char *pbase = e_problem + (int64_t)period * prow * kRowBytes;
+    const float *mp = m_problem + (int64_t)period * prow;
+    float v[NV], mr[RB];
+    u32x4 w[RB];
+    uint32_t w4[RB];
 #pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        v.x += __shfl_xor(v.x, o); v.y += __shfl_xor(v.y, o); v.z += __shfl_xor(v.z, o); v.w += __shfl_xor(v.w, o);
-      }
-      if (lane < 4) {
-        const int chunk = period * 2 * S + 2 * lane + hh;
-        const float val = lane == 0 ? v.x : (lane == 1 ? v.y : (lane == 2 ? v.z : v.w));
-        if (chunk < C) a.chunk_scores[problem * a.score_cap + chunk] = val;
+    for (int i = 0; i < RB; ++i) {
+      const int row = 64 * i + lane < nrows ? 64 * i + lane : 0;
+      mr[i] = mp[row];
+      if constexpr (S == 4) {
+        const u32x3 d = __builtin_nontemporal_load((const u32x3 *)(pbase + (int64_t)combo * prow * 12 + row * 12));
+        w[i] = u32x4{d.x, d.y, d.z, 0u};
+      } else {
+        w[i] = __builtin_nontemporal_load((const u32x4 *)(pbase + (int64_t)combo * prow * 16 + row * 16));
+        w4[i] = __builtin_nontemporal_load((const uint32_t *)(pbase + (int64_t)combos * prow * 16 + (int64_t)combo * prow * 4 + row * 4));
       }
     }
-  } else {
-    // groups of eight sums as 20-bit floats: [lane half][group][rows_pad] x 16 bytes, then x 4 bytes
-    const int G8 = S / 8, combos = 2 * G8;
-    const char *e_problem = (const char *)a.e_buf + problem * a.n_periods * prow * (combos * 20);
-    for (int task = wave; task < (p1 - p0) * combos; task += 4) {
-      const int period = p0 + task / combos, combo = task % combos;   // combo = half * G8 + group
-      const int hh = combo / G8, g8 = combo % G8;
-      const char *pbase = e_problem + (int64_t)period * prow * (combos * 20);
-      const char *src_lo = pbase + (int64_t)combo * prow * 16, *src_hi = pbase + (int64_t)combos * prow * 16 + (int64_t)combo * prow * 4;
-      const float *mp = m_problem + (int64_t)period * prow;
-      float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-      for (int row = lane; row < nrows; row += 64) {
-        const float wgt = exp2f(mp[row] - s_ref[row]);
-        const u32x4 w = __builtin_nontemporal_load((const u32x4 *)(src_lo + row * 16));
-        const uint32_t w4 = __builtin_nontemporal_load((const uint32_t *)(src_hi + row * 4));
+#pragma unroll
+    for (int i = 0; i < NV; ++i) v[i] = 0.f;
+#pragma unroll
+    for (int i = 0; i < RB; ++i) {
+      const float wgt = exp2f(mr[i] - ref[i]);
+      if constexpr (S == 4) {
+        v[0] += __uint_as_float(w[i].x << 8) * wgt;
+        v[1] += __uint_as_float(__builtin_amdgcn_alignbit(w[i].y, w[i].x, 24) << 8) * wgt;
+        v[2] += __uint_as_float(__builtin_amdgcn_alignbit(w[i].z, w[i].y, 16) << 8) * wgt;
+        v[3] += __uint_as_float(w[i].z & 0xFFFFFF00u) * wgt;
+      } else {
         uint32_t q[8];
-        q[0] = w.x & 0xFFFFFu;
-        q[1] = (w.x >> 20) | ((w.y & 0xFFu) << 12);
-        q[2] = (w.y >> 8) & 0xFFFFFu;
-        q[3] = (w.y >> 28) | ((w.z & 0xFFFFu) << 4);
-        q[4] = (w.z >> 16) | ((w.w & 0xFu) << 16);
-        q[5] = (w.w >> 4) & 0xFFFFFu;
-        q[6] = (w.w >> 24) | ((w4 & 0xFFFu) << 8);
-        q[7] = w4 >> 12;
+        q[0] = w[i].x & 0xFFFFFu;
+        q[1] = (w[i].x >> 20) | ((w[i].y & 0xFFu) << 12);
+        q[2] = (w[i].y >> 8) & 0xFFFFFu;
+        q[3] = (w[i].y >> 28) | ((w[i].z & 0xFFFFu) << 4);
+        q[4] = (w[i].z >> 16) | ((w[i].w & 0xFu) << 16);
+        q[5] = (w[i].w >> 4) & 0xFFFFFu;
+        q[6] = (w[i].w >> 24) | ((w4[i] & 0xFFFu) << 8);
+        q[7] = w4[i] >> 12;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) v[i] += __uint_as_float(q[i] << 11) * wgt;
+        for (int j = 0; j < 8; ++j) v[j] += __uint_as_float(q[j] << 11) * wgt;
       }
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) v[i] += __shfl_xor(v[i], o);
-      }
-      if (lane < 8) {
-        float val = v[0];
-#pragma unroll
-        for (int i = 1; i < 8; ++i) val = lane == i ? v[i] : val;
-        const int chunk = period * 2 * S + 2 * (8 * g8 + lane) + hh;
-        if (chunk < C) a.chunk_scores[problem * a.score_cap + chunk] = val;
-      }
+    }
+    const float val = wave_sum_scatter<NV>(v);
+    constexpr int kLanes = 64 / NV;   // lanes that hold the same total
+    if (lane % kLanes == 0) {
+      const int chunk = period * 2 * S + 2 * (8 * g8 + lane / kLanes) + hh;
+      if (chunk < C) scores[chunk] = val;
     }
   }
 }
 
 int launch_single_scores(const ScoreArgs &a, int n_leaders_slice, int batch_slice, hipStream_t s) {
   int max_periods = 0;
+  int64_t periods = 0;
   for (int b = 0; b < batch_slice; ++b) {
     const int P = a.seq.seqlen[b] - a.window;
     const int np = (P + kSinglePeriod - 1) / kSinglePeriod;
     max_periods = np > max_periods ? np : max_periods;
+    periods += np;
   }
   if (max_periods == 0 || n_leaders_slice <= 0) return CHUNKKV_OK;
-  if (a.rows_pad > 256 || kSingleHalf % a.chunk != 0 || (kSingleHalf / a.chunk) % 4 != 0) return CHUNKKV_ERR_UNSUPPORTED;
-  dim3 grid((max_periods + kPeriodsPerGroup - 1) / kPeriodsPerGroup, batch_slice * a.n_kv_heads, n_leaders_slice);
-  hipLaunchKernelGGL(single_scores_kernel, grid, dim3(256), 0, s, a);
+  if (a.rows_pad != 128 && a.rows_pad != 256) return CHUNKKV_ERR_UNSUPPORTED;
+  // at most about kScoresTargetWgs workgroups (eight per CU, one generation), with at least one task for each of their four wavefronts
+  const int sums = kSingleHalf / a.chunk, least = sums == 16 ? 1 : 2;
+  int64_t ppw = (periods * a.n_kv_heads * n_leaders_slice + kScoresTargetWgs - 1) / kScoresTargetWgs;
+  ppw = ppw < least ? least : (ppw > kScoresMaxPeriods ? kScoresMaxPeriods : ppw);
+  dim3 grid((max_periods + (int)ppw - 1) / (int)ppw, batch_slice * a.n_kv_heads, n_leaders_slice);
+  const bool wide = a.rows_pad == 256;
+  switch (sums) {
+    case 4: hipLaunchKernelGGL((wide ? single_scores_kernel<4, 4> : single_scores_kernel<4, 2>), grid, dim3(256), 0, s, a, (int)ppw); break;
+    case 8: hipLaunchKernelGGL((wide ? single_scores_kernel<8, 4> : single_scores_kernel<8, 2>), grid, dim3(256), 0, s, a, (int)ppw); break;
+    case 16: hipLaunchKernelGGL((wide ? single_scores_kernel<16, 4> : single_scores_kernel<16, 2>), grid, dim3(256), 0, s, a, (int)ppw); break;
+    default: return CHUNKKV_ERR_UNSUPPORTED;
+  }
   return hipGetLastError() == hipSuccess ? CHUNKKV_OK : CHUNKKV_ERR_LAUNCH;
 }
 
