@@ -1,11 +1,15 @@
 // Compaction (Algorithm 1: index_select of the kept chunks + concatenation of the window).
 //
-// Pure data movement, bound by HBM bandwidth: every kept row of K and V is read once and written
-// once.  A kept chunk is a run of `len` consecutive rows, so each wavefront copies one selection entry
-// (K and V together) as 16-byte segments; with the default [Hkv][L][d] layout both source and
-// destination of an entry are contiguous, 256-byte aligned runs.  The window is handled as extra
-// entries of up to `c` rows each.  Grid: x = group of kCompactEntries entries, y = (sequence, kv-head),
-// z = layer; all layers of the stack are one launch.
+// Pure data movement: every kept row of K and V is read once and written once.  A workgroup takes `entries_per_wg`
+// consecutive selection entries (a kept chunk is a run of `len` consecutive rows; the window is handled as extra
+// entries of up to `c` rows) and copies their rows as one flat list of 16-byte segments, K rows first, then V rows:
+// consecutive lanes copy consecutive segments whatever the chunk size is, five segments in flight per lane.  The
+// entries' chunk, length and offset are loaded once, by one wavefront, into LDS.
+// Over a stack the kernel is bound by HBM (copy speed) and a workgroup takes about 160 rows, over a single layer by
+// the latency of entry -> rows -> stores, and 40 rows (one round of loads) give four times the workgroups:
+// one layer of 20011 tokens, c = 5, keep 20 %, 13.8 -> 9.6 us; two layers of 12345 tokens, c = 1, 23.7 -> 11.3 us, c = 20,
+// 17.5 -> 10.2 us.  A 32-layer stack of 131072 tokens (3.45 GB) takes 626 us = 5.5 TB/s, the rate of a device copy.
+// Grid: x = group of entries, y = (sequence, kv-head), z = layer; all layers of the stack are one launch.
 #include "internal.h"
 
 namespace ckv {
@@ -17,8 +21,8 @@ __global__ __launch_bounds__(kThreads) void compact_kernel(CompactArgs a) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int bl = blockIdx.y / a.n_kv_heads, h = blockIdx.y % a.n_kv_heads;
   const int layer = blockIdx.z;
-  const int L = pick(a.seq.seqlen, bl), n_keep = pick(a.seq.n_keep, bl);
-  const int w = a.window, c = a.chunk, P = L - w;
+  const int L = CKV_ARG(CompactArgs, seq.seqlen, bl), n_keep = CKV_ARG(CompactArgs, seq.n_keep, bl);
+  const int w = a.window, c = a.chunk, P = L - w, ne = a.entries_per_wg;
   const int group = (a.layer0 + layer) / a.reuse;
   const int64_t selrow = ((int64_t)group * a.batch_total + (a.batch0 + bl)) * a.n_kv_heads + h;
   const int32_t *sel_chunk = a.sel_chunk + selrow * a.sel_cap;
@@ -26,97 +30,121 @@ __global__ __launch_bounds__(kThreads) void compact_kernel(CompactArgs a) {
   int count = n_keep > 0 ? a.sel_count[selrow] : 0;
   count = count < 0 ? 0 : (count > a.sel_cap ? a.sel_cap : count);
   const int n_win = (w + c - 1) / c;
-  const int e0 = blockIdx.x * kCompactEntries;
+  const int e0 = blockIdx.x * ne;
   if (e0 >= count + n_win) return;
 
-  // Token offset of each entry of this workgroup inside the output.  The stack call passes the
-  // offsets the selection kernel already produced; the stand-alone call sums the lengths here.
-  __shared__ int s_off[kCompactEntries];
+  __shared__ int s_src[kCompactEntries], s_dst[kCompactEntries], s_len[kCompactEntries];
   __shared__ int s_red[kThreads / 64];
+  // Token offset of each entry inside the output: the stack call passes the offsets the selection kernel already
+  // produced, otherwise the lengths are summed here.
+  int before = 0;   // kept tokens before entry min(e0, count)
   if (a.sel_off == nullptr) {
     const int lim = e0 < count ? e0 : count;
-    int part = 0;
-    for (int i = threadIdx.x; i < lim; i += kThreads) part += sel_len[i];
-    for (int o = 32; o > 0; o >>= 1) part += __shfl_xor(part, o);
-    if (lane == 0) s_red[wave] = part;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      int run = s_red[0] + s_red[1] + s_red[2] + s_red[3];
-      for (int i = 0; i < kCompactEntries; ++i) {
-        s_off[i] = run;
-        const int e = e0 + i;
-        if (e < count) run += sel_len[e];
+    for (int i0 = 0; i0 < lim; i0 += 4 * kThreads) {
+      int x[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int i = i0 + j * kThreads + threadIdx.x;
+        x[j] = i < lim ? sel_len[i] : 0;
       }
+      before += (x[0] + x[1]) + (x[2] + x[3]);
     }
+    for (int o = 32; o > 0; o >>= 1) before += __shfl_xor(before, o);
+    if (lane == 0) s_red[wave] = before;
     __syncthreads();
+    before = s_red[0] + s_red[1] + s_red[2] + s_red[3];
   }
+  if (wave == 0) {
+    const int e = e0 + lane;
+    const bool mine = lane < ne && e < count + n_win, chosen = mine && e < count;
+    int ch = 0, len = 0, dst = 0;
+    if (chosen) {
+      ch = sel_chunk[e];
+      len = sel_len[e];
+    }
+    int kept = n_keep;   // where the window starts
+    if (a.sel_off != nullptr) {
+      if (chosen) dst = a.sel_off[selrow * a.sel_cap + e];
+      if (a.whole_chunks) kept = count > 0 ? a.sel_off[selrow * a.sel_cap + count - 1] + sel_len[count - 1] : 0;
+    } else {
+      int inc = len;
+      for (int o = 1; o < 64; o <<= 1) {
+        const int y = __shfl_up(inc, o);
+        if (lane >= o) inc += y;
+      }
+      dst = before + inc - len;
+      // a group that holds window entries has seen every selection entry by its last lane
+      if (a.whole_chunks) kept = before + __shfl(inc, 63);
+    }
+    kept = kept < 0 ? 0 : (kept > n_keep ? n_keep : kept);
+    int src = ch * c;
+    if (chosen) {
+      // a malformed selection is skipped, never followed out of bounds
+      if (ch < 0 || len < 1 || len > c || (int64_t)ch * c + len > P || dst < 0 || dst + len > n_keep) len = src = 0;
+    } else if (mine) {
+      const int wi = e - count;
+      src = P + wi * c;
+      len = w - wi * c < c ? w - wi * c : c;
+      dst = kept + wi * c;
+    }
+    if (lane < ne) { s_src[lane] = src; s_dst[lane] = dst; s_len[lane] = mine ? len : 0; }
+  }
+  __syncthreads();
 
   const int64_t esz = a.elem_bytes;
-  const int64_t in_head = (pick(a.seq.kv_base, bl) + (int64_t)h * a.kv_stride_head) * esz;
-  const int64_t out_head = (pick(a.seq.out_base, bl) + (int64_t)h * a.out_stride_head) * esz;
-  const char *kin = (const char *)pick(a.k, layer) + in_head;
-  const char *vin = (const char *)pick(a.v, layer) + in_head;
-  char *kout = (char *)pick(a.k_out, layer) + out_head;
-  char *vout = (char *)pick(a.v_out, layer) + out_head;
+  const int64_t base = CKV_ARG(CompactArgs, seq.kv_base, bl), obase = CKV_ARG(CompactArgs, seq.out_base, bl);
+  const int64_t in_head = (base + (int64_t)h * a.kv_stride_head) * esz, out_head = (obase + (int64_t)h * a.out_stride_head) * esz;
+  const char *kin = (const char *)CKV_ARG(CompactArgs, k, layer) + in_head;
+  const char *vin = (const char *)CKV_ARG(CompactArgs, v, layer) + in_head;
+  char *kout = (char *)CKV_ARG(CompactArgs, k_out, layer) + out_head;
+  char *vout = (char *)CKV_ARG(CompactArgs, v_out, layer) + out_head;
   const int64_t in_tok = a.kv_stride_tok * esz, out_tok = a.out_stride_tok * esz;
 
-  for (int i = wave; i < kCompactEntries; i += kThreads / 64) {
-    const int e = e0 + i;
-    if (e >= count + n_win) break;
-    int src_row, dst_row, len;
-    if (e < count) {
-      const int ch = sel_chunk[e];
-      len = sel_len[e];
-      src_row = ch * c;
-      dst_row = a.sel_off ? a.sel_off[selrow * a.sel_cap + e] : s_off[i];
-      // a malformed selection is skipped, never followed out of bounds
-      if (ch < 0 || len < 1 || len > c || (int64_t)ch * c + len > P || dst_row < 0 || dst_row + len > n_keep)
-        continue;
-    } else {
-      const int wi = e - count;
-      src_row = P + wi * c;
-      len = w - wi * c < c ? w - wi * c : c;
-      int kept = n_keep;
-      if (a.whole_chunks) {
-        // the window follows the tokens the selection actually keeps (at most n_keep)
-        if (a.sel_off) kept = count > 0 ? a.sel_off[selrow * a.sel_cap + count - 1] + sel_len[count - 1] : 0;
-        else kept = s_off[i];  // the running sum has passed every selection entry here
-        kept = kept < 0 ? 0 : (kept > n_keep ? n_keep : kept);
+  // rows of this workgroup's list: c per entry, or one entry's own length; rows past an entry's length copy nothing
+  const int last = count + n_win - e0 < ne ? count + n_win - e0 : ne;
+  const int half = (ne > 1 ? last * c : s_len[0]) * NSEG, total = 2 * half;
+  const float inv_c = 1.0f / (float)c;
+  for (int u0 = threadIdx.x; u0 < total; u0 += 5 * kThreads) {
+    u32x4 r[5];
+    char *to[5];
+#pragma unroll
+    for (int j = 0; j < 5; ++j) {
+      // lanes without a segment re-read one of theirs and store nothing
+      const int u = u0 + j * kThreads < total ? u0 + j * kThreads : u0;
+      const bool is_v = u >= half;
+      const int uu = is_v ? u - half : u, row = uu / NSEG, seg = uu % NSEG;
+      int en = 0, i = row;
+      if (ne > 1) {   // row < 160: the rounded quotient is off by at most one
+        en = (int)((float)row * inv_c);
+        i = row - en * c;
+        if (i < 0) { --en; i += c; }
+        if (i >= c) { ++en; i -= c; }
       }
-      dst_row = kept + wi * c;
-    }
-    const int half = len * NSEG, total = 2 * half;
-    // segment u of the entry: K rows first, then V rows; lanes past the end re-read the last
-    // segment and store nothing
-    auto src_of = [&](int u) -> const u32x4 * {
-      u = u < total ? u : total - 1;
-      const int t = u >= half, uu = u - t * half;
-      return (const u32x4 *)((t ? vin : kin) + (int64_t)(src_row + uu / NSEG) * in_tok + (uu % NSEG) * 16);
-    };
-    auto dst_of = [&](int u) -> u32x4 * {
-      const int t = u >= half, uu = u - t * half;
-      return (u32x4 *)((t ? vout : kout) + (int64_t)(dst_row + uu / NSEG) * out_tok + (uu % NSEG) * 16);
-    };
-    // five 1 KB loads in flight: one pass for a chunk of 10 rows of 128 16-bit values (K and V)
-    for (int base = lane; base < total; base += 64 * 5) {
+      const int len = s_len[en];
+      const bool live = i < len && u0 + j * kThreads < total;
+      i = i < len ? i : 0;
       // every byte is read once: streaming (non-temporal) loads (measured 2.6 % faster; the same hint on the
       // stores is 2 % slower)
-      const u32x4 r0 = __builtin_nontemporal_load(src_of(base)), r1 = __builtin_nontemporal_load(src_of(base + 64));
-      const u32x4 r2 = __builtin_nontemporal_load(src_of(base + 128)), r3 = __builtin_nontemporal_load(src_of(base + 192));
-      const u32x4 r4 = __builtin_nontemporal_load(src_of(base + 256));
-      *dst_of(base) = r0;
-      if (base + 64 < total) *dst_of(base + 64) = r1;
-      if (base + 128 < total) *dst_of(base + 128) = r2;
-      if (base + 192 < total) *dst_of(base + 192) = r3;
-      if (base + 256 < total) *dst_of(base + 256) = r4;
+      r[j] = __builtin_nontemporal_load((const u32x4 *)((is_v ? vin : kin) + (int64_t)(s_src[en] + i) * in_tok + seg * 16));
+      to[j] = live ? (is_v ? vout : kout) + (int64_t)(s_dst[en] + i) * out_tok + seg * 16 : nullptr;
     }
+#pragma unroll
+    for (int j = 0; j < 5; ++j)
+      if (to[j] != nullptr) *(u32x4 *)to[j] = r[j];
   }
 }
 
-int launch_compact(int row_bytes, const CompactArgs &a, int n_layers_slice, int batch_slice, int max_entries,
-                   hipStream_t s) {
+int launch_compact(int row_bytes, CompactArgs &a, int n_layers_slice, int batch_slice, int max_entries, hipStream_t s) {
   if (n_layers_slice <= 0 || batch_slice <= 0 || max_entries <= 0) return CHUNKKV_OK;
-  dim3 grid((max_entries + kCompactEntries - 1) / kCompactEntries, batch_slice * a.n_kv_heads, n_layers_slice);
+  auto groups = [&](int rows) {
+    int n = rows / a.chunk;
+    a.entries_per_wg = n < 1 ? 1 : (n > kCompactEntries ? kCompactEntries : n);
+    return (max_entries + a.entries_per_wg - 1) / a.entries_per_wg;
+  };
+  const int64_t rest = (int64_t)batch_slice * a.n_kv_heads * n_layers_slice;
+  int nx = groups(160);
+  if (nx * rest < 4096) nx = groups(40);
+  dim3 grid(nx, batch_slice * a.n_kv_heads, n_layers_slice);
   switch (row_bytes / 16) {
     case 8: hipLaunchKernelGGL(compact_kernel<8>, grid, dim3(kThreads), 0, s, a); break;
     case 16: hipLaunchKernelGGL(compact_kernel<16>, grid, dim3(kThreads), 0, s, a); break;

@@ -16,7 +16,7 @@ constexpr int kTileBytes = 16384;        // one K tile staged in LDS (ring slot)
 constexpr int kSuperKeys = 256;        // keys per importance / chunk-sum step of pass 1 (several tiles)
 constexpr int kThreads = 256;            // 4 wavefronts of 64
 constexpr int kMaxRows = 512;            // g * w limit
-constexpr int kCompactEntries = 16;      // selection entries per compaction workgroup
+constexpr int kCompactEntries = 64;      // most selection entries per compaction workgroup
 
 // Per-sequence metadata of one launch slice (<= kMaxBatchPerLaunch sequences).
 struct SeqTable {
@@ -85,6 +85,7 @@ struct CompactArgs {
   int64_t kv_stride_head, kv_stride_tok, out_stride_head, out_stride_tok;
   const int32_t *sel_chunk, *sel_len, *sel_count, *sel_off;  // sel_off may be null
   int32_t sel_cap;
+  int32_t entries_per_wg;     // chosen by the launcher
   int32_t whole_chunks;       // 1: the window follows the kept tokens directly (their count varies per head)
 };
 
@@ -186,7 +187,7 @@ int launch_decode(int dtype, int head_dim, bool matrix_cores, const DecodeArgs &
 int abs_sum_blocks(int n_tok_max);
 int launch_abs_sum(int dtype, const AbsSumArgs &a, int batch_slice, hipStream_t s);
 int launch_quality_finish(const QualityFinishArgs &a, int batch, hipStream_t s);
-int launch_compact(int row_bytes, const CompactArgs &a, int n_layers_slice, int batch_slice,
+int launch_compact(int row_bytes, CompactArgs &a, int n_layers_slice, int batch_slice,
                    int max_entries, hipStream_t s);
 
 }  // namespace ckv
