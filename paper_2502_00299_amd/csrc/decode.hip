@@ -384,9 +384,11 @@ __global__ __launch_bounds__(kCombineThreads) void decode_combine_kernel(DecodeA
     for (int e = 0; e < 4; ++e) acc[e] *= f0;
 #pragma unroll
     for (int u = 0; u < UN; ++u) {
-      const float f = s0 + u * NG < used ? __builtin_amdgcn_exp2f(p[u].x - mm) : 0.f;
+      const bool on = s0 + u * NG < used;   // what was read in place of a missing range must not count, be it infinite
+      const float f = on ? __builtin_amdgcn_exp2f(p[u].x - mm) : 0.f;
       lsum += p[u].y * f;
-      acc[0] += o4[u].x * f; acc[1] += o4[u].y * f; acc[2] += o4[u].z * f; acc[3] += o4[u].w * f;
+      acc[0] += on ? o4[u].x * f : 0.f; acc[1] += on ? o4[u].y * f : 0.f;
+      acc[2] += on ? o4[u].z * f : 0.f; acc[3] += on ? o4[u].w * f : 0.f;
     }
     m = mm;
   }

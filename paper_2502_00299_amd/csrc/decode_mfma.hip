@@ -46,6 +46,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef __fp16 fp16x2 __attribute__((ext_vector_type(2)));
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kStepKeys = 32;
 static constexpr float kNegBig = -1.0e30f;
@@ -98,6 +99,7 @@ __global__ __launch_bounds__(NW * 64, 1) void decode_mfma_kernel(DecodeArgs a) {
   constexpr int NMT = HD / 16;              // 16-dim output tiles
   constexpr int NSET = G == 4 ? 1 : 2;      // products per output tile
   constexpr bool BF = DT == CHUNKKV_BF16;
+  const u16x2 kLeastPart = BF ? u16x2{0x0080, 0x0080} : u16x2{0x0001, 0x0001};
 
   extern __shared__ __align__(16) char smem[];
 
@@ -278,6 +280,17 @@ __global__ __launch_bounds__(NW * 64, 1) void decode_mfma_kernel(DecodeArgs a) {
         else { pf[0][i2] = part == 0 ? w0 : w1; pf[1][i2] = w2; }
       }
     }
+
+    // No part is zero: an infinite value has an infinite product with every weight, and with a zero part it would be
+    // NaN.  The least part is 2^-126 (bf16) or 2^-24 before its scale of 2^-15 to 2^-35 (fp16); rows that are not there
+    // read as zero values.
+#pragma unroll
+    for (int st = 0; st < NSET; ++st)
+#pragma unroll
+      for (int i2 = 0; i2 < 4; ++i2) {
+        const uint32_t w = pf[st][i2];   // a scalar: a bit cast of a vector's element takes its first one
+        pf[st][i2] = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, w), kLeastPart));
+      }
 
     // behind V of step s: the next NST - 1 slot pairs and K of step s + NST
     __builtin_amdgcn_s_waitcnt(vm_imm((2 * NST - 1) * NLD));

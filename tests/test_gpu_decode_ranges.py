@@ -91,3 +91,25 @@ def test_strides_past_32_bit_offsets(lib):
     q, k, v = (torch.randn(s, generator=gen, device=DEV).to(torch.bfloat16) for s in ((hq, d), (hkv, n, d), (hkv, n, d)))
     out, lse = run(lib, torch.bfloat16, n, hq, hkv, d, k, v, q, stride_tok=(1 << 22) + 64)   # 259 rows of 8 MB: past 2^31
     check(out, lse, q, k, v, n)
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
+@pytest.mark.parametrize("n,hq,d", [(200, 4, 128), (1000, 7, 128), (5000, 4, 64)])
+def test_infinite_values_stay_infinite(lib, dtype, n, hq, d):
+    """An infinity in V under an ordinary weight, under an exact power of two (parts of it are zero) and under a tiny
+    one reaches the output as that infinity; everything else stays what it is."""
+    gen = torch.Generator(device=DEV).manual_seed(n)
+    q, k, v = (torch.randn(s, generator=gen, device=DEV).to(dtype) for s in ((hq, d), (1, n, d), (1, n, d)))
+    q[:, 0], k[0, :, 0] = 4.0, 0.0
+    k[0, n // 2, 0], k[0, 7, 0] = 0.0, -40.0 if d == 128 else -30.0   # token 7: 14 or 15 nats below its like
+    k[0, n - 1] = 0.0
+    inf_at = {1: (n // 2, float("inf")), 2: (7, float("-inf")), 3: (n - 1, float("inf")), 5: (0, float("inf"))}
+    finite = v.clone()
+    for col, (tok, val) in inf_at.items():
+        v[0, tok, col] = val
+    out, lse = run(lib, dtype, n, hq, 1, d, k, v, q)
+    for col, (_, val) in inf_at.items():
+        assert (out[:, col] == val).all(), (col, out[:, col])
+    cols = [i for i in range(d) if i not in inf_at]
+    want, _ = orc.decode_attention(bits(q), bits(k), bits(finite))
+    assert (np.abs(out - want)[:, cols].max(axis=1) / np.abs(want).max(axis=1)).max() <= TOL
