@@ -93,6 +93,15 @@ def test_strides_past_32_bit_offsets(lib):
     check(out, lse, q, k, v, n)
 
 
+def test_cache_past_32_bit_offsets(lib):
+    """Rows 64 KB apart, as in a cache that holds all layers of a token together: 2.6 GB, each range within 2^31 bytes."""
+    n, d, hq, hkv = 40000, 128, 8, 2
+    gen = torch.Generator(device=DEV).manual_seed(4)
+    q, k, v = (torch.randn(s, generator=gen, device=DEV).to(torch.bfloat16) for s in ((hq, d), (hkv, n, d), (hkv, n, d)))
+    out, lse = run(lib, torch.bfloat16, n, hq, hkv, d, k, v, q, stride_tok=32768)
+    check(out, lse, q, k, v, n)
+
+
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
 @pytest.mark.parametrize("n,hq,d", [(200, 4, 128), (1000, 7, 128), (5000, 4, 64)])
 def test_infinite_values_stay_infinite(lib, dtype, n, hq, d):
