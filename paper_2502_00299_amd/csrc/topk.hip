@@ -27,6 +27,7 @@ constexpr int kTopkList = 512;   // candidates ranked by comparing all pairs
 __device__ __forceinline__ uint32_t order_key(float x) {
   uint32_t u = __float_as_uint(x);
   if (u == 0x80000000u) u = 0;  // -0 ranks as +0
+  if (u == 0xFFFFFFFFu) u = 0xFFFFFFFEu;   // key 0 is no chunk's: the lowest NaN shares the next one's
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 

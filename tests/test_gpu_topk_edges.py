@@ -50,3 +50,23 @@ def test_selection_is_exact(lib, C, kind, whole):
             assert k == len(want[0])
             assert np.array_equal(sc[h, :k].cpu().numpy(), want[0]) and np.array_equal(sl[h, :k].cpu().numpy(), want[1])
             assert (sc[h, k:] == -7).all() and (sl[h, k:] == -7).all()
+
+
+@pytest.mark.parametrize("C", [100, 3000, 20000])
+def test_the_lowest_nan_is_selected_last(lib, C):
+    """A score whose bits are all ones is the lowest of all keys: never ahead of a number, in no form of the kernel."""
+    c, w, keep = 3, 2, 3 * (C // 2)
+    s = scores_of("spread", C, 1, np.random.default_rng(C))
+    t = torch.from_numpy(s).to(DEV)
+    t.view(torch.int32)[0, 5] = -1
+    prob = lib.Problem(1, 1, 64, w, c, lib.F32, [C * c + w], [keep], [0], (C * c + w) * 64, 64)
+    sc = torch.full((1, prob.sel_cap), -7, dtype=torch.int32, device=DEV)
+    sl, n = torch.full_like(sc, -7), torch.full((1,), -7, dtype=torch.int32, device=DEV)
+    full = torch.zeros((1, prob.score_cap), dtype=torch.float32, device=DEV)
+    full.view(torch.int32)[:, :C] = t.view(torch.int32)
+    lib.chunkkv_chunk_topk(prob, full, sc, sl, n)
+    torch.cuda.synchronize()
+    s[0, 5] = -1.0
+    want = orc.chunk_topk(s[0], C * c, c, keep)
+    k = int(n[0])
+    assert k == len(want[0]) and np.array_equal(sc[0, :k].cpu().numpy(), want[0]) and np.array_equal(sl[0, :k].cpu().numpy(), want[1])
