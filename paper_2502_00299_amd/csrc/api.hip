@@ -156,6 +156,22 @@ inline int64_t decode_even_rows(int64_t rows_times_wgs) {
   const int64_t r = (rows_times_wgs + kDecodeTargetWorkgroups - 1) / kDecodeTargetWorkgroups;
   return r < kDecodeMinRows ? kDecodeMinRows : (r + 127) / 128 * 128;
 }
+// The size of the workspace that callers see is that of about kDecodeTargetWorkgroups ranges of one length over the whole
+// batch, whatever the kernel makes of it: workspaces and the static call's limit do not depend on how a cache happens to
+// be cut.  Returns that number of ranges of the longest sequence.
+int64_t decode_even_splits(const chunkkv_problem *p, bool compacted) {
+  int64_t n_max = 1, n_sum = 0;
+  for (int b = 0; b < p->batch; ++b) {
+    const int64_t n = decode_tokens(p, compacted, b);
+    n_max = n > n_max ? n : n_max;
+    n_sum += n;
+  }
+  const int g = p->n_q_heads / p->n_kv_heads;
+  const int G = p->dtype != CHUNKKV_F32 && g > 4 ? 8 : (g > 2 ? 4 : g);
+  const int64_t launches = (p->batch + kMaxBatchPerLaunch - 1) / kMaxBatchPerLaunch;
+  const int64_t rows = decode_even_rows(n_sum * p->n_kv_heads * ((g + G - 1) / G) / launches);
+  return (n_max + rows - 1) / rows;
+}
 // rows[i]: rows per range of sequence b0 + i; returns the largest number of ranges
 int decode_rows(const chunkkv_problem *p, bool compacted, int b0, int nb, int32_t *rows) {
   const bool mfma = decode_on_matrix_cores(p, compacted);
@@ -168,8 +184,14 @@ int decode_rows(const chunkkv_problem *p, bool compacted, int b0, int nb, int32_
     n_sum += n;
     n_max = n > n_max ? n : n_max;
   }
+  // a very uneven batch: no more ranges of its longest sequence than the static scratch or the even cut has room for
+  int64_t most = (CHUNKKV_STATIC_SCRATCH_BYTES - 512) / ((int64_t)p->batch * p->n_q_heads * (p->head_dim * 4 + 8));
+  const int64_t n_even = decode_even_splits(p, compacted);
+  most = most > n_even ? most : n_even;
+  const int64_t least = ((n_max + most - 1) / most + kDecodeStepRows - 1) / kDecodeStepRows * kDecodeStepRows;
   if (!mfma) {
-    const int64_t r = decode_even_rows(n_sum * per_seq);
+    int64_t r = decode_even_rows(n_sum * per_seq);
+    if (r < least) r = (least + 127) / 128 * 128;
     for (int i = 0; i < nb; ++i) rows[i] = (int32_t)r;
     return (int)((n_max + r - 1) / r);
   }
@@ -194,6 +216,7 @@ int decode_rows(const chunkkv_problem *p, bool compacted, int b0, int nb, int32_
   rounds = rounds < 1 ? 1 : (rounds > kDecodeMaxRounds ? kDecodeMaxRounds : rounds);
   const int64_t limit = decode_row_limit(p, compacted);
   int64_t r = n_max <= kDecodeDirectRows ? kDecodeDirectRows : shortest(rounds * kDecodeCUs);
+  r = r > least ? r : least;
   r = r < limit ? r : limit;
   for (int i = 0; i < nb; ++i) {
     const int64_t n = decode_tokens(p, compacted, b0 + i), s = n > 0 ? (n + r - 1) / r : 1;
@@ -214,19 +237,7 @@ int decode_plan(const chunkkv_problem *p, bool compacted, DecodePlan *pl) {
   pl->off_ml = 0;
   pl->off_o = align256(heads * pl->n_split * sizeof(float2));
   pl->total = pl->off_o + align256(heads * pl->n_split * p->head_dim * sizeof(float));
-  // The size callers see is that of about kDecodeTargetWorkgroups ranges over the whole batch, whatever the kernel
-  // makes of it: workspaces and the static call's limit do not depend on how a cache happens to be cut.
-  int64_t n_max = 1, n_sum = 0;
-  for (int b = 0; b < p->batch; ++b) {
-    const int64_t n = decode_tokens(p, compacted, b);
-    n_max = n > n_max ? n : n_max;
-    n_sum += n;
-  }
-  const int g = p->n_q_heads / p->n_kv_heads;
-  const int G = p->dtype != CHUNKKV_F32 && g > 4 ? 8 : (g > 2 ? 4 : g);
-  const int64_t launches = (p->batch + kMaxBatchPerLaunch - 1) / kMaxBatchPerLaunch;
-  const int64_t rows_even = decode_even_rows(n_sum * p->n_kv_heads * ((g + G - 1) / G) / launches);
-  const size_t n_even = (size_t)((n_max + rows_even - 1) / rows_even);
+  const size_t n_even = (size_t)decode_even_splits(p, compacted);
   const size_t even = align256(heads * n_even * sizeof(float2)) + align256(heads * n_even * p->head_dim * sizeof(float));
   pl->total = even > pl->total ? even : pl->total;
   return CHUNKKV_OK;

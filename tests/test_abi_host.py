@@ -227,6 +227,15 @@ def test_missing_library_fails_loudly(tmp_path):
         pkg.load_library(str(tmp_path / "nope.so"))
 
 
+def test_static_decode_takes_what_the_even_cut_fits():
+    """One long sequence among short ones: cutting it finer must not push the partial results past the static scratch."""
+    lens = [30848] + [33] * 15
+    p = pkg.Problem(8, 1, 128, 16, 10, pkg.BF16, lens, [1] * 16, [0] * 16, 128 * 40000, 128)
+    even = 16 * 8 * ((30848 + 255) // 256) * (128 * 4 + 8)
+    assert even < 8 << 20
+    assert even <= pkg.chunkkv_decode_workspace_bytes(p, False) <= 8 << 20
+
+
 def test_decode_argument_checks(lib):
     p = good(out_base=[0], out_stride_head=848 * 128, out_stride_tok=128)
     cp = p.as_c()
