@@ -1,10 +1,14 @@
 """Host-side checks of the C-ABI library that need no GPU: it loads, exports every symbol the header
 declares, and every argument check returns its status before anything is enqueued."""
+import copy
 import ctypes as C
 import os
+import pickle
 import re
 
+import numpy as np
 import pytest
+import torch
 
 import paper_2502_00299_amd as pkg
 
@@ -220,6 +224,63 @@ def test_quality_metrics_argument_checks(lib):
     assert call(wsb=ws - 1) == 4
     bad = good(out_base=[0], out_stride_head=848 * 128, out_stride_tok=100)
     assert pkg.chunkkv_quality_workspace_bytes(bad) == 0
+
+
+def contents(cp):
+    """Everything the C struct of a Problem tells the library."""
+    arrays = ("seqlen", "n_keep", "kv_base", "out_base")
+    return {n: getattr(cp, n)[:cp.batch] if n in arrays else getattr(cp, n) for n, _ in cp._fields_}
+
+
+HOLDERS = {"list": list, "array": np.array, "tensor": torch.tensor, "list of tensors": lambda x: [torch.tensor(i) for i in x]}
+
+
+@pytest.mark.parametrize("holder", sorted(HOLDERS))
+@pytest.mark.parametrize("field", ["seqlen", "n_keep", "kv_base", "out_base"])
+def test_kept_struct_follows_changes_in_place(lib, field, holder):
+    """A decoding loop that adds to its lengths or moves its offsets: the next call sees the new ones."""
+    values = dict(seqlen=[8192, 4096], n_keep=[816, 400], kv_base=[0, 8192 * 1024], out_base=[0, 848 * 1024])
+    p = good(**{n: HOLDERS[holder](x) for n, x in values.items()}, out_stride_head=128, out_stride_tok=1024, score_cap=7000)
+    before = pkg.chunkkv_workspace_bytes(p, 1, 1)
+    assert contents(p._c()._obj) == contents(p.as_c())
+    if holder == "list of tensors":
+        getattr(p, field)[1] += 8
+    else:
+        getattr(p, field)[0] += 8
+    assert contents(p._c()._obj) == contents(p.as_c())
+    assert contents(p._c()._obj)[field] != values[field]
+    if field == "seqlen":
+        p.seqlen[0] += 60000
+        assert pkg.chunkkv_workspace_bytes(p, 1, 1) > before
+
+
+def test_kept_struct_follows_assignments(lib):
+    p = good()
+    for name, value in dict(window=16, chunk=5, dtype=pkg.F16, sel_cap=2000, score_cap=3000, softmax_scale=0.25, flags=2, n_q_heads=16,
+                            n_kv_heads=4, head_dim=64, kv_stride_head=64, kv_stride_tok=256, out_stride_head=128, out_stride_tok=512,
+                            seqlen=[4096], n_keep=[17], kv_base=[64], out_base=[128]).items():
+        was = contents(p._c()._obj)[name]
+        setattr(p, name, value)
+        now = contents(p._c()._obj)
+        assert now == contents(p.as_c()) and now[name] == value != was
+    vars(p)["window"] = 8
+    assert p._c()._obj.window == 8
+    p.softmax_scale = torch.tensor(0.5)
+    p.window = torch.tensor(4)
+    p._c()
+    p.window += 1
+    p.softmax_scale += 0.25
+    assert (p._c()._obj.window, p._c()._obj.softmax_scale) == (5, 0.75)
+
+
+def test_kept_struct_is_not_a_field(lib):
+    p = good()
+    p._c()
+    assert pkg.Problem(**vars(p)) == p
+    for q in (copy.copy(p), copy.deepcopy(p), pickle.loads(pickle.dumps(p))):
+        assert q == p and q._c() is not p._c() and contents(q._c()._obj) == contents(p._c()._obj)
+        q.window = 16
+        assert p._c()._obj.window == 32 and q._c()._obj.window == 16
 
 
 def test_missing_library_fails_loudly(tmp_path):
