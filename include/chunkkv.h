@@ -221,6 +221,8 @@ int chunkkv_jaccard(const chunkkv_problem *prob, int32_t n_groups, const int32_t
  * Products and sums are fp32 (16-bit inputs are exact in fp32): an output element differs from the exact value
  * by about 1e-6 of the largest magnitude in its head's output row (an element near zero is a difference of
  * large terms, so the error is relative to the row, not to the element); lse to about 1e-6 absolute.
+ * Softmax weights keep their size however small: exact to fp32 for fp32 and bf16 caches, and for fp16 caches to 2^-72 of
+ * the head's largest weight.  An infinity in V reaches the output as one.
  * Asynchronous on `stream`; two launches; no allocation.  Errors as for chunkkv_score.                  */
 size_t chunkkv_decode_workspace_bytes(const chunkkv_problem *prob, int32_t compacted);
 int chunkkv_decode_attention(const chunkkv_problem *prob, int32_t compacted, const int32_t *kv_len, const void *q,

@@ -15,11 +15,18 @@
 //            head column per lane), V^T comes out of LDS with transposing reads (ds_read_b64_tr_b16).
 //
 // 16 head columns are more than the G = 4 or 8 heads of a workgroup, and the spare ones carry precision: a weight is
-// an fp32 number and the operands are 16 bits wide, so it is cut into three exact parts (bf16: the upper 8 bits of
-// what is left, three times; fp16: 11 bits, the parts scaled up by 2^15, 2^25 and 2^35 so that they stay in range).
-// With G = 4 the parts of a head occupy columns h, h + 4, h + 8 of one product; with G = 8 the first two parts
-// share one product and the third takes a second one.  Products of 16-bit numbers are exact in the fp32
-// accumulators, so nothing is rounded below fp32.
+// an fp32 number and the operands are 16 bits wide, so it is cut into parts whose sum it is.  bf16: the upper 8 bits of
+// what is left, three times, exact.  fp16: 11 bits of what is left, four times, the parts scaled up by 2^15, 2^26, 2^37
+// and 2^48 so that they stay in range: exact for weights down to 2^-49 (34 nats below the reference, which is within a
+// factor of 2 of the largest weight so far), and below that what is cut off is less than 2^-72.
+// With G = 4 the parts of a head occupy columns h, h + 4, h + 8 and h + 12 of one product; with G = 8 the first two parts
+// share one product and the others a second one.  Products of 16-bit numbers are exact in the fp32 accumulators, so
+// nothing else is rounded below fp32.
+//
+// A part may be zero under a weight that is not, and zero times an infinite value is NaN.  So a workgroup whose merged
+// output holds something that is not finite goes through its rows a second time with every part at least the type's
+// least number, and takes those elements from there: an infinity stays one.  Ordinary caches never do; the check costs
+// them one barrier.
 //
 // The reference of the online softmax is lazy: it moves when a step's weights of a head column reach 16 (bf16: their
 // sum; fp16: when one reaches 1.97, the range its scaled parts have room for), a few times per wavefront.  The bound
@@ -87,9 +94,16 @@ __device__ __forceinline__ void read_v4(uint32_t a0, uint32_t a1, uint32_t a2, u
 
 constexpr int vm_imm(int n) { return (n & 0xF) | ((n >> 4) << 14) | 0x0F70; }
 
+// The integer form of isfinite, kept from the optimizer: the build lets it assume that nothing is NaN.
+__device__ __forceinline__ bool finite_bits(float x) {
+  uint32_t u = __float_as_uint(x);
+  asm("" : "+v"(u));
+  return (u & 0x7F800000u) != 0x7F800000u;
+}
+
 // DT: bf16 or fp16, HD: head dim, G: 4 or 8 query heads per workgroup, NW: wavefronts, NST: K/V slot pairs per wavefront
 template <int DT, int HD, int G, int NW, int NST>
-__global__ __launch_bounds__(NW * 64, 1) void decode_mfma_kernel(DecodeArgs a) {
+__global__ __launch_bounds__(NW * 64, 2) void decode_mfma_kernel(DecodeArgs a) {
   constexpr int ROWB = HD * 2;              // bytes per row
   constexpr int SEGS = ROWB / 16;           // 16-byte segments per row
   constexpr int RPL = 1024 / ROWB;          // rows one 1 KB load fills
@@ -102,6 +116,7 @@ __global__ __launch_bounds__(NW * 64, 1) void decode_mfma_kernel(DecodeArgs a) {
   const u16x2 kLeastPart = BF ? u16x2{0x0080, 0x0080} : u16x2{0x0001, 0x0001};
 
   extern __shared__ __align__(16) char smem[];
+  __shared__ volatile int s_again;   // some element of the merged output is not finite
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -165,8 +180,6 @@ __global__ __launch_bounds__(NW * 64, 1) void decode_mfma_kernel(DecodeArgs a) {
   };
   auto kslot = [&](int s) { return ring + (uint32_t)((s % NST) * (2 * SLOT)); };
   auto vslot = [&](int s) { return ring + (uint32_t)((s % NST) * (2 * SLOT) + SLOT); };
-#pragma unroll
-  for (int s = 0; s < NST; ++s) { issue(a.k, koff, s, kslot(s)); issue(a.v, voff, s, vslot(s)); }
 
   // LDS addresses: K fragment of row 16 t + n, segment 4 ks + q; V piece of keys 16 t + 4 q + (n / 4), dims 16 mt + 4 (n % 4)
   uint32_t kaddr[NKS], vaddr[NMT];
@@ -181,174 +194,198 @@ __global__ __launch_bounds__(NW * 64, 1) void decode_mfma_kernel(DecodeArgs a) {
   static_assert(SEGS == 16 || SEGS == 8, "rows 16 apart share the swizzle");
 
   const float c1 = a.scale_log2e;
-  float m = kNegBig, l = 0.f;
-  f32x4 acc[NSET][NMT];
+  if (tid == 0) s_again = 0;
+  uint32_t redo = 0;   // bit i: element tid + 64 NW i of the output was not finite in the first pass
+  for (int pass = 0;; ++pass) {
 #pragma unroll
-  for (int s = 0; s < NSET; ++s)
+    for (int s = 0; s < NST; ++s) { issue(a.k, koff, s, kslot(s)); issue(a.v, voff, s, vslot(s)); }
+    float m = kNegBig, l = 0.f;
+    f32x4 acc[NSET][NMT];
 #pragma unroll
-    for (int mt = 0; mt < NMT; ++mt) acc[s][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int s = 0; s < NSET; ++s)
+#pragma unroll
+      for (int mt = 0; mt < NMT; ++mt) acc[s][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  for (int s = 0; s < nstep; ++s) {
-    // behind K of step s: its V and the slot pairs of the next NST - 1 steps
-    __builtin_amdgcn_s_waitcnt(vm_imm((2 * NST - 1) * NLD));
-    const uint32_t ks_ = kslot(s), vs_ = vslot(s);
-    u32x4 kf[2][NKS];
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-      for (int ks = 0; ks < NKS; ++ks) kf[t][ks] = *(const u32x4 *)(smem + (ks_ + kaddr[ks] + (uint32_t)(t * 16 * ROWB)));
-    f32x4 sc[2];
-#pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      // two chains, added at the end: half the roundings at full magnitude
-      f32x4 even = {0.f, 0.f, 0.f, 0.f}, odd = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int ks = 0; ks < NKS; ks += 2) {
-        even = mma16<DT>(kf[t][ks], qf[ks], even);
-        odd = mma16<DT>(kf[t][ks + 1], qf[ks + 1], odd);
-      }
-      sc[t] = even + odd;
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_waitcnt(0xC07F);   // the fragments are in registers: the K slot is free
-    issue(a.k, koff, s + NST, ks_);
-
-    const int key0 = (wave + s * NW) * kStepKeys;
-    if (key0 + kStepKeys > len) {
+    for (int s = 0; s < nstep; ++s) {
+      // behind K of step s: its V and the slot pairs of the next NST - 1 steps
+      __builtin_amdgcn_s_waitcnt(vm_imm((2 * NST - 1) * NLD));
+      const uint32_t ks_ = kslot(s), vs_ = vslot(s);
+      u32x4 kf[2][NKS];
 #pragma unroll
       for (int t = 0; t < 2; ++t)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) sc[t][i] = key0 + 16 * t + 4 * q + i < len ? sc[t][i] : -3.0e38f;
-    }
-    float p[8];
-    auto weights = [&]() __attribute__((always_inline)) {
+        for (int ks = 0; ks < NKS; ++ks) kf[t][ks] = *(const u32x4 *)(smem + (ks_ + kaddr[ks] + (uint32_t)(t * 16 * ROWB)));
+      f32x4 sc[2];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) p[i] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[i / 4][i % 4], c1, -m));
-    };
-    weights();
-    float sum = ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
-    float over = sum;
-    if constexpr (!BF)
-      over = fmaxf(fmaxf(fmaxf(p[0], p[1]), fmaxf(p[2], p[3])), fmaxf(fmaxf(p[4], p[5]), fmaxf(p[6], p[7])));
-    constexpr float kOver = BF ? 16.f : 1.96875f;   // fp16: 2^15 times it is the largest 11-bit number below 2^16
-    if (__builtin_amdgcn_ballot_w64(over >= kOver) != 0) {
-      // move the reference of the head columns that outgrew it (the four lanes of a column together)
-      float mx = fmaxf(fmaxf(fmaxf(sc[0][0], sc[0][1]), fmaxf(sc[0][2], sc[0][3])), fmaxf(fmaxf(sc[1][0], sc[1][1]), fmaxf(sc[1][2], sc[1][3])));
-      mx = fmaxf(mx, __shfl_xor(mx, 16));
-      mx = fmaxf(mx, __shfl_xor(mx, 32));
-      over = fmaxf(over, __shfl_xor(over, 16));
-      over = fmaxf(over, __shfl_xor(over, 32));
-      const float m_new = over >= kOver ? mx * c1 : m;
-      const float f = __builtin_amdgcn_exp2f(m - m_new);
-      m = m_new;
-      l *= f;
+      for (int t = 0; t < 2; ++t) {
+        // two chains, added at the end: half the roundings at full magnitude
+        f32x4 even = {0.f, 0.f, 0.f, 0.f}, odd = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int st = 0; st < NSET; ++st)
-#pragma unroll
-        for (int mt = 0; mt < NMT; ++mt) acc[st][mt] *= f;
-      weights();
-      sum = ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
-    }
-    l += sum;
-
-    // the weights' parts as B operands: element i = key 4 q + i (i < 4) or 16 + 4 q + i - 4
-    u32x4 pf[NSET];
-#pragma unroll
-    for (int i2 = 0; i2 < 4; ++i2) {
-      if constexpr (BF) {
-        float x[2][NSET];
-#pragma unroll
-        for (int e = 0; e < 2; ++e) {
-          const float p0 = p[2 * i2 + e];
-          const float p1 = p0 - __uint_as_float(__float_as_uint(p0) & 0xFFFF0000u);
-          const float p2 = p1 - __uint_as_float(__float_as_uint(p1) & 0xFFFF0000u);
-          if constexpr (G == 4) x[e][0] = part == 0 ? p0 : (part == 1 ? p1 : p2);
-          else { x[e][0] = part == 0 ? p0 : p1; x[e][1] = p2; }
+        for (int ks = 0; ks < NKS; ks += 2) {
+          even = mma16<DT>(kf[t][ks], qf[ks], even);
+          odd = mma16<DT>(kf[t][ks + 1], qf[ks + 1], odd);
         }
-#pragma unroll
-        for (int st = 0; st < NSET; ++st)   // upper halves: the truncation
-          pf[st][i2] = __builtin_amdgcn_perm(__float_as_uint(x[1][st]), __float_as_uint(x[0][st]), 0x07060302u);
-      } else {
-        const float a0 = p[2 * i2] * 32768.f, b0 = p[2 * i2 + 1] * 32768.f;   // exact
-        const fp16x2 h0 = __builtin_amdgcn_cvt_pkrtz(a0, b0);
-        const float a1 = (a0 - (float)h0[0]) * 1024.f, b1 = (b0 - (float)h0[1]) * 1024.f;
-        const fp16x2 h1 = __builtin_amdgcn_cvt_pkrtz(a1, b1);
-        const float a2 = (a1 - (float)h1[0]) * 1024.f, b2 = (b1 - (float)h1[1]) * 1024.f;
-        const fp16x2 h2 = __builtin_amdgcn_cvt_pkrtz(a2, b2);
-        const uint32_t w0 = __builtin_bit_cast(uint32_t, h0), w1 = __builtin_bit_cast(uint32_t, h1), w2 = __builtin_bit_cast(uint32_t, h2);
-        if constexpr (G == 4) pf[0][i2] = part == 0 ? w0 : (part == 1 ? w1 : w2);
-        else { pf[0][i2] = part == 0 ? w0 : w1; pf[1][i2] = w2; }
+        sc[t] = even + odd;
       }
-    }
+      __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_s_waitcnt(0xC07F);   // the fragments are in registers: the K slot is free
+      issue(a.k, koff, s + NST, ks_);
 
-    // No part is zero: an infinite value has an infinite product with every weight, and with a zero part it would be
-    // NaN.  The least part is 2^-126 (bf16) or 2^-24 before its scale of 2^-15 to 2^-35 (fp16); rows that are not there
-    // read as zero values.
+      const int key0 = (wave + s * NW) * kStepKeys;
+      if (key0 + kStepKeys > len) {
 #pragma unroll
-    for (int st = 0; st < NSET; ++st)
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) sc[t][i] = key0 + 16 * t + 4 * q + i < len ? sc[t][i] : -3.0e38f;
+      }
+      float p[8];
+      auto weights = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) p[i] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[i / 4][i % 4], c1, -m));
+      };
+      weights();
+      float sum = ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
+      float over = sum;
+      if constexpr (!BF)
+        over = fmaxf(fmaxf(fmaxf(p[0], p[1]), fmaxf(p[2], p[3])), fmaxf(fmaxf(p[4], p[5]), fmaxf(p[6], p[7])));
+      constexpr float kOver = BF ? 16.f : 1.96875f;   // fp16: 2^15 times it is the largest 11-bit number below 2^16
+      if (__builtin_amdgcn_ballot_w64(over >= kOver) != 0) {
+        // move the reference of the head columns that outgrew it (the four lanes of a column together)
+        float mx = fmaxf(fmaxf(fmaxf(sc[0][0], sc[0][1]), fmaxf(sc[0][2], sc[0][3])), fmaxf(fmaxf(sc[1][0], sc[1][1]), fmaxf(sc[1][2], sc[1][3])));
+        mx = fmaxf(mx, __shfl_xor(mx, 16));
+        mx = fmaxf(mx, __shfl_xor(mx, 32));
+        over = fmaxf(over, __shfl_xor(over, 16));
+        over = fmaxf(over, __shfl_xor(over, 32));
+        const float m_new = over >= kOver ? mx * c1 : m;
+        const float f = __builtin_amdgcn_exp2f(m - m_new);
+        m = m_new;
+        l *= f;
+#pragma unroll
+        for (int st = 0; st < NSET; ++st)
+#pragma unroll
+          for (int mt = 0; mt < NMT; ++mt) acc[st][mt] *= f;
+        weights();
+        sum = ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
+      }
+      l += sum;
+
+      // the weights' parts as B operands: element i = key 4 q + i (i < 4) or 16 + 4 q + i - 4
+      u32x4 pf[NSET];
 #pragma unroll
       for (int i2 = 0; i2 < 4; ++i2) {
-        const uint32_t w = pf[st][i2];   // a scalar: a bit cast of a vector's element takes its first one
-        pf[st][i2] = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, w), kLeastPart));
+        if constexpr (BF) {
+          float x[2][NSET];
+#pragma unroll
+          for (int e = 0; e < 2; ++e) {
+            const float p0 = p[2 * i2 + e];
+            const float p1 = p0 - __uint_as_float(__float_as_uint(p0) & 0xFFFF0000u);
+            const float p2 = p1 - __uint_as_float(__float_as_uint(p1) & 0xFFFF0000u);
+            if constexpr (G == 4) x[e][0] = part == 0 ? p0 : (part == 1 ? p1 : p2);
+            else { x[e][0] = part == 0 ? p0 : p1; x[e][1] = p2; }
+          }
+#pragma unroll
+          for (int st = 0; st < NSET; ++st)   // upper halves: the truncation
+            pf[st][i2] = __builtin_amdgcn_perm(__float_as_uint(x[1][st]), __float_as_uint(x[0][st]), 0x07060302u);
+        } else {
+          const float a0 = p[2 * i2] * 32768.f, b0 = p[2 * i2 + 1] * 32768.f;   // exact
+          const fp16x2 h0 = __builtin_amdgcn_cvt_pkrtz(a0, b0);
+          const float a1 = (a0 - (float)h0[0]) * 2048.f, b1 = (b0 - (float)h0[1]) * 2048.f;   // what is left of a number below 2^16 is below 2^5
+          const fp16x2 h1 = __builtin_amdgcn_cvt_pkrtz(a1, b1);
+          const float a2 = (a1 - (float)h1[0]) * 2048.f, b2 = (b1 - (float)h1[1]) * 2048.f;
+          const fp16x2 h2 = __builtin_amdgcn_cvt_pkrtz(a2, b2);
+          const float a3 = (a2 - (float)h2[0]) * 2048.f, b3 = (b2 - (float)h2[1]) * 2048.f;
+          const fp16x2 h3 = __builtin_amdgcn_cvt_pkrtz(a3, b3);
+          const uint32_t w0 = __builtin_bit_cast(uint32_t, h0), w1 = __builtin_bit_cast(uint32_t, h1), w2 = __builtin_bit_cast(uint32_t, h2), w3 = __builtin_bit_cast(uint32_t, h3);
+          if constexpr (G == 4) pf[0][i2] = part < 2 ? (part == 0 ? w0 : w1) : (part == 2 ? w2 : w3);
+          else { pf[0][i2] = part == 0 ? w0 : w1; pf[1][i2] = part == 0 ? w2 : w3; }
+        }
       }
 
-    // behind V of step s: the next NST - 1 slot pairs and K of step s + NST
-    __builtin_amdgcn_s_waitcnt(vm_imm((2 * NST - 1) * NLD));
+      // Second pass: no part is zero.  The least one is 2^-126 (bf16) or 2^-24 before its scale (fp16); rows that are not
+      // there read as zero values.
+      if (pass != 0) {
 #pragma unroll
-    for (int m4 = 0; m4 < NMT; m4 += 4) {
-      u32x4 vf[4];
-      read_v4<16 * ROWB>(vs_ + vaddr[m4], vs_ + vaddr[m4 + 1], vs_ + vaddr[m4 + 2], vs_ + vaddr[m4 + 3], vf);
+        for (int st = 0; st < NSET; ++st)
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int st = 0; st < NSET; ++st) acc[st][m4 + i] = mma16<DT>(vf[i], pf[st], acc[st][m4 + i]);
-    }
-    issue(a.v, voff, s + NST, vs_);
-  }
+          for (int i2 = 0; i2 < 4; ++i2) {
+            const uint32_t w = pf[st][i2];   // a scalar: a bit cast of a vector's element takes its first one
+            pf[st][i2] = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, w), kLeastPart));
+          }
+      }
 
-  // ---- parts of a head -> its output (lanes n < G), lanes of a column -> its sum
-  l += __shfl_xor(l, 16);
-  l += __shfl_xor(l, 32);
-  constexpr float kS0 = BF ? 1.f : 0x1p-15f, kS1 = BF ? 1.f : 0x1p-25f, kS2 = BF ? 1.f : 0x1p-35f;
+      // behind V of step s: the next NST - 1 slot pairs and K of step s + NST
+      __builtin_amdgcn_s_waitcnt(vm_imm((2 * NST - 1) * NLD));
 #pragma unroll
-  for (int mt = 0; mt < NMT; ++mt)
+      for (int m4 = 0; m4 < NMT; m4 += 4) {
+        u32x4 vf[4];
+        read_v4<16 * ROWB>(vs_ + vaddr[m4], vs_ + vaddr[m4 + 1], vs_ + vaddr[m4 + 2], vs_ + vaddr[m4 + 3], vf);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const float x = acc[0][mt][i];
-      if constexpr (G == 4) acc[0][mt][i] = x * kS0 + (row_shl<4>(x) * kS1 + row_shl<8>(x) * kS2);
-      else acc[0][mt][i] = x * kS0 + (row_shl<8>(x) * kS1 + acc[1][mt][i] * kS2);
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int st = 0; st < NSET; ++st) acc[st][m4 + i] = mma16<DT>(vf[i], pf[st], acc[st][m4 + i]);
+      }
+      issue(a.v, voff, s + NST, vs_);
     }
-  // ---- merge the wavefronts through LDS, in wavefront order
-  __syncthreads();   // the slots are dead
-  float *s_m = (float *)smem, *s_l = s_m + NW * G, *s_o = s_l + NW * G;   // [NW][G], [NW][G], [NW][G][HD]
-  if (n < G) {
-    if (q == 0) { s_m[wave * G + n] = m; s_l[wave * G + n] = l; }
+
+    // ---- parts of a head -> its output (lanes n < G), lanes of a column -> its sum
+    l += __shfl_xor(l, 16);
+    l += __shfl_xor(l, 32);
+    constexpr float kS0 = BF ? 1.f : 0x1p-15f, kS1 = BF ? 1.f : 0x1p-26f, kS2 = BF ? 1.f : 0x1p-37f, kS3 = BF ? 0.f : 0x1p-48f;
 #pragma unroll
-    for (int mt = 0; mt < NMT; ++mt) *(f32x4 *)(s_o + (wave * G + n) * HD + 16 * mt + 4 * q) = acc[0][mt];
-  }
-  __syncthreads();
-  for (int t = tid; t < G * HD; t += NW * 64) {
-    const int j = t / HD, e = t % HD;
-    if (j0 + j >= g) break;
-    float M = s_m[j];
+    for (int mt = 0; mt < NMT; ++mt)
 #pragma unroll
-    for (int w = 1; w < NW; ++w) M = fmaxf(M, s_m[w * G + j]);
-    float L = 0.f, o = 0.f;
+      for (int i = 0; i < 4; ++i) {
+        const float x = acc[0][mt][i];
+        if constexpr (G == 4) {
+          const float rest = BF ? row_shl<8>(x) : row_shl<8>(x) * kS2 + row_shl<12>(x) * kS3;
+          acc[0][mt][i] = x * kS0 + (row_shl<4>(x) * kS1 + rest);
+        } else {
+          const float y = acc[1][mt][i], rest = BF ? y : y * kS2 + row_shl<8>(y) * kS3;
+          acc[0][mt][i] = x * kS0 + (row_shl<8>(x) * kS1 + rest);
+        }
+      }
+    // ---- merge the wavefronts through LDS, in wavefront order
+    __syncthreads();   // the slots are dead
+    float *s_m = (float *)smem, *s_l = s_m + NW * G, *s_o = s_l + NW * G;   // [NW][G], [NW][G], [NW][G][HD]
+    if (n < G) {
+      if (q == 0) { s_m[wave * G + n] = m; s_l[wave * G + n] = l; }
 #pragma unroll
-    for (int w = 0; w < NW; ++w) {
-      const float f = __builtin_amdgcn_exp2f(s_m[w * G + j] - M);
-      L += s_l[w * G + j] * f;
-      o += s_o[(w * G + j) * HD + e] * f;
+      for (int mt = 0; mt < NMT; ++mt) *(f32x4 *)(s_o + (wave * G + n) * HD + 16 * mt + 4 * q) = acc[0][mt];
     }
-    const int64_t hd = (int64_t)b * a.n_q_heads + (int64_t)h * g + j0 + j;
-    if (a.n_split == 1) {   // one range per head: no merge kernel follows
-      a.out[hd * HD + e] = L > 0.f ? o / L : 0.f;
-      if (a.lse != nullptr && e == 0) a.lse[hd] = L > 0.f ? (M + __builtin_log2f(L)) * 0.6931471805599453f : -__builtin_inff();
-    } else {
-      const int64_t slot = hd * a.n_split + split;
-      if (e == 0) a.part_ml[slot] = make_float2(M, L);
-      a.part_o[slot * HD + e] = o;
+    __syncthreads();
+    uint32_t bad = 0;
+    for (int t = tid, i = 0; t < G * HD; t += NW * 64, ++i) {
+      const int j = t / HD, e = t % HD;
+      if (j0 + j >= g) break;
+      if (pass != 0 && (redo >> i & 1) == 0) continue;
+      float M = s_m[j];
+#pragma unroll
+      for (int w = 1; w < NW; ++w) M = fmaxf(M, s_m[w * G + j]);
+      float L = 0.f, o = 0.f;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) {
+        const float f = __builtin_amdgcn_exp2f(s_m[w * G + j] - M);
+        L += s_l[w * G + j] * f;
+        o += s_o[(w * G + j) * HD + e] * f;
+      }
+      bad |= finite_bits(o) ? 0u : 1u << i;
+      const int64_t hd = (int64_t)b * a.n_q_heads + (int64_t)h * g + j0 + j;
+      if (a.n_split == 1) {   // one range per head: no merge kernel follows
+        a.out[hd * HD + e] = L > 0.f ? o / L : 0.f;
+        if (a.lse != nullptr && e == 0) a.lse[hd] = L > 0.f ? (M + __builtin_log2f(L)) * 0.6931471805599453f : -__builtin_inff();
+      } else {
+        const int64_t slot = hd * a.n_split + split;
+        if (e == 0) a.part_ml[slot] = make_float2(M, L);
+        a.part_o[slot * HD + e] = o;
+      }
     }
+    if (pass != 0) break;
+    if (bad != 0) s_again = 1;
+    // a barrier for LDS alone: nothing waits for the stores
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    if (s_again == 0) break;
+    redo = bad;
+    __builtin_amdgcn_s_waitcnt(vm_imm(0));   // the stores: the waits of the second pass count loads only
   }
 }
 

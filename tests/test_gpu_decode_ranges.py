@@ -122,3 +122,33 @@ def test_infinite_values_stay_infinite(lib, dtype, n, hq, d):
     cols = [i for i in range(d) if i not in inf_at]
     want, _ = orc.decode_attention(bits(q), bits(k), bits(finite))
     assert (np.abs(out - want)[:, cols].max(axis=1) / np.abs(want).max(axis=1)).max() <= TOL
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
+@pytest.mark.parametrize("nats", [25.0, 30.0, 40.0, 60.0])
+@pytest.mark.parametrize("n,hq,d", [(200, 4, 128), (600, 8, 128), (5000, 4, 64)])
+def test_weights_far_below_the_reference(lib, dtype, n, hq, d, nats):
+    """Every 32nd token `nats` above the rest, its value zero where theirs is not: the small weights keep their size.  fp16
+    cuts a weight off below 2^-72; otherwise it is rounded as its exponent is, by 2^-19 (half an ulp of 60 log2 e) and
+    half an ulp of v_exp.  An infinity under such a weight, cut off or not, is an infinity."""
+    k = torch.zeros((1, n, d), device=DEV)
+    k[0, ::32, 5] = nats
+    q = torch.zeros((hq, d), device=DEV)
+    q[:, 5] = 1.0
+    v = torch.zeros((1, n, d), device=DEV)
+    v[0, :, 1] = 30000.0
+    v[0, ::32, 1] = 0.0
+    v[0, ::32, 2] = 1.0
+    v[0, 5, 7], v[0, 64, 9] = float("inf"), float("-inf")
+    q, k, v = q.to(dtype), k.to(dtype), v.to(dtype)
+    out, lse = run(lib, dtype, n, hq, 1, d, k, v, q, scale=1.0)
+    peaks = (n + 31) // 32
+    total = peaks + (n - peaks) * np.exp(-nats)
+    value = float(v[0, 1, 1].float())
+    want = (n - peaks) * np.exp(-nats) * value / total
+    cut = (n - peaks) * 2.0 ** -72 * value / total if dtype == torch.float16 else 0.0
+    assert np.abs(out[:, 1] - want).max() <= cut + 1e-5 * want, (out[:, 1], want)
+    assert np.abs(out[:, 2] * total / peaks - 1).max() <= 1e-6
+    assert (out[:, 7] == np.inf).all() and (out[:, 9] == -np.inf).all()
+    assert (np.delete(out, (1, 2, 7, 9), axis=1) == 0).all()
+    assert np.abs(lse - nats - np.log(total) + 0.0).max() <= 1e-5
