@@ -142,14 +142,10 @@ struct DecodePlan {
 inline int64_t decode_tokens(const chunkkv_problem *p, bool compacted, int b) {
   return compacted ? (int64_t)p->n_keep[b] + p->window : p->seqlen[b];
 }
-// longest range whose rows, and the step behind them, the matrix-core kernel's 32-bit byte offsets reach
-inline int64_t decode_row_limit(const chunkkv_problem *p, bool compacted) {
-  const int64_t tok = (compacted ? p->out_stride_tok : p->kv_stride_tok) * elem_bytes(p->dtype);
-  return (((int64_t)1 << 31) - 1) / tok / kDecodeStepRows * kDecodeStepRows - 2 * kDecodeStepRows;
-}
+// The matrix-core kernel reaches the rows of a step by 32-bit byte offsets: rows up to 64 MB apart.
 bool decode_on_matrix_cores(const chunkkv_problem *p, bool compacted) {
-  if (p->dtype == CHUNKKV_F32) return false;
-  return decode_row_limit(p, compacted) > kDecodeDirectRows;
+  const int64_t tok = (compacted ? p->out_stride_tok : p->kv_stride_tok) * elem_bytes(p->dtype);
+  return p->dtype != CHUNKKV_F32 && tok * kDecodeStepRows < (int64_t)1 << 31;
 }
 // rows per range that give about kDecodeTargetWorkgroups workgroups
 inline int64_t decode_even_rows(int64_t rows_times_wgs) {
@@ -214,10 +210,8 @@ int decode_rows(const chunkkv_problem *p, bool compacted, int b0, int nb, int32_
   };
   int64_t rounds = (n_sum * per_seq + kDecodeRangeRows * kDecodeCUs / 2) / (kDecodeRangeRows * kDecodeCUs);
   rounds = rounds < 1 ? 1 : (rounds > kDecodeMaxRounds ? kDecodeMaxRounds : rounds);
-  const int64_t limit = decode_row_limit(p, compacted);
   int64_t r = n_max <= kDecodeDirectRows ? kDecodeDirectRows : shortest(rounds * kDecodeCUs);
   r = r > least ? r : least;
-  r = r < limit ? r : limit;
   for (int i = 0; i < nb; ++i) {
     const int64_t n = decode_tokens(p, compacted, b0 + i), s = n > 0 ? (n + r - 1) / r : 1;
     const int64_t even = (n + s - 1) / s;

@@ -413,7 +413,7 @@ __global__ __launch_bounds__(kCombineThreads) void decode_combine_kernel(DecodeA
   }
 }
 
-// fp32 caches; for 16-bit caches only strides beyond the matrix-core kernel's offsets come here, one head at a time
+// fp32 caches; for 16-bit caches only rows more than 64 MB apart come here, one head at a time
 template <int DT, int HD>
 int launch_decode_valu(const DecodeArgs &a, int batch_slice, int g, hipStream_t s) {
   const int G = DT == CHUNKKV_F32 ? decode_heads_per_wg(DT, g) : 1;

@@ -39,7 +39,7 @@
 // 109 us over eight sequences of 10 to 55 thousand tokens in 1024 ranges: the second workgroup covers the ends of the
 // first).  16-byte segments are XOR-swizzled on the global-address side so that both the
 // fragment reads and the transposing reads touch all banks evenly.  The buffer descriptor covers exactly the rows of
-// the key range: rows past the end read as zero.
+// a step that are there: rows past the end read as zero.
 // Grid: x = key range, y = (batch of G query heads, kv-head), z = sequence.
 #include <mutex>
 #include <type_traits>
@@ -143,7 +143,6 @@ __global__ __launch_bounds__(NW * 64, 2) void decode_mfma_kernel(DecodeArgs a) {
 
   const int64_t tok = a.stride_tok * 2;
   const int64_t off0 = (CKV_ARG(DecodeArgs, base, bl) + (int64_t)h * a.stride_head) * 2 + (int64_t)r0 * tok;
-  const int span = len > 0 ? (int)((uint32_t)(len - 1) * (uint32_t)tok + ROWB) : 0;
   // query operand (first in the queue of loads): column n holds head n % G (heads the kv-head does not have
   // read as zero)
   const int head = n % G, part = n / G;
@@ -166,17 +165,18 @@ __global__ __launch_bounds__(NW * 64, 2) void decode_mfma_kernel(DecodeArgs a) {
     koff[j] = (uint32_t)row * (uint32_t)tok + (uint32_t)((pos ^ kswz(row)) * 16);
     voff[j] = (uint32_t)row * (uint32_t)tok + (uint32_t)((pos ^ vswz(row)) * 16);
   }
-  // Steps past the last one are issued too, through an empty descriptor (no memory traffic, zeros into the slot), so
-  // the number of loads in flight is a compile-time constant at every wait.
+  // A descriptor covers the rows of one step, so only 32 rows have to be within reach of 32-bit offsets.  Steps past the
+  // last one are issued too, through an empty descriptor (no memory traffic, zeros into the slot), so the number of loads
+  // in flight is a compile-time constant at every wait.
   const uint32_t ring = (uint32_t)(wave * (2 * NST * SLOT));
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)smem;
   auto issue = [&](const void *base, const uint32_t *off, int step, uint32_t slot) __attribute__((always_inline)) {
-    const bool live = step < nstep;
-    const uint32_t so = live ? (uint32_t)((wave + step * NW) * kStepKeys) * (uint32_t)tok : 0u;
-    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void *)((const char *)base + off0), 0, live ? span : 0, 0x00020000);
+    const int first = (wave + step * NW) * kStepKeys, last = (first + kStepKeys < len ? first + kStepKeys : len) - 1;
+    const uint32_t span = step < nstep ? (uint32_t)(last - first) * (uint32_t)tok + ROWB : 0u;
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void *)((const char *)base + off0 + first * tok), 0, (int)span, 0x00020000);
 #pragma unroll
     for (int j = 0; j < NLD; ++j)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void *)(smem + slot + j * 1024), 16, off[j], so, 0, 2);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void *)(smem + slot + j * 1024), 16, off[j], 0, 0, 2);
   };
   auto kslot = [&](int s) { return ring + (uint32_t)((s % NST) * (2 * SLOT)); };
   auto vslot = [&](int s) { return ring + (uint32_t)((s % NST) * (2 * SLOT) + SLOT); };

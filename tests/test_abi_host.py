@@ -297,6 +297,17 @@ def test_static_decode_takes_what_the_even_cut_fits():
     assert even <= pkg.chunkkv_decode_workspace_bytes(p, False) <= 8 << 20
 
 
+@pytest.mark.parametrize("pitch", [1 << 17, 1 << 19, 1 << 21, 1 << 23, 1 << 25])
+def test_static_decode_does_not_depend_on_the_row_pitch(pitch):
+    """Rows 256 KB to 64 MB apart, as in a cache that holds the layers and sequences of a token together: the ranges, and
+    with them the room the partial results need, are those of rows that lie together."""
+    keep = [10000] + [4000] * 39
+    p = pkg.Problem(32, 8, 64, 8, 10, pkg.BF16, [10008] * 40, keep, [0] * 40, 64, 512, [0] * 40, 64, 512)
+    packed = pkg.chunkkv_decode_workspace_bytes(p, True)
+    p.out_stride_tok = pitch
+    assert 0 < packed == pkg.chunkkv_decode_workspace_bytes(p, True) <= 8 << 20
+
+
 def test_decode_argument_checks(lib):
     p = good(out_base=[0], out_stride_head=848 * 128, out_stride_tok=128)
     cp = p.as_c()

@@ -85,16 +85,18 @@ def test_one_token_far_above_many(lib, dtype, peak):
     assert np.abs(lse - 25.0).max() <= 1e-5
 
 
-def test_strides_past_32_bit_offsets(lib):
-    n, d, hq, hkv = 3, 128, 8, 2
+@pytest.mark.parametrize("n,stride_tok", [(3, 1 << 22), (300, 1 << 22), (33, (1 << 25) - 128), (33, 1 << 25)])
+def test_strides_past_32_bit_offsets(lib, n, stride_tok):
+    """Rows 8 and 64 MB apart: the offsets of a head, and past 64 MB those of a step, do not fit 32 bits."""
+    d, hq, hkv = 128, 8, 2
     gen = torch.Generator(device=DEV).manual_seed(3)
     q, k, v = (torch.randn(s, generator=gen, device=DEV).to(torch.bfloat16) for s in ((hq, d), (hkv, n, d), (hkv, n, d)))
-    out, lse = run(lib, torch.bfloat16, n, hq, hkv, d, k, v, q, stride_tok=(1 << 22) + 64)   # 259 rows of 8 MB: past 2^31
+    out, lse = run(lib, torch.bfloat16, n, hq, hkv, d, k, v, q, stride_tok=stride_tok + 64)
     check(out, lse, q, k, v, n)
 
 
 def test_cache_past_32_bit_offsets(lib):
-    """Rows 64 KB apart, as in a cache that holds all layers of a token together: 2.6 GB, each range within 2^31 bytes."""
+    """Rows 64 KB apart, as in a cache that holds all layers of a token together: 2.6 GB."""
     n, d, hq, hkv = 40000, 128, 8, 2
     gen = torch.Generator(device=DEV).manual_seed(4)
     q, k, v = (torch.randn(s, generator=gen, device=DEV).to(torch.bfloat16) for s in ((hq, d), (hkv, n, d), (hkv, n, d)))
