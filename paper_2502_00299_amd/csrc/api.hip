@@ -4,6 +4,7 @@
 
 #include <mutex>
 
+#include "decode_plan.h"
 #include "internal.h"
 
 namespace ckv {
@@ -77,7 +78,6 @@ int static_scratch(void **out) {
   return CHUNKKV_OK;
 }
 
-inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
 int check_problem(const chunkkv_problem *p, bool need_out) {
@@ -118,124 +118,6 @@ int check_problem(const chunkkv_problem *p, bool need_out) {
 }
 
 bool misaligned(const void *p) { return ((uintptr_t)p & 15) != 0; }
-
-// Key ranges and workspace of the decode-attention call: a pure function of the problem.
-// 16-bit caches (matrix-core kernel): few ranges mean few starts, ends and partial results, many even out unequal
-// sequences.  One to four workgroups per CU (a whole number: with one and a half, half the CUs wait), about
-// kDecodeRangeRows rows each.  Microseconds with 256 / 512 / 1024 workgroups: 13171 tokens of 8 kv-heads 15.9 / 16.5 /
-// 22.0; 30000 tokens 26.5 / 25.6 / 28.9; 131072 tokens 87.2 / 88.3 / 88.3; eight sequences of 10 to 55 thousand tokens,
-// 4 kv-heads 124 / 109 / 96 (2048: 98); five of 600 to 30000 57 / 51 / 47.  A sequence is cut into equal ranges.
-// Up to kDecodeDirectRows rows a head is one range of one step per wavefront and needs no merge (256 tokens of 8
-// kv-heads: 7.7 us in one launch, 8.4 in ranges and merge; 512 tokens: 9.2 and 8.5).
-// fp32 caches (vector-ALU kernel): ranges of one length for the slice, about kDecodeTargetWorkgroups of them, never
-// fewer than kDecodeMinRows rows.
-constexpr int kDecodeCUs = 256;
-constexpr int kDecodeTargetWorkgroups = 1024;
-constexpr int kDecodeMinRows = 256;
-constexpr int kDecodeRangeRows = 448, kDecodeMaxRounds = 4;
-constexpr int kDecodeDirectRows = 256;
-constexpr int kDecodeStepRows = 32;    // rows a wavefront of the matrix-core kernel takes in one step
-struct DecodePlan {
-  int n_split;
-  size_t off_ml, off_o, total;
-};
-inline int64_t decode_tokens(const chunkkv_problem *p, bool compacted, int b) {
-  return compacted ? (int64_t)p->n_keep[b] + p->window : p->seqlen[b];
-}
-// The matrix-core kernel reaches the rows of a step by 32-bit byte offsets: rows up to 64 MB apart.
-bool decode_on_matrix_cores(const chunkkv_problem *p, bool compacted) {
-  const int64_t tok = (compacted ? p->out_stride_tok : p->kv_stride_tok) * elem_bytes(p->dtype);
-  return p->dtype != CHUNKKV_F32 && tok * kDecodeStepRows < (int64_t)1 << 31;
-}
-// rows per range that give about kDecodeTargetWorkgroups workgroups
-inline int64_t decode_even_rows(int64_t rows_times_wgs) {
-  const int64_t r = (rows_times_wgs + kDecodeTargetWorkgroups - 1) / kDecodeTargetWorkgroups;
-  return r < kDecodeMinRows ? kDecodeMinRows : (r + 127) / 128 * 128;
-}
-// The size of the workspace that callers see is that of about kDecodeTargetWorkgroups ranges of one length over the whole
-// batch, whatever the kernel makes of it: workspaces and the static call's limit do not depend on how a cache happens to
-// be cut.  Returns that number of ranges of the longest sequence.
-int64_t decode_even_splits(const chunkkv_problem *p, bool compacted) {
-  int64_t n_max = 1, n_sum = 0;
-  for (int b = 0; b < p->batch; ++b) {
-    const int64_t n = decode_tokens(p, compacted, b);
-    n_max = n > n_max ? n : n_max;
-    n_sum += n;
-  }
-  const int g = p->n_q_heads / p->n_kv_heads;
-  const int G = p->dtype != CHUNKKV_F32 && g > 4 ? 8 : (g > 2 ? 4 : g);
-  const int64_t launches = (p->batch + kMaxBatchPerLaunch - 1) / kMaxBatchPerLaunch;
-  const int64_t rows = decode_even_rows(n_sum * p->n_kv_heads * ((g + G - 1) / G) / launches);
-  return (n_max + rows - 1) / rows;
-}
-// rows[i]: rows per range of sequence b0 + i; returns the largest number of ranges
-int decode_rows(const chunkkv_problem *p, bool compacted, int b0, int nb, int32_t *rows) {
-  const bool mfma = decode_on_matrix_cores(p, compacted);
-  const int g = p->n_q_heads / p->n_kv_heads;
-  const int G = mfma || p->dtype == CHUNKKV_F32 ? decode_heads_per_wg(p->dtype, g) : 1;
-  const int64_t per_seq = (int64_t)p->n_kv_heads * ((g + G - 1) / G);   // workgroups of one range of a sequence
-  int64_t n_sum = 0, n_max = 1;
-  for (int i = 0; i < nb; ++i) {
-    const int64_t n = decode_tokens(p, compacted, b0 + i);
-    n_sum += n;
-    n_max = n > n_max ? n : n_max;
-  }
-  // a very uneven batch: no more ranges of its longest sequence than the static scratch or the even cut has room for
-  int64_t most = (CHUNKKV_STATIC_SCRATCH_BYTES - 512) / ((int64_t)p->batch * p->n_q_heads * (p->head_dim * 4 + 8));
-  const int64_t n_even = decode_even_splits(p, compacted);
-  most = most > n_even ? most : n_even;
-  const int64_t least = ((n_max + most - 1) / most + kDecodeStepRows - 1) / kDecodeStepRows * kDecodeStepRows;
-  if (!mfma) {
-    int64_t r = decode_even_rows(n_sum * per_seq);
-    if (r < least) r = (least + 127) / 128 * 128;
-    for (int i = 0; i < nb; ++i) rows[i] = (int32_t)r;
-    return (int)((n_max + r - 1) / r);
-  }
-  int64_t splits = 1;
-  auto wgs = [&](int64_t r) {
-    int64_t w = 0;
-    for (int i = 0; i < nb; ++i) w += (decode_tokens(p, compacted, b0 + i) + r - 1) / r;
-    return w * per_seq;
-  };
-  // the shortest range length (in steps) that gives at most `target` workgroups, or one range per head
-  const int64_t lo0 = p->batch <= kMaxBatchPerLaunch && nb * per_seq <= kDecodeCUs / 4 ? 4 : kDecodeMinRows / kDecodeStepRows;
-  const int64_t hi0 = (n_max + kDecodeStepRows - 1) / kDecodeStepRows > lo0 ? (n_max + kDecodeStepRows - 1) / kDecodeStepRows : lo0;
-  auto shortest = [&](int64_t target) {
-    int64_t lo = lo0, hi = hi0;
-    while (lo < hi) {
-      const int64_t mid = (lo + hi) / 2;
-      if (wgs(mid * kDecodeStepRows) <= target) hi = mid; else lo = mid + 1;
-    }
-    return lo * kDecodeStepRows;
-  };
-  int64_t rounds = (n_sum * per_seq + kDecodeRangeRows * kDecodeCUs / 2) / (kDecodeRangeRows * kDecodeCUs);
-  rounds = rounds < 1 ? 1 : (rounds > kDecodeMaxRounds ? kDecodeMaxRounds : rounds);
-  int64_t r = n_max <= kDecodeDirectRows ? kDecodeDirectRows : shortest(rounds * kDecodeCUs);
-  r = r > least ? r : least;
-  for (int i = 0; i < nb; ++i) {
-    const int64_t n = decode_tokens(p, compacted, b0 + i), s = n > 0 ? (n + r - 1) / r : 1;
-    const int64_t even = (n + s - 1) / s;
-    rows[i] = (int32_t)(even < 1 ? 32 : (even + 31) / 32 * 32);
-    splits = s > splits ? s : splits;
-  }
-  return (int)splits;
-}
-int decode_plan(const chunkkv_problem *p, bool compacted, DecodePlan *pl) {
-  int32_t rows[kMaxBatchPerLaunch];
-  pl->n_split = 1;
-  for (int b0 = 0; b0 < p->batch; b0 += kMaxBatchPerLaunch) {
-    const int s = decode_rows(p, compacted, b0, p->batch - b0 < kMaxBatchPerLaunch ? p->batch - b0 : kMaxBatchPerLaunch, rows);
-    pl->n_split = s > pl->n_split ? s : pl->n_split;
-  }
-  const size_t heads = (size_t)p->batch * p->n_q_heads;
-  pl->off_ml = 0;
-  pl->off_o = align256(heads * pl->n_split * sizeof(float2));
-  pl->total = pl->off_o + align256(heads * pl->n_split * p->head_dim * sizeof(float));
-  const size_t n_even = (size_t)decode_even_splits(p, compacted);
-  const size_t even = align256(heads * n_even * sizeof(float2)) + align256(heads * n_even * p->head_dim * sizeof(float));
-  pl->total = even > pl->total ? even : pl->total;
-  return CHUNKKV_OK;
-}
 
 // Workspace layout and key-range split; a pure function of (problem, n_layers, reuse).
 int make_plan(const chunkkv_problem *p, int n_layers, int reuse, Plan *pl) {
@@ -712,7 +594,8 @@ int chunkkv_jaccard(const chunkkv_problem *prob, int32_t n_groups, const int32_t
 
 size_t chunkkv_decode_workspace_bytes(const chunkkv_problem *prob, int32_t compacted) {
   DecodePlan pl;
-  if (check_problem(prob, compacted != 0) || decode_plan(prob, compacted != 0, &pl)) return 0;
+  if (check_problem(prob, compacted != 0)) return 0;
+  decode_plan(prob, compacted != 0, &pl);
   return pl.total;
 }
 
@@ -724,7 +607,7 @@ int chunkkv_decode_attention(const chunkkv_problem *prob, int32_t compacted, con
   if (!q || !k || !v || !out) return CHUNKKV_ERR_NULL;
   if (misaligned(q) || misaligned(k) || misaligned(v)) return CHUNKKV_ERR_SHAPE;
   DecodePlan pl;
-  if ((rc = decode_plan(prob, compacted != 0, &pl))) return rc;
+  decode_plan(prob, compacted != 0, &pl);
   if (!workspace || workspace_bytes < pl.total) return CHUNKKV_ERR_WORKSPACE;
   hipStream_t s = (hipStream_t)stream;
   const float scale = prob->softmax_scale > 0.f ? prob->softmax_scale : 1.0f / sqrtf((float)prob->head_dim);
@@ -742,8 +625,7 @@ int chunkkv_decode_attention(const chunkkv_problem *prob, int32_t compacted, con
     a.stride_tok = compacted ? prob->out_stride_tok : prob->kv_stride_tok;
     a.batch0 = b0; a.n_q_heads = prob->n_q_heads; a.n_kv_heads = prob->n_kv_heads; a.group = prob->n_q_heads / prob->n_kv_heads;
     a.scale_log2e = scale * 1.4426950408889634f;
-    a.n_split = pl.n_split;
-    decode_rows(prob, compacted != 0, b0, nb, a.rows_per_split);
+    decode_cut(prob, compacted != 0, b0, nb, &a.cut);
     const bool mfma = decode_on_matrix_cores(prob, compacted != 0);
     { Timed t(kDecode, s); rc = launch_decode(prob->dtype, prob->head_dim, mfma, a, nb, s); }
     if (rc) return rc;
@@ -758,7 +640,7 @@ int chunkkv_decode_attention_static(const chunkkv_problem *prob, int32_t compact
   int rc = check_problem(prob, compacted != 0);
   if (rc) return rc;
   DecodePlan pl;
-  if ((rc = decode_plan(prob, compacted != 0, &pl))) return rc;
+  decode_plan(prob, compacted != 0, &pl);
   if (pl.total > kStaticScratchBytes) return CHUNKKV_ERR_WORKSPACE;
   void *ws = nullptr;
   if ((rc = static_scratch(&ws))) return rc;
@@ -776,8 +658,8 @@ struct QualityPlan {
 };
 int quality_plan(const chunkkv_problem *p, QualityPlan *q) {
   DecodePlan df, dk;
-  int rc;
-  if ((rc = decode_plan(p, false, &df)) || (rc = decode_plan(p, true, &dk))) return rc;
+  decode_plan(p, false, &df);
+  decode_plan(p, true, &dk);
   int full_max = 0, kept_max = 0;
   for (int b = 0; b < p->batch; ++b) {
     full_max = p->seqlen[b] > full_max ? p->seqlen[b] : full_max;

@@ -130,7 +130,7 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(DecodeArgs a) {
     n = a.kv_len[(int64_t)b * a.n_kv_heads + h];
     n = n < 0 ? 0 : (n > cap ? cap : n);
   }
-  const int rps = CKV_ARG(DecodeArgs, rows_per_split, bl);
+  const int rps = CKV_ARG(DecodeArgs, cut.rows_per_split, bl);
   const int r0 = split * rps;
   const int r1 = r0 + rps < n ? r0 + rps : n;
   if (r0 >= n && split > 0) return;   // the merge knows how many ranges hold rows
@@ -332,8 +332,7 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(DecodeArgs a) {
 #pragma unroll
         for (int e = 0; e < EPL; ++e) acc[e] += s_o[w][j][sg][e] * f;
       }
-      const int64_t head = (int64_t)b * a.n_q_heads + (int64_t)h * g + j0 + j;
-      const int64_t slot = head * a.n_split + split;
+      const int64_t slot = (int64_t)CKV_ARG(DecodeArgs, cut.first_split, bl) * a.n_q_heads + ((int64_t)h * g + j0 + j) * CKV_ARG(DecodeArgs, cut.splits, bl) + split;
       if (sg == 0) a.part_ml[slot] = make_float2(M, Lsum);
       float *po = a.part_o + slot * HD + sg * EPL;
 #pragma unroll
@@ -359,12 +358,13 @@ __global__ __launch_bounds__(kCombineThreads) void decode_combine_kernel(DecodeA
     const int x = a.kv_len[(int64_t)b * a.n_kv_heads + hq / (a.n_q_heads / a.n_kv_heads)];
     n = x < 0 ? 0 : (x > n ? n : x);
   }
-  const int rps = CKV_ARG(DecodeArgs, rows_per_split, bl);
+  const int rps = CKV_ARG(DecodeArgs, cut.rows_per_split, bl);
   const int used = n > 0 ? (n + rps - 1) / rps : 1;
-  const float2 *ml = a.part_ml + head * a.n_split;
+  const int64_t slot = (int64_t)CKV_ARG(DecodeArgs, cut.first_split, bl) * a.n_q_heads + (int64_t)hq * CKV_ARG(DecodeArgs, cut.splits, bl);
+  const float2 *ml = a.part_ml + slot;
   const int t = threadIdx.x, col = t % TPR, grp = t / TPR;
   __shared__ float s_acc[NG][HD + 2];
-  const float *po = a.part_o + head * a.n_split * HD + col * 4;
+  const float *po = a.part_o + slot * HD + col * 4;
   float acc[4] = {0.f, 0.f, 0.f, 0.f}, m = kDecodeNegBig, lsum = 0.f;
   for (int s0 = grp; s0 < used; s0 += UN * NG) {
     float2 p[UN];
@@ -417,7 +417,7 @@ __global__ __launch_bounds__(kCombineThreads) void decode_combine_kernel(DecodeA
 template <int DT, int HD>
 int launch_decode_valu(const DecodeArgs &a, int batch_slice, int g, hipStream_t s) {
   const int G = DT == CHUNKKV_F32 ? decode_heads_per_wg(DT, g) : 1;
-  const dim3 grid(a.n_split, batch_slice * a.n_kv_heads, (g + G - 1) / G);
+  const dim3 grid(a.cut.n_split, batch_slice * a.n_kv_heads, (g + G - 1) / G);
   if (G == 1) hipLaunchKernelGGL((decode_kernel<DT, HD, 1>), grid, dim3(kThreads), 0, s, a);
   else if constexpr (DT == CHUNKKV_F32) {
     if (G == 2) hipLaunchKernelGGL((decode_kernel<DT, HD, 2>), grid, dim3(kThreads), 0, s, a);
@@ -435,13 +435,13 @@ int launch_decode_hd(int dtype, bool matrix_cores, const DecodeArgs &a, int batc
   else if (dtype == CHUNKKV_F16) rc = launch_decode_valu<CHUNKKV_F16, HD>(a, batch_slice, g, s);
   else rc = launch_decode_valu<CHUNKKV_F32, HD>(a, batch_slice, g, s);
   if (rc) return rc;
-  if (matrix_cores && a.n_split == 1) return CHUNKKV_OK;   // the range kernel wrote the outputs
+  if (matrix_cores && a.cut.n_split == 1) return CHUNKKV_OK;   // the range kernel wrote the outputs
   hipLaunchKernelGGL((decode_combine_kernel<HD>), dim3(a.n_q_heads, batch_slice), dim3(kCombineThreads), 0, s, a);
   return hipGetLastError() == hipSuccess ? CHUNKKV_OK : CHUNKKV_ERR_LAUNCH;
 }
 
 int launch_decode(int dtype, int head_dim, bool matrix_cores, const DecodeArgs &a, int batch_slice, hipStream_t s) {
-  if (a.n_split == 0 || batch_slice * a.n_kv_heads == 0) return CHUNKKV_OK;
+  if (a.cut.n_split == 0 || batch_slice * a.n_kv_heads == 0) return CHUNKKV_OK;
   if (head_dim == 128) return launch_decode_hd<128>(dtype, matrix_cores, a, batch_slice, s);
   if (head_dim == 64) return launch_decode_hd<64>(dtype, matrix_cores, a, batch_slice, s);
   return CHUNKKV_ERR_UNSUPPORTED;

@@ -116,7 +116,7 @@ __global__ __launch_bounds__(NW * 64, 2) void decode_mfma_kernel(DecodeArgs a) {
   const u16x2 kLeastPart = BF ? u16x2{0x0080, 0x0080} : u16x2{0x0001, 0x0001};
 
   extern __shared__ __align__(16) char smem[];
-  __shared__ volatile int s_again;   // some element of the merged output is not finite
+  __shared__ int s_again;   // some element of the merged output is not finite
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -129,7 +129,9 @@ __global__ __launch_bounds__(NW * 64, 2) void decode_mfma_kernel(DecodeArgs a) {
   }
   const int g = a.group, b = a.batch0 + bl;
 
-  const int cap = CKV_ARG(DecodeArgs, n_tok, bl), rps = CKV_ARG(DecodeArgs, rows_per_split, bl);
+  const int cap = CKV_ARG(DecodeArgs, n_tok, bl), rps = CKV_ARG(DecodeArgs, cut.rows_per_split, bl);
+  const int splits = CKV_ARG(DecodeArgs, cut.splits, bl);
+  const int64_t slot0 = (int64_t)CKV_ARG(DecodeArgs, cut.first_split, bl) * a.n_q_heads + (int64_t)(h * g) * splits + split;   // first partial result
   int nrow = cap;
   if (a.kv_len != nullptr) {
     nrow = a.kv_len[(int64_t)b * a.n_kv_heads + h];
@@ -370,19 +372,19 @@ __global__ __launch_bounds__(NW * 64, 2) void decode_mfma_kernel(DecodeArgs a) {
       }
       bad |= finite_bits(o) ? 0u : 1u << i;
       const int64_t hd = (int64_t)b * a.n_q_heads + (int64_t)h * g + j0 + j;
-      if (a.n_split == 1) {   // one range per head: no merge kernel follows
+      if (a.cut.n_split == 1) {   // one range per head: no merge kernel follows
         a.out[hd * HD + e] = L > 0.f ? o / L : 0.f;
         if (a.lse != nullptr && e == 0) a.lse[hd] = L > 0.f ? (M + __builtin_log2f(L)) * 0.6931471805599453f : -__builtin_inff();
       } else {
-        const int64_t slot = hd * a.n_split + split;
+        const int64_t slot = slot0 + (j0 + j) * splits;
         if (e == 0) a.part_ml[slot] = make_float2(M, L);
         a.part_o[slot * HD + e] = o;
       }
     }
     if (pass != 0) break;
     if (bad != 0) s_again = 1;
-    // a barrier for LDS alone: nothing waits for the stores
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    // a barrier for LDS alone, s_again's address its operand so that it is read again behind it: nothing waits for the stores
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::"v"(&s_again) : "memory");
     if (s_again == 0) break;
     redo = bad;
     __builtin_amdgcn_s_waitcnt(vm_imm(0));   // the stores: the waits of the second pass count loads only
@@ -405,10 +407,10 @@ int launch_decode_mfma_cfg(const DecodeArgs &a, dim3 grid, hipStream_t s) {
 template <int DT, int HD>
 int launch_decode_mfma_hd(const DecodeArgs &a, int batch_slice, int g, hipStream_t s) {
   const int G = g <= 4 ? 4 : 8;
-  const dim3 grid(a.n_split, a.n_kv_heads * ((g + G - 1) / G), batch_slice);
+  const dim3 grid(a.cut.n_split, a.n_kv_heads * ((g + G - 1) / G), batch_slice);
   constexpr int NST = HD == 128 ? 1 : 2;
   // one range per head: eight wavefronts share it
-  if (a.n_split == 1) return G == 4 ? launch_decode_mfma_cfg<DT, HD, 4, 8, NST>(a, grid, s) : launch_decode_mfma_cfg<DT, HD, 8, 8, NST>(a, grid, s);
+  if (a.cut.n_split == 1) return G == 4 ? launch_decode_mfma_cfg<DT, HD, 4, 8, NST>(a, grid, s) : launch_decode_mfma_cfg<DT, HD, 8, 8, NST>(a, grid, s);
   return G == 4 ? launch_decode_mfma_cfg<DT, HD, 4, 4, NST>(a, grid, s) : launch_decode_mfma_cfg<DT, HD, 8, 4, NST>(a, grid, s);
 }
 

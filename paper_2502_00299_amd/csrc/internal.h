@@ -7,11 +7,11 @@
 #include <type_traits>
 
 #include "chunkkv.h"
+#include "decode_plan.h"
 
 namespace ckv {
 
 constexpr int kMaxLayersPerLaunch = 32;  // pointer tables travel as kernel arguments
-constexpr int kMaxBatchPerLaunch = 16;
 constexpr int kTileBytes = 16384;        // one K tile staged in LDS (ring slot)
 constexpr int kSuperKeys = 256;        // keys per importance / chunk-sum step of pass 1 (several tiles)
 constexpr int kThreads = 256;            // 4 wavefronts of 64
@@ -93,16 +93,15 @@ struct CompactArgs {
 struct DecodeArgs {
   const void *q, *k, *v;
   float *out, *lse;           // [batch_total][Hq][d], [batch_total][Hq] or null
-  float2 *part_ml;            // [batch_total * Hq][n_split]  (max in log2 units, sum)
-  float *part_o;              // [batch_total * Hq][n_split][d]
+  float2 *part_ml;            // (max in log2 units, sum) of every range: cut.first_split[i] * Hq entries of the sequences before, then [Hq][cut.splits[i]]
+  float *part_o;              // [d] each, in the same order
   const int32_t *kv_len;      // [batch_total][Hkv] tokens to attend to, or null (= n_tok)
   int32_t n_tok[kMaxBatchPerLaunch];  // tokens the cache of a sequence holds per head
-  int32_t rows_per_split[kMaxBatchPerLaunch];  // rows of one key range of the sequence
   int64_t base[kMaxBatchPerLaunch];   // element offset of the sequence in k / v
   int64_t stride_head, stride_tok;
   int32_t batch0, n_q_heads, n_kv_heads, group;   // group: query heads per kv-head
   float scale_log2e;
-  int32_t n_split;            // pitch of the partial results; 1: every head is one range and no merge follows
+  DecodeCut cut;
 };
 
 // Absolute mass of one layer's cache (quality.hip): sum of |K| + |V| over blocks of rows of every (sequence, kv-head).
@@ -122,13 +121,6 @@ struct QualityFinishArgs {
   float *l1_loss, *attn_cos;                  // [B], [B][Hq]
   int32_t n_q_heads, n_kv_heads, blocks_full, blocks_kept;
 };
-
-// Query heads of one kv-head that a decode workgroup serves.  16-bit caches (matrix cores): 4 or 8; 5..7 heads are one
-// padded batch of 8, not two passes over K and V.  fp32 caches (vector ALU): 1, 2 or 4 (registers).
-inline int decode_heads_per_wg(int dtype, int g) {
-  if (dtype != CHUNKKV_F32) return g > 4 ? 8 : 4;
-  return g > 2 ? 4 : g;
-}
 
 // Reads element i of a small table that travels as a kernel argument.  A chain of selects on the
 // (wavefront-uniform) index keeps the table in scalar registers; a dynamic subscript would make the
@@ -166,7 +158,6 @@ struct ScoreGeom {
   int nqw;         // blocks held by one wavefront
   int wq;          // wavefronts splitting the rows (the other 4/wq split keys)
 };
-inline int elem_bytes(int dtype) { return dtype == CHUNKKV_F32 ? 4 : 2; }  // bf16 and fp16: 2
 bool score_geometry(int dtype, int head_dim, int rows, ScoreGeom *g);
 
 // Launchers (each checks hipGetLastError and returns a chunkkv_status).
