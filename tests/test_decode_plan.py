@@ -75,3 +75,20 @@ def test_every_row_is_in_one_range_and_the_results_fit(cut):
             assert n_split == max(x[1] for x in seqs)
             assert places * hq <= results, prob
         assert b == len(n)
+
+
+@pytest.mark.parametrize("hkv,n,least", [(32, [4096] + [64] * 15, 6), (16, [4096] + [128] * 15, 8), (15, [4096] + [64] * 15, 8),
+                                         (64, [131072] + [300] * 15, 12), (16, [8111] * 3 + [400] * 13, 4)])
+def test_short_sequences_do_not_keep_long_ones_from_being_cut(cut, hkv, n, least):
+    (_, [(_, seqs)]), = cut([(BF16, hkv, hkv, 128, hkv * 128, n)])
+    assert seqs[0][1] >= least
+
+
+def test_no_range_is_far_longer_than_a_cu_s_share(cut):
+    """Twice the rows of the whole launch over 256 CUs at most, however uneven the batch, or the few hundred rows a range has anyway."""
+    rng = random.Random(6)
+    problems = [p for p in (drawn(rng) for _ in range(4000)) if p[0] != F32 and p[4] < 1 << 25 and len(p[5]) <= 16]
+    for prob, (_, [(_, seqs)]) in zip(problems, cut(problems)):
+        dt, hq, hkv, d, pitch, n = prob
+        share = -(-sum(n) * workgroups_per_range(dt, hq, hkv) // 256)
+        assert max(rows for rows, _, _ in seqs) <= max(2 * share + 31, 512), prob

@@ -154,3 +154,24 @@ def test_weights_far_below_the_reference(lib, dtype, n, hq, d, nats):
     assert (out[:, 7] == np.inf).all() and (out[:, 9] == -np.inf).all()
     assert (np.delete(out, (1, 2, 7, 9), axis=1) == 0).all()
     assert np.abs(lse - nats - np.log(total) + 0.0).max() <= 1e-5
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("lens,hq,hkv", [([4111] + [61] * 15, 32, 32), ([50, 3000, 1, 700, 513, 2999], 14, 2), ([900] * 16 + [4000, 33], 8, 8)])
+def test_uneven_batches(lib, dtype, lens, hq, hkv):
+    """Sequences cut into different numbers of ranges share the places of the workspace; 18 sequences take two launches."""
+    d, B = 64, len(lens)
+    gen = torch.Generator(device=DEV).manual_seed(B)
+    base = [sum(lens[:i]) * hkv * d for i in range(B)]
+    q = torch.randn((B, hq, d), generator=gen, device=DEV).to(dtype)
+    k, v = (torch.randn(sum(lens) * hkv * d, generator=gen, device=DEV).to(dtype) for _ in range(2))
+    prob = lib.Problem(hq, hkv, d, 1, 1, lib.F32 if dtype == torch.float32 else lib.BF16, lens, [0] * B, base, d, hkv * d)
+    out, lse = torch.full((B, hq, d), 7.0, device=DEV), torch.full((B, hq), 7.0, device=DEV)
+    room = lib.chunkkv_decode_workspace_bytes(prob, False)
+    ws = torch.full((room + 4096,), 0x5A, dtype=torch.uint8, device=DEV)
+    lib.chunkkv_decode_attention(prob, False, None, q, k, v, out, lse, ws[:room])
+    torch.cuda.synchronize()
+    assert (ws[room:] == 0x5A).all()
+    for b, n in enumerate(lens):
+        kk, vv = (x[base[b]:base[b] + n * hkv * d].view(n, hkv, d).transpose(0, 1).contiguous() for x in (k, v))
+        check(out[b].cpu().numpy(), lse[b].cpu().numpy(), q[b], kk, vv, n)
