@@ -347,6 +347,8 @@ __global__ __launch_bounds__(NW * 64, 2) void decode_mfma_kernel(DecodeArgs a) {
         }
       }
     // ---- merge the wavefronts through LDS, in wavefront order
+    // the loads of the empty steps past the last one still write zeros into the slots
+    __builtin_amdgcn_s_waitcnt(vm_imm(0));
     __syncthreads();   // the slots are dead
     float *s_m = (float *)smem, *s_l = s_m + NW * G, *s_o = s_l + NW * G;   // [NW][G], [NW][G], [NW][G][HD]
     if (n < G) {
