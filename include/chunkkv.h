@@ -223,7 +223,7 @@ int chunkkv_jaccard(const chunkkv_problem *prob, int32_t n_groups, const int32_t
  * large terms, so the error is relative to the row, not to the element); lse to about 1e-6 absolute.
  * Softmax weights keep their size however small: exact to fp32 for fp32 and bf16 caches, and for fp16 caches to 2^-72 of
  * the head's largest weight.  An infinity in V reaches the output as one.
- * Asynchronous on `stream`; two launches; no allocation.  Errors as for chunkkv_score.                  */
+ * Asynchronous on `stream`; one or two launches per 16 sequences; no allocation.  Errors as for chunkkv_score.                  */
 size_t chunkkv_decode_workspace_bytes(const chunkkv_problem *prob, int32_t compacted);
 int chunkkv_decode_attention(const chunkkv_problem *prob, int32_t compacted, const int32_t *kv_len, const void *q,
                              const void *k, const void *v, float *out, float *lse, void *workspace,

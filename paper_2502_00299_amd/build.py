@@ -17,7 +17,7 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
          # packed-fp32 instructions are kept out of the generated code on purpose
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-         # no kernel relies on NaN propagation: lets max() compile to one instruction
+         # lets max() compile to one instruction; where a kernel looks for NaN it looks at the bits
          "-fno-honor-nans",
          "-I", os.path.join(ROOT, "include"), "-I", CSRC]
 

@@ -2,19 +2,21 @@
 // (the stage whose cache Eq. 1 sizes and whose latency Section 4.4 tabulates; Algorithm 1's output is its
 // input).  out_i = sum_t softmax_t(scale * q_i . k_t) v_t, query head i reading kv-head i / g.
 //
-// Bound by HBM bandwidth: every K and V row is read once, g dot products and g axpys per row are far below
-// the vector ALU's rate, so this is a streaming kernel on the vector ALU, not a matrix-core kernel.  A row
-// (d elements) is spread over LPR = d * element size / 16 lanes, 16 bytes each, so one load instruction of
-// a wavefront reads 64 / LPR consecutive rows as one contiguous piece.  The lanes of a row reduce their
+// This file holds the vector-ALU kernel and the merge of the key ranges.  16-bit caches go to the matrix-core kernel of
+// decode_mfma.hip; here remain fp32 caches, and 16-bit ones whose rows are more than 64 MB apart, one head at a time.
+//
+// Bound by HBM bandwidth: every K and V row is read once, and the g dot products and g axpys of an fp32 row are within the
+// vector ALU's rate.  A row (d elements) is spread over LPR = d * element size / 16 lanes, 16 bytes each, so one load
+// instruction of a wavefront reads 64 / LPR consecutive rows as one contiguous piece.  The lanes of a row reduce their
 // partial dot products with DPP adds (no LDS).  Each group of LPR lanes runs its own online softmax over the
 // rows it meets; the groups of a wavefront, the wavefronts of a workgroup and the key ranges of a head are
 // merged afterwards by the usual (max, sum, weighted output) rule, always in the same order.
-// With 16 lanes per row and 4 or 8 heads per workgroup the 4 x G partial dot products of a step are not
+// With 16 lanes per row and 4 heads per workgroup (fp32, d = 64) the 4 x 4 partial dot products of a step are not
 // all-reduced but reduce-scattered: the lanes hold them in an order permuted by their own index (the rows
 // they load and the heads they keep in registers are XOR-swizzled), so each of the four halving steps is
-// one DPP add per kept value and lane (4u + jb) of a row group ends with the complete scores of row u for
-// heads jb*G/4 .. jb*G/4 + G/4 - 1.  That lane alone does the softmax arithmetic of those scores; the
-// weights reach the 16 lanes again as DPP row broadcasts feeding the value accumulation.
+// one DPP add per kept value and lane (4u + j) of a row group ends with the complete score of row u for
+// head j.  That lane alone does the softmax arithmetic of that score; the weights reach the 16 lanes again as DPP
+// row broadcasts feeding the value accumulation.
 // Grid: x = key range, y = (sequence, kv-head), z = batch of G query heads of the kv-head.
 #include <type_traits>
 #include <utility>
@@ -140,24 +142,19 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(DecodeArgs a) {
   const char *vbase = (const char *)a.v + head_off + seg * 16;
   const int64_t tok = a.stride_tok * ESZ;
 
-  // reduce-scatter variant (see the file header): lane (4 * ub + jb) of a row group owns row ub, heads jb * NR ..
-  constexpr bool kScatter = LPR == 16 && U == 4 && (G == 4 || G == 8);
-  constexpr int LG = G == 8 ? 3 : 2;   // log2(G) where the variant applies
-  constexpr int NR = kScatter ? G / 4 : 1;
+  // reduce-scatter variant (see the file header): lane (4 * ub + jb) of a row group owns row ub, head jb
+  constexpr bool kScatter = LPR == 16 && U == 4 && G == 4;
   const int ub = kScatter ? (lane & 15) >> 2 : 0, jb = kScatter ? lane & 3 : 0;
-  const int jsw = jb << (LG - 2);      // register j holds head j ^ jsw
 
   u32x4 qreg[G];
 #pragma unroll
   for (int j = 0; j < G; ++j) {
-    const int jh = j ^ jsw;
+    const int jh = j ^ jb;   // register j holds head j ^ jb
     qreg[j] = u32x4{0, 0, 0, 0};
     if (j0 + jh < g)
       qreg[j] = *(const u32x4 *)((const char *)a.q + ((int64_t)b * a.n_q_heads + (int64_t)h * g + j0 + jh) * ROWB + seg * 16);
   }
-  float m_own[NR], l_own[NR];          // scatter variant: statistics of the heads this lane owns
-#pragma unroll
-  for (int x = 0; x < NR; ++x) { m_own[x] = kDecodeNegBig; l_own[x] = 0.f; }
+  float m_own = kDecodeNegBig, l_own = 0.f;   // scatter variant: statistics of the head this lane owns
   float m[G], l[G], o[G][EPL];
 #pragma unroll
   for (int j = 0; j < G; ++j) {
@@ -186,50 +183,43 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(DecodeArgs a) {
 #pragma unroll
         for (int jj = 0; jj < G; ++jj) x[u][jj] = dot16<DT>(kr[u], qreg[jj]);
       // four halving steps; the partner lane differs in bit 3 / bits 0-2 / bit 1 / bit 0 of the lane index
-      constexpr int J3 = 3 << (LG - 2);
-      float y[2][G], z[G], t[G / 2], r[NR];
+      float y[2][G], z[G], t[2];
 #pragma unroll
       for (int u = 0; u < 2; ++u)
 #pragma unroll
         for (int jj = 0; jj < G; ++jj) y[u][jj] = x[u][jj] + dpp_get<0x128>(x[u ^ 2][jj]);   // row_ror:8
 #pragma unroll
-      for (int jj = 0; jj < G; ++jj) z[jj] = y[0][jj] + dpp_get<0x141>(y[1][jj ^ J3]);        // row_half_mirror
+      for (int jj = 0; jj < G; ++jj) z[jj] = y[0][jj] + dpp_get<0x141>(y[1][jj ^ 3]);         // row_half_mirror
 #pragma unroll
-      for (int jj = 0; jj < G / 2; ++jj) t[jj] = z[jj] + dpp_get<0x4E>(z[jj ^ (G / 2)]);      // quad_perm [2,3,0,1]
+      for (int jj = 0; jj < 2; ++jj) t[jj] = z[jj] + dpp_get<0x4E>(z[jj ^ 2]);                // quad_perm [2,3,0,1]
+      const float r = t[0] + dpp_get<0xB1>(t[1]);                                             // quad_perm [1,0,3,2]
+      // r: row ub of the step, head jb.  Softmax statistics per head: maximum over the four rows, which sit in the
+      // lanes 4, 8 and 12 further on.
+      const float sc = base + ub * RPW + grp < r1 ? r * c1 : -3.0e38f;
+      float smax = fmaxf(sc, dpp_get<0x128>(sc));
+      smax = fmaxf(smax, dpp_get<0x124>(smax));   // row_ror:4; the value is already the same 8 lanes apart
+      if (__builtin_amdgcn_ballot_w64(smax > m_own) != 0) {
+        const float m_new = fmaxf(m_own, smax);
+        const float f = __builtin_amdgcn_exp2f(m_own - m_new);
+        l_own *= f;
+        m_own = m_new;
+        // the outputs of a head live in all 16 lanes: its factor comes from the lane that owns it
+        static_for(std::make_integer_sequence<int, G>{}, [&](auto j_c) __attribute__((always_inline)) {
+          constexpr int JJ = decltype(j_c)::value;
+          const float fb = row_bcast<JJ>(f);
 #pragma unroll
-      for (int jj = 0; jj < NR; ++jj) r[jj] = t[jj] + dpp_get<0xB1>(t[jj ^ (G / 4)]);         // quad_perm [1,0,3,2]
-      // r[x]: row ub of the step, head jb * NR + x.  Softmax statistics per head: maximum over the four rows,
-      // which sit in the lanes 4, 8 and 12 further on.
-      const bool valid_own = base + ub * RPW + grp < r1;
-      float p[NR];
-#pragma unroll
-      for (int xx = 0; xx < NR; ++xx) {
-        const float sc = valid_own ? r[xx] * c1 : -3.0e38f;
-        float smax = fmaxf(sc, dpp_get<0x128>(sc));
-        smax = fmaxf(smax, dpp_get<0x124>(smax));   // row_ror:4; the value is already the same 8 lanes apart
-        if (__builtin_amdgcn_ballot_w64(smax > m_own[xx]) != 0) {
-          const float m_new = fmaxf(m_own[xx], smax);
-          const float f = __builtin_amdgcn_exp2f(m_own[xx] - m_new);
-          l_own[xx] *= f;
-          m_own[xx] = m_new;
-          // the outputs of head jbp * NR + xx live in all 16 lanes: its factor comes from lane jbp
-          static_for(std::make_integer_sequence<int, 4>{}, [&](auto jbp_c) __attribute__((always_inline)) {
-            constexpr int JBP = decltype(jbp_c)::value;
-            const float fb = row_bcast<JBP>(f);
-#pragma unroll
-            for (int e = 0; e < EPL; ++e) o[JBP * NR + xx][e] *= fb;
-          });
-        }
-        p[xx] = __builtin_amdgcn_exp2f(sc - m_own[xx]);
-        l_own[xx] += p[xx];
+          for (int e = 0; e < EPL; ++e) o[JJ][e] *= fb;
+        });
       }
+      const float p = __builtin_amdgcn_exp2f(sc - m_own);
+      l_own += p;
       static_for(std::make_integer_sequence<int, U>{}, [&](auto u_c) __attribute__((always_inline)) {
         constexpr int UU = decltype(u_c)::value;
         float vf[EPL];
         widen16<DT>(vr[UU], vf);
         static_for(std::make_integer_sequence<int, G>{}, [&](auto j_c) __attribute__((always_inline)) {
           constexpr int JJ = decltype(j_c)::value;
-          const float pb = row_bcast<4 * UU + JJ / NR>(p[JJ % NR]);   // weight of (row UU, head JJ)
+          const float pb = row_bcast<4 * UU + JJ>(p);   // weight of (row UU, head JJ)
 #pragma unroll
           for (int e = 0; e < EPL; ++e) o[JJ][e] = __builtin_fmaf(pb, vf[e], o[JJ][e]);
         });
@@ -276,16 +266,12 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(DecodeArgs a) {
   }
   if constexpr (kScatter) {
     // back to the replicated form the merges below expect: every lane learns (m, l) of every head
-    float lsum[NR];
-#pragma unroll
-    for (int xx = 0; xx < NR; ++xx) {
-      lsum[xx] = l_own[xx] + dpp_get<0x128>(l_own[xx]);
-      lsum[xx] += dpp_get<0x124>(lsum[xx]);
-    }
+    float lsum = l_own + dpp_get<0x128>(l_own);
+    lsum += dpp_get<0x124>(lsum);
     static_for(std::make_integer_sequence<int, G>{}, [&](auto j_c) __attribute__((always_inline)) {
       constexpr int JJ = decltype(j_c)::value;
-      m[JJ] = row_bcast<JJ / NR>(m_own[JJ % NR]);
-      l[JJ] = row_bcast<JJ / NR>(lsum[JJ % NR]);
+      m[JJ] = row_bcast<JJ>(m_own);
+      l[JJ] = row_bcast<JJ>(lsum);
     });
   }
 

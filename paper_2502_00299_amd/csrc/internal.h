@@ -133,7 +133,7 @@ __device__ __forceinline__ T pick(const T (&arr)[N], int i) {
   return r;
 }
 
-// Element i of a table inside a kernel's argument struct (the kernel's only parameter): one scalar load from the
+// Element i of a table inside a kernel's argument struct (the kernel's first parameter): one scalar load from the
 // argument segment, where a chain of selects would load the whole table first.
 template <typename T>
 __device__ __forceinline__ T kernarg_at(size_t offset, int i) {
