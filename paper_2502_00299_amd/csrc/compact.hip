@@ -80,7 +80,7 @@ __global__ __launch_bounds__(kThreads) void compact_kernel(CompactArgs a) {
     int src = ch * c;
     if (chosen) {
       // a malformed selection is skipped, never followed out of bounds
-      if (ch < 0 || len < 1 || len > c || (int64_t)ch * c + len > P || dst < 0 || dst + len > n_keep) len = src = 0;
+      if (ch < 0 || len < 1 || len > c || (int64_t)ch * c + len > P || dst < 0 || dst > n_keep - len) len = src = 0;
     } else if (mine) {
       const int wi = e - count;
       src = P + wi * c;

@@ -235,6 +235,30 @@ def test_compact_bit_exact(lib, case):
             assert torch.equal(k_out.view_as(li.k), li.k) and torch.equal(v_out.view_as(li.v), li.v)
 
 
+@pytest.mark.parametrize("c", [10, 200])
+def test_compact_skips_malformed_entries(lib, c):
+    """Lengths whose running sum passes the largest int, chunks outside the prefix, empty entries: none of them is copied,
+    nothing is written outside the output, and the window follows the budget."""
+    d, w, P, n_keep, guard = 64, 16, 3000, 2000, 4096
+    n = n_keep + w
+    k, v = (torch.randn(((P + w) * d,), device=DEV).to(torch.bfloat16) for _ in range(2))
+    prob = lib.Problem(1, 1, d, w, c, lib.BF16, [P + w], [n_keep], [0], (P + w) * d, d, sel_cap=n_keep // c + 8)
+    entries = [(0, c), (1, 2 ** 31 - 5 - c), (3, c), (4, c), (-1, 3), (P // c, c), (2 ** 31 // c, 1), (2, 0)]
+    sel_chunk, sel_len, sel_count = alloc_sel(prob)
+    sel_chunk[0, 0, 0, :len(entries)] = torch.tensor([e[0] for e in entries])
+    sel_len[0, 0, 0, :len(entries)] = torch.tensor([e[1] for e in entries])
+    sel_count[0, 0, 0] = len(entries)
+    outs = [torch.full((guard + n * d + guard,), 7.0, dtype=torch.bfloat16, device=DEV) for _ in range(2)]
+    lib.chunkkv_compact(prob, k, v, sel_chunk, sel_len, sel_count, *[x[guard:guard + n * d] for x in outs])
+    torch.cuda.synchronize()
+    for x, src in zip(outs, (k, v)):
+        want = torch.full_like(x, 7.0)
+        body = want[guard:guard + n * d].view(n, d)
+        body[:c] = src.view(-1, d)[:c]
+        body[n_keep:] = src.view(-1, d)[P:]
+        assert torch.equal(x, want)
+
+
 # ------------------------------------------------------------------ whole stack
 STACK_CASES = {
     "tiny_f32_x3": (small("tiny", n_layers=3), [1, 2, 3]),
