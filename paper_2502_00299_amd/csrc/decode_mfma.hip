@@ -3,10 +3,10 @@
 // Bound by HBM bandwidth: every K and V row is read once.  The vector ALU cannot keep up with that stream once a
 // kv-head serves more than four query heads (two dot products' worth of work per loaded value and head), so both
 // contractions run on the matrix cores and the vector work per 32 keys is one exponential per key and head.
-// Measured against the streaming vector-ALU kernel this replaced for 16-bit caches (d = 128, per layer): eight
-// sequences of 10 to 55 thousand tokens with 7 heads per kv-head 139 -> 94 us (4.1 -> 6.0 TB/s), 13171 tokens with 4 heads
-// 16.0 -> 14.0 us + merge, 883 tokens 12.6 -> 8.8 us with the merge.  Short caches are bound by latency: launch,
-// arguments, first rows, merge of the wavefronts.
+// Measured against the streaming vector-ALU kernel this replaced for 16-bit caches (d = 128, per layer with the merge):
+// eight sequences of 10 to 55 thousand tokens with 7 heads per kv-head 142 -> 97 us (4.0 -> 5.9 TB/s), 13171 tokens with 4
+// heads 18.9 -> 15.7 us, 848 tokens 13.4 -> 10.0 us.  Short caches are bound by latency: launch, arguments, first rows,
+// merge of the wavefronts.
 //
 //   scores   S[key][head] = K Q^T   v_mfma_f32_16x16x32: keys are the M dimension (16 per tile, two tiles of a
 //            32-key step), query heads the N dimension.  A lane ends with the scores of keys 4q..4q+3 of both
