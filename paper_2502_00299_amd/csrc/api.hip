@@ -11,6 +11,9 @@ namespace ckv {
 namespace {
 
 constexpr int kTargetWorkgroups = 4096;  // ~4 resident rounds of 2 workgroups on each of 256 CUs
+// Single-pass scoring with 256 rows: up to this many workgroups (one per CU) leave half the places empty, so two of them,
+// with 128 rows each, share a key range.  K is read twice, the second time from L2.
+constexpr int64_t kRowSplitWorkgroups = 256;
 constexpr int kSinglePeriodKeys = 160;   // granule of the single-pass kernel's key ranges
 // Key tiles (16 KB) one scoring launch set should hold.  Measured on MI355X: every extra dependent launch
 // costs ~30 us of idle GPU, more than splitting the stack into sets wins back, so one set it is.
@@ -158,6 +161,7 @@ int make_plan(const chunkkv_problem *p, int n_layers, int reuse, Plan *pl) {
   pl->rows_pad_s = rows > 128 ? 256 : 128;
   pl->n_periods = 0;
   pl->max_split_s = 1;
+  int room = 1;   // pairs of floats per row the workspace holds for the ranges' statistics (one float each, at most twice as many)
   if (pl->single_ok) {
     for (int b = 0; b < p->batch; ++b) {
       const int np = ceil_div(p->seqlen[b], kSinglePeriodKeys);
@@ -168,14 +172,15 @@ int make_plan(const chunkkv_problem *p, int n_layers, int reuse, Plan *pl) {
     // key ranges: single_periods_per_range() periods each, a function of the sequence alone
     for (int b = 0; b < p->batch; ++b) {
       const int np = ceil_div(p->seqlen[b], kSinglePeriodKeys);
-      const int sp = ceil_div(np, single_periods_per_range(np));
+      const int sp = ceil_div(np, single_periods_per_range(np)), per = ceil_div(np, 32) < 8 ? 8 : ceil_div(np, 32);
       if (sp > pl->max_split_s) pl->max_split_s = sp;
+      if (ceil_div(np, per) > room) room = ceil_div(np, per);
     }
   }
   const size_t problems = (size_t)pl->n_leaders * p->batch * p->n_kv_heads;
   size_t part_bytes = problems * pl->max_split0 * pl->rows_pad * sizeof(float2);
   if (pl->single_ok) {
-    const size_t pb = problems * pl->max_split_s * pl->rows_pad_s * sizeof(float2);
+    const size_t pb = problems * room * pl->rows_pad_s * sizeof(float2);
     part_bytes = pb > part_bytes ? pb : part_bytes;
   }
   size_t off = 0;
@@ -254,6 +259,7 @@ int run_score(const chunkkv_problem *p, const Plan &pl, const void *const *q, co
       a.n_periods = pl.n_periods;
       a.e_buf = ws + pl.off_ebuf;
       a.m_period = (float *)(ws + pl.off_mper);
+      a.row_stats = (float *)(ws + pl.off_part);
       a.max_split = pl.max_split_s;
       a.rows_pad = pl.rows_pad_s;
       int splits = 1;
@@ -262,7 +268,8 @@ int run_score(const chunkkv_problem *p, const Plan &pl, const void *const *q, co
         const int sp = ceil_div(np, single_periods_per_range(np));
         splits = sp > splits ? sp : splits;
       }
-      { Timed t(kStats, s); rc = launch_score_single(p->dtype, a, dim3(splits, nb * p->n_kv_heads, ng), s); }
+      a.row_groups = pl.rows_pad_s == 256 && (int64_t)splits * nb * p->n_kv_heads * ng <= kRowSplitWorkgroups ? 2 : 1;
+      { Timed t(kStats, s); rc = launch_score_single(p->dtype, a, dim3(splits, nb * p->n_kv_heads, ng * a.row_groups), s); }
       if (rc) return rc;
       { Timed t(kColsum, s); rc = launch_single_scores(a, ng, nb, s); }
       if (rc) return rc;

@@ -52,6 +52,8 @@ struct ScoreArgs {
   int32_t n_periods;       // pitch of e_buf / m_period: max over sequences of ceil(L / 160)
   void *e_buf;             // [problem][n_periods][rows_pad][2 lane halves][80 / c] x 3 bytes: per-(chunk, row) sums of e
   float *m_period;         // [problem][n_periods][rows_pad]  reference those sums are relative to
+  float *row_stats;        // [problem][max_split][rows_pad]  log2 of a row's sum over a key range
+  int32_t row_groups;      // workgroups that share the rows of a key range (1 or 2)
 };
 
 // Caller-supplied row log-sum-exps -> row references of the importance pass.
@@ -143,11 +145,30 @@ __device__ __forceinline__ T kernarg_at(size_t offset, int i) {
 #define CKV_ARG(STRUCT, FIELD, I) kernarg_at<std::remove_cv_t<std::remove_extent_t<decltype(STRUCT::FIELD)>>>(offsetof(STRUCT, FIELD), (I))
 
 // Single-pass scoring: periods (160 keys) one workgroup walks, for a sequence of n_periods periods.  A function
-// of the sequence alone (about 32 ranges per sequence and kv-head, at least 8 periods each), so the key ranges,
+// of the sequence alone (at most 32 ranges per sequence and kv-head, at least 4 periods each), so the key ranges,
 // and with them every rounding of a score, do not depend on how many layers or sequences share a launch.
+constexpr int kSingleMaxRanges = 32, kSingleLeastPeriods = 4;
 __host__ __device__ inline int single_periods_per_range(int n_periods) {
-  const int p = (n_periods + 31) / 32;
-  return p < 8 ? 8 : p;
+  const int p = (n_periods + kSingleMaxRanges - 1) / kSingleMaxRanges;
+  return p < kSingleLeastPeriods ? kSingleLeastPeriods : p + (p & 1);
+}
+
+// log2 of the sum of a row over its key ranges, in range order, eight loads in flight
+__device__ __forceinline__ float merge_row_stats(const float *ps, int n, int pitch) {
+  float m = -1.0e30f, l = 0.f;
+  for (int s0 = 0; s0 < n; s0 += 8) {
+    float x[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) x[i] = ps[(int64_t)(s0 + i < n ? s0 + i : n - 1) * pitch];
+    float mm = m;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) mm = fmaxf(mm, x[i]);
+    l *= __builtin_amdgcn_exp2f(m - mm);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) l += s0 + i < n ? __builtin_amdgcn_exp2f(x[i] - mm) : 0.f;
+    m = mm;
+  }
+  return m + __builtin_log2f(l);
 }
 
 // Geometry of the scoring kernels for one (dtype, head_dim, row count).

@@ -206,23 +206,7 @@ __global__ __launch_bounds__(256) void single_scores_kernel(ScoreArgs a, int per
   {
     const int np_total = (L + kSinglePeriod - 1) / kSinglePeriod, ppr = single_periods_per_range(np_total);
     const int nsplit = (np_total + ppr - 1) / ppr;
-    float m = -1.0e30f, l = 0.f;
-    if (tid < nrows) {
-      const float2 *ps = a.part_stats + problem * a.max_split * a.rows_pad + tid;
-      for (int s0 = 0; s0 < nsplit; s0 += 8) {
-        float2 x[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) x[i] = ps[(int64_t)(s0 + i < nsplit ? s0 + i : nsplit - 1) * a.rows_pad];
-        float mm = m;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) mm = fmaxf(mm, x[i].x);
-        l *= exp2f(m - mm);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) l += s0 + i < nsplit ? x[i].y * exp2f(x[i].x - mm) : 0.f;
-        m = mm;
-      }
-    }
-    s_ref[tid] = tid < nrows ? m + log2f(l) : 3.0e38f;
+    s_ref[tid] = tid < nrows ? merge_row_stats(a.row_stats + problem * a.max_split * a.rows_pad + tid, nsplit, a.rows_pad) : 3.0e38f;
   }
   __syncthreads();
   float ref[RB];

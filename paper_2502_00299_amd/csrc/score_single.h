@@ -28,10 +28,16 @@
 // read as zero).  The ring holds two periods; a period is 5 slots of 32 key rows, slot t holding the rows of
 // step t in M-index order, so the permutation above lives in the global addresses of the loads and the operand
 // reads are "lane register + compile-time slot offset".  The 16-byte segments of a row are XOR-swizzled by the
-// M index (global-address side), so the reads of 16 consecutive lanes hit distinct banks.  One barrier per
-// period: when every wavefront has read the last slot of period p, the loads of period p + 1 (issued a period
-// earlier) are waited for and the whole of period p + 2 is issued into the half that p occupied, so 40 KB per
-// workgroup are in flight for a full period.
+// M index (global-address side), so the reads of 16 consecutive lanes hit distinct banks.  A slot is refilled as soon as
+// every wavefront has its fragments in registers (one barrier per step, two per period where a step is short), so 48 to 64
+// KB per workgroup are in flight all the time; refilled a period at a time, 40 KB were, and none of it while the last of it
+// was awaited: 16 layers of 131072 tokens 1327 -> 1250 us.  The waits count the loads and stores behind the awaited one.
+//
+// A call on one layer is short: launch, queries, a few periods per workgroup, and code that every workgroup fetches and
+// runs through once.  Hence one instance of the period for all periods (the ragged last one masked through the operand the
+// products are added to), the window keys in a short loop of their own, the queries through LDS, key ranges of as few as
+// four periods, and for the shortest launches two workgroups that share the rows of a key range.  One layer, c = 5, 256 rows,
+// 20011 tokens: 46 -> 21 us (of that 16: registers no longer spilled in the loop); 128 rows, 8192 tokens, c = 10: 16.5 -> 12.
 //
 // A wavefront holds NQ blocks of 32 window rows as resident operand fragments and the four wavefronts of a
 // workgroup split the rows, so each K fragment read from LDS feeds NQ matrix instructions.  The work advances
@@ -55,7 +61,7 @@ constexpr int kSpStepBytes = 32 * 256;                  // one ring slot: 32 row
 constexpr int kSpPeriodBytes = kSpSteps * kSpStepBytes; // 40 KB
 constexpr int kSpRingBytes = 2 * kSpPeriodBytes;        // two periods
 constexpr float kSpBig = 1.2676506e30f;                 // 2^100: a step whose sum reaches this is redone
-constexpr int kSpLoadsPerPeriod = 2 * kSpSteps;         // 1 KB loads a wavefront issues per period
+constexpr int kNonTemporal = 2;                         // cache policy of a buffer access: streaming
 constexpr int kSpMaxSeg = 5;                            // chunk segments 16 consecutive keys can touch (c >= 5)
 
 typedef unsigned int u32x3 __attribute__((ext_vector_type(3)));
@@ -81,17 +87,23 @@ __device__ __forceinline__ void pack20(const float (&v)[8], u32x4 &lo, uint32_t 
   hi = (q[6] >> 8) | (q[7] << 12);
 }
 
+// Nothing about x is known behind this: what follows from it is formed from here on.
+__device__ __forceinline__ void opaque(int &x) {
+#if defined(__HIP_DEVICE_COMPILE__)   // the host pass knows no vector registers
+  asm volatile("" : "+v"(x));
+#endif
+}
+
 // period-relative key of position u of lane half 0's own sequence (lane half 1: + C)
 template <int C>
 __host__ __device__ constexpr int sp_key(int u) { return 2 * C * (u / C) + u % C; }
 
 template <int DT>
-__device__ __forceinline__ f32x16 mma0(const u32x4 &a, const u32x4 &b) {  // first product of a chain: C = 0
-  const f32x16 z = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+__device__ __forceinline__ f32x16 mma0(const u32x4 &a, const u32x4 &b, const f32x16 &c) {  // first product of a chain
   if constexpr (DT == CHUNKKV_BF16)
-    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), z, 0, 0, 0);
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
   else
-    return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), z, 0, 0, 0);
+    return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
 }
 
 // DT: chunkkv_dtype (16-bit), C: chunk size, NQ: 32-row blocks per wavefront (rows_pad = 128 * NQ)
@@ -108,10 +120,10 @@ __global__ __launch_bounds__(kThreads, 2) void score_single_kernel(ScoreArgs a) 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wavefront-uniform, and known to be
   const int n = lane & 31, half = lane >> 5;
-  const int bl = blockIdx.y / a.n_kv_heads, h = blockIdx.y % a.n_kv_heads, z = blockIdx.z;
-  const int split = blockIdx.x;
+  const int bl = blockIdx.y / a.n_kv_heads, h = blockIdx.y % a.n_kv_heads, z = blockIdx.z / a.row_groups;
+  const int split = blockIdx.x, row0 = (blockIdx.z % a.row_groups) * (128 * NQ);   // first window row of this workgroup
   const int g = a.n_q_heads / a.n_kv_heads, w = a.window;
-  const int L = pick(a.seq.seqlen, bl), P = L - w, nrows = g * w;
+  const int L = CKV_ARG(ScoreArgs, seq.seqlen, bl), P = L - w, nrows = g * w;
   const int64_t problem = ((int64_t)(a.leader0 + z) * a.batch_total + (a.batch0 + bl)) * a.n_kv_heads + h;
 
   const int np_total = (L + kSpPeriod - 1) / kSpPeriod;
@@ -119,11 +131,12 @@ __global__ __launch_bounds__(kThreads, 2) void score_single_kernel(ScoreArgs a) 
   const int u0 = split * ppr;
   const int u1 = u0 + ppr < np_total ? u0 + ppr : np_total;
   if (u0 >= np_total) return;
-  const int np = u1 - u0;               // periods of this workgroup
+  const int np_prefix = (P + kSpPeriod - 1) / kSpPeriod;   // periods with keys before the window
+  const int np = (u1 < np_prefix ? u1 : np_prefix) - u0;   // periods of this workgroup: none, if it has window keys alone
   const int range0 = u0 * kSpPeriod;    // its first key
 
-  const char *qbase = (const char *)pick(a.q, z) + ((int64_t)(a.batch0 + bl) * a.n_q_heads + (int64_t)h * g) * w * ROWB;
-  const char *kbase = (const char *)pick(a.k, z) + (pick(a.seq.kv_base, bl) + (int64_t)h * a.kv_stride_head) * ESZ;
+  const char *qbase = (const char *)CKV_ARG(ScoreArgs, q, z) + ((int64_t)(a.batch0 + bl) * a.n_q_heads + (int64_t)h * g) * w * ROWB;
+  const char *kbase = (const char *)CKV_ARG(ScoreArgs, k, z) + (CKV_ARG(ScoreArgs, seq.kv_base, bl) + (int64_t)h * a.kv_stride_head) * ESZ;
   const int64_t ktok = a.kv_stride_tok * ESZ;
   const float c1 = a.scale_log2e;
 
@@ -131,8 +144,6 @@ __global__ __launch_bounds__(kThreads, 2) void score_single_kernel(ScoreArgs a) 
   // 8 wave + 4 j + l / 16, 16-byte position l % 16, and fetches the segment that position holds after the
   // swizzle, of the key that M index stands for in step t.  M index 8 wave + 4 j + b is position
   // u = 16 t + 4 wave + b of lane half j, so the two loads of a step differ by a lane constant.
-  const __amdgpu_buffer_rsrc_t krsrc =
-      __builtin_amdgcn_make_buffer_rsrc((void *)kbase, 0, (int)((uint32_t)(L - 1) * (uint32_t)ktok + ROWB), 0x00020000);
   uint32_t klane[kSpSteps], kdelta;
   {
     const int b = lane / 16, pos = lane % 16;
@@ -144,45 +155,45 @@ __global__ __launch_bounds__(kThreads, 2) void score_single_kernel(ScoreArgs a) 
     }
     kdelta = (uint32_t)(C * (int)ktok + (seg1 - seg0) * 16);
   }
-  // all five slots of period prel, into ring half prel & 1
-  auto issue_period = [&](int prel) __attribute__((always_inline)) {
+  // step T of period prel, into its slot of the ring; periods that are not there read as zero, so that the number of loads
+  // in flight is a compile-time constant at every wait
+  const int kbytes = (int)((uint32_t)(L - 1) * (uint32_t)ktok + ROWB);
+  auto issue_step = [&](int prel, auto t_c) __attribute__((always_inline)) {
+    constexpr int T = decltype(t_c)::value;
+    const __amdgpu_buffer_rsrc_t krsrc = __builtin_amdgcn_make_buffer_rsrc((void *)kbase, 0, prel < np ? kbytes : 0, 0x00020000);
     const uint32_t off = (uint32_t)(range0 + prel * kSpPeriod) * (uint32_t)ktok;  // wavefront-uniform
-    char *dst = smem + (prel & 1) * kSpPeriodBytes + wave * 2048;
-#pragma unroll
-    for (int t = 0; t < kSpSteps; ++t) {
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(krsrc, (__attribute__((address_space(3))) void *)(dst + t * kSpStepBytes), 16,
-                                               klane[t], off, 0, 0);
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(krsrc, (__attribute__((address_space(3))) void *)(dst + t * kSpStepBytes + 1024),
-                                               16, klane[t] + kdelta, off, 0, 0);
-    }
+    char *dst = smem + (prel & 1) * kSpPeriodBytes + wave * 2048 + T * kSpStepBytes;
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(krsrc, (__attribute__((address_space(3))) void *)dst, 16, klane[T], off, 0, 0);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(krsrc, (__attribute__((address_space(3))) void *)(dst + 1024), 16, klane[T] + kdelta, off, 0, 0);
   };
-  issue_period(0);
-  if (np > 1) issue_period(1);
-
-  // wavefronts whose rows are all padding only move K
-  const bool active = wave * NQ * 32 < nrows;
-
-  // ---- window queries: resident operand fragments (lane n: row n of the block, elements 16 ks + 8 half ..)
-  u32x4 qf[NQ][NKS];
+  // The window queries come through the ring as well (a row block is 8 KB, like a step): read straight into operand
+  // fragments, every load would touch 32 lines, 10 thousand cycles for 64 KB.  The first steps of K share the way.
+  constexpr int kQSlot = NQ == 2 ? 2 : 3;   // ring slots of the row blocks start here
+  issue_step(0, std::integral_constant<int, 0>{});
+  issue_step(0, std::integral_constant<int, 1>{});
+  if constexpr (NQ == 1) issue_step(0, std::integral_constant<int, 2>{});
+  {
+    const __amdgpu_buffer_rsrc_t qrsrc = __builtin_amdgcn_make_buffer_rsrc((void *)qbase, 0, nrows * ROWB, 0x00020000);   // rows past the last read as zero
+    char *dst = smem + (kQSlot + wave * NQ) * kSpStepBytes;
+    const uint32_t off = (uint32_t)(row0 + wave * NQ * 32) * ROWB;
 #pragma unroll
-  for (int qi = 0; qi < NQ; ++qi) {
-    const int row = (wave * NQ + qi) * 32 + n;
-#pragma unroll
-    for (int ks = 0; ks < NKS; ++ks) {
-      qf[qi][ks] = u32x4{0, 0, 0, 0};
-      if (row < nrows) qf[qi][ks] = *(const u32x4 *)(qbase + (int64_t)row * ROWB + (2 * ks + half) * 16);
+    for (int j = 0; j < 8 * NQ; ++j) {
+      const int row = 4 * (j % 8) + lane / 16;
+      const uint32_t vo = (uint32_t)(row * ROWB + ((lane % 16) ^ (row & 15)) * 16), so = off + (uint32_t)(j / 8 * kSpStepBytes);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(qrsrc, (__attribute__((address_space(3))) void *)(dst + j * 1024), 16, vo, so, 0, 0);
     }
   }
+
+  // wavefronts whose rows are all padding only move K
+  const bool active = row0 + wave * NQ * 32 < nrows;
+
   float m_run[NQ], l_run[NQ], slot[NQ][S];
-  int lim[NQ];  // last key the row may see
 #pragma unroll
   for (int qi = 0; qi < NQ; ++qi) {
     m_run[qi] = kNegBig;
     l_run[qi] = 0.f;
 #pragma unroll
     for (int s = 0; s < S; ++s) slot[qi][s] = 0.f;
-    const int row = (wave * NQ + qi) * 32 + n;
-    lim[qi] = P + (row < nrows ? row % w : 0);
   }
 
   // ---- K operand fragments: lane (n, half) reads row n of a slot, segment 2 ks + half, at its swizzled position.
@@ -192,6 +203,21 @@ __global__ __launch_bounds__(kThreads, 2) void score_single_kernel(ScoreArgs a) 
 #pragma unroll
   for (int ks = 0; ks < NKS; ++ks) kaddr[ks] = (uint32_t)(n * ROWB + (((2 * ks + half) ^ (n & 15)) * 16));
   static_assert(kSpPeriodBytes == 0xA000 && 32 * ROWB <= 0x2000, "ring half flip");
+  // window queries: resident operand fragments (lane n: row n of the block, elements 16 ks + 8 half ..)
+  u32x4 qf[NQ][NKS];
+  __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+#pragma unroll
+  for (int qi = 0; qi < NQ; ++qi)
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks) qf[qi][ks] = *(const u32x4 *)(smem + (kaddr[ks] + (uint32_t)((kQSlot + wave * NQ + qi) * kSpStepBytes)));
+  lds_barrier();   // every wavefront's rows are in registers and its part of the first steps has landed
+  if constexpr (NQ == 2) issue_step(0, std::integral_constant<int, 2>{});
+  issue_step(0, std::integral_constant<int, 3>{});
+  issue_step(0, std::integral_constant<int, 4>{});
+  issue_step(1, std::integral_constant<int, 0>{});
+  issue_step(1, std::integral_constant<int, 1>{});
+  issue_step(1, std::integral_constant<int, 2>{});
+  issue_step(1, std::integral_constant<int, 3>{});
   auto frag = [&](auto t_c, int ks) __attribute__((always_inline)) {
     constexpr int T = decltype(t_c)::value;
     return *(const u32x4 *)(smem + (kaddr[ks] + (uint32_t)(T * kSpStepBytes)));
@@ -208,11 +234,30 @@ __global__ __launch_bounds__(kThreads, 2) void score_single_kernel(ScoreArgs a) 
   // 24-bit floats); m [rows_pad] floats.  Consecutive lanes write consecutive pieces.
   constexpr int G8 = S / 8;                                  // groups of eight sums per lane half
   constexpr int kPeriodRowBytes = S == 4 ? 24 : 2 * G8 * 20;  // E bytes per period and row
-  char *e_problem = (char *)a.e_buf + (int64_t)problem * a.n_periods * a.rows_pad * kPeriodRowBytes;
-  char *m_problem = (char *)a.m_period + (int64_t)problem * a.n_periods * a.rows_pad * 4;
-  const uint32_t lane_row = (uint32_t)(wave * NQ * 32 + n);
-  const uint32_t lane_m = lane_row * 4u;
-  const int key_half = C * half;  // period-relative key of the lane half's position 0
+  constexpr int kPeriodStores = NQ * (S == 4 ? 2 : 2 * G8 + 1);   // store instructions of a wavefront per period
+  // Buffer stores: one address register at a time, and the lane half that has no reference to store has its offset out of
+  // range, so the period's end is no branch (which would let the compiler move sums across it).  The wide ones keep the
+  // scalar offset a constant: with a register there the compiler takes the data registers for free at once, and the
+  // vector instruction behind the store overwrote them before they were read.
+  const uint32_t rp = (uint32_t)a.rows_pad;
+  const __amdgpu_buffer_rsrc_t e_rsrc = __builtin_amdgcn_make_buffer_rsrc(
+      (char *)a.e_buf + problem * a.n_periods * a.rows_pad * kPeriodRowBytes, 0, (int)((uint32_t)a.n_periods * rp * (uint32_t)kPeriodRowBytes), 0x00020000);
+  const __amdgpu_buffer_rsrc_t m_rsrc = __builtin_amdgcn_make_buffer_rsrc(
+      (char *)a.m_period + problem * a.n_periods * a.rows_pad * 4, 0, (int)((uint32_t)a.n_periods * rp * 4u), 0x00020000);
+  const uint32_t lane_row = (uint32_t)(row0 + wave * NQ * 32 + n);
+  const uint32_t e_lane = (uint32_t)half * (uint32_t)(S == 4 ? 1 : G8) * rp + lane_row, m_lane = half == 0 ? lane_row * 4u : 0x7FFFFFFFu;
+  // What the products of a step are added to: zero, but minus infinity for keys that are not before the window, which
+  // only the ragged last period has.  It takes the code of the others: a workgroup would run through code of its own once,
+  // and fetching that took longer than four periods.
+  f32x16 mask = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  const int ragged = P % kSpPeriod != 0 ? P / kSpPeriod - u0 : -1;   // period of the range, if it is in it
+  auto set_mask = [&](auto t_c) __attribute__((always_inline)) {
+    constexpr int T = decltype(t_c)::value;
+    int lim = P % kSpPeriod - C * half;   // first position, as a key of lane half 0, that is not before the window
+    opaque(lim);                          // the masks are formed here, not kept for all steps
+#pragma unroll
+    for (int v = 0; v < 16; ++v) mask[v] = sp_key<C>(16 * T + v) < lim ? 0.f : -__builtin_inff();
+  };
 
   // logits of one micro-step; REFILL: the fragments are re-read from slot TR behind their product
   auto chain = [&](f32x16 &dst, auto qi_c, auto refill_c, auto tr_c) __attribute__((always_inline)) {
@@ -220,43 +265,26 @@ __global__ __launch_bounds__(kThreads, 2) void score_single_kernel(ScoreArgs a) 
     constexpr bool REFILL = decltype(refill_c)::value;
 #pragma unroll
     for (int ks = 0; ks < NKS; ++ks) {
-      if (ks == 0) dst = mma0<DT>(kf[0], qf[QI][0]);
+      if (ks == 0) dst = mma0<DT>(kf[0], qf[QI][0], mask);
       else mma<DT>(dst, kf[ks], qf[QI][ks]);  // D[key][row]
       if constexpr (REFILL) kf[ks] = frag(tr_c, ks);
     }
   };
 
-  // exponentials of one micro-step against the current reference: sums per chunk segment of the step (seg[]),
-  // window keys (lw, masked periods only)
-  auto exps = [&](const f32x16 &x, auto qi_c, int pkey0, auto t_c, auto masked_c, float (&seg)[kSpMaxSeg], float &lw)
-      __attribute__((always_inline)) {
+  // exponentials of one micro-step against the current reference: sums per chunk segment of the step
+  auto exps = [&](const f32x16 &x, auto qi_c, auto t_c, float (&seg)[kSpMaxSeg]) __attribute__((always_inline)) {
     constexpr int T = decltype(t_c)::value, QI = decltype(qi_c)::value;
-    constexpr bool MASKED = decltype(masked_c)::value;
     const float negm = -m_run[QI];
-    lw = 0.f;
     constexpr int U0 = 16 * T;
 #pragma unroll
-    for (int v4 = 0; v4 < 16; v4 += 4) {
-      float e[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) e[i] = __builtin_fmaf(x[v4 + i], c1, negm);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) e[i] = fast_exp2(e[i]);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int u = U0 + v4 + i, sg = u / C - U0 / C;
-        if constexpr (MASKED) {
-          const int key = pkey0 + key_half + sp_key<C>(u);
-          lw += (key >= P && key <= lim[QI]) ? e[i] : 0.f;   // window keys count for the row sum only
-          e[i] = key < P ? e[i] : 0.f;
-        }
-        const bool first = v4 + i == 0 || (u % C == 0);
-        seg[sg] = first ? e[i] : seg[sg] + e[i];
-      }
+    for (int v = 0; v < 16; ++v) {
+      const float e = fast_exp2(__builtin_fmaf(x[v], c1, negm));
+      const int u = U0 + v, sg = u / C - U0 / C;
+      seg[sg] = v == 0 || u % C == 0 ? e : seg[sg] + e;
     }
   };
 
-  // The unmasked micro-step in issue order: eight slots of one matrix instruction of the NEXT micro-step (with
+  // The micro-step in issue order: eight slots of one matrix instruction of the NEXT micro-step (with
   // its fragment re-read) and the vector work of two keys of THIS one, software-pipelined over the slots (the
   // scaling of slot k + 1, the exponentials of slot k, the adds of slot k - 1), so that nothing in a slot
   // waits for anything in the same slot and the vector work of a slot takes about as long as its matrix
@@ -273,7 +301,7 @@ __global__ __launch_bounds__(kThreads, 2) void score_single_kernel(ScoreArgs a) 
 #pragma unroll
     for (int k = 0; k <= NKS; ++k) {
       if (k < NKS) {
-        if (k == 0) dst = mma0<DT>(kf[0], qf[QNX][0]);
+        if (k == 0) dst = mma0<DT>(kf[0], qf[QNX][0], mask);
         else mma<DT>(dst, kf[k], qf[QNX][k]);
         if constexpr (REFILL) kf[k] = frag(tr_c, k);
       }
@@ -304,53 +332,62 @@ __global__ __launch_bounds__(kThreads, 2) void score_single_kernel(ScoreArgs a) 
   // of the micro-step after it, the exponentials of this one.
   // prel: period relative to the range; T: step within the period; QI: row block; TILE: accumulator tile that
   // holds this micro-step's logits.
-  auto micro = [&](int prel, auto t_c, auto qi_c, auto tile_c, auto masked_c) __attribute__((always_inline)) {
+  auto micro = [&](int prel, auto t_c, auto qi_c, auto tile_c) __attribute__((always_inline)) {
     constexpr int T = decltype(t_c)::value, QI = decltype(qi_c)::value, TILE = decltype(tile_c)::value;
-    constexpr bool MASKED = decltype(masked_c)::value;
     constexpr bool STEP_END = QI == NQ - 1;                 // the next micro-step belongs to the next step
     constexpr int TNX = STEP_END ? (T + 1) % kSpSteps : T;  // its step ...
     constexpr int QNX = STEP_END ? 0 : QI + 1;              // ... and row block
     // if it is the last use of its block's fragments they are re-read for the block after (slot TR)
     constexpr bool REFILL = QNX == NQ - 1;
     constexpr int TR = (TNX + 1) % kSpSteps;
-    // This micro-step's re-reads are the first that touch the next period: every wavefront has then read the
-    // last slot of this period.  The loads of the next period, issued a period ago, are waited for; behind the
-    // barrier the half this period occupied is free and takes the period after next.
-    if constexpr (REFILL && TR == 0) {
-      __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+    // The re-reads take step R (counted from this period's first).  Its loads are waited for, with those of later steps in
+    // flight; behind the barrier it is there for all, and every wavefront has the fragments of step R - 2 in registers,
+    // whose slot is free.  Two row blocks per wavefront: at every step, the slot takes step R + 8.  One row block: a step is
+    // too short for a barrier of its own (32 layers of 32768 tokens 579 us), so at steps 3 and 5, for the steps up to the next.
+    if constexpr (REFILL && NQ == 2) {
+      constexpr int R = T + 1, RN = R + 8;
+      // the sums of one period leave within the last eight steps, of two from step 5 - 3 on back
+      constexpr int kStores = kPeriodStores * (T < 3 ? 2 : 1);
+      if (active && prel >= 2) __builtin_amdgcn_s_waitcnt(vmcnt_imm(7 * 2 + kStores));
+      else __builtin_amdgcn_s_waitcnt(vmcnt_imm(7 * 2));
       __builtin_amdgcn_s_barrier();
-      if (prel + 2 < np) issue_period(prel + 2);
+      issue_step(prel + RN / kSpSteps, std::integral_constant<int, RN % kSpSteps>{});
+    }
+    if constexpr (REFILL && NQ == 1 && (TR == 0 || TR == 3)) {
+      if (active && prel >= 1) __builtin_amdgcn_s_waitcnt(vmcnt_imm(4 * 2 + kPeriodStores));
+      else __builtin_amdgcn_s_waitcnt(vmcnt_imm(4 * 2));
+      __builtin_amdgcn_s_barrier();
+      if constexpr (TR == 3) {
+        issue_step(prel + 1, std::integral_constant<int, 4>{});
+        issue_step(prel + 2, std::integral_constant<int, 0>{});
+        issue_step(prel + 2, std::integral_constant<int, 1>{});
+      } else {
+        issue_step(prel + 2, std::integral_constant<int, 2>{});
+        issue_step(prel + 2, std::integral_constant<int, 3>{});
+      }
+    }
+    if constexpr (REFILL && TR == 0) {
 #pragma unroll
       for (int ks = 0; ks < NKS; ++ks) kaddr[ks] ^= (uint32_t)kSpPeriodBytes;
     }
     if (active) {
       // (at the very end of the range the matrix work multiplies stale rows of the ring: in bounds, never used)
-      const int pkey0 = range0 + prel * kSpPeriod;
-      float seg[kSpMaxSeg], lw = 0.f;
+      if constexpr (STEP_END)
+        if (__builtin_expect(prel + (T == kSpSteps - 1 ? 1 : 0) == ragged, 0)) set_mask(std::integral_constant<int, TNX>{});
+      float seg[kSpMaxSeg];
       constexpr int NSEG = (16 * T + 15) / C - (16 * T) / C + 1;
       static_assert(NSEG <= kSpMaxSeg, "segments per step");
-      if constexpr (MASKED) {
-        chain(acc[TILE ^ 1], std::integral_constant<int, QNX>{}, std::integral_constant<bool, REFILL>{},
-              std::integral_constant<int, TR>{});
-        exps(acc[TILE], qi_c, pkey0, t_c, masked_c, seg, lw);
-      } else {
-        fused(acc[TILE ^ 1], acc[TILE], std::integral_constant<int, QNX>{}, std::integral_constant<bool, REFILL>{},
-              std::integral_constant<int, TR>{}, qi_c, t_c, seg);
-      }
+      fused(acc[TILE ^ 1], acc[TILE], std::integral_constant<int, QNX>{}, std::integral_constant<bool, REFILL>{},
+            std::integral_constant<int, TR>{}, qi_c, t_c, seg);
       float tot = seg[0];
 #pragma unroll
       for (int sg = 1; sg < NSEG; ++sg) tot += seg[sg];
-      if constexpr (MASKED) tot += lw;
-      if (__builtin_amdgcn_ballot_w64(tot >= kSpBig) != 0) {
+      if (__builtin_expect(__builtin_amdgcn_ballot_w64(tot >= kSpBig) != 0, 0)) {
         // rare: a sum reached 2^100 (always on the first step of a range).  Lanes that did move their
         // reference to the step's own maximum, rescale what they hold and redo the step.
-        float bm = -3.0e38f;
+        float bm = acc[TILE][0];
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          float xv = acc[TILE][v];
-          if constexpr (MASKED) xv = (pkey0 + key_half + sp_key<C>(16 * T + v)) <= lim[QI] ? xv : -3.0e38f;
-          bm = fmaxf(bm, xv);
-        }
+        for (int v = 1; v < 16; ++v) bm = fmaxf(bm, acc[TILE][v]);
         // the two lane halves of a row move together, so a row has one reference per period
         bm = fmaxf(bm, __shfl_xor(bm, 32));
         const bool mine = __shfl_xor(tot, 32) >= kSpBig || tot >= kSpBig;
@@ -360,7 +397,7 @@ __global__ __launch_bounds__(kThreads, 2) void score_single_kernel(ScoreArgs a) 
         for (int s = 0; s < S; ++s) slot[QI][s] *= f;
         l_run[QI] *= f;
         m_run[QI] = m_new;
-        exps(acc[TILE], qi_c, pkey0, t_c, masked_c, seg, lw);
+        exps(acc[TILE], qi_c, t_c, seg);
       }
       // commit: every segment goes to its chunk's register (the first segment of a chunk in a period starts
       // the register afresh)
@@ -371,7 +408,6 @@ __global__ __launch_bounds__(kThreads, 2) void score_single_kernel(ScoreArgs a) 
         const bool fresh = sl * C >= 16 * T;
         slot[QI][sl] = fresh ? seg[sg] : slot[QI][sl] + seg[sg];
       }
-      if constexpr (MASKED) l_run[QI] += lw;
       if constexpr (T == kSpSteps - 1) {
         // end of the period: the sums and the reference they are relative to leave the lane.  Streaming
         // (non-temporal) stores: the 1.2 GB a launch writes is read back by the next kernel only, and a read
@@ -380,12 +416,11 @@ __global__ __launch_bounds__(kThreads, 2) void score_single_kernel(ScoreArgs a) 
 #pragma unroll
         for (int s = 0; s < S; ++s) sum += slot[QI][s];
         l_run[QI] += sum;
-        const uint32_t pbase = (uint32_t)(u0 + prel) * (uint32_t)a.rows_pad;
-        const uint32_t rp = (uint32_t)a.rows_pad, row = lane_row + (uint32_t)(QI * 32);
-        char *pdst = e_problem + pbase * (uint32_t)kPeriodRowBytes;
+        const uint32_t pbase = (uint32_t)(u0 + prel) * rp, ebase = pbase * (uint32_t)kPeriodRowBytes;   // wavefront-uniform
+        constexpr uint32_t row = QI * 32;
         if constexpr (S == 4) {
-          __builtin_nontemporal_store(pack24(slot[QI][0], slot[QI][1], slot[QI][2], slot[QI][3]),
-                                      (u32x3 *)(pdst + ((uint32_t)half * rp + row) * 12u));
+          __builtin_amdgcn_raw_buffer_store_b96(pack24(slot[QI][0], slot[QI][1], slot[QI][2], slot[QI][3]), e_rsrc,
+                                                (int)(e_lane * 12u + (ebase + row * 12u)), 0, kNonTemporal);
         } else {
 #pragma unroll
           for (int g8 = 0; g8 < G8; ++g8) {
@@ -395,72 +430,93 @@ __global__ __launch_bounds__(kThreads, 2) void score_single_kernel(ScoreArgs a) 
             u32x4 lo;
             uint32_t hi;
             pack20(v8, lo, hi);
-            const uint32_t cell = ((uint32_t)(half * G8 + g8)) * rp + row;
-            __builtin_nontemporal_store(lo, (u32x4 *)(pdst + cell * 16u));
-            __builtin_nontemporal_store(hi, (uint32_t *)(pdst + (uint32_t)(2 * G8) * rp * 16u + cell * 4u));
+            const uint32_t cell = (uint32_t)g8 * rp + row;
+            __builtin_amdgcn_raw_buffer_store_b128(lo, e_rsrc, (int)(e_lane * 16u + (ebase + cell * 16u)), 0, kNonTemporal);
+            __builtin_amdgcn_raw_buffer_store_b32(hi, e_rsrc, (int)(e_lane * 4u + (ebase + (uint32_t)(2 * G8) * rp * 16u + cell * 4u)), 0, kNonTemporal);
           }
         }
-        if (half == 0) __builtin_nontemporal_store(m_run[QI], (float *)(m_problem + (pbase * 4u + lane_m + (uint32_t)(QI * 32 * 4))));
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(m_run[QI]), m_rsrc, (int)m_lane, (int)((pbase + row) * 4u), kNonTemporal);
       }
     }
   };
 
   // one step (all row blocks of the wavefront); P0: accumulator tile of the step's first micro-step
-  auto step = [&](int prel, auto t_c, auto p0_c, auto masked_c) __attribute__((always_inline)) {
+  auto step = [&](int prel, auto t_c, auto p0_c) __attribute__((always_inline)) {
     constexpr int P0 = decltype(p0_c)::value;
-    micro(prel, t_c, std::integral_constant<int, 0>{}, std::integral_constant<int, P0>{}, masked_c);
+    micro(prel, t_c, std::integral_constant<int, 0>{}, std::integral_constant<int, P0>{});
     if constexpr (NQ == 2)
-      micro(prel, t_c, std::integral_constant<int, 1>{}, std::integral_constant<int, P0 ^ 1>{}, masked_c);
+      micro(prel, t_c, std::integral_constant<int, 1>{}, std::integral_constant<int, P0 ^ 1>{});
   };
-  // one period; PP: tile of its first micro-step (NQ = 2: always 0; NQ = 1: alternates with the period)
-  auto period = [&](int prel, auto pp_c, auto masked_c) __attribute__((always_inline)) {
-    constexpr int PP = decltype(pp_c)::value;
+  auto period = [&](int prel) __attribute__((always_inline)) {
     constexpr int ALT = NQ == 1 ? 1 : 0;  // the tile alternates from step to step
-    step(prel, std::integral_constant<int, 0>{}, std::integral_constant<int, PP>{}, masked_c);
-    step(prel, std::integral_constant<int, 1>{}, std::integral_constant<int, PP ^ ALT>{}, masked_c);
-    step(prel, std::integral_constant<int, 2>{}, std::integral_constant<int, PP>{}, masked_c);
-    step(prel, std::integral_constant<int, 3>{}, std::integral_constant<int, PP ^ ALT>{}, masked_c);
-    step(prel, std::integral_constant<int, 4>{}, std::integral_constant<int, PP>{}, masked_c);
+    step(prel, std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{});
+    step(prel, std::integral_constant<int, 1>{}, std::integral_constant<int, ALT>{});
+    step(prel, std::integral_constant<int, 2>{}, std::integral_constant<int, 0>{});
+    step(prel, std::integral_constant<int, 3>{}, std::integral_constant<int, ALT>{});
+    step(prel, std::integral_constant<int, 4>{}, std::integral_constant<int, 0>{});
+    if constexpr (NQ == 1) acc[0] = acc[1];   // an odd number of micro-steps: the next period starts with the same tile
   };
 
-  // ---- prologue: period 0 landed (the loads of period 1 may still be out), fragments of block 0, logits of
-  // micro-step 0
-  if (np > 1) __builtin_amdgcn_s_waitcnt(vmcnt_imm(kSpLoadsPerPeriod));
-  else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
-  __builtin_amdgcn_s_barrier();
-  if (active) {
+  // ---- fragments of block 0, logits of micro-step 0
+  if (active && np > 0) {
+    if (ragged == 0) set_mask(std::integral_constant<int, 0>{});
 #pragma unroll
     for (int ks = 0; ks < NKS; ++ks) kf[ks] = frag(std::integral_constant<int, 0>{}, ks);
     chain(acc[0], std::integral_constant<int, 0>{}, std::integral_constant<bool, NQ == 1>{}, std::integral_constant<int, 1>{});
   }
+  for (int prel = 0; prel < np; ++prel) period(prel);
 
-  // periods whose keys are all prefix keys run without masks
-  int n_clean = (P - range0) / kSpPeriod;
-  n_clean = n_clean < 0 ? 0 : (n_clean > np ? np : n_clean);
-  int prel = 0;
-  if constexpr (NQ == 2) {
-    for (; prel < n_clean; ++prel) period(prel, std::integral_constant<int, 0>{}, std::false_type{});
-    for (; prel < np; ++prel) period(prel, std::integral_constant<int, 0>{}, std::true_type{});
-  } else {
-    for (; prel + 2 <= n_clean; prel += 2) {
-      period(prel, std::integral_constant<int, 0>{}, std::false_type{});
-      period(prel + 1, std::integral_constant<int, 1>{}, std::false_type{});
+  // ---- window keys, which count for the row sums only: the last range takes them, 32 at a time in their order, each
+  // against its own maximum.  All of them fit the ring (no more than 256 rows of one head).
+  if (u1 == np_total) {
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+    lds_barrier();   // the ring is dead
+    const __amdgpu_buffer_rsrc_t krsrc = __builtin_amdgcn_make_buffer_rsrc((void *)kbase, 0, kbytes, 0x00020000);
+    const uint32_t row = (uint32_t)(8 * wave + lane / 16), seg = (uint32_t)((lane % 16) ^ (int)(row & 15));
+    for (int key0 = P, sl = 0; key0 < L; key0 += 32, ++sl) {
+      char *dst = smem + sl * kSpStepBytes + wave * 2048;
+      const uint32_t vo = row * (uint32_t)ktok + seg * 16u, v1 = (row + 4u) * (uint32_t)ktok + (seg ^ 4u) * 16u, off = (uint32_t)key0 * (uint32_t)ktok;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(krsrc, (__attribute__((address_space(3))) void *)dst, 16, vo, off, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(krsrc, (__attribute__((address_space(3))) void *)(dst + 1024), 16, v1, off, 0, 0);
     }
-    for (; prel < np; ++prel) {
-      if (prel & 1) period(prel, std::integral_constant<int, 1>{}, std::true_type{});
-      else period(prel, std::integral_constant<int, 0>{}, std::true_type{});
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+    lds_barrier();
+    if (active) {
+      for (int key0 = P, sl = 0; key0 < L; key0 += 32, ++sl) {
+#pragma unroll
+        for (int ks = 0; ks < NKS; ++ks) kf[ks] = *(const u32x4 *)(smem + ((kaddr[ks] & 0x1FFFu) + (uint32_t)(sl * kSpStepBytes)));
+#pragma unroll
+        for (int qi = 0; qi < NQ; ++qi) {
+          f32x16 x = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int ks = 0; ks < NKS; ++ks) mma<DT>(x, kf[ks], qf[qi][ks]);
+          const int r = row0 + (wave * NQ + qi) * 32 + n;
+          const int lim = P + (r < nrows ? r % w : 0) - key0 - 4 * half;   // last key the row may see
+          float bm = kNegBig;
+#pragma unroll
+          for (int v = 0; v < 16; ++v) bm = fmaxf(bm, 8 * (v / 4) + v % 4 <= lim ? x[v] : kNegBig);
+          bm = fmaxf(bm, __shfl_xor(bm, 32));   // the lane halves of a row share its reference
+          const float m_new = fmaxf(m_run[qi], bm * c1);
+          float sum = 0.f;
+#pragma unroll
+          for (int v = 0; v < 16; ++v) sum += 8 * (v / 4) + v % 4 <= lim ? fast_exp2(__builtin_fmaf(x[v], c1, -m_new)) : 0.f;
+          l_run[qi] = __builtin_fmaf(l_run[qi], fast_exp2(m_run[qi] - m_new), sum);
+          m_run[qi] = m_new;
+        }
+      }
     }
   }
 
-  // per-range (reference, sum) of every row for the merge (the lane halves share the reference)
+  // the range's log2 sum of every row for the merge (the lane halves share the reference)
   if (active) {
 #pragma unroll
     for (int qi = 0; qi < NQ; ++qi) {
-      const int row = (wave * NQ + qi) * 32 + n;
+      const int row = row0 + (wave * NQ + qi) * 32 + n;
       const float l = l_run[qi] + __shfl_xor(l_run[qi], 32);
-      if (half == 0) a.part_stats[(problem * a.max_split + split) * a.rows_pad + row] = make_float2(m_run[qi], l);
+      if (half == 0) a.row_stats[(problem * a.max_split + split) * a.rows_pad + row] = m_run[qi] + __builtin_log2f(l);
     }
   }
+  __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));   // the empty loads past the last step still write zeros into the ring
 }
 
 template <int DT, int C, int NQ>
@@ -479,7 +535,7 @@ int launch_single_cfg(const ScoreArgs &a, dim3 grid, hipStream_t s) {
 // every compiled geometry of one storage type: chunk size x row blocks per wavefront
 template <int DT>
 int launch_single_dt(const ScoreArgs &a, dim3 grid, hipStream_t s) {
-  const int nq = a.rows_pad / 128;
+  const int nq = a.rows_pad / (128 * a.row_groups);
   if (nq != 1 && nq != 2) return CHUNKKV_ERR_UNSUPPORTED;
   switch (a.chunk) {
     case 5: return nq == 1 ? launch_single_cfg<DT, 5, 1>(a, grid, s) : launch_single_cfg<DT, 5, 2>(a, grid, s);

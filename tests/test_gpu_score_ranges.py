@@ -1,0 +1,63 @@
+"""Single-pass scoring where its kernel can go wrong: the ragged last period, a range that holds window keys alone, the
+largest window, workgroups that share the rows of a range, wavefronts without rows, and every compiled chunk size; scores
+against plain float64."""
+import math
+
+import pytest
+import torch
+
+import paper_2502_00299_amd as ckv
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+KIND = {ckv.BF16: torch.bfloat16, ckv.F16: torch.float16}
+
+
+def oracle_scores(q, k, w, c):
+    """[Hkv][C] chunk scores of one sequence in float64: q [Hq][w][d], k [Hkv][L][d]."""
+    g, (hkv, L, d) = q.shape[0] // k.shape[0], k.shape
+    P = L - w
+    seen = torch.arange(L)[None, :] <= P + torch.arange(w)[:, None]
+    out = torch.zeros(hkv, (P + c - 1) // c, dtype=torch.float64)
+    for h in range(hkv):
+        s = (q[h * g:(h + 1) * g].double() @ k[h].double().T) / math.sqrt(d)
+        p = torch.softmax(s.masked_fill(~seen, float("-inf")), dim=2)[:, :, :P].sum((0, 1))
+        out[h].index_add_(0, torch.arange(P) // c, p)
+    return out
+
+
+# (prefix tokens, window, query heads per kv-head, chunk size): periods are 160 keys, ranges four of them or more
+CASES = [
+    (1, 32, 4, 5), (159, 32, 4, 10), (160, 32, 4, 20), (161, 64, 4, 5),
+    (640, 96, 2, 10),        # four whole periods, then a range that holds window keys alone
+    (639, 32, 7, 5), (641, 32, 7, 10), (2000, 32, 7, 20),   # 224 rows: the last wavefront of the second row group has none
+    (1281, 64, 4, 5), (1439, 64, 4, 10), (1440, 64, 4, 20),
+    (1290, 256, 1, 10),      # the largest window one head can have
+    (3333, 17, 4, 5), (3333, 16, 5, 10), (3333, 25, 3, 20),
+    (9001, 64, 4, 5),        # more than one round of ranges
+]
+
+
+@pytest.mark.parametrize("dtype", [ckv.BF16, ckv.F16])
+@pytest.mark.parametrize("P,w,g,c", CASES)
+def test_scores_match_float64(dtype, P, w, g, c):
+    gen = torch.Generator().manual_seed(P * 7 + w)
+    hkv, d, L = 2, 128, P + w
+    q = torch.randn((hkv * g, w, d), generator=gen).to(KIND[dtype])
+    k = torch.randn((hkv, L, d), generator=gen).to(KIND[dtype])
+    want = oracle_scores(q, k, w, c)
+    prob = ckv.Problem(hkv * g, hkv, d, w, c, dtype, [L], [0], [0], L * d, d)
+    ws = torch.full((ckv.chunkkv_workspace_bytes(prob),), 0xFF, dtype=torch.uint8, device=DEV)   # NaNs: nothing may be read unwritten
+    scores = torch.full((hkv, prob.score_cap), float("nan"), device=DEV)
+    ckv.chunkkv_score(prob, q.to(DEV), k.to(DEV), scores, None, ws)
+    got = scores.cpu().double()[:, :want.shape[1]]
+    # sums are stored with 12 mantissa bits, 2^-13 each, which up to 256 rows average out; fp32 around that is 1e-6
+    assert float(((got - want).abs() / want).max()) < 1.3e-4
+    # a few layers in one launch (no shared rows) give the same scores as one alone
+    n = 5
+    many = ckv.Problem(hkv * g, hkv, d, w, c, dtype, [L] * n, [0] * n, [i * hkv * L * d for i in range(n)], L * d, d)
+    ws = torch.full((ckv.chunkkv_workspace_bytes(many),), 0xFF, dtype=torch.uint8, device=DEV)
+    scores5 = torch.full((n, hkv, many.score_cap), float("nan"), device=DEV)
+    ckv.chunkkv_score(many, q.to(DEV).expand(n, -1, -1, -1).contiguous(), k.to(DEV).expand(n, -1, -1, -1).contiguous(), scores5, None, ws)
+    for i in range(n):
+        assert torch.equal(scores5[i, :, :want.shape[1]], scores[:, :want.shape[1]])
