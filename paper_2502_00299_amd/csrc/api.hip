@@ -11,6 +11,14 @@ namespace ckv {
 namespace {
 
 constexpr int kTargetWorkgroups = 4096;  // ~4 resident rounds of 2 workgroups on each of 256 CUs
+// Two-pass scoring of up to this many key tiles: pass 1 merges the row statistics of the ranges itself, every workgroup for
+// itself while its first tiles travel.  A kernel in between took 5 us, and 9 to 49 for one layer of a hundred ranges or more:
+// 16000 tokens 34.3 -> 28.9 us a call, 19000 with 64 rows 66 -> 42, 120602 in fp32 288 -> 234.  Above it that kernel is a
+// percent or two and merging everywhere more (10 layers of 109334 tokens, 224 rows 906 us, 947 merged).
+constexpr int64_t kMergeTiles = 16384, kMergeWorkgroups = 1536;
+// So there are at most kMaxRanges ranges, and kGoodRanges as long as that asks for no more than kRangeTiles tiles in a row
+// and leaves no CU without a workgroup: 120602 tokens, 4 heads, fp32 in 32 / 63 / 236 ranges 147 / 81 / 90 us.
+constexpr int kGoodRanges = 32, kMaxRanges = 64, kRangeTiles = 8;
 // Single-pass scoring with 256 rows: up to this many workgroups (one per CU) leave half the places empty, so two of them,
 // with 128 rows each, share a key range.  K is read twice, the second time from L2.
 constexpr int64_t kRowSplitWorkgroups = 256;
@@ -24,6 +32,7 @@ struct Plan {
   int n_leaders, rows_pad;
   int batch_leaders;  // leader layers scored per launch set (the unit that overlaps with compaction)
   int tpw0, tpw1, max_split0;
+  int merge0;         // two-pass scoring: pass 1 merges the row statistics itself
   int fuse_chunks;
   // single-pass path: usable for this problem?  geometry and workspace
   int single_ok, rows_pad_s, n_periods, max_split_s;
@@ -151,10 +160,22 @@ int make_plan(const chunkkv_problem *p, int n_layers, int reuse, Plan *pl) {
   pl->tpw1 = (int)((tiles1 * heads + kTargetWorkgroups - 1) / kTargetWorkgroups);
   if (pl->tpw0 < 1) pl->tpw0 = 1;
   if (pl->tpw1 < 1) pl->tpw1 = 1;
-  pl->max_split0 = 1;
+  pl->max_split0 = 1;   // room for the ranges' pairs
+  int most0 = 1;        // tiles of the longest sequence
   for (int b = 0; b < p->batch; ++b) {
-    const int s = ceil_div(ceil_div(p->seqlen[b], TK), pl->tpw0);
+    const int t = ceil_div(p->seqlen[b], TK), s = ceil_div(t, pl->tpw0);
     if (s > pl->max_split0) pl->max_split0 = s;
+    if (t > most0) most0 = t;
+  }
+  pl->merge0 = tiles0 * heads <= kMergeTiles;
+  if (pl->merge0) {
+    const int64_t per_cu = (tiles0 * heads + 255) / 256;
+    int64_t least = per_cu > kRangeTiles ? per_cu : kRangeTiles;
+    if (least > ceil_div(most0, kGoodRanges)) least = ceil_div(most0, kGoodRanges);
+    if (least < ceil_div(most0, kMaxRanges)) least = ceil_div(most0, kMaxRanges);
+    if (pl->tpw0 < least) pl->tpw0 = (int)least;
+    // every workgroup of pass 1 merges: three rounds of them at most (the same 120602 tokens 92 us, with 1892 workgroups 106)
+    if (tiles1 * heads > kMergeWorkgroups) pl->tpw1 = (int)((tiles1 * heads + kMergeWorkgroups - 1) / kMergeWorkgroups);
   }
   // single-pass path
   pl->single_ok = single_pass_ok(p->dtype, p->head_dim, rows, p->chunk) ? 1 : 0;
@@ -246,13 +267,8 @@ int run_score(const chunkkv_problem *p, const Plan &pl, const void *const *q, co
     }
     int rc;
     if (lse) {
-      LseArgs la;
-      memset(&la, 0, sizeof(la));
-      for (int i = 0; i < ng; ++i) la.lse[i] = lse[i];
-      la.refs = a.refs; la.leader0 = leader0; la.batch0 = b0; la.batch_total = p->batch;
-      la.n_q_heads = p->n_q_heads; la.n_kv_heads = p->n_kv_heads; la.window = p->window; la.rows_pad = pl.rows_pad;
-      { Timed t(kCombine, s); rc = launch_lse_refs(la, ng, nb, s); }
-      if (rc) return rc;
+      a.use_lse = 1;
+      for (int i = 0; i < ng; ++i) a.lse[i] = lse[i];
     } else if (pl.single_ok && !(p->flags & CHUNKKV_FLAG_TWO_PASS) && !token_imp) {
       // one pass over K: per-(chunk, row) sums and the references they are relative to; then the merge of the
       // range statistics and the weighted row sum in one small kernel
@@ -279,8 +295,12 @@ int run_score(const chunkkv_problem *p, const Plan &pl, const void *const *q, co
       a.tiles_per_wg = pl.tpw0;
       { Timed t(kStats, s); rc = launch_score_pass(0, p->dtype, p->head_dim, pl.geom, a, dim3(split0, nb * p->n_kv_heads, ng), s); }
       if (rc) return rc;
-      { Timed t(kCombine, s); rc = launch_stats_combine(a, ng, nb, TK, s); }
-      if (rc) return rc;
+      if (pl.merge0) {
+        a.stats_tiles = pl.tpw0;
+      } else {
+        { Timed t(kCombine, s); rc = launch_stats_combine(a, ng, nb, TK, s); }
+        if (rc) return rc;
+      }
     }
     a.tiles_per_wg = pl.tpw1;
     { Timed t(kColsum, s); rc = launch_score_pass(1, p->dtype, p->head_dim, pl.geom, a, dim3(split1, nb * p->n_kv_heads, ng), s); }

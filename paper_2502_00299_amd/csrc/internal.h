@@ -42,11 +42,14 @@ struct ScoreArgs {
   int32_t max_split;       // pitch of part_stats in splits
   int32_t rows_pad;        // g*w rounded up to 32
   float2 *part_stats;      // [problem][max_split][rows_pad]  (running max, sum) in log2 units
-  float *refs;             // [problem][rows_pad]  max + log2(sum)
+  float *refs;             // [problem][rows_pad]  max + log2(sum), where pass 1 does not merge
   float *chunk_scores;     // [leader][batch_total][Hkv][score_cap]
   int32_t score_cap;
   float *token_imp;        // [leader][batch_total][Hkv][imp_pitch] or null
   int64_t imp_pitch;
+  const float *lse[kMaxLayersPerLaunch];  // pass 1 with use_lse: per leader layer [batch_total][Hq][w], natural log
+  int32_t use_lse;
+  int32_t stats_tiles;     // pass 1: > 0 = merge the pairs of pass 0 here; key tiles of one of its ranges
   int32_t fuse_chunks;     // pass 1: 1 = super-tiles hold whole chunks and chunk sums are written
   // single-pass path (score_single.h): key ranges are single_periods_per_range() whole periods of 160 keys
   int32_t n_periods;       // pitch of e_buf / m_period: max over sequences of ceil(L / 160)
@@ -54,14 +57,6 @@ struct ScoreArgs {
   float *m_period;         // [problem][n_periods][rows_pad]  reference those sums are relative to
   float *row_stats;        // [problem][max_split][rows_pad]  log2 of a row's sum over a key range
   int32_t row_groups;      // workgroups that share the rows of a key range (1 or 2)
-};
-
-// Caller-supplied row log-sum-exps -> row references of the importance pass.
-struct LseArgs {
-  const float *lse[kMaxLayersPerLaunch];  // per leader layer: [batch_total][Hq][w], natural log
-  float *refs;                            // [problem][rows_pad], log2 units
-  int32_t leader0, batch0, batch_total;
-  int32_t n_q_heads, n_kv_heads, window, rows_pad;
 };
 
 struct TopkArgs {
@@ -190,7 +185,6 @@ int launch_chunk_sums(const ScoreArgs &a, int n_leaders_slice, int batch_slice, 
 int launch_score_single(int dtype, const ScoreArgs &a, dim3 grid, hipStream_t s);
 int launch_jaccard(const int32_t *sel_chunk, const int32_t *sel_len, const int32_t *sel_count, int sel_cap, int chunk,
                    int rows_per_group, int n_pairs, float *out, hipStream_t s);
-int launch_lse_refs(const LseArgs &a, int n_leaders_slice, int batch_slice, hipStream_t s);
 int launch_single_scores(const ScoreArgs &a, int n_leaders_slice, int batch_slice, hipStream_t s);
 bool single_pass_ok(int dtype, int head_dim, int rows, int chunk);
 int launch_topk(const TopkArgs &a, int n_groups, int batch_slice, hipStream_t s);

@@ -6,10 +6,9 @@
 // normalised, so the work is two passes over K:
 //   pass 0  (keys x rows orientation: a lane owns one window row)  streams K, keeps a running
 //           (max, sum) per row in registers, and writes one partial pair per row and key range;
-//   -----   a tiny kernel merges the partial pairs into ref_r = max_r + log2(sum_r) (or, when the caller
-//           supplies each row's log-sum-exp, converts that and pass 0 does not run at all);
-//   pass 1  (rows x keys orientation: a lane owns one key)  streams K again with the accumulators
-//           started at -ref_r/(scale*log2e) (kept in registers for bf16 caches, where they are the C
+//   -----   the partial pairs are merged into ref_r = max_r + log2(sum_r), in short launches by pass 1 itself, otherwise
+//           by a tiny kernel (a caller's log-sum-exp per row is taken as it is, and pass 0 does not run);
+//   pass 1  (rows x keys orientation: a lane owns one key)  streams K again with the accumulators started at -ref_r/(scale*log2e) (kept in registers for bf16 caches, where they are the C
 //           operand of a block's first MFMA), so p = exp2(acc*scale*log2e); p is summed over the rows in
 //           registers, across the two lane halves by one shuffle, across wavefronts in LDS, and once
 //           per super-tile of kSuperKeys keys the per-token importance is reduced to chunk sums with a
@@ -82,6 +81,24 @@ __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_s_barrier();
 }
 
+// max + log2(sum) of a row's (max, sum) pairs, in range order, eight loads in flight
+__device__ __forceinline__ float merge_pairs(const float2 *ps, int n, int pitch) {
+  float m = kNegBig, l = 0.f;
+  for (int s0 = 0; s0 < n; s0 += 8) {
+    float2 x[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) x[i] = ps[(int64_t)(s0 + i < n ? s0 + i : n - 1) * pitch];
+    float mm = m;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) mm = fmaxf(mm, x[i].x);
+    l *= fast_exp2(m - mm);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) l += s0 + i < n ? x[i].y * fast_exp2(x[i].x - mm) : 0.f;
+    m = mm;
+  }
+  return m + __builtin_log2f(l);
+}
+
 // DT: chunkkv_dtype, HD: head dim, NQW: 32-row blocks per wavefront, WQ: wavefronts splitting the rows.
 // Two workgroups per CU, except where the operand fragments alone need more than half the register file
 // (four row blocks per wavefront; fp32 operands at head_dim 128).
@@ -109,7 +126,7 @@ __global__ __launch_bounds__(kThreads, ((NQW >= 4 || (DT == CHUNKKV_F32 && HD ==
   const int bl = blockIdx.y / a.n_kv_heads, h = blockIdx.y % a.n_kv_heads, z = blockIdx.z;
   const int split = blockIdx.x;
   const int g = a.n_q_heads / a.n_kv_heads, w = a.window, c = a.chunk;
-  const int L = pick(a.seq.seqlen, bl), P = L - w, nrows = g * w;
+  const int L = CKV_ARG(ScoreArgs, seq.seqlen, bl), P = L - w, nrows = g * w;
   const int64_t problem = ((int64_t)(a.leader0 + z) * a.batch_total + (a.batch0 + bl)) * a.n_kv_heads + h;
 
   // Work units: pass 0 walks tiles of TK keys over [0, L); pass 1 walks super-tiles over [0, P), each
@@ -128,8 +145,8 @@ __global__ __launch_bounds__(kThreads, ((NQW >= 4 || (DT == CHUNKKV_F32 && HD ==
   const int nblk = nt * KPW;  // key blocks this wavefront walks: block b = (tile b / KPW, kb = wk + (b % KPW) * WK)
   auto tile_key0 = [&](int i) __attribute__((always_inline)) { return (u0 + i / spt) * sstride + (i % spt) * TK; };
 
-  const char *qbase = (const char *)pick(a.q, z) + ((int64_t)(a.batch0 + bl) * a.n_q_heads + (int64_t)h * g) * w * ROWB;
-  const char *kbase = (const char *)pick(a.k, z) + (pick(a.seq.kv_base, bl) + (int64_t)h * a.kv_stride_head) * ESZ;
+  const char *qbase = (const char *)CKV_ARG(ScoreArgs, q, z) + ((int64_t)(a.batch0 + bl) * a.n_q_heads + (int64_t)h * g) * w * ROWB;
+  const char *kbase = (const char *)CKV_ARG(ScoreArgs, k, z) + (CKV_ARG(ScoreArgs, seq.kv_base, bl) + (int64_t)h * a.kv_stride_head) * ESZ;
   const int64_t ktok = a.kv_stride_tok * ESZ;
   const float c1 = a.scale_log2e;
 
@@ -187,10 +204,21 @@ __global__ __launch_bounds__(kThreads, ((NQW >= 4 || (DT == CHUNKKV_F32 && HD ==
     const int row = (wq * NQW + qi) * 32 + n;
     lim[qi] = P + (row < nrows ? row % w : 0);
   }
-  // pass 1: accumulator start values, so that acc*c1 = logit*c1 - ref (padding rows end at -1e30)
+  // pass 1: accumulator start values, so that acc*c1 = logit*c1 - ref (padding rows end at -1e30).  The reference is the
+  // caller's log-sum-exp, or (stats_tiles) merged from the key ranges' pairs while the first tiles travel, or what
+  // stats_combine_kernel made of them
   if constexpr (PASS == 1) {
-    for (int r = tid; r < WQ * NQW * 32; r += kThreads)
-      s_start[r] = (r < nrows ? -a.refs[problem * a.rows_pad + r] : kNegBig) / c1;
+    const float *lse = a.use_lse ? CKV_ARG(ScoreArgs, lse, z) + ((int64_t)(a.batch0 + bl) * a.n_q_heads + (int64_t)h * g) * w : nullptr;
+    const int ranges = a.stats_tiles > 0 ? ((L + TK - 1) / TK + a.stats_tiles - 1) / a.stats_tiles : 0;
+    for (int r = tid; r < WQ * NQW * 32; r += kThreads) {
+      float start = kNegBig;
+      if (r < nrows) {
+        if (lse != nullptr) start = -(lse[r] * 1.4426950408889634f);
+        else if (ranges > 0) start = -merge_pairs(a.part_stats + problem * a.max_split * a.rows_pad + r, ranges, a.rows_pad);
+        else start = -a.refs[problem * a.rows_pad + r];
+      }
+      s_start[r] = start / c1;
+    }
   }
 
   // Lane's LDS address of fragment segment ks of key block b: row n of the block, 16-byte segment

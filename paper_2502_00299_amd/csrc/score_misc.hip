@@ -1,5 +1,5 @@
-// Small kernels around the two scoring passes: merging the per-range softmax statistics, and the
-// chunk sums for chunk sizes too large to fit one key tile.
+// Small kernels around the scoring kernels: merging the per-range softmax statistics, chunk sums for chunk sizes too large to fit one key tile, and the row
+// reduction of the single-pass scoring.
 #include "internal.h"
 
 namespace ckv {
@@ -50,8 +50,8 @@ int launch_score_single(int dtype, const ScoreArgs &a, dim3 grid, hipStream_t s)
 
 // ref_r = max_r + log2(sum_r) over all key ranges of a problem.  Four lanes share a row: each merges a
 // quarter of the ranges in one pass ((m, l) pairs merge associatively), then the four partial pairs are
-// merged with two shuffles, always in the same order.  Latency is all there is to it (a layer of 16000 tokens has
-// 125 ranges): one pair at a time took 23 us, with kCombineAhead pairs of a lane in flight it takes 5.
+// merged with two shuffles, always in the same order, kCombineAhead pairs of a lane in flight.  For launches of several
+// rounds of workgroups: in shorter ones the second pass merges the pairs itself.
 // grid: x = (sequence, kv-head), y = leader, z = block of 64 rows; 256 threads.
 constexpr int kCombineAhead = 8;
 __global__ __launch_bounds__(256) void stats_combine_kernel(ScoreArgs a, int tile_keys) {
@@ -96,24 +96,6 @@ int launch_stats_combine(const ScoreArgs &a, int n_leaders_slice, int batch_slic
   if (n_leaders_slice <= 0 || batch_slice <= 0) return CHUNKKV_OK;
   dim3 grid(batch_slice * a.n_kv_heads, n_leaders_slice, (a.rows_pad + 63) / 64);
   hipLaunchKernelGGL(stats_combine_kernel, grid, dim3(256), 0, s, a, tile_keys);
-  return hipGetLastError() == hipSuccess ? CHUNKKV_OK : CHUNKKV_ERR_LAUNCH;
-}
-
-// ref_r = lse_r * log2(e): the caller's natural-log normalisation of a window row in the importance pass's
-// units.  grid: x = (sequence, kv-head), y = leader; one thread per (padded) row.
-__global__ void lse_refs_kernel(LseArgs a) {
-  const int bl = blockIdx.x / a.n_kv_heads, h = blockIdx.x % a.n_kv_heads, z = blockIdx.y;
-  const int g = a.n_q_heads / a.n_kv_heads, w = a.window, nrows = g * w;
-  const int64_t problem = ((int64_t)(a.leader0 + z) * a.batch_total + (a.batch0 + bl)) * a.n_kv_heads + h;
-  const float *lse = pick(a.lse, z) + ((int64_t)(a.batch0 + bl) * a.n_q_heads + (int64_t)h * g) * w;
-  for (int row = threadIdx.x; row < a.rows_pad; row += blockDim.x)
-    a.refs[problem * a.rows_pad + row] = row < nrows ? lse[row] * 1.4426950408889634f : 0.f;
-}
-
-int launch_lse_refs(const LseArgs &a, int n_leaders_slice, int batch_slice, hipStream_t s) {
-  if (n_leaders_slice <= 0 || batch_slice <= 0) return CHUNKKV_OK;
-  dim3 grid(batch_slice * a.n_kv_heads, n_leaders_slice);
-  hipLaunchKernelGGL(lse_refs_kernel, grid, dim3(a.rows_pad < 256 ? a.rows_pad : 256), 0, s, a);
   return hipGetLastError() == hipSuccess ? CHUNKKV_OK : CHUNKKV_ERR_LAUNCH;
 }
 

@@ -61,3 +61,32 @@ def test_scores_match_float64(dtype, P, w, g, c):
     ckv.chunkkv_score(many, q.to(DEV).expand(n, -1, -1, -1).contiguous(), k.to(DEV).expand(n, -1, -1, -1).contiguous(), scores5, None, ws)
     for i in range(n):
         assert torch.equal(scores5[i, :, :want.shape[1]], scores[:, :want.shape[1]])
+
+
+# Two passes, where pass 1 merges the row statistics of the ranges itself: one range, a whole number of loads of eight ranges
+# and one more, 63 ranges (the most), a batch whose sequences have different numbers of them, and the last and first sizes
+# on either side of the line from which a kernel merges them.
+TWO_PASS = [
+    (ckv.F32, 64, [40], 2, 2, 16, 3), (ckv.F32, 64, [8 * 64, 33], 2, 2, 16, 1), (ckv.BF16, 128, [9 * 64, 640, 65], 2, 4, 16, 8),
+    (ckv.F16, 64, [64 * 128 + 1, 500], 1, 4, 32, 16), (ckv.F32, 128, [16000], 4, 1, 16, 33), (ckv.BF16, 128, [20011], 1, 8, 32, 300),
+    (ckv.BF16, 128, [131072], 8, 1, 16, 10), (ckv.BF16, 128, [131073], 8, 1, 16, 10),
+]
+
+
+@pytest.mark.parametrize("dtype,d,lens,hkv,g,w,c", TWO_PASS)
+def test_two_pass_scores_match_float64(dtype, d, lens, hkv, g, w, c):
+    kind = {ckv.F32: torch.float32, **KIND}[dtype]
+    gen = torch.Generator().manual_seed(sum(lens))
+    q = torch.randn((len(lens), hkv * g, w, d), generator=gen).to(kind)
+    k = torch.randn((sum(lens), hkv, d), generator=gen).to(kind)      # packed
+    base = [sum(lens[:i]) * hkv * d for i in range(len(lens))]
+    prob = ckv.Problem(hkv * g, hkv, d, w, c, dtype, lens, [0] * len(lens), base, d, hkv * d, flags=ckv.FLAG_TWO_PASS)
+    ws = torch.full((ckv.chunkkv_workspace_bytes(prob),), 0xFF, dtype=torch.uint8, device=DEV)
+    scores = torch.full((len(lens), hkv, prob.score_cap), float("nan"), device=DEV)
+    ckv.chunkkv_score(prob, q.to(DEV), k.to(DEV), scores, None, ws)
+    for b, n in enumerate(lens):
+        at = sum(lens[:b])
+        want = oracle_scores(q[b], k[at:at + n].transpose(0, 1).contiguous(), w, c)
+        got = scores[b].cpu().double()[:, :want.shape[1]]
+        # the reference of a row is one float below 32 (2^-20 in the exponent of every weight), the sums are fp32
+        assert float(((got - want).abs() / want).max()) < 4e-6
