@@ -35,7 +35,7 @@ struct Plan {
   int merge0;         // two-pass scoring: pass 1 merges the row statistics itself
   int fuse_chunks;
   // single-pass path: usable for this problem?  geometry and workspace
-  int single_ok, rows_pad_s, n_periods, max_split_s;
+  int single_ok, n_periods_fit, rows_pad_s, n_periods, max_split_s;
   size_t off_part, off_refs, off_scores, off_seloff, off_imp, off_ebuf, off_mper, total;
 };
 
@@ -131,6 +131,18 @@ int check_problem(const chunkkv_problem *p, bool need_out) {
 
 bool misaligned(const void *p) { return ((uintptr_t)p & 15) != 0; }
 
+// Do the single-pass kernels score a group with this chunk size (no log-sum-exps, no token importance asked for)?
+bool takes_one_pass(const chunkkv_problem *p, const Plan &pl, int chunk) {
+  return !(p->flags & CHUNKKV_FLAG_TWO_PASS) && pl.n_periods_fit && single_pass_ok(p->dtype, p->head_dim, (p->n_q_heads / p->n_kv_heads) * p->window, chunk);
+}
+
+// Super-tiles a workgroup of the importance pass takes, of `units` in the launch.  Where every workgroup merges the row
+// statistics, three rounds of them at most (120602 tokens, 63 ranges 92 us, with 1892 workgroups 106).
+int pass1_tiles_per_wg(int64_t units, bool merge) {
+  const int64_t wgs = merge ? kMergeWorkgroups : kTargetWorkgroups, n = (units + wgs - 1) / wgs;
+  return n < 1 ? 1 : (int)n;
+}
+
 // Workspace layout and key-range split; a pure function of (problem, n_layers, reuse).
 int make_plan(const chunkkv_problem *p, int n_layers, int reuse, Plan *pl) {
   if (n_layers < 1 || reuse < 1) return CHUNKKV_ERR_SHAPE;
@@ -157,9 +169,7 @@ int make_plan(const chunkkv_problem *p, int n_layers, int reuse, Plan *pl) {
   pl->batch_leaders = ceil_div(pl->n_leaders, nsets);
   const int64_t heads = (int64_t)pl->batch_leaders * p->n_kv_heads;
   pl->tpw0 = (int)((tiles0 * heads + kTargetWorkgroups - 1) / kTargetWorkgroups);
-  pl->tpw1 = (int)((tiles1 * heads + kTargetWorkgroups - 1) / kTargetWorkgroups);
   if (pl->tpw0 < 1) pl->tpw0 = 1;
-  if (pl->tpw1 < 1) pl->tpw1 = 1;
   pl->max_split0 = 1;   // room for the ranges' pairs
   int most0 = 1;        // tiles of the longest sequence
   for (int b = 0; b < p->batch; ++b) {
@@ -174,22 +184,21 @@ int make_plan(const chunkkv_problem *p, int n_layers, int reuse, Plan *pl) {
     if (least > ceil_div(most0, kGoodRanges)) least = ceil_div(most0, kGoodRanges);
     if (least < ceil_div(most0, kMaxRanges)) least = ceil_div(most0, kMaxRanges);
     if (pl->tpw0 < least) pl->tpw0 = (int)least;
-    // every workgroup of pass 1 merges: three rounds of them at most (the same 120602 tokens 92 us, with 1892 workgroups 106)
-    if (tiles1 * heads > kMergeWorkgroups) pl->tpw1 = (int)((tiles1 * heads + kMergeWorkgroups - 1) / kMergeWorkgroups);
   }
+  pl->tpw1 = pass1_tiles_per_wg(tiles1 * heads, pl->merge0);
   // single-pass path
-  pl->single_ok = single_pass_ok(p->dtype, p->head_dim, rows, p->chunk) ? 1 : 0;
   pl->rows_pad_s = rows > 128 ? 256 : 128;
   pl->n_periods = 0;
   pl->max_split_s = 1;
   int room = 1;   // pairs of floats per row the workspace holds for the ranges' statistics (one float each, at most twice as many)
+  for (int b = 0; b < p->batch; ++b) {
+    const int np = ceil_div(p->seqlen[b], kSinglePeriodKeys);
+    if (np > pl->n_periods) pl->n_periods = np;
+  }
+  // the kernels address E of one problem with 32-bit byte offsets
+  pl->n_periods_fit = (int64_t)pl->n_periods * pl->rows_pad_s * 80 < (int64_t)1 << 32;
+  pl->single_ok = pl->n_periods_fit && single_pass_ok(p->dtype, p->head_dim, rows, p->chunk);
   if (pl->single_ok) {
-    for (int b = 0; b < p->batch; ++b) {
-      const int np = ceil_div(p->seqlen[b], kSinglePeriodKeys);
-      if (np > pl->n_periods) pl->n_periods = np;
-    }
-    // the kernels address E of one problem with 32-bit byte offsets
-    if ((int64_t)pl->n_periods * pl->rows_pad_s * 80 >= (int64_t)1 << 32) pl->single_ok = 0;
     // key ranges: single_periods_per_range() periods each, a function of the sequence alone
     for (int b = 0; b < p->batch; ++b) {
       const int np = ceil_div(p->seqlen[b], kSinglePeriodKeys);
@@ -232,11 +241,13 @@ void fill_seq(SeqTable *t, const chunkkv_problem *p, int b0, int nb) {
   }
 }
 
-// Scores leader layers [g0, g0+ng) (pointer tables already gathered) for all sequences.
+// Scores ng leader layers (pointer tables already gathered) for all sequences; leaders[i] is the index of the i-th, whose
+// problems of the workspace and scores are its own, chunks[i] its chunk size.  Chunk sizes differ only where two passes score
+// (pl and p are then those of any of them).
 // lse == nullptr: the row normalisation is computed here; otherwise lse[i] is leader i's caller-supplied
 // [B][Hq][w] array and only the importance pass runs.
 int run_score(const chunkkv_problem *p, const Plan &pl, const void *const *q, const void *const *k,
-              const float *const *lse, int ng, int leader0, float *chunk_scores, float *token_imp,
+              const float *const *lse, int ng, const int32_t *leaders, const int32_t *chunks, float *chunk_scores, float *token_imp,
               int64_t imp_pitch, char *ws, hipStream_t s) {
   const int TK = pl.geom.tile_keys;
   for (int b0 = 0; b0 < p->batch; b0 += kMaxBatchPerLaunch) {
@@ -245,7 +256,8 @@ int run_score(const chunkkv_problem *p, const Plan &pl, const void *const *q, co
     memset(&a, 0, sizeof(a));
     for (int i = 0; i < ng; ++i) { a.q[i] = q[i]; a.k[i] = k[i]; }
     fill_seq(&a.seq, p, b0, nb);
-    a.leader0 = leader0; a.batch0 = b0; a.batch_total = p->batch;
+    for (int i = 0; i < ng; ++i) { a.leader[i] = leaders[i]; a.chunk_of[i] = chunks[i]; }
+    a.batch0 = b0; a.batch_total = p->batch;
     a.n_q_heads = p->n_q_heads; a.n_kv_heads = p->n_kv_heads; a.window = p->window; a.chunk = p->chunk;
     a.kv_stride_head = p->kv_stride_head; a.kv_stride_tok = p->kv_stride_tok;
     const float scale = p->softmax_scale > 0.f ? p->softmax_scale : 1.0f / sqrtf((float)p->head_dim);
@@ -258,18 +270,27 @@ int run_score(const chunkkv_problem *p, const Plan &pl, const void *const *q, co
     a.fuse_chunks = pl.fuse_chunks;
     if (!pl.fuse_chunks && !token_imp) { a.token_imp = (float *)(ws + pl.off_imp); a.imp_pitch = (int64_t)p->score_cap * p->chunk; }
     int split0 = 1, split1 = 0;
-    const int stride1 = pl.fuse_chunks ? (kSuperKeys / p->chunk) * p->chunk : kSuperKeys;
+    int64_t units1 = 0;   // super-tiles of all sequences and layers
+    auto super_tiles = [&](int i, int z) { return ceil_div(a.seq.seqlen[i] - p->window, pl.fuse_chunks ? (kSuperKeys / chunks[z]) * chunks[z] : kSuperKeys); };
+    bool mixed = false;
+    for (int z = 0; z < ng; ++z) {
+      mixed |= chunks[z] != chunks[0];
+      for (int i = 0; i < nb; ++i) units1 += super_tiles(i, z);
+    }
+    const int tpw1 = mixed ? pass1_tiles_per_wg(units1 * p->n_kv_heads, pl.merge0) : pl.tpw1;
     for (int i = 0; i < nb; ++i) {
       const int s0 = ceil_div(ceil_div(a.seq.seqlen[i], TK), pl.tpw0);
-      const int s1 = ceil_div(ceil_div(a.seq.seqlen[i] - p->window, stride1), pl.tpw1);
       split0 = s0 > split0 ? s0 : split0;
-      split1 = s1 > split1 ? s1 : split1;
+      for (int z = 0; z < ng; ++z) {
+        const int s1 = ceil_div(super_tiles(i, z), tpw1);
+        split1 = s1 > split1 ? s1 : split1;
+      }
     }
     int rc;
     if (lse) {
       a.use_lse = 1;
       for (int i = 0; i < ng; ++i) a.lse[i] = lse[i];
-    } else if (pl.single_ok && !(p->flags & CHUNKKV_FLAG_TWO_PASS) && !token_imp) {
+    } else if (takes_one_pass(p, pl, chunks[0]) && !token_imp) {
       // one pass over K: per-(chunk, row) sums and the references they are relative to; then the merge of the
       // range statistics and the weighted row sum in one small kernel
       a.n_periods = pl.n_periods;
@@ -302,7 +323,7 @@ int run_score(const chunkkv_problem *p, const Plan &pl, const void *const *q, co
         if (rc) return rc;
       }
     }
-    a.tiles_per_wg = pl.tpw1;
+    a.tiles_per_wg = tpw1;
     { Timed t(kColsum, s); rc = launch_score_pass(1, p->dtype, p->head_dim, pl.geom, a, dim3(split1, nb * p->n_kv_heads, ng), s); }
     if (rc) return rc;
     if (!pl.fuse_chunks) {
@@ -313,7 +334,7 @@ int run_score(const chunkkv_problem *p, const Plan &pl, const void *const *q, co
   return CHUNKKV_OK;
 }
 
-int run_topk(const chunkkv_problem *p, const float *chunk_scores, int group0, int n_groups, int32_t *sel_chunk,
+int run_topk(const chunkkv_problem *p, const int32_t *chunks, const float *chunk_scores, int group0, int n_groups, int32_t *sel_chunk,
              int32_t *sel_len, int32_t *sel_count, int32_t *sel_off, hipStream_t s) {
   for (int b0 = 0; b0 < p->batch; b0 += kMaxBatchPerLaunch) {
     const int nb = p->batch - b0 < kMaxBatchPerLaunch ? p->batch - b0 : kMaxBatchPerLaunch;
@@ -321,7 +342,8 @@ int run_topk(const chunkkv_problem *p, const float *chunk_scores, int group0, in
     memset(&a, 0, sizeof(a));
     fill_seq(&a.seq, p, b0, nb);
     a.group0 = group0;
-    a.batch0 = b0; a.batch_total = p->batch; a.n_kv_heads = p->n_kv_heads; a.window = p->window; a.chunk = p->chunk;
+    for (int i = 0; i < n_groups; ++i) a.chunk_of[i] = chunks[i];
+    a.batch0 = b0; a.batch_total = p->batch; a.n_kv_heads = p->n_kv_heads; a.window = p->window;
     a.chunk_scores = chunk_scores; a.score_cap = p->score_cap; a.sel_cap = p->sel_cap;
     a.sel_chunk = sel_chunk; a.sel_len = sel_len; a.sel_count = sel_count; a.sel_off = sel_off;
     a.whole_chunks = (p->flags & CHUNKKV_FLAG_WHOLE_CHUNKS) ? 1 : 0;
@@ -332,7 +354,8 @@ int run_topk(const chunkkv_problem *p, const float *chunk_scores, int group0, in
   return CHUNKKV_OK;
 }
 
-int run_compact(const chunkkv_problem *p, int l_begin, int n_layers, int reuse, const void *const *k, const void *const *v,
+// chunks[i]: chunk size of the i-th reuse group from that of layer l_begin on
+int run_compact(const chunkkv_problem *p, const int32_t *chunks, int l_begin, int n_layers, int reuse, const void *const *k, const void *const *v,
                 void *const *k_out, void *const *v_out, const int32_t *sel_chunk, const int32_t *sel_len,
                 const int32_t *sel_count, const int32_t *sel_off, hipStream_t s) {
   const int esz = elem_bytes(p->dtype);
@@ -347,21 +370,15 @@ int run_compact(const chunkkv_problem *p, int l_begin, int n_layers, int reuse, 
       }
       fill_seq(&a.seq, p, b0, nb);
       a.layer0 = l0; a.reuse = reuse; a.batch0 = b0; a.batch_total = p->batch;
-      a.n_kv_heads = p->n_kv_heads; a.window = p->window; a.chunk = p->chunk; a.elem_bytes = esz;
+      for (int i = 0; i < nl; ++i) a.chunk_of[i] = chunks[(l0 + i) / reuse - l_begin / reuse];
+      a.n_kv_heads = p->n_kv_heads; a.window = p->window; a.elem_bytes = esz;
       a.kv_stride_head = p->kv_stride_head; a.kv_stride_tok = p->kv_stride_tok;
       a.out_stride_head = p->out_stride_head; a.out_stride_tok = p->out_stride_tok;
       a.sel_chunk = sel_chunk; a.sel_len = sel_len; a.sel_count = sel_count; a.sel_off = sel_off;
       a.sel_cap = p->sel_cap;
       a.whole_chunks = (p->flags & CHUNKKV_FLAG_WHOLE_CHUNKS) ? 1 : 0;
-      int max_entries = 0;
-      for (int i = 0; i < nb; ++i) {
-        const int nk = a.seq.n_keep[i];
-        int e = (nk > 0 ? ceil_div(nk, p->chunk) + 1 : 0) + ceil_div(p->window, p->chunk);
-        if (nk > 0 && e - ceil_div(p->window, p->chunk) > p->sel_cap) e = p->sel_cap + ceil_div(p->window, p->chunk);
-        max_entries = e > max_entries ? e : max_entries;
-      }
       int rc;
-      { Timed t(kCompact, s); rc = launch_compact(p->head_dim * esz, a, nl, nb, max_entries, s); }
+      { Timed t(kCompact, s); rc = launch_compact(p->head_dim * esz, a, nl, nb, s); }
       if (rc) return rc;
     }
   }
@@ -427,7 +444,8 @@ static int score_entry(const chunkkv_problem *prob, const void *q_obs, const voi
   rc = make_plan(prob, 1, 1, &pl);
   if (rc) return rc;
   if (!workspace || workspace_bytes < pl.total) return CHUNKKV_ERR_WORKSPACE;
-  return run_score(prob, pl, &q_obs, &k, with_lse ? &lse : nullptr, 1, 0, chunk_scores, token_importance,
+  const int32_t leader = 0;
+  return run_score(prob, pl, &q_obs, &k, with_lse ? &lse : nullptr, 1, &leader, &prob->chunk, chunk_scores, token_importance,
                    (int64_t)prob->score_cap * prob->chunk, (char *)workspace, (hipStream_t)stream);
 }
 
@@ -449,7 +467,7 @@ int chunkkv_chunk_topk(const chunkkv_problem *prob, const float *chunk_scores, i
   int rc = check_problem(prob, false);
   if (rc) return rc;
   if (!chunk_scores || !sel_chunk || !sel_len || !sel_count) return CHUNKKV_ERR_NULL;
-  return run_topk(prob, chunk_scores, 0, 1, sel_chunk, sel_len, sel_count, nullptr, (hipStream_t)stream);
+  return run_topk(prob, &prob->chunk, chunk_scores, 0, 1, sel_chunk, sel_len, sel_count, nullptr, (hipStream_t)stream);
 }
 
 int chunkkv_compact(const chunkkv_problem *prob, const void *k, const void *v, const int32_t *sel_chunk,
@@ -458,7 +476,7 @@ int chunkkv_compact(const chunkkv_problem *prob, const void *k, const void *v, c
   if (rc) return rc;
   if (!k || !v || !sel_chunk || !sel_len || !sel_count || !k_out || !v_out) return CHUNKKV_ERR_NULL;
   if (misaligned(k) || misaligned(v) || misaligned(k_out) || misaligned(v_out)) return CHUNKKV_ERR_SHAPE;
-  return run_compact(prob, 0, 1, 1, &k, &v, &k_out, &v_out, sel_chunk, sel_len, sel_count, nullptr,
+  return run_compact(prob, &prob->chunk, 0, 1, 1, &k, &v, &k_out, &v_out, sel_chunk, sel_len, sel_count, nullptr,
                      (hipStream_t)stream);
 }
 
@@ -492,16 +510,18 @@ static int stack_groups(const chunkkv_problem *prob, const Plan &pl, int g_begin
     const int ng = g_end - g0 < pl.batch_leaders ? g_end - g0 : pl.batch_leaders;
     const void *qs[kMaxLayersPerLaunch], *ks[kMaxLayersPerLaunch];
     const float *ls[kMaxLayersPerLaunch];
+    int32_t leaders[kMaxLayersPerLaunch], chunks[kMaxLayersPerLaunch];
     for (int i = 0; i < ng; ++i) {
       qs[i] = q_obs[(g0 + i) * reuse]; ks[i] = k[(g0 + i) * reuse];
       ls[i] = with_lse ? lse[(g0 + i) * reuse] : nullptr;
+      leaders[i] = g0 + i; chunks[i] = prob->chunk;
     }
-    int rc = run_score(prob, pl, qs, ks, with_lse ? ls : nullptr, ng, g0, scores, nullptr, 0, ws, s);
+    int rc = run_score(prob, pl, qs, ks, with_lse ? ls : nullptr, ng, leaders, chunks, scores, nullptr, 0, ws, s);
     if (rc) return rc;
-    rc = run_topk(prob, scores, g0, ng, sel_chunk, sel_len, sel_count, sel_off, s);
+    rc = run_topk(prob, chunks, scores, g0, ng, sel_chunk, sel_len, sel_count, sel_off, s);
     if (rc) return rc;
     const int l_begin = g0 * reuse, l_end = (g0 + ng) * reuse < n_layers ? (g0 + ng) * reuse : n_layers;
-    rc = run_compact(prob, l_begin, l_end, reuse, k, v, k_out, v_out, sel_chunk, sel_len, sel_count, sel_off, s);
+    rc = run_compact(prob, chunks, l_begin, l_end, reuse, k, v, k_out, v_out, sel_chunk, sel_len, sel_count, sel_off, s);
     if (rc) return rc;
   }
   return CHUNKKV_OK;
@@ -522,6 +542,52 @@ static int stack_entry(const chunkkv_problem *prob, int32_t n_layers, int32_t re
   return stack_groups(prob, pl, 0, pl.n_leaders, n_layers, reuse, q_obs, k, v, lse, with_lse, k_out, v_out, sel_chunk,
                       sel_len, sel_count, (char *)workspace, (hipStream_t)stream);
 }
+
+}  // extern "C"
+
+// A stack whose groups' chunk sizes differ, each kernel launched over all groups it can take at once: the single-pass
+// kernels once per chunk size they are compiled for, pass 0 and pass 1 once for all other groups, selection and gather once
+// for all.  One run of groups after the other is a chain of four or five launches that do not fill the chip, per run: eight
+// sizes over 16 layers of 12345 tokens 355 us, together 212.  `pl` is the plan of the chunk size that needs the most
+// workspace; the others fit its regions.
+static int stack_mixed(const chunkkv_problem *prob, const Plan &pl, int32_t n_layers, int32_t reuse, const int32_t *chunks,
+                       const void *const *q_obs, const void *const *k, const void *const *v, const float *const *lse,
+                       void *const *k_out, void *const *v_out, int32_t *sel_chunk, int32_t *sel_len, int32_t *sel_count,
+                       char *ws, hipStream_t s) {
+  const int n_groups = pl.n_leaders;
+  float *scores = (float *)(ws + pl.off_scores);
+  int32_t *sel_off = (int32_t *)(ws + pl.off_seloff);
+  bool done[kMaxLayersPerLaunch] = {};
+  for (int first = 0; first < n_groups; ++first) {
+    if (done[first]) continue;
+    chunkkv_problem run = *prob;
+    run.chunk = chunks[first];
+    Plan rp;
+    int rc = make_plan(&run, n_layers, reuse, &rp);
+    if (rc) return rc;
+    rp.off_part = pl.off_part; rp.off_refs = pl.off_refs; rp.off_scores = pl.off_scores; rp.off_seloff = pl.off_seloff;
+    rp.off_imp = pl.off_imp; rp.off_ebuf = pl.off_ebuf; rp.off_mper = pl.off_mper;
+    auto one_pass = [&](int c) { return !lse && takes_one_pass(prob, pl, c); };
+    const void *qs[kMaxLayersPerLaunch], *ks[kMaxLayersPerLaunch];
+    const float *ls[kMaxLayersPerLaunch];
+    int32_t leaders[kMaxLayersPerLaunch], cs[kMaxLayersPerLaunch];
+    int ng = 0;
+    for (int g = first; g < n_groups; ++g) {
+      if (done[g] || (one_pass(chunks[first]) ? chunks[g] != chunks[first] : one_pass(chunks[g]))) continue;
+      done[g] = true;
+      qs[ng] = q_obs[g * reuse]; ks[ng] = k[g * reuse]; ls[ng] = lse ? lse[g * reuse] : nullptr;
+      leaders[ng] = g; cs[ng] = chunks[g];
+      ++ng;
+    }
+    rc = run_score(&run, rp, qs, ks, lse ? ls : nullptr, ng, leaders, cs, scores, nullptr, 0, ws, s);
+    if (rc) return rc;
+  }
+  int rc = run_topk(prob, chunks, scores, 0, n_groups, sel_chunk, sel_len, sel_count, sel_off, s);
+  if (rc) return rc;
+  return run_compact(prob, chunks, 0, n_layers, reuse, k, v, k_out, v_out, sel_chunk, sel_len, sel_count, sel_off, s);
+}
+
+extern "C" {
 
 size_t chunkkv_workspace_bytes_hybrid(const chunkkv_problem *prob, int32_t n_layers, int32_t reuse,
                                       const int32_t *chunk_per_group) {
@@ -554,6 +620,24 @@ int chunkkv_compress_stack_hybrid(const chunkkv_problem *prob, int32_t n_layers,
   int rc = check_stack_pointers(n_layers, reuse, q_obs, k, v, lse, with_lse, k_out, v_out, sel_chunk, sel_len, sel_count);
   if (rc) return rc;
   if (!workspace || workspace_bytes < need) return CHUNKKV_ERR_WORKSPACE;
+  // Groups of different sizes together, if a launch can carry them all and every size is formed in the importance pass; one
+  // size (one run) is the plain stack call.
+  const int n_groups = ceil_div(n_layers, reuse);
+  bool together = n_groups <= kMaxLayersPerLaunch, differ = false;
+  Plan most;
+  most.total = 0;
+  for (int g = 0; together && g < n_groups; ++g) {
+    together = chunk_per_group[g] <= kSuperKeys;
+    differ |= chunk_per_group[g] != chunk_per_group[0];
+    chunkkv_problem run = *prob;
+    run.chunk = chunk_per_group[g];
+    Plan pl;
+    if ((rc = make_plan(&run, n_layers, reuse, &pl))) return rc;
+    if (pl.total > most.total) most = pl;
+  }
+  if (together && differ)
+    return stack_mixed(prob, most, n_layers, reuse, chunk_per_group, q_obs, k, v, lse, k_out, v_out, sel_chunk, sel_len,
+                       sel_count, (char *)workspace, (hipStream_t)stream);
   return for_chunk_runs(prob, n_layers, reuse, chunk_per_group, [&](const chunkkv_problem &run, int g0, int g1) {
     Plan pl;
     const int r = make_plan(&run, n_layers, reuse, &pl);
@@ -601,12 +685,13 @@ int chunkkv_compress_layer(const chunkkv_problem *prob, int32_t layer, int32_t r
   int32_t *sc = sel_chunk + row0 * prob->sel_cap, *sl = sel_len + row0 * prob->sel_cap, *cnt = sel_count + row0;
   if (leader) {
     float *scores = (float *)(ws + pl.off_scores);
-    rc = run_score(prob, pl, &q_obs, &k, lse ? &lse : nullptr, 1, 0, scores, nullptr, 0, ws, s);
+    const int32_t leader0 = 0;
+    rc = run_score(prob, pl, &q_obs, &k, lse ? &lse : nullptr, 1, &leader0, &prob->chunk, scores, nullptr, 0, ws, s);
     if (rc) return rc;
-    rc = run_topk(prob, scores, 0, 1, sc, sl, cnt, nullptr, s);
+    rc = run_topk(prob, &prob->chunk, scores, 0, 1, sc, sl, cnt, nullptr, s);
     if (rc) return rc;
   }
-  return run_compact(prob, 0, 1, 1, &k, &v, &k_out, &v_out, sc, sl, cnt, nullptr, s);
+  return run_compact(prob, &prob->chunk, 0, 1, 1, &k, &v, &k_out, &v_out, sc, sl, cnt, nullptr, s);
 }
 
 int chunkkv_jaccard(const chunkkv_problem *prob, int32_t n_groups, const int32_t *sel_chunk, const int32_t *sel_len,

@@ -17,13 +17,19 @@ namespace ckv {
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
+// selection entries of a workgroup
+__host__ __device__ inline int compact_entries(int rows, int chunk) {
+  const int n = rows / chunk;
+  return n < 1 ? 1 : (n > kCompactEntries ? kCompactEntries : n);
+}
+
 template <int NSEG>  // 16-byte segments per row
 __global__ __launch_bounds__(kThreads) void compact_kernel(CompactArgs a) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int bl = blockIdx.y / a.n_kv_heads, h = blockIdx.y % a.n_kv_heads;
   const int layer = blockIdx.z;
   const int L = CKV_ARG(CompactArgs, seq.seqlen, bl), n_keep = CKV_ARG(CompactArgs, seq.n_keep, bl);
-  const int w = a.window, c = a.chunk, P = L - w, ne = a.entries_per_wg;
+  const int w = a.window, c = CKV_ARG(CompactArgs, chunk_of, layer), P = L - w, ne = compact_entries(a.rows_per_wg, c);
   const int group = (a.layer0 + layer) / a.reuse;
   const int64_t selrow = ((int64_t)group * a.batch_total + (a.batch0 + bl)) * a.n_kv_heads + h;
   const int32_t *sel_chunk = a.sel_chunk + selrow * a.sel_cap;
@@ -135,16 +141,31 @@ __global__ __launch_bounds__(kThreads) void compact_kernel(CompactArgs a) {
   }
 }
 
-int launch_compact(int row_bytes, CompactArgs &a, int n_layers_slice, int batch_slice, int max_entries, hipStream_t s) {
-  if (n_layers_slice <= 0 || batch_slice <= 0 || max_entries <= 0) return CHUNKKV_OK;
-  auto groups = [&](int rows) {
-    int n = rows / a.chunk;
-    a.entries_per_wg = n < 1 ? 1 : (n > kCompactEntries ? kCompactEntries : n);
-    return (max_entries + a.entries_per_wg - 1) / a.entries_per_wg;
+int launch_compact(int row_bytes, CompactArgs &a, int n_layers_slice, int batch_slice, hipStream_t s) {
+  if (n_layers_slice <= 0 || batch_slice <= 0) return CHUNKKV_OK;
+  int64_t total = 0;   // workgroups with entries, of one kv-head per sequence
+  auto groups = [&](int rows) {   // most workgroups of a head
+    a.rows_per_wg = rows;
+    int most = 0;
+    total = 0;
+    for (int z = 0; z < n_layers_slice; ++z) {
+      const int c = a.chunk_of[z], ne = compact_entries(rows, c);
+      int entries = 0;
+      for (int i = 0; i < batch_slice; ++i) {
+        const int nk = a.seq.n_keep[i], n_win = (a.window + c - 1) / c;
+        int e = nk > 0 ? (nk + c - 1) / c + 1 : 0;
+        e = (e > a.sel_cap ? a.sel_cap : e) + n_win;
+        entries = e > entries ? e : entries;
+      }
+      const int n = (entries + ne - 1) / ne;
+      most = n > most ? n : most;
+      total += n;
+    }
+    return most;
   };
-  const int64_t rest = (int64_t)batch_slice * a.n_kv_heads * n_layers_slice;
   int nx = groups(160);
-  if (nx * rest < 4096) nx = groups(40);
+  if (total * batch_slice * a.n_kv_heads < 4096) nx = groups(40);
+  if (nx <= 0) return CHUNKKV_OK;
   dim3 grid(nx, batch_slice * a.n_kv_heads, n_layers_slice);
   switch (row_bytes / 16) {
     case 8: hipLaunchKernelGGL(compact_kernel<8>, grid, dim3(kThreads), 0, s, a); break;

@@ -32,10 +32,11 @@ struct ScoreArgs {
   const void *q[kMaxLayersPerLaunch];
   const void *k[kMaxLayersPerLaunch];
   SeqTable seq;
-  int32_t leader0;         // index of this slice's first leader layer
+  int32_t leader[kMaxLayersPerLaunch];    // leader index of every slice layer: whose problems of the workspace are its own
+  int32_t chunk_of[kMaxLayersPerLaunch];  // importance pass: chunk size of every slice layer
   int32_t batch0;          // index of this slice's first sequence
   int32_t batch_total;
-  int32_t n_q_heads, n_kv_heads, window, chunk;
+  int32_t n_q_heads, n_kv_heads, window, chunk;   // chunk: of all slice layers, everywhere but in the importance pass
   int64_t kv_stride_head, kv_stride_tok;
   float scale_log2e;       // softmax scale * log2(e)
   int32_t tiles_per_wg;    // pass 0: key tiles, pass 1: super-tiles (kSuperKeys) each workgroup walks
@@ -62,7 +63,8 @@ struct ScoreArgs {
 struct TopkArgs {
   SeqTable seq;
   int32_t group0;             // first selection group of this launch
-  int32_t batch0, batch_total, n_kv_heads, window, chunk;
+  int32_t chunk_of[kMaxLayersPerLaunch];   // chunk size of every group of the launch
+  int32_t batch0, batch_total, n_kv_heads, window;
   const float *chunk_scores;  // [group][batch_total][Hkv][score_cap]
   int32_t score_cap, sel_cap;
   int32_t *sel_chunk, *sel_len, *sel_count;
@@ -77,12 +79,13 @@ struct CompactArgs {
   void *v_out[kMaxLayersPerLaunch];
   SeqTable seq;
   int32_t layer0, reuse;      // selection group of slice layer z is (layer0 + z) / reuse
-  int32_t batch0, batch_total, n_kv_heads, window, chunk;
+  int32_t chunk_of[kMaxLayersPerLaunch];   // chunk size of every slice layer
+  int32_t batch0, batch_total, n_kv_heads, window;
   int32_t elem_bytes;
   int64_t kv_stride_head, kv_stride_tok, out_stride_head, out_stride_tok;
   const int32_t *sel_chunk, *sel_len, *sel_count, *sel_off;  // sel_off may be null
   int32_t sel_cap;
-  int32_t entries_per_wg;     // chosen by the launcher
+  int32_t rows_per_wg;        // chosen by the launcher: rows a workgroup copies, in whole entries
   int32_t whole_chunks;       // 1: the window follows the kept tokens directly (their count varies per head)
 };
 
@@ -193,7 +196,6 @@ int launch_decode(int dtype, int head_dim, bool matrix_cores, const DecodeArgs &
 int abs_sum_blocks(int n_tok_max);
 int launch_abs_sum(int dtype, const AbsSumArgs &a, int batch_slice, hipStream_t s);
 int launch_quality_finish(const QualityFinishArgs &a, int batch, hipStream_t s);
-int launch_compact(int row_bytes, CompactArgs &a, int n_layers_slice, int batch_slice,
-                   int max_entries, hipStream_t s);
+int launch_compact(int row_bytes, CompactArgs &a, int n_layers_slice, int batch_slice, hipStream_t s);
 
 }  // namespace ckv

@@ -125,9 +125,9 @@ __global__ __launch_bounds__(kThreads, ((NQW >= 4 || (DT == CHUNKKV_F32 && HD ==
   const bool active = (4 / WQ == WK) ? true : (wk < WK);  // wavefronts beyond the key blocks only load
   const int bl = blockIdx.y / a.n_kv_heads, h = blockIdx.y % a.n_kv_heads, z = blockIdx.z;
   const int split = blockIdx.x;
-  const int g = a.n_q_heads / a.n_kv_heads, w = a.window, c = a.chunk;
+  const int g = a.n_q_heads / a.n_kv_heads, w = a.window, c = PASS == 1 ? CKV_ARG(ScoreArgs, chunk_of, z) : 1;
   const int L = CKV_ARG(ScoreArgs, seq.seqlen, bl), P = L - w, nrows = g * w;
-  const int64_t problem = ((int64_t)(a.leader0 + z) * a.batch_total + (a.batch0 + bl)) * a.n_kv_heads + h;
+  const int64_t problem = ((int64_t)CKV_ARG(ScoreArgs, leader, z) * a.batch_total + (a.batch0 + bl)) * a.n_kv_heads + h;
 
   // Work units: pass 0 walks tiles of TK keys over [0, L); pass 1 walks super-tiles over [0, P), each
   // advancing `sstride` keys (a multiple of c when chunk sums are fused) and made of `spt` tiles.

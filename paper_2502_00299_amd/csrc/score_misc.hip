@@ -56,7 +56,7 @@ int launch_score_single(int dtype, const ScoreArgs &a, dim3 grid, hipStream_t s)
 constexpr int kCombineAhead = 8;
 __global__ __launch_bounds__(256) void stats_combine_kernel(ScoreArgs a, int tile_keys) {
   const int bl = blockIdx.x / a.n_kv_heads, h = blockIdx.x % a.n_kv_heads, z = blockIdx.y;
-  const int64_t problem = ((int64_t)(a.leader0 + z) * a.batch_total + (a.batch0 + bl)) * a.n_kv_heads + h;
+  const int64_t problem = ((int64_t)CKV_ARG(ScoreArgs, leader, z) * a.batch_total + (a.batch0 + bl)) * a.n_kv_heads + h;
   const int L = CKV_ARG(ScoreArgs, seq.seqlen, bl);
   const int ntiles = (L + tile_keys - 1) / tile_keys;
   const int nsplit = (ntiles + a.tiles_per_wg - 1) / a.tiles_per_wg;
@@ -104,7 +104,7 @@ int launch_stats_combine(const ScoreArgs &a, int n_leaders_slice, int batch_slic
 __global__ void chunk_sums_kernel(ScoreArgs a) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int bl = blockIdx.y / a.n_kv_heads, h = blockIdx.y % a.n_kv_heads, z = blockIdx.z;
-  const int64_t problem = ((int64_t)(a.leader0 + z) * a.batch_total + (a.batch0 + bl)) * a.n_kv_heads + h;
+  const int64_t problem = ((int64_t)CKV_ARG(ScoreArgs, leader, z) * a.batch_total + (a.batch0 + bl)) * a.n_kv_heads + h;
   const int P = pick(a.seq.seqlen, bl) - a.window, c = a.chunk;
   const int C = (P + c - 1) / c;
   const int ci = blockIdx.x * 4 + wave;
@@ -174,7 +174,7 @@ __global__ __launch_bounds__(256) void single_scores_kernel(ScoreArgs a, int per
   typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int bl = blockIdx.y / a.n_kv_heads, h = blockIdx.y % a.n_kv_heads, z = blockIdx.z;
-  const int64_t problem = ((int64_t)(a.leader0 + z) * a.batch_total + (a.batch0 + bl)) * a.n_kv_heads + h;
+  const int64_t problem = ((int64_t)CKV_ARG(ScoreArgs, leader, z) * a.batch_total + (a.batch0 + bl)) * a.n_kv_heads + h;
   const int L = CKV_ARG(ScoreArgs, seq.seqlen, bl), P = L - a.window, c = kSingleHalf / S;
   const int C = (P + c - 1) / c;
   const int np = (P + kSinglePeriod - 1) / kSinglePeriod;   // periods that hold prefix keys

@@ -124,7 +124,7 @@ __global__ __launch_bounds__(kThreads, 2) void score_single_kernel(ScoreArgs a) 
   const int split = blockIdx.x, row0 = (blockIdx.z % a.row_groups) * (128 * NQ);   // first window row of this workgroup
   const int g = a.n_q_heads / a.n_kv_heads, w = a.window;
   const int L = CKV_ARG(ScoreArgs, seq.seqlen, bl), P = L - w, nrows = g * w;
-  const int64_t problem = ((int64_t)(a.leader0 + z) * a.batch_total + (a.batch0 + bl)) * a.n_kv_heads + h;
+  const int64_t problem = ((int64_t)CKV_ARG(ScoreArgs, leader, z) * a.batch_total + (a.batch0 + bl)) * a.n_kv_heads + h;
 
   const int np_total = (L + kSpPeriod - 1) / kSpPeriod;
   const int ppr = single_periods_per_range(np_total);

@@ -43,7 +43,7 @@ __global__ __launch_bounds__(T) void topk_kernel(TopkArgs a) {
   int32_t *sel_chunk = a.sel_chunk + row * a.sel_cap;
   int32_t *sel_len = a.sel_len + row * a.sel_cap;
   int32_t *sel_off = a.sel_off ? a.sel_off + row * a.sel_cap : nullptr;
-  const int c = a.chunk, P = CKV_ARG(TopkArgs, seq.seqlen, bl) - a.window, n_keep = CKV_ARG(TopkArgs, seq.n_keep, bl);
+  const int c = CKV_ARG(TopkArgs, chunk_of, blockIdx.y), P = CKV_ARG(TopkArgs, seq.seqlen, bl) - a.window, n_keep = CKV_ARG(TopkArgs, seq.n_keep, bl);
   const int C = (P + c - 1) / c;
   // exact budget: ceil(n_keep / c) chunks, the lowest-ranked one cut; whole-chunk mode: floor(n_keep / c)
   // chunks (at most C), none cut
@@ -238,10 +238,11 @@ int launch_topk(const TopkArgs &a, int n_groups, int batch_slice, hipStream_t s)
   if (n_groups <= 0 || batch_slice <= 0) return CHUNKKV_OK;
   dim3 grid(batch_slice * a.n_kv_heads, n_groups);
   int c_max = 0;
-  for (int i = 0; i < batch_slice; ++i) {
-    const int C = (a.seq.seqlen[i] - a.window + a.chunk - 1) / a.chunk;
-    c_max = C > c_max ? C : c_max;
-  }
+  for (int j = 0; j < n_groups; ++j)
+    for (int i = 0; i < batch_slice; ++i) {
+      const int C = (a.seq.seqlen[i] - a.window + a.chunk_of[j] - 1) / a.chunk_of[j];
+      c_max = C > c_max ? C : c_max;
+    }
   // few chunks: 256 threads (cheaper barriers); a thread's chunks are unrolled, so no more of them than needed (a
   // workgroup runs through the code once, and bringing it in costs)
   if (c_max <= 256) hipLaunchKernelGGL((topk_kernel<256, 1, true>), grid, dim3(256), 0, s, a);

@@ -107,3 +107,53 @@ def test_uniform_table_equals_plain_stack_call(lib):
     for a, b in zip(outs[0][1] + outs[0][2], outs[1][1] + outs[1][2]):
         assert torch.equal(a, b)
     assert torch.equal(outs[0][0][2], outs[1][0][2])
+
+
+# One launch per kernel for groups of different sizes, where it can carry them (32 groups, chunks of at most 256 tokens), one run
+# after the other where it cannot: each group comes out as in the uniform call with its chunk size.  With the caller's
+# log-sum-exps nothing in a score depends on how the launch is cut, so it does to the bit; 17 sequences take two launches.
+@pytest.mark.parametrize("table,reuse,batch,dtype", [
+    ([5, 256, 1, 20, 33], 2, 3, "bf16"), ([10, 3, 10, 7], 1, 17, "f16"), ([20, 300, 5], 1, 2, "f32"),
+    ([3, 10, 1] * 11, 1, 1, "bf16"),       # 33 groups
+])
+def test_groups_of_different_sizes_equal_uniform_calls(lib, table, reuse, batch, dtype):
+    gen = torch.Generator(device=DEV).manual_seed(len(table))
+    kind, dt = {"bf16": (torch.bfloat16, lib.BF16), "f16": (torch.float16, lib.F16), "f32": (torch.float32, lib.F32)}[dtype]
+    hq, hkv, d, w, lens = 4, 2, 64, 16, [700 + 37 * i for i in range(batch)]
+    n = len(table) * reuse
+    total = sum(lens) * hkv * d
+    base = [sum(lens[:i]) * hkv * d for i in range(batch)]
+    k = [torch.randn(total, generator=gen, device=DEV).to(kind) for _ in range(n)]
+    v = [torch.randn(total, generator=gen, device=DEV).to(kind) for _ in range(n)]
+    q = [torch.randn((batch, hq, w, d), generator=gen, device=DEV).to(kind) for _ in range(n)]
+    lse = [torch.rand((batch, hq, w), generator=gen, device=DEV) + 6 for _ in range(n)]
+    keep = [(m - w) // 5 for m in lens]
+
+    def call(chunk):
+        prob = lib.Problem(hq, hkv, d, w, 1, dt, lens, keep, base, d, hkv * d)     # capacities of the smallest chunks
+        cap, score_cap = prob.sel_cap, prob.score_cap
+        prob = lib.Problem(hq, hkv, d, w, chunk if isinstance(chunk, int) else min(chunk), dt, lens, keep, base, d, hkv * d,
+                           sel_cap=cap, score_cap=score_cap)
+        groups = len(table)
+        sel = [torch.zeros((groups, batch, hkv, cap), dtype=torch.int32, device=DEV) for _ in range(2)]
+        cnt = torch.zeros((groups, batch, hkv), dtype=torch.int32, device=DEV)
+        ko = [torch.zeros(prob.out_elements(), dtype=kind, device=DEV) for _ in range(n)]
+        vo = [torch.zeros_like(ko[0]) for _ in range(n)]
+        if isinstance(chunk, int):
+            ws = torch.empty(lib.chunkkv_workspace_bytes(prob, n, reuse), dtype=torch.uint8, device=DEV)
+            lib.chunkkv_compress_stack_lse(prob, reuse, q, k, v, lse, ko, vo, *sel, cnt, ws)
+        else:
+            ws = torch.empty(lib.chunkkv_workspace_bytes_hybrid(prob, n, reuse, chunk), dtype=torch.uint8, device=DEV)
+            lib.chunkkv_compress_stack_hybrid(prob, reuse, chunk, q, k, v, lse, ko, vo, *sel, cnt, ws)
+        return sel, cnt, ko, vo
+
+    got = call(table)
+    for c in sorted(set(table)):
+        want = call(c)
+        for g in [g for g, x in enumerate(table) if x == c]:
+            assert torch.equal(got[1][g], want[1][g])
+            for a, b in zip(got[0], want[0]):
+                live = torch.arange(a.shape[-1], device=DEV) < got[1][g][..., None]
+                assert torch.equal(a[g] * live, b[g] * live), (c, g)
+            for layer in range(g * reuse, (g + 1) * reuse):
+                assert torch.equal(got[2][layer], want[2][layer]) and torch.equal(got[3][layer], want[3][layer]), (c, layer)
