@@ -354,10 +354,12 @@ int run_topk(const chunkkv_problem *p, const int32_t *chunks, const float *chunk
   return CHUNKKV_OK;
 }
 
-// chunks[i]: chunk size of the i-th reuse group from that of layer l_begin on
+// chunks[i]: chunk size of the i-th reuse group from that of layer l_begin on.  With chunk_scores (and a single launch's
+// worth of layers and sequences): selects and gathers in one launch if that suits the problem, otherwise does nothing;
+// *selected says which.
 int run_compact(const chunkkv_problem *p, const int32_t *chunks, int l_begin, int n_layers, int reuse, const void *const *k, const void *const *v,
                 void *const *k_out, void *const *v_out, const int32_t *sel_chunk, const int32_t *sel_len,
-                const int32_t *sel_count, const int32_t *sel_off, hipStream_t s) {
+                const int32_t *sel_count, const int32_t *sel_off, hipStream_t s, const float *chunk_scores = nullptr, bool *selected = nullptr) {
   const int esz = elem_bytes(p->dtype);
   for (int l0 = l_begin; l0 < n_layers; l0 += kMaxLayersPerLaunch) {
     const int nl = n_layers - l0 < kMaxLayersPerLaunch ? n_layers - l0 : kMaxLayersPerLaunch;
@@ -378,11 +380,26 @@ int run_compact(const chunkkv_problem *p, const int32_t *chunks, int l_begin, in
       a.sel_cap = p->sel_cap;
       a.whole_chunks = (p->flags & CHUNKKV_FLAG_WHOLE_CHUNKS) ? 1 : 0;
       int rc;
-      { Timed t(kCompact, s); rc = launch_compact(p->head_dim * esz, a, nl, nb, s); }
+      { Timed t(kCompact, s); rc = launch_compact(p->head_dim * esz, a, nl, nb, chunk_scores, p->score_cap, selected, s); }
       if (rc) return rc;
     }
   }
   return CHUNKKV_OK;
+}
+
+// Selection of the reuse groups from that of layer l_begin on and gather of layers [l_begin, l_end) with it. 
+int run_selection(const chunkkv_problem *p, const int32_t *chunks, const float *chunk_scores, int group0, int n_groups, int l_begin, int l_end,
+                  int reuse, const void *const *k, const void *const *v, void *const *k_out, void *const *v_out, int32_t *sel_chunk,
+                  int32_t *sel_len, int32_t *sel_count, int32_t *sel_off, hipStream_t s) {
+  int rc;
+  if (l_end - l_begin <= kMaxLayersPerLaunch && p->batch <= kMaxBatchPerLaunch) {
+    bool selected = false;
+    rc = run_compact(p, chunks, l_begin, l_end, reuse, k, v, k_out, v_out, sel_chunk, sel_len, sel_count, nullptr, s, chunk_scores, &selected);
+    if (rc || selected) return rc;
+  }
+  rc = run_topk(p, chunks, chunk_scores, group0, n_groups, sel_chunk, sel_len, sel_count, sel_off, s);
+  if (rc) return rc;
+  return run_compact(p, chunks, l_begin, l_end, reuse, k, v, k_out, v_out, sel_chunk, sel_len, sel_count, sel_off, s);
 }
 
 }  // namespace
@@ -518,10 +535,8 @@ static int stack_groups(const chunkkv_problem *prob, const Plan &pl, int g_begin
     }
     int rc = run_score(prob, pl, qs, ks, with_lse ? ls : nullptr, ng, leaders, chunks, scores, nullptr, 0, ws, s);
     if (rc) return rc;
-    rc = run_topk(prob, chunks, scores, g0, ng, sel_chunk, sel_len, sel_count, sel_off, s);
-    if (rc) return rc;
     const int l_begin = g0 * reuse, l_end = (g0 + ng) * reuse < n_layers ? (g0 + ng) * reuse : n_layers;
-    rc = run_compact(prob, chunks, l_begin, l_end, reuse, k, v, k_out, v_out, sel_chunk, sel_len, sel_count, sel_off, s);
+    rc = run_selection(prob, chunks, scores, g0, ng, l_begin, l_end, reuse, k, v, k_out, v_out, sel_chunk, sel_len, sel_count, sel_off, s);
     if (rc) return rc;
   }
   return CHUNKKV_OK;
@@ -582,9 +597,7 @@ static int stack_mixed(const chunkkv_problem *prob, const Plan &pl, int32_t n_la
     rc = run_score(&run, rp, qs, ks, lse ? ls : nullptr, ng, leaders, cs, scores, nullptr, 0, ws, s);
     if (rc) return rc;
   }
-  int rc = run_topk(prob, chunks, scores, 0, n_groups, sel_chunk, sel_len, sel_count, sel_off, s);
-  if (rc) return rc;
-  return run_compact(prob, chunks, 0, n_layers, reuse, k, v, k_out, v_out, sel_chunk, sel_len, sel_count, sel_off, s);
+  return run_selection(prob, chunks, scores, 0, n_groups, 0, n_layers, reuse, k, v, k_out, v_out, sel_chunk, sel_len, sel_count, sel_off, s);
 }
 
 extern "C" {
@@ -688,8 +701,7 @@ int chunkkv_compress_layer(const chunkkv_problem *prob, int32_t layer, int32_t r
     const int32_t leader0 = 0;
     rc = run_score(prob, pl, &q_obs, &k, lse ? &lse : nullptr, 1, &leader0, &prob->chunk, scores, nullptr, 0, ws, s);
     if (rc) return rc;
-    rc = run_topk(prob, &prob->chunk, scores, 0, 1, sc, sl, cnt, nullptr, s);
-    if (rc) return rc;
+    return run_selection(prob, &prob->chunk, scores, 0, 1, 0, 1, 1, &k, &v, &k_out, &v_out, sc, sl, cnt, nullptr, s);
   }
   return run_compact(prob, &prob->chunk, 0, 1, 1, &k, &v, &k_out, &v_out, sc, sl, cnt, nullptr, s);
 }

@@ -1,6 +1,6 @@
 // Compaction (Algorithm 1: index_select of the kept chunks + concatenation of the window).
 //
-// Pure data movement: every kept row of K and V is read once and written once.  A workgroup takes `entries_per_wg`
+// Pure data movement: every kept row of K and V is read once and written once.  A workgroup takes `rows_per_wg` rows' worth of
 // consecutive selection entries (a kept chunk is a run of `len` consecutive rows; the window is handled as extra
 // entries of up to `c` rows) and copies their rows as one flat list of 16-byte segments, K rows first, then V rows:
 // consecutive lanes copy consecutive segments whatever the chunk size is, five segments in flight per lane.  The
@@ -11,16 +11,69 @@
 // 17.5 -> 10.2 us.  A 32-layer stack of 131072 tokens (3.45 GB) takes 626 us = 5.5 TB/s; a plain device
 // copy of 1 to 4 GiB reaches 4.9 to 5.1.
 // Grid: x = group of entries, y = (sequence, kv-head), z = layer; all layers of the stack are one launch.
-#include "internal.h"
+#include "select.h"
 
 namespace ckv {
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
+// Selection and gather in one launch, by chunks of the longest head and workgroups.  us of a call, together and apart: 62
+// chunks 22.0 / 24.3; 816 chunks, 176 workgroups 25.7 / 28.3; 28 layers of 216 chunks, 4000 workgroups 63 / 66; 16 of 816, 8400
+// workgroups 106 / 101.  More chunks take 1024 threads, and as long as every workgroup has a CU: 3990 chunks, 208 workgroups
+// 43.8 / 46.9; 3274 chunks, 2 layers, 400 workgroups 53 / 47.
+constexpr int kSelectCompactChunks = 1024, kSelectCompactWorkgroups = 4096;
+constexpr int kSelectCompactWideChunks = 4096, kSelectCompactWideWorkgroups = 256;
+
 // selection entries of a workgroup
 __host__ __device__ inline int compact_entries(int rows, int chunk) {
   const int n = rows / chunk;
   return n < 1 ? 1 : (n > kCompactEntries ? kCompactEntries : n);
+}
+
+// Copies the rows of entries [0, n) of the lists (source token, destination token, length) of one layer, sequence and
+// kv-head; ne: entries a workgroup can have.
+template <int NSEG, int T>  // 16-byte segments per row, threads
+__device__ __forceinline__ void copy_entries(const CompactArgs &a, int layer, int bl, int h, int c, int ne, int n, const int *s_src, const int *s_dst, const int *s_len) {
+  const int64_t esz = a.elem_bytes;
+  const int64_t base = CKV_ARG(CompactArgs, seq.kv_base, bl), obase = CKV_ARG(CompactArgs, seq.out_base, bl);
+  const int64_t in_head = (base + (int64_t)h * a.kv_stride_head) * esz, out_head = (obase + (int64_t)h * a.out_stride_head) * esz;
+  const char *kin = (const char *)CKV_ARG(CompactArgs, k, layer) + in_head;
+  const char *vin = (const char *)CKV_ARG(CompactArgs, v, layer) + in_head;
+  char *kout = (char *)CKV_ARG(CompactArgs, k_out, layer) + out_head;
+  char *vout = (char *)CKV_ARG(CompactArgs, v_out, layer) + out_head;
+  const int64_t in_tok = a.kv_stride_tok * esz, out_tok = a.out_stride_tok * esz;
+
+  // rows of this workgroup's list: c per entry, or one entry's own length; rows past an entry's length copy nothing
+  const int half = (ne > 1 ? n * c : s_len[0]) * NSEG, total = 2 * half;
+  const float inv_c = 1.0f / (float)c;
+  for (int u0 = threadIdx.x; u0 < total; u0 += 5 * T) {
+    u32x4 r[5];
+    char *to[5];
+#pragma unroll
+    for (int j = 0; j < 5; ++j) {
+      // lanes without a segment re-read one of theirs and store nothing
+      const int u = u0 + j * T < total ? u0 + j * T : u0;
+      const bool is_v = u >= half;
+      const int uu = is_v ? u - half : u, row = uu / NSEG, seg = uu % NSEG;
+      int en = 0, i = row;
+      if (ne > 1) {   // row < 160: the rounded quotient is off by at most one
+        en = (int)((float)row * inv_c);
+        i = row - en * c;
+        if (i < 0) { --en; i += c; }
+        if (i >= c) { ++en; i -= c; }
+      }
+      const int len = s_len[en];
+      const bool live = i < len && u0 + j * T < total;
+      i = i < len ? i : 0;
+      // every byte is read once: streaming (non-temporal) loads (measured 2.6 % faster; the same hint on the
+      // stores is 2 % slower)
+      r[j] = __builtin_nontemporal_load((const u32x4 *)((is_v ? vin : kin) + (int64_t)(s_src[en] + i) * in_tok + seg * 16));
+      to[j] = live ? (is_v ? vout : kout) + (int64_t)(s_dst[en] + i) * out_tok + seg * 16 : nullptr;
+    }
+#pragma unroll
+    for (int j = 0; j < 5; ++j)
+      if (to[j] != nullptr) *(u32x4 *)to[j] = r[j];
+  }
 }
 
 template <int NSEG>  // 16-byte segments per row
@@ -97,51 +150,44 @@ __global__ __launch_bounds__(kThreads) void compact_kernel(CompactArgs a) {
     if (lane < ne) { s_src[lane] = src; s_dst[lane] = dst; s_len[lane] = mine ? len : 0; }
   }
   __syncthreads();
-
-  const int64_t esz = a.elem_bytes;
-  const int64_t base = CKV_ARG(CompactArgs, seq.kv_base, bl), obase = CKV_ARG(CompactArgs, seq.out_base, bl);
-  const int64_t in_head = (base + (int64_t)h * a.kv_stride_head) * esz, out_head = (obase + (int64_t)h * a.out_stride_head) * esz;
-  const char *kin = (const char *)CKV_ARG(CompactArgs, k, layer) + in_head;
-  const char *vin = (const char *)CKV_ARG(CompactArgs, v, layer) + in_head;
-  char *kout = (char *)CKV_ARG(CompactArgs, k_out, layer) + out_head;
-  char *vout = (char *)CKV_ARG(CompactArgs, v_out, layer) + out_head;
-  const int64_t in_tok = a.kv_stride_tok * esz, out_tok = a.out_stride_tok * esz;
-
-  // rows of this workgroup's list: c per entry, or one entry's own length; rows past an entry's length copy nothing
-  const int last = count + n_win - e0 < ne ? count + n_win - e0 : ne;
-  const int half = (ne > 1 ? last * c : s_len[0]) * NSEG, total = 2 * half;
-  const float inv_c = 1.0f / (float)c;
-  for (int u0 = threadIdx.x; u0 < total; u0 += 5 * kThreads) {
-    u32x4 r[5];
-    char *to[5];
-#pragma unroll
-    for (int j = 0; j < 5; ++j) {
-      // lanes without a segment re-read one of theirs and store nothing
-      const int u = u0 + j * kThreads < total ? u0 + j * kThreads : u0;
-      const bool is_v = u >= half;
-      const int uu = is_v ? u - half : u, row = uu / NSEG, seg = uu % NSEG;
-      int en = 0, i = row;
-      if (ne > 1) {   // row < 160: the rounded quotient is off by at most one
-        en = (int)((float)row * inv_c);
-        i = row - en * c;
-        if (i < 0) { --en; i += c; }
-        if (i >= c) { ++en; i -= c; }
-      }
-      const int len = s_len[en];
-      const bool live = i < len && u0 + j * kThreads < total;
-      i = i < len ? i : 0;
-      // every byte is read once: streaming (non-temporal) loads (measured 2.6 % faster; the same hint on the
-      // stores is 2 % slower)
-      r[j] = __builtin_nontemporal_load((const u32x4 *)((is_v ? vin : kin) + (int64_t)(s_src[en] + i) * in_tok + seg * 16));
-      to[j] = live ? (is_v ? vout : kout) + (int64_t)(s_dst[en] + i) * out_tok + seg * 16 : nullptr;
-    }
-#pragma unroll
-    for (int j = 0; j < 5; ++j)
-      if (to[j] != nullptr) *(u32x4 *)to[j] = r[j];
-  }
+  copy_entries<NSEG, kThreads>(a, layer, bl, h, c, ne, count + n_win - e0 < ne ? count + n_win - e0 : ne, s_src, s_dst, s_len);
 }
 
-int launch_compact(int row_bytes, CompactArgs &a, int n_layers_slice, int batch_slice, hipStream_t s) {
+// Selection and gather in one launch: every workgroup selects the chunks of its head for itself and keeps the places that
+// are its own; one workgroup per head and reuse group writes the selection out.  For short launches over few chunks, where a
+// dependent launch costs more than the selection's 2 to 5 us.
+template <int NSEG, int T, int KR>
+__global__ __launch_bounds__(T) void select_compact_kernel(CompactArgs a, const float *chunk_scores, int score_cap) {
+  const int bl = blockIdx.y / a.n_kv_heads, h = blockIdx.y % a.n_kv_heads, layer = blockIdx.z;
+  const int n_keep = CKV_ARG(CompactArgs, seq.n_keep, bl), w = a.window, c = CKV_ARG(CompactArgs, chunk_of, layer);
+  const int P = CKV_ARG(CompactArgs, seq.seqlen, bl) - w, ne = compact_entries(a.rows_per_wg, c), n_win = (w + c - 1) / c;
+  const int e0 = blockIdx.x * ne;
+  if (e0 >= (n_keep > 0 ? (n_keep + c - 1) / c + 1 : 0) + n_win) return;   // more entries there cannot be
+  const int group = (a.layer0 + layer) / a.reuse;
+  const int64_t selrow = ((int64_t)group * a.batch_total + (a.batch0 + bl)) * a.n_kv_heads + h;
+  const bool writer = blockIdx.x == 0 && (layer == 0 || (a.layer0 + layer) % a.reuse == 0);
+  int32_t *sel_chunk = const_cast<int32_t *>(a.sel_chunk) + selrow * a.sel_cap, *sel_len = const_cast<int32_t *>(a.sel_len) + selrow * a.sel_cap;
+  __shared__ int s_src[kCompactEntries], s_dst[kCompactEntries], s_len[kCompactEntries];
+  const Selected sel = select_chunks<T, KR, true>(chunk_scores + selrow * score_cap, P, c, n_keep, a.whole_chunks != 0, [&](int i, int pos, int len, int off) {
+    if (pos >= e0 && pos < e0 + ne) { s_src[pos - e0] = i * c; s_dst[pos - e0] = off; s_len[pos - e0] = len; }
+    if (writer && pos < a.sel_cap) { sel_chunk[pos] = i; sel_len[pos] = len; }
+  });
+  if (writer && threadIdx.x == 0) const_cast<int32_t *>(a.sel_count)[selrow] = sel.count;
+  const int wi = e0 + (int)threadIdx.x - sel.count;   // window entry of this thread, if it is one
+  if ((int)threadIdx.x < ne && wi >= 0 && wi < n_win) {
+    s_src[threadIdx.x] = P + wi * c;
+    s_dst[threadIdx.x] = sel.kept + wi * c;
+    s_len[threadIdx.x] = w - wi * c < c ? w - wi * c : c;
+  }
+  __syncthreads();
+  const int n = sel.count + n_win - e0;
+  if (n > 0) copy_entries<NSEG, T>(a, layer, bl, h, c, ne, n < ne ? n : ne, s_src, s_dst, s_len);
+}
+
+// With chunk_scores: selects as well where that fits (see select_compact_kernel), and says so in *selected; where it does not
+// nothing is launched.
+int launch_compact(int row_bytes, CompactArgs &a, int n_layers_slice, int batch_slice, const float *chunk_scores, int score_cap,
+                   bool *selected, hipStream_t s) {
   if (n_layers_slice <= 0 || batch_slice <= 0) return CHUNKKV_OK;
   int64_t total = 0;   // workgroups with entries, of one kv-head per sequence
   auto groups = [&](int rows) {   // most workgroups of a head
@@ -167,6 +213,31 @@ int launch_compact(int row_bytes, CompactArgs &a, int n_layers_slice, int batch_
   if (total * batch_slice * a.n_kv_heads < 4096) nx = groups(40);
   if (nx <= 0) return CHUNKKV_OK;
   dim3 grid(nx, batch_slice * a.n_kv_heads, n_layers_slice);
+  if (chunk_scores != nullptr) {
+    int most = 0;   // chunks of a head
+    for (int z = 0; z < n_layers_slice; ++z)
+      for (int i = 0; i < batch_slice; ++i) {
+        const int C = (a.seq.seqlen[i] - a.window + a.chunk_of[z] - 1) / a.chunk_of[z];
+        most = C > most ? C : most;
+      }
+    const int64_t heads = (int64_t)batch_slice * a.n_kv_heads;
+    const bool wide = most > kSelectCompactChunks;
+    if (wide) grid.x = groups(160);   // few workgroups, each wide and long
+    *selected = wide ? most <= kSelectCompactWideChunks && total * heads <= kSelectCompactWideWorkgroups : total * heads <= kSelectCompactWorkgroups;
+    if (!*selected) return CHUNKKV_OK;
+    const dim3 block(wide ? 1024 : kThreads);
+#define CKV_SELECT(NSEG) \
+  hipLaunchKernelGGL((wide ? select_compact_kernel<NSEG, 1024, 4> : most <= kThreads ? select_compact_kernel<NSEG, kThreads, 1> : select_compact_kernel<NSEG, kThreads, 4>), \
+                     grid, block, 0, s, a, chunk_scores, score_cap)
+    switch (row_bytes / 16) {
+      case 8: CKV_SELECT(8); break;
+      case 16: CKV_SELECT(16); break;
+      case 32: CKV_SELECT(32); break;
+      default: return CHUNKKV_ERR_UNSUPPORTED;
+    }
+#undef CKV_SELECT
+    return hipGetLastError() == hipSuccess ? CHUNKKV_OK : CHUNKKV_ERR_LAUNCH;
+  }
   switch (row_bytes / 16) {
     case 8: hipLaunchKernelGGL(compact_kernel<8>, grid, dim3(kThreads), 0, s, a); break;
     case 16: hipLaunchKernelGGL(compact_kernel<16>, grid, dim3(kThreads), 0, s, a); break;
