@@ -31,7 +31,7 @@ struct Plan {
   ScoreGeom geom;
   int n_leaders, rows_pad;
   int batch_leaders;  // leader layers scored per launch set (the unit that overlaps with compaction)
-  int tpw0, tpw1, max_split0;
+  int tpw0, max_split0;
   int merge0;         // two-pass scoring: pass 1 merges the row statistics itself
   int fuse_chunks;
   // single-pass path: usable for this problem?  geometry and workspace
@@ -152,11 +152,9 @@ int make_plan(const chunkkv_problem *p, int n_layers, int reuse, Plan *pl) {
   pl->rows_pad = pl->geom.nqw * pl->geom.wq * 32;
   const int TK = pl->geom.tile_keys;
   pl->fuse_chunks = p->chunk <= kSuperKeys;
-  const int stride1 = pl->fuse_chunks ? (kSuperKeys / p->chunk) * p->chunk : kSuperKeys;
-  int64_t tiles0 = 0, tiles1 = 0;
+  int64_t tiles0 = 0;
   for (int b = 0; b < p->batch; ++b) {
     tiles0 += ceil_div(p->seqlen[b], TK);
-    tiles1 += ceil_div(p->seqlen[b] - p->window, stride1);
   }
   // leader layers per launch set: enough key tiles (~kTilesPerLaunch) to amortise workgroup start-up,
   // few enough that compaction of one set overlaps scoring of the next; sets are balanced in size
@@ -185,7 +183,6 @@ int make_plan(const chunkkv_problem *p, int n_layers, int reuse, Plan *pl) {
     if (least < ceil_div(most0, kMaxRanges)) least = ceil_div(most0, kMaxRanges);
     if (pl->tpw0 < least) pl->tpw0 = (int)least;
   }
-  pl->tpw1 = pass1_tiles_per_wg(tiles1 * heads, pl->merge0);
   // single-pass path
   pl->rows_pad_s = rows > 128 ? 256 : 128;
   pl->n_periods = 0;
@@ -270,14 +267,18 @@ int run_score(const chunkkv_problem *p, const Plan &pl, const void *const *q, co
     a.fuse_chunks = pl.fuse_chunks;
     if (!pl.fuse_chunks && !token_imp) { a.token_imp = (float *)(ws + pl.off_imp); a.imp_pitch = (int64_t)p->score_cap * p->chunk; }
     int split0 = 1, split1 = 0;
+    // Super-tiles: smaller ones where a launch would leave CUs without a workgroup (512 tokens in fp32, 4 workgroups 12 us,
+    // 16 of them 8); the sums of a chunk are the same bits whatever super-tile it lies in.
+    a.super_keys = kSuperKeys;
+    auto super_tiles = [&](int i, int z) { return ceil_div(a.seq.seqlen[i] - p->window, pl.fuse_chunks ? super_stride(a.super_keys, chunks[z]) : kSuperKeys); };
     int64_t units1 = 0;   // super-tiles of all sequences and layers
-    auto super_tiles = [&](int i, int z) { return ceil_div(a.seq.seqlen[i] - p->window, pl.fuse_chunks ? (kSuperKeys / chunks[z]) * chunks[z] : kSuperKeys); };
-    bool mixed = false;
-    for (int z = 0; z < ng; ++z) {
-      mixed |= chunks[z] != chunks[0];
-      for (int i = 0; i < nb; ++i) units1 += super_tiles(i, z);
+    for (;; a.super_keys /= 2) {
+      units1 = 0;
+      for (int z = 0; z < ng; ++z)
+        for (int i = 0; i < nb; ++i) units1 += super_tiles(i, z);
+      if (!pl.fuse_chunks || units1 * p->n_kv_heads >= 256 || a.super_keys / 2 < TK || a.super_keys <= 64) break;
     }
-    const int tpw1 = mixed ? pass1_tiles_per_wg(units1 * p->n_kv_heads, pl.merge0) : pl.tpw1;
+    const int tpw1 = pass1_tiles_per_wg(units1 * p->n_kv_heads, pl.merge0);
     for (int i = 0; i < nb; ++i) {
       const int s0 = ceil_div(ceil_div(a.seq.seqlen[i], TK), pl.tpw0);
       split0 = s0 > split0 ? s0 : split0;

@@ -13,7 +13,9 @@ namespace ckv {
 
 constexpr int kMaxLayersPerLaunch = 32;  // pointer tables travel as kernel arguments
 constexpr int kTileBytes = 16384;        // one K tile staged in LDS (ring slot)
-constexpr int kSuperKeys = 256;        // keys per importance / chunk-sum step of pass 1 (several tiles)
+constexpr int kSuperKeys = 256;        // most keys per importance / chunk-sum step of pass 1 (several tiles)
+// keys of such a super-tile of at most `keys`: whole chunks
+__host__ __device__ inline int super_stride(int keys, int chunk) { return (chunk <= keys ? keys / chunk : kSuperKeys / chunk) * chunk; }
 constexpr int kThreads = 256;            // 4 wavefronts of 64
 constexpr int kMaxRows = 512;            // g * w limit
 constexpr int kCompactEntries = 64;      // most selection entries per compaction workgroup
@@ -39,7 +41,7 @@ struct ScoreArgs {
   int32_t n_q_heads, n_kv_heads, window, chunk;   // chunk: of all slice layers, everywhere but in the importance pass
   int64_t kv_stride_head, kv_stride_tok;
   float scale_log2e;       // softmax scale * log2(e)
-  int32_t tiles_per_wg;    // pass 0: key tiles, pass 1: super-tiles (kSuperKeys) each workgroup walks
+  int32_t tiles_per_wg;    // pass 0: key tiles, pass 1: super-tiles each workgroup walks
   int32_t max_split;       // pitch of part_stats in splits
   int32_t rows_pad;        // g*w rounded up to 32
   float2 *part_stats;      // [problem][max_split][rows_pad]  (running max, sum) in log2 units
@@ -51,6 +53,7 @@ struct ScoreArgs {
   const float *lse[kMaxLayersPerLaunch];  // pass 1 with use_lse: per leader layer [batch_total][Hq][w], natural log
   int32_t use_lse;
   int32_t stats_tiles;     // pass 1: > 0 = merge the pairs of pass 0 here; key tiles of one of its ranges
+  int32_t super_keys;      // pass 1: super-tiles of at most this many keys
   int32_t fuse_chunks;     // pass 1: 1 = super-tiles hold whole chunks and chunk sums are written
   // single-pass path (score_single.h): key ranges are single_periods_per_range() whole periods of 160 keys
   int32_t n_periods;       // pitch of e_buf / m_period: max over sequences of ceil(L / 160)

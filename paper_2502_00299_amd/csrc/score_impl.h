@@ -11,7 +11,7 @@
 //   pass 1  (rows x keys orientation: a lane owns one key)  streams K again with the accumulators started at -ref_r/(scale*log2e) (kept in registers for bf16 caches, where they are the C
 //           operand of a block's first MFMA), so p = exp2(acc*scale*log2e); p is summed over the rows in
 //           registers, across the two lane halves by one shuffle, across wavefronts in LDS, and once
-//           per super-tile of kSuperKeys keys the per-token importance is reduced to chunk sums with a
+//           per super-tile of up to kSuperKeys keys the per-token importance is reduced to chunk sums with a
 //           fixed-order segmented sum in LDS (super-tiles advance by a multiple of c, so no chunk
 //           straddles two of them and no atomics are needed: results are deterministic).
 //
@@ -131,7 +131,7 @@ __global__ __launch_bounds__(kThreads, ((NQW >= 4 || (DT == CHUNKKV_F32 && HD ==
 
   // Work units: pass 0 walks tiles of TK keys over [0, L); pass 1 walks super-tiles over [0, P), each
   // advancing `sstride` keys (a multiple of c when chunk sums are fused) and made of `spt` tiles.
-  const int sstride = PASS == 0 ? TK : (a.fuse_chunks ? (kSuperKeys / c) * c : kSuperKeys);
+  const int sstride = PASS == 0 ? TK : (a.fuse_chunks ? super_stride(a.super_keys, c) : kSuperKeys);
   const int spt = (sstride + TK - 1) / TK;
   const int span = PASS == 0 ? L : P;
   const int nunits = (span + sstride - 1) / sstride;
