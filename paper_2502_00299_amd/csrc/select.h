@@ -17,6 +17,8 @@
 // the three-pass radix select over consecutive chunks that this replaced, us per launch back to back:
 //   chunks per head   62: 11.8 -> 4.3   816: 12.4 -> 5.5   2000: 13.2 -> 8.1   4000: 14.7 -> 7.3   13101: 20.7 -> 14.5
 //   (128 heads: 21.4 -> 14.7)   20000: 54 -> 26   131072: 479 -> 133
+// Past 16384 chunks the scores are re-read, eight loads in flight per thread (one before): 40201: 70 -> 61.5, 131000: 149 -> 127.
+// 32 or 64 keys per thread in registers there do not fit into 128 registers: 26200: 34 -> 101.
 #pragma once
 #include "internal.h"
 
@@ -74,7 +76,14 @@ __device__ __forceinline__ Selected select_chunks(const float *scores, int P, in
       for (int j = 0; j < KR; ++j)
         if (KR <= 4 || j * T < C) f(j * T + tid, kreg[j]);
     } else {
-      for (int i = tid; i < C; i += T) f(i, order_key(scores[i]) - low);
+      for (int i0 = tid; i0 < C; i0 += 8 * T) {
+        float x[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) x[j] = scores[i0 + j * T < C ? i0 + j * T : C - 1];
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+          if (i0 + j * T < C) f(i0 + j * T, order_key(x[j]) - low);
+      }
     }
   };
   // f(chunk index, rank) for every own chunk with pred(index, key), rank = how many such chunks lie before it
