@@ -19,9 +19,10 @@ constexpr int64_t kMergeTiles = 16384, kMergeWorkgroups = 1536;
 // So there are at most kMaxRanges ranges, and kGoodRanges as long as that asks for no more than kRangeTiles tiles in a row
 // and leaves no CU without a workgroup: 120602 tokens, 4 heads, fp32 in 32 / 63 / 236 ranges 147 / 81 / 90 us.
 constexpr int kGoodRanges = 32, kMaxRanges = 64, kRangeTiles = 8;
-// Single-pass scoring with 256 rows: up to this many workgroups (one per CU) leave half the places empty, so two of them,
-// with 128 rows each, share a key range.  K is read twice, the second time from L2.
-constexpr int64_t kRowSplitWorkgroups = 256;
+// Single-pass scoring with 256 rows: up to this many workgroups leave half the CUs empty, so two of them, with 128 rows each,
+// share a key range; K is read twice.  us of a call on one layer, split / not: 104 workgroups 26.9 / 30.0, 128 of them at 65536
+// tokens 59.6 / 69.8; 200 36.1 / 35.9, 256 at 20011 tokens 42.6 / 41.8, 256 at 131072 155 / 140.
+constexpr int64_t kRowSplitWorkgroups = 128;
 constexpr int kSinglePeriodKeys = 160;   // granule of the single-pass kernel's key ranges
 // Key tiles (16 KB) one scoring launch set should hold.  Measured on MI355X: every extra dependent launch
 // costs ~30 us of idle GPU, more than splitting the stack into sets wins back, so one set it is.

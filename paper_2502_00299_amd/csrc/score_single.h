@@ -28,10 +28,10 @@
 // read as zero).  The ring holds two periods; a period is 5 slots of 32 key rows, slot t holding the rows of
 // step t in M-index order, so the permutation above lives in the global addresses of the loads and the operand
 // reads are "lane register + compile-time slot offset".  The 16-byte segments of a row are XOR-swizzled by the
-// M index (global-address side), so the reads of 16 consecutive lanes hit distinct banks.  A slot is refilled as soon as
-// every wavefront has its fragments in registers (one barrier per step, two per period where a step is short), so 48 to 64
-// KB per workgroup are in flight all the time; refilled a period at a time, 40 KB were, and none of it while the last of it
-// was awaited: 16 layers of 131072 tokens 1327 -> 1250 us.  The waits count the loads and stores behind the awaited one.
+// M index (global-address side), so the reads of 16 consecutive lanes hit distinct banks.  Slots are refilled twice per
+// period, as soon as every wavefront has their fragments in registers, so 32 to 56 KB per workgroup are in flight all the
+// time; refilled a period at a time, 40 KB were, and none of it while the last of it was awaited: 16 layers of 131072 tokens
+// 1327 -> 1240 us, ten layers of a ragged batch at c = 20 964 -> 858.  The waits count the loads and stores behind the awaited one.
 //
 // A call on one layer is short: launch, queries, a few periods per workgroup, and code that every workgroup fetches and
 // runs through once.  Hence one instance of the period for all periods (the ragged last one masked through the operand the
@@ -340,20 +340,19 @@ __global__ __launch_bounds__(kThreads, 2) void score_single_kernel(ScoreArgs a) 
     // if it is the last use of its block's fragments they are re-read for the block after (slot TR)
     constexpr bool REFILL = QNX == NQ - 1;
     constexpr int TR = (TNX + 1) % kSpSteps;
-    // The re-reads take step R (counted from this period's first).  Its loads are waited for, with those of later steps in
-    // flight; behind the barrier it is there for all, and every wavefront has the fragments of step R - 2 in registers,
-    // whose slot is free.  Two row blocks per wavefront: at every step, the slot takes step R + 8.  One row block: a step is
-    // too short for a barrier of its own (32 layers of 32768 tokens 579 us), so at steps 3 and 5, for the steps up to the next.
-    if constexpr (REFILL && NQ == 2) {
-      constexpr int R = T + 1, RN = R + 8;
-      // the sums of one period leave within the last eight steps, of two from step 5 - 3 on back
-      constexpr int kStores = kPeriodStores * (T < 3 ? 2 : 1);
-      if (active && prel >= 2) __builtin_amdgcn_s_waitcnt(vmcnt_imm(7 * 2 + kStores));
-      else __builtin_amdgcn_s_waitcnt(vmcnt_imm(7 * 2));
-      __builtin_amdgcn_s_barrier();
-      issue_step(prel + RN / kSpSteps, std::integral_constant<int, RN % kSpSteps>{});
+    // Ring hand-over, twice per period: where the re-reads come to step 3 or to the next period's first.  The loads of the steps
+    // up to the next hand-over are waited for, with those of four later steps (and the sums of one period, which leave behind
+    // the awaited loads) in flight; behind the barrier they are there for all, and every wavefront has the fragments of step
+    // TR - 1 in registers, so the slots of the steps up to TR - 2 are free.  At every step: 16 layers of 20011 tokens, c = 5,
+    // 225 instead of 218 us, and 32 layers of 32768 tokens with 128 rows 579 instead of 518.
+    // With two row blocks per wavefront the first period's step 2 is loaded behind the queries: a wait of its own.
+    if constexpr (REFILL && NQ == 2 && TR == 2) {
+      if (__builtin_expect(prel == 0, 0)) {
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm(6 * 2));
+        __builtin_amdgcn_s_barrier();
+      }
     }
-    if constexpr (REFILL && NQ == 1 && (TR == 0 || TR == 3)) {
+    if constexpr (REFILL && (TR == 0 || TR == 3)) {
       if (active && prel >= 1) __builtin_amdgcn_s_waitcnt(vmcnt_imm(4 * 2 + kPeriodStores));
       else __builtin_amdgcn_s_waitcnt(vmcnt_imm(4 * 2));
       __builtin_amdgcn_s_barrier();
