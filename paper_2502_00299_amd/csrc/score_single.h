@@ -24,7 +24,7 @@
 // inputs that happens once per range.  Values more than 2^126 below the reference vanish: their probability is
 // below what fp32 chunk scores can represent.
 //
-// K: HBM -> LDS by buffer loads with an LDS destination (16 bytes per lane, rows past the end of the sequence
+// K: HBM -> LDS by buffer loads with an LDS destination (16 bytes per lane, rows past the end of the prefix
 // read as zero).  The ring holds two periods; a period is 5 slots of 32 key rows, slot t holding the rows of
 // step t in M-index order, so the permutation above lives in the global addresses of the loads and the operand
 // reads are "lane register + compile-time slot offset".  The 16-byte segments of a row are XOR-swizzled by the
@@ -155,9 +155,10 @@ __global__ __launch_bounds__(kThreads, 2) void score_single_kernel(ScoreArgs a) 
     }
     kdelta = (uint32_t)(C * (int)ktok + (seg1 - seg0) * 16);
   }
-  // step T of period prel, into its slot of the ring; periods that are not there read as zero, so that the number of loads
-  // in flight is a compile-time constant at every wait
-  const int kbytes = (int)((uint32_t)(L - 1) * (uint32_t)ktok + ROWB);
+  // step T of period prel, into its slot of the ring.  Only prefix keys: window rows in the last period read as zero (its
+  // masked logits are minus infinity plus a product, which an infinite key would make NaN), and so do periods that are not
+  // there, so that the number of loads in flight is a compile-time constant at every wait.
+  const int kbytes = (int)((uint32_t)(P - 1) * (uint32_t)ktok + ROWB);
   auto issue_step = [&](int prel, auto t_c) __attribute__((always_inline)) {
     constexpr int T = decltype(t_c)::value;
     const __amdgpu_buffer_rsrc_t krsrc = __builtin_amdgcn_make_buffer_rsrc((void *)kbase, 0, prel < np ? kbytes : 0, 0x00020000);
@@ -470,7 +471,7 @@ __global__ __launch_bounds__(kThreads, 2) void score_single_kernel(ScoreArgs a) 
   if (u1 == np_total) {
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
     lds_barrier();   // the ring is dead
-    const __amdgpu_buffer_rsrc_t krsrc = __builtin_amdgcn_make_buffer_rsrc((void *)kbase, 0, kbytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t krsrc = __builtin_amdgcn_make_buffer_rsrc((void *)kbase, 0, (int)((uint32_t)(L - 1) * (uint32_t)ktok + ROWB), 0x00020000);
     const uint32_t row = (uint32_t)(8 * wave + lane / 16), seg = (uint32_t)((lane % 16) ^ (int)(row & 15));
     for (int key0 = P, sl = 0; key0 < L; key0 += 32, ++sl) {
       char *dst = smem + sl * kSpStepBytes + wave * 2048;

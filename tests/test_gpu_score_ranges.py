@@ -90,3 +90,26 @@ def test_two_pass_scores_match_float64(dtype, d, lens, hkv, g, w, c):
         got = scores[b].cpu().double()[:, :want.shape[1]]
         # the reference of a row is one float below 32 (2^-20 in the exponent of every weight), the sums are fp32
         assert float(((got - want).abs() / want).max()) < 4e-6
+
+
+# An infinity in a window key that some rows do not see: minus infinity as the logit of those that do (weight 0), nothing
+# for the others, though their products with it are plus infinity.
+@pytest.mark.parametrize("flags", [0, ckv.FLAG_TWO_PASS])
+@pytest.mark.parametrize("dtype", [ckv.BF16, ckv.F16])
+@pytest.mark.parametrize("P,w,g,c", [(1, 32, 4, 5), (159, 32, 4, 10), (641, 32, 7, 10), (1281, 64, 4, 20), (1290, 256, 1, 10)])
+def test_infinite_key_that_rows_do_not_see(P, w, g, c, dtype, flags):
+    gen = torch.Generator().manual_seed(P)
+    hkv, d, L, at = 2, 128, P + w, w // 2
+    q = torch.randn((hkv * g, w, d), generator=gen)
+    k = torch.randn((hkv, L, d), generator=gen)
+    q[:, :at, 3], q[:, at:, 3] = 0.5, -0.5
+    k[:, P + at, 3] = float("inf")
+    q, k = q.to(KIND[dtype]), k.to(KIND[dtype])
+    want = oracle_scores(q, k, w, c)
+    assert torch.isfinite(want).all()
+    prob = ckv.Problem(hkv * g, hkv, d, w, c, dtype, [L], [0], [0], L * d, d, flags=flags)
+    ws = torch.full((ckv.chunkkv_workspace_bytes(prob),), 0xFF, dtype=torch.uint8, device=DEV)
+    scores = torch.full((hkv, prob.score_cap), float("nan"), device=DEV)
+    ckv.chunkkv_score(prob, q.to(DEV), k.to(DEV), scores, None, ws)
+    got = scores.cpu().double()[:, :want.shape[1]]
+    assert float(((got - want).abs() / want).max()) < 1.3e-4   # as above; a NaN fails as well
