@@ -8,6 +8,7 @@
 
 #include "chunkkv.h"
 #include "decode_plan.h"
+#include "score_plan.h"
 
 namespace ckv {
 

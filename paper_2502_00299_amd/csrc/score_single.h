@@ -158,14 +158,13 @@ __global__ __launch_bounds__(kThreads, 2) void score_single_kernel(ScoreArgs a) 
   // step T of period prel, into its slot of the ring.  Only prefix keys: window rows in the last period read as zero (its
   // masked logits are minus infinity plus a product, which an infinite key would make NaN), and so do periods that are not
   // there, so that the number of loads in flight is a compile-time constant at every wait.
-  const int kbytes = (int)((uint32_t)(P - 1) * (uint32_t)ktok + ROWB);
   auto issue_step = [&](int prel, auto t_c) __attribute__((always_inline)) {
     constexpr int T = decltype(t_c)::value;
-    const __amdgpu_buffer_rsrc_t krsrc = __builtin_amdgcn_make_buffer_rsrc((void *)kbase, 0, prel < np ? kbytes : 0, 0x00020000);
-    const uint32_t off = (uint32_t)(range0 + prel * kSpPeriod) * (uint32_t)ktok;  // wavefront-uniform
+    const RingRows rows = ring_rows(range0 + prel * kSpPeriod, P, (uint32_t)ktok, ROWB, prel < np);  // wavefront-uniform
+    const __amdgpu_buffer_rsrc_t krsrc = __builtin_amdgcn_make_buffer_rsrc((void *)kbase, 0, (int)rows.records, 0x00020000);
     char *dst = smem + (prel & 1) * kSpPeriodBytes + wave * 2048 + T * kSpStepBytes;
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(krsrc, (__attribute__((address_space(3))) void *)dst, 16, klane[T], off, 0, 0);
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(krsrc, (__attribute__((address_space(3))) void *)(dst + 1024), 16, klane[T] + kdelta, off, 0, 0);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(krsrc, (__attribute__((address_space(3))) void *)dst, 16, klane[T], rows.offset, 0, 0);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(krsrc, (__attribute__((address_space(3))) void *)(dst + 1024), 16, klane[T] + kdelta, rows.offset, 0, 0);
   };
   // The window queries come through the ring as well (a row block is 8 KB, like a step): read straight into operand
   // fragments, every load would touch 32 lines, 10 thousand cycles for 64 KB.  The first steps of K share the way.
@@ -180,8 +179,9 @@ __global__ __launch_bounds__(kThreads, 2) void score_single_kernel(ScoreArgs a) 
 #pragma unroll
     for (int j = 0; j < 8 * NQ; ++j) {
       const int row = 4 * (j % 8) + lane / 16;
-      const uint32_t vo = (uint32_t)(row * ROWB + ((lane % 16) ^ (row & 15)) * 16), so = off + (uint32_t)(j / 8 * kSpStepBytes);
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(qrsrc, (__attribute__((address_space(3))) void *)(dst + j * 1024), 16, vo, so, 0, 0);
+      // (no scalar offset: a wavefront without rows starts behind the last record)
+      const uint32_t vo = off + (uint32_t)(j / 8 * kSpStepBytes + row * ROWB + ((lane % 16) ^ (row & 15)) * 16);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(qrsrc, (__attribute__((address_space(3))) void *)(dst + j * 1024), 16, vo, 0, 0, 0);
     }
   }
 
