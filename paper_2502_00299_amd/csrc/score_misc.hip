@@ -134,7 +134,7 @@ int launch_chunk_sums(const ScoreArgs &a, int n_leaders_slice, int batch_slice, 
 //   ref_r = m_r + log2(sum_r), merged from the (reference, sum) pairs the key ranges left for row r
 //           (pairs merge associatively; always in the same order: range by range);
 //   score[chunk] = sum over rows of E[chunk][row] * exp2(m[chunk][row] - ref[row]).
-// A workgroup of 256 threads merges the statistics of its problem (one row per thread, eight ranges' pairs in flight)
+// A workgroup of 256 threads merges the statistics of its problem (one row per thread, sixteen ranges' pairs in flight)
 // and then takes `periods_per_wg` consecutive periods.  Per period the scoring kernel left, for each lane half h and
 // each group of eight consecutive chunks of that half, rows_pad pieces of 16 + 4 bytes (eight sums as 20-bit floats:
 // 8 exponent and 12 mantissa bits; chunk size 20 has four chunks per half: pieces of 12 bytes, four 24-bit floats), and
@@ -223,7 +223,8 @@ __global__ __launch_bounds__(256) void single_scores_kernel(ScoreArgs a, int per
   {
     const int np_total = (L + kSinglePeriod - 1) / kSinglePeriod, ppr = single_periods_per_range(np_total);
     const int nsplit = (np_total + ppr - 1) / ppr;
-    s_ref[tid] = tid < nrows ? merge_row_stats(a.row_stats + problem * a.max_split * a.rows_pad + tid, nsplit, a.rows_pad) : 3.0e38f;
+    s_ref[tid] = tid < nrows ? merge_row_stats(a.row_stats + problem * a.max_split * a.rows_pad + tid, m_problem + tid, a.refs + problem * nrows + tid,
+                                               nsplit, ppr, np, a.rows_pad) : 3.0e38f;
   }
   __syncthreads();
   float ref[RB];
@@ -280,12 +281,14 @@ int launch_single_scores(const ScoreArgs &a, int n_leaders_slice, int batch_slic
   }
   if (max_periods == 0 || n_leaders_slice <= 0) return CHUNKKV_OK;
   if (a.rows_pad != 128 && a.rows_pad != 256) return CHUNKKV_ERR_UNSUPPORTED;
-  // at most about kScoresTargetWgs workgroups (eight per CU, one generation), with at least one task for each of their four wavefronts
-  const int sums = kSingleHalf / a.chunk, least = sums == 16 ? 1 : 2;
+  // at most about kScoresTargetWgs workgroups (eight per CU, one generation), with at least one task for each of their four
+  // wavefronts; with 256 rows at least two periods, as 32 ranges of them are 64 KB of statistics for a period's 20 (32 calls
+  // on 20011 tokens, 16 of them scored, c = 5: 927 us, with one period 968)
+  const bool wide = a.rows_pad == 256;
+  const int sums = kSingleHalf / a.chunk, least = sums == 16 && !wide ? 1 : 2;
   int64_t ppw = (periods * a.n_kv_heads * n_leaders_slice + kScoresTargetWgs - 1) / kScoresTargetWgs;
   ppw = ppw < least ? least : (ppw > kScoresMaxPeriods ? kScoresMaxPeriods : ppw);
   dim3 grid((max_periods + (int)ppw - 1) / (int)ppw, batch_slice * a.n_kv_heads, n_leaders_slice);
-  const bool wide = a.rows_pad == 256;
   switch (sums) {
     case 4: hipLaunchKernelGGL((wide ? single_scores_kernel<4, 4> : single_scores_kernel<4, 2>), grid, dim3(256), 0, s, a, (int)ppw); break;
     case 8: hipLaunchKernelGGL((wide ? single_scores_kernel<8, 4> : single_scores_kernel<8, 2>), grid, dim3(256), 0, s, a, (int)ppw); break;

@@ -507,13 +507,15 @@ __global__ __launch_bounds__(kThreads, 2) void score_single_kernel(ScoreArgs a) 
     }
   }
 
-  // the range's log2 sum of every row for the merge (the lane halves share the reference)
+  // the range's sum of every row for the merge (the lane halves share the reference): relative to the reference of its last
+  // period, which is in the workspace already, and in the last range to one of its own, which the window keys may have moved
   if (active) {
 #pragma unroll
     for (int qi = 0; qi < NQ; ++qi) {
       const int row = row0 + (wave * NQ + qi) * 32 + n;
       const float l = l_run[qi] + __shfl_xor(l_run[qi], 32);
-      if (half == 0) a.row_stats[(problem * a.max_split + split) * a.rows_pad + row] = m_run[qi] + __builtin_log2f(l);
+      if (half == 0) a.row_stats[(problem * a.max_split + split) * a.rows_pad + row] = l;
+      if (half == 0 && u1 == np_total && row < nrows) a.refs[problem * nrows + row] = m_run[qi];
     }
   }
   __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));   // the empty loads past the last step still write zeros into the ring

@@ -63,6 +63,24 @@ def test_scores_match_float64(dtype, P, w, g, c):
         assert torch.equal(scores5[i, :, :want.shape[1]], scores[:, :want.shape[1]])
 
 
+# The row totals keep the bits of their ranges' sums: all prefix logits are X and scale * log2(e) is one, so the sums are whole
+# numbers, every score is 65 c / P, and the only rounding is that of X + log2(P) at 2^13.. (its last bit is 2^-10).  A rounding
+# per range on top of it takes all of these prefixes past the bound.
+@pytest.mark.parametrize("dtype", [ckv.BF16, ckv.F16])
+@pytest.mark.parametrize("P", [2561, 6400, 19200, 25600, 25000])
+def test_row_totals_are_rounded_once(P, dtype):
+    hkv, d, w, c, X = 2, 128, 65, 5, 8448.0
+    q, k = torch.zeros((hkv, w, d), dtype=KIND[dtype], device=DEV), torch.zeros((hkv, P + w, d), dtype=KIND[dtype], device=DEV)
+    q[..., 3], k[:, :P, 3] = 1.0, X
+    prob = ckv.Problem(hkv, hkv, d, w, c, dtype, [P + w], [0], [0], (P + w) * d, d, softmax_scale=0.6931472)
+    ws = torch.full((ckv.chunkkv_workspace_bytes(prob),), 0xFF, dtype=torch.uint8, device=DEV)
+    scores = torch.full((hkv, prob.score_cap), float("nan"), device=DEV)
+    ckv.chunkkv_score(prob, q, k, scores, None, ws)
+    got = scores[:, :P // c].cpu().double()
+    # half of the last bit, as a weight; the sum of 65 weights and the hardware's log2 and exp2 are 1e-5 of that at most
+    assert float((got / (w * c / P) - 1).abs().max()) < (2.0 ** 2.0 ** -11 - 1) * 1.03
+
+
 # Two passes, where pass 1 merges the row statistics of the ranges itself: one range, a whole number of loads of eight ranges
 # and one more, 63 ranges (the most), a batch whose sequences have different numbers of them, and the last and first sizes
 # on either side of the line from which a kernel merges them.
