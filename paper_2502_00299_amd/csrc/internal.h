@@ -15,8 +15,6 @@ namespace ckv {
 constexpr int kMaxLayersPerLaunch = 32;  // pointer tables travel as kernel arguments
 constexpr int kTileBytes = 16384;        // one K tile staged in LDS (ring slot)
 constexpr int kSuperKeys = 256;        // most keys per importance / chunk-sum step of pass 1 (several tiles)
-// keys of such a super-tile of at most `keys`: whole chunks
-__host__ __device__ inline int super_stride(int keys, int chunk) { return (chunk <= keys ? keys / chunk : kSuperKeys / chunk) * chunk; }
 constexpr int kThreads = 256;            // 4 wavefronts of 64
 constexpr int kMaxRows = 512;            // g * w limit
 constexpr int kCompactEntries = 64;      // most selection entries per compaction workgroup
@@ -55,7 +53,7 @@ struct ScoreArgs {
   const float *lse[kMaxLayersPerLaunch];  // pass 1 with use_lse: per leader layer [batch_total][Hq][w], natural log
   int32_t use_lse;
   int32_t stats_tiles;     // pass 1: > 0 = merge the pairs of pass 0 here; key tiles of one of its ranges
-  int32_t super_keys;      // pass 1: super-tiles of at most this many keys
+  int32_t super_keys;      // pass 1: super-tiles of at most this many keys, or of one chunk
   int32_t fuse_chunks;     // pass 1: 1 = super-tiles hold whole chunks and chunk sums are written
   // single-pass path (score_single.h): key ranges are single_periods_per_range() whole periods of 160 keys
   int32_t n_periods;       // pitch of e_buf / m_period: max over sequences of ceil(L / 160)

@@ -21,4 +21,8 @@ CKV_HOST_DEVICE RingRows ring_rows(int first, int prefix, uint32_t pitch, uint32
   return {present ? (uint32_t)(prefix - 1) * pitch + row_bytes : 0u, present ? (uint32_t)first * pitch : 0u};
 }
 
+// Keys of a super-tile (importance pass) of at most `keys`: whole chunks, one where none fits.  Smaller `keys` never make it
+// larger.
+CKV_HOST_DEVICE int super_stride(int keys, int chunk) { return chunk <= keys ? keys / chunk * chunk : chunk; }
+
 }  // namespace ckv

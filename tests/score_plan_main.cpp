@@ -1,4 +1,5 @@
-// Walks the ring loads of the single-pass scoring kernel: reads "prefix pitch row_bytes" lines from stdin and, for every
+// With "stride": reads "keys chunk" lines and prints the keys of a super-tile.  Otherwise:
+// walks the ring loads of the single-pass scoring kernel: reads "prefix pitch row_bytes" lines from stdin and, for every
 // period of the sequence and the ones behind it, those with prefix keys present and not, checks what the descriptor of that period lets
 // through (a lane offset below its records less the scalar offset) against the prefix's rows.  One "ok" or the first fault per line.
 #include <cstdio>
@@ -22,7 +23,9 @@ static const char *walk(int prefix, uint32_t pitch, uint32_t row_bytes) {
   return "ok";
 }
 
-int main() {
+int main(int argc, char **) {
+  int keys, chunk;
+  while (argc > 1 && std::scanf("%d %d", &keys, &chunk) == 2) std::printf("%d\n", ckv::super_stride(keys, chunk));
   int prefix;
   unsigned pitch, row_bytes;
   while (std::scanf("%d %u %u", &prefix, &pitch, &row_bytes) == 3) std::printf("%s\n", walk(prefix, pitch, row_bytes));
