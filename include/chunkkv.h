@@ -278,7 +278,8 @@ int chunkkv_decode_attention_static(const chunkkv_problem *prob, int32_t compact
  * milliseconds and the number of launches:
  *   0 score pass 0 (softmax statistics) or the single-pass kernel   1 statistics merge
  *   2 score pass 1 (importance, chunk sums) or the single-pass row reduction
- *   3 chunk sums for c larger than a key tile   4 chunk selection   5 compaction   6 decode attention
+ *   3 chunk sums for c larger than a key tile   4 chunk selection   5 compaction, or selection and
+ *     compaction where one kernel does both (short launches; then none under 4)   6 decode attention
  * total_ms and launches are host arrays of CHUNKKV_TIMING_KINDS entries.  Process-wide and not thread-safe:
  * one measurement at a time, no compression calls from other threads meanwhile.  It changes no result.   */
 #define CHUNKKV_TIMING_KINDS 7

@@ -310,7 +310,7 @@ int run_score(const chunkkv_problem *p, const Plan &pl, const void *const *q, co
       a.row_groups = pl.rows_pad_s == 256 && (int64_t)splits * nb * p->n_kv_heads * ng <= kRowSplitWorkgroups ? 2 : 1;
       { Timed t(kStats, s); rc = launch_score_single(p->dtype, a, dim3(splits, nb * p->n_kv_heads, ng * a.row_groups), s); }
       if (rc) return rc;
-      { Timed t(kColsum, s); rc = launch_single_scores(a, ng, nb, s); }
+      if (units1 > 0) { Timed t(kColsum, s); rc = launch_single_scores(a, ng, nb, s); }
       if (rc) return rc;
       continue;
     }
@@ -325,6 +325,7 @@ int run_score(const chunkkv_problem *p, const Plan &pl, const void *const *q, co
         if (rc) return rc;
       }
     }
+    if (units1 == 0) continue;   // no prefix: nothing to sum
     a.tiles_per_wg = tpw1;
     { Timed t(kColsum, s); rc = launch_score_pass(1, p->dtype, p->head_dim, pl.geom, a, dim3(split1, nb * p->n_kv_heads, ng), s); }
     if (rc) return rc;
@@ -356,48 +357,63 @@ int run_topk(const chunkkv_problem *p, const int32_t *chunks, const float *chunk
   return CHUNKKV_OK;
 }
 
-// chunks[i]: chunk size of the i-th reuse group from that of layer l_begin on.  With chunk_scores (and a single launch's
-// worth of layers and sequences): selects and gathers in one launch if that suits the problem, otherwise does nothing;
-// *selected says which.
+// Arguments of a gather: layers [l0, l0 + nl) and sequences [b0, b0 + nb), of the pointers' first layer on.  chunks[i]: chunk
+// size of the i-th reuse group from that of layer l_begin on.
+void fill_compact(CompactArgs *a, const chunkkv_problem *p, const int32_t *chunks, int l_begin, int l0, int nl, int b0, int nb, int reuse,
+                  const void *const *k, const void *const *v, void *const *k_out, void *const *v_out, const int32_t *sel_chunk,
+                  const int32_t *sel_len, const int32_t *sel_count, const int32_t *sel_off) {
+  memset(a, 0, sizeof(*a));
+  for (int i = 0; i < nl; ++i) {
+    a->k[i] = k[l0 + i]; a->v[i] = v[l0 + i]; a->k_out[i] = k_out[l0 + i]; a->v_out[i] = v_out[l0 + i];
+    a->chunk_of[i] = chunks[(l0 + i) / reuse - l_begin / reuse];
+  }
+  fill_seq(&a->seq, p, b0, nb);
+  a->layer0 = l0; a->reuse = reuse; a->batch0 = b0; a->batch_total = p->batch;
+  a->n_kv_heads = p->n_kv_heads; a->window = p->window; a->elem_bytes = elem_bytes(p->dtype);
+  a->kv_stride_head = p->kv_stride_head; a->kv_stride_tok = p->kv_stride_tok;
+  a->out_stride_head = p->out_stride_head; a->out_stride_tok = p->out_stride_tok;
+  a->sel_chunk = sel_chunk; a->sel_len = sel_len; a->sel_count = sel_count; a->sel_off = sel_off;
+  a->sel_cap = p->sel_cap;
+  a->whole_chunks = (p->flags & CHUNKKV_FLAG_WHOLE_CHUNKS) ? 1 : 0;
+}
+
 int run_compact(const chunkkv_problem *p, const int32_t *chunks, int l_begin, int n_layers, int reuse, const void *const *k, const void *const *v,
                 void *const *k_out, void *const *v_out, const int32_t *sel_chunk, const int32_t *sel_len,
-                const int32_t *sel_count, const int32_t *sel_off, hipStream_t s, const float *chunk_scores = nullptr, bool *selected = nullptr) {
-  const int esz = elem_bytes(p->dtype);
+                const int32_t *sel_count, const int32_t *sel_off, hipStream_t s) {
+  const int row_bytes = p->head_dim * elem_bytes(p->dtype);
   for (int l0 = l_begin; l0 < n_layers; l0 += kMaxLayersPerLaunch) {
     const int nl = n_layers - l0 < kMaxLayersPerLaunch ? n_layers - l0 : kMaxLayersPerLaunch;
     for (int b0 = 0; b0 < p->batch; b0 += kMaxBatchPerLaunch) {
       const int nb = p->batch - b0 < kMaxBatchPerLaunch ? p->batch - b0 : kMaxBatchPerLaunch;
       CompactArgs a;
-      memset(&a, 0, sizeof(a));
-      for (int i = 0; i < nl; ++i) {
-        a.k[i] = k[l0 + i]; a.v[i] = v[l0 + i]; a.k_out[i] = k_out[l0 + i]; a.v_out[i] = v_out[l0 + i];
-      }
-      fill_seq(&a.seq, p, b0, nb);
-      a.layer0 = l0; a.reuse = reuse; a.batch0 = b0; a.batch_total = p->batch;
-      for (int i = 0; i < nl; ++i) a.chunk_of[i] = chunks[(l0 + i) / reuse - l_begin / reuse];
-      a.n_kv_heads = p->n_kv_heads; a.window = p->window; a.elem_bytes = esz;
-      a.kv_stride_head = p->kv_stride_head; a.kv_stride_tok = p->kv_stride_tok;
-      a.out_stride_head = p->out_stride_head; a.out_stride_tok = p->out_stride_tok;
-      a.sel_chunk = sel_chunk; a.sel_len = sel_len; a.sel_count = sel_count; a.sel_off = sel_off;
-      a.sel_cap = p->sel_cap;
-      a.whole_chunks = (p->flags & CHUNKKV_FLAG_WHOLE_CHUNKS) ? 1 : 0;
+      fill_compact(&a, p, chunks, l_begin, l0, nl, b0, nb, reuse, k, v, k_out, v_out, sel_chunk, sel_len, sel_count, sel_off);
       int rc;
-      { Timed t(kCompact, s); rc = launch_compact(p->head_dim * esz, a, nl, nb, chunk_scores, p->score_cap, selected, s); }
+      { Timed t(kCompact, s); rc = launch_compact(row_bytes, a, nl, nb, s); }
       if (rc) return rc;
     }
   }
   return CHUNKKV_OK;
 }
 
-// Selection of the reuse groups from that of layer l_begin on and gather of layers [l_begin, l_end) with it. 
+// Selection of the reuse groups from that of layer l_begin on and gather of layers [l_begin, l_end) with it: in one launch
+// where one can carry them and that suits the problem.
 int run_selection(const chunkkv_problem *p, const int32_t *chunks, const float *chunk_scores, int group0, int n_groups, int l_begin, int l_end,
                   int reuse, const void *const *k, const void *const *v, void *const *k_out, void *const *v_out, int32_t *sel_chunk,
                   int32_t *sel_len, int32_t *sel_count, int32_t *sel_off, hipStream_t s) {
+  const int row_bytes = p->head_dim * elem_bytes(p->dtype), nl = l_end - l_begin;
   int rc;
-  if (l_end - l_begin <= kMaxLayersPerLaunch && p->batch <= kMaxBatchPerLaunch) {
-    bool selected = false;
-    rc = run_compact(p, chunks, l_begin, l_end, reuse, k, v, k_out, v_out, sel_chunk, sel_len, sel_count, nullptr, s, chunk_scores, &selected);
-    if (rc || selected) return rc;
+  if (nl <= kMaxLayersPerLaunch && p->batch <= kMaxBatchPerLaunch) {
+    CompactArgs a;
+    fill_compact(&a, p, chunks, l_begin, l_begin, nl, 0, p->batch, reuse, k, v, k_out, v_out, sel_chunk, sel_len, sel_count, sel_off);
+    const SelectInGather how = select_in_gather(a, nl, p->batch);
+    if (how.yes) {
+      Timed t(kCompact, s);
+      return launch_select_compact(row_bytes, a, nl, p->batch, chunk_scores, p->score_cap, how, s);
+    }
+    rc = run_topk(p, chunks, chunk_scores, group0, n_groups, sel_chunk, sel_len, sel_count, sel_off, s);
+    if (rc) return rc;
+    Timed t(kCompact, s);
+    return launch_compact(row_bytes, a, nl, p->batch, s);
   }
   rc = run_topk(p, chunks, chunk_scores, group0, n_groups, sel_chunk, sel_len, sel_count, sel_off, s);
   if (rc) return rc;

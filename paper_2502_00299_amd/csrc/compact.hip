@@ -184,60 +184,73 @@ __global__ __launch_bounds__(T) void select_compact_kernel(CompactArgs a, const 
   if (n > 0) copy_entries<NSEG, T>(a, layer, bl, h, c, ne, n < ne ? n : ne, s_src, s_dst, s_len);
 }
 
-// With chunk_scores: selects as well where that fits (see select_compact_kernel), and says so in *selected; where it does not
-// nothing is launched.
-int launch_compact(int row_bytes, CompactArgs &a, int n_layers_slice, int batch_slice, const float *chunk_scores, int score_cap,
-                   bool *selected, hipStream_t s) {
-  if (n_layers_slice <= 0 || batch_slice <= 0) return CHUNKKV_OK;
-  int64_t total = 0;   // workgroups with entries, of one kv-head per sequence
-  auto groups = [&](int rows) {   // most workgroups of a head
-    a.rows_per_wg = rows;
-    int most = 0;
-    total = 0;
-    for (int z = 0; z < n_layers_slice; ++z) {
-      const int c = a.chunk_of[z], ne = compact_entries(rows, c);
-      int entries = 0;
-      for (int i = 0; i < batch_slice; ++i) {
-        const int nk = a.seq.n_keep[i], n_win = (a.window + c - 1) / c;
-        int e = nk > 0 ? (nk + c - 1) / c + 1 : 0;
-        e = (e > a.sel_cap ? a.sel_cap : e) + n_win;
-        entries = e > entries ? e : entries;
-      }
-      const int n = (entries + ne - 1) / ne;
-      most = n > most ? n : most;
-      total += n;
+// Workgroups of a launch with `rows` rows each.
+struct GatherGroups {
+  int most;        // of a head
+  int64_t total;   // with entries, of all heads
+};
+static GatherGroups gather_groups(const CompactArgs &a, int n_layers_slice, int batch_slice, int rows) {
+  GatherGroups g = {0, 0};
+  for (int z = 0; z < n_layers_slice; ++z) {
+    const int c = a.chunk_of[z], ne = compact_entries(rows, c), n_win = (a.window + c - 1) / c;
+    int entries = 0;
+    for (int i = 0; i < batch_slice; ++i) {
+      const int nk = a.seq.n_keep[i];
+      int e = nk > 0 ? (nk + c - 1) / c + 1 : 0;
+      e = (e > a.sel_cap ? a.sel_cap : e) + n_win;
+      entries = e > entries ? e : entries;
     }
-    return most;
-  };
-  int nx = groups(160);
-  if (total * batch_slice * a.n_kv_heads < 4096) nx = groups(40);
-  if (nx <= 0) return CHUNKKV_OK;
-  dim3 grid(nx, batch_slice * a.n_kv_heads, n_layers_slice);
-  if (chunk_scores != nullptr) {
-    int most = 0;   // chunks of a head
-    for (int z = 0; z < n_layers_slice; ++z)
-      for (int i = 0; i < batch_slice; ++i) {
-        const int C = (a.seq.seqlen[i] - a.window + a.chunk_of[z] - 1) / a.chunk_of[z];
-        most = C > most ? C : most;
-      }
-    const int64_t heads = (int64_t)batch_slice * a.n_kv_heads;
-    const bool wide = most > kSelectCompactChunks;
-    if (wide) grid.x = groups(160);   // few workgroups, each wide and long
-    *selected = wide ? most <= kSelectCompactWideChunks && total * heads <= kSelectCompactWideWorkgroups : total * heads <= kSelectCompactWorkgroups;
-    if (!*selected) return CHUNKKV_OK;
-    const dim3 block(wide ? 1024 : kThreads);
-#define CKV_SELECT(NSEG) \
-  hipLaunchKernelGGL((wide ? select_compact_kernel<NSEG, 1024, 4> : most <= kThreads ? select_compact_kernel<NSEG, kThreads, 1> : select_compact_kernel<NSEG, kThreads, 4>), \
-                     grid, block, 0, s, a, chunk_scores, score_cap)
-    switch (row_bytes / 16) {
-      case 8: CKV_SELECT(8); break;
-      case 16: CKV_SELECT(16); break;
-      case 32: CKV_SELECT(32); break;
-      default: return CHUNKKV_ERR_UNSUPPORTED;
-    }
-#undef CKV_SELECT
-    return hipGetLastError() == hipSuccess ? CHUNKKV_OK : CHUNKKV_ERR_LAUNCH;
+    const int n = (entries + ne - 1) / ne;
+    g.most = n > g.most ? n : g.most;
+    g.total += (int64_t)n * batch_slice * a.n_kv_heads;
   }
+  return g;
+}
+// Sets the rows of a workgroup: fewer in a launch that would leave CUs without one.
+static GatherGroups choose_rows(CompactArgs &a, int n_layers_slice, int batch_slice) {
+  a.rows_per_wg = 160;
+  GatherGroups g = gather_groups(a, n_layers_slice, batch_slice, a.rows_per_wg);
+  if (g.total >= 4096) return g;
+  a.rows_per_wg = 40;
+  return gather_groups(a, n_layers_slice, batch_slice, a.rows_per_wg);
+}
+
+int launch_select_compact(int row_bytes, CompactArgs &a, int n_layers_slice, int batch_slice, const float *chunk_scores, int score_cap,
+                          const SelectInGather &how, hipStream_t s) {
+  a.rows_per_wg = how.rows_per_wg;
+  const dim3 grid(how.groups, batch_slice * a.n_kv_heads, n_layers_slice), block(how.wide ? 1024 : kThreads);
+#define CKV_SELECT(NSEG) \
+  hipLaunchKernelGGL((how.wide ? select_compact_kernel<NSEG, 1024, 4> : how.chunks <= kThreads ? select_compact_kernel<NSEG, kThreads, 1> : select_compact_kernel<NSEG, kThreads, 4>), \
+                     grid, block, 0, s, a, chunk_scores, score_cap)
+  switch (row_bytes / 16) {
+    case 8: CKV_SELECT(8); break;
+    case 16: CKV_SELECT(16); break;
+    case 32: CKV_SELECT(32); break;
+    default: return CHUNKKV_ERR_UNSUPPORTED;
+  }
+#undef CKV_SELECT
+  return hipGetLastError() == hipSuccess ? CHUNKKV_OK : CHUNKKV_ERR_LAUNCH;
+}
+
+SelectInGather select_in_gather(CompactArgs &a, int n_layers_slice, int batch_slice) {
+  SelectInGather how = {};
+  for (int z = 0; z < n_layers_slice; ++z)
+    for (int i = 0; i < batch_slice; ++i) {
+      const int C = (a.seq.seqlen[i] - a.window + a.chunk_of[z] - 1) / a.chunk_of[z];
+      how.chunks = C > how.chunks ? C : how.chunks;
+    }
+  if (how.chunks > kSelectCompactWideChunks) return how;
+  how.wide = how.chunks > kSelectCompactChunks;
+  GatherGroups g = choose_rows(a, n_layers_slice, batch_slice);
+  how.rows_per_wg = how.wide ? 160 : a.rows_per_wg;   // few workgroups, each wide and long
+  if (how.wide) g = gather_groups(a, n_layers_slice, batch_slice, how.rows_per_wg);
+  how.groups = g.most;
+  how.yes = g.total <= (how.wide ? kSelectCompactWideWorkgroups : kSelectCompactWorkgroups);
+  return how;
+}
+
+int launch_compact(int row_bytes, CompactArgs &a, int n_layers_slice, int batch_slice, hipStream_t s) {
+  const dim3 grid(choose_rows(a, n_layers_slice, batch_slice).most, batch_slice * a.n_kv_heads, n_layers_slice);
   switch (row_bytes / 16) {
     case 8: hipLaunchKernelGGL(compact_kernel<8>, grid, dim3(kThreads), 0, s, a); break;
     case 16: hipLaunchKernelGGL(compact_kernel<16>, grid, dim3(kThreads), 0, s, a); break;

@@ -213,7 +213,14 @@ int launch_decode(int dtype, int head_dim, bool matrix_cores, const DecodeArgs &
 int abs_sum_blocks(int n_tok_max);
 int launch_abs_sum(int dtype, const AbsSumArgs &a, int batch_slice, hipStream_t s);
 int launch_quality_finish(const QualityFinishArgs &a, int batch, hipStream_t s);
-int launch_compact(int row_bytes, CompactArgs &a, int n_layers_slice, int batch_slice, const float *chunk_scores, int score_cap,
-                   bool *selected, hipStream_t s);
+int launch_compact(int row_bytes, CompactArgs &a, int n_layers_slice, int batch_slice, hipStream_t s);
+// Does the gather select as well, and how: decided before anything is launched.
+struct SelectInGather {
+  bool yes, wide;    // wide: 1024 threads
+  int chunks, groups, rows_per_wg;   // chunks of the longest head, workgroups of a head
+};
+SelectInGather select_in_gather(CompactArgs &a, int n_layers_slice, int batch_slice);
+int launch_select_compact(int row_bytes, CompactArgs &a, int n_layers_slice, int batch_slice, const float *chunk_scores, int score_cap,
+                          const SelectInGather &how, hipStream_t s);
 
 }  // namespace ckv
