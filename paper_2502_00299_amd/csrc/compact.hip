@@ -17,11 +17,15 @@ namespace ckv {
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
-// Selection and gather in one launch, by chunks of the longest head and workgroups.  us of a call, together and apart: 62
-// chunks 22.0 / 24.3; 816 chunks, 176 workgroups 25.7 / 28.3; 28 layers of 216 chunks, 4000 workgroups 63 / 66; 16 of 816, 8400
-// workgroups 106 / 101.  More chunks take 1024 threads, and as long as every workgroup has a CU: 3990 chunks, 208 workgroups
-// 43.8 / 46.9; 3274 chunks, 2 layers, 400 workgroups 53 / 47.
-constexpr int kSelectCompactChunks = 1024, kSelectCompactWorkgroups = 4096;
+// Selection and gather in one launch, by chunks of the longest head and workgroups.  Every workgroup selects for itself, which
+// costs little as long as all of them run at once, or with one chunk per thread.  us of a call, together and apart:
+//   up to 256 chunks: 64, 1024 workgroups 24.2 / 27.9; 200, 2816 32.8 / 33.7; 256, 3584 34.8 / 36.6; 200, 5376 49.4 / 49.1
+//   up to 1024: 300, 1024 workgroups 20.4 / 21.7; 400, 1344 24.5 / 25.0; 1024, 1408 23.3 / 26.6; 300, 1536 25.8 / 25.7;
+//     800, 1968 33.2 / 30.7; 300, 2048 33.6 / 29.6; 512, 3456 43.6 / 39.7; 300, 4096 50.7 / 42.1
+//   more chunks take 1024 threads, and as long as every workgroup has a CU: 3000, 152 workgroups 30.5 / 32.7; 4000, 208
+//     35.8 / 38.5; 3000, 304 43.5 / 36.3
+constexpr int kSelectCompactFewChunks = kThreads, kSelectCompactFewWorkgroups = 4096;
+constexpr int kSelectCompactChunks = 1024, kSelectCompactWorkgroups = 1408;
 constexpr int kSelectCompactWideChunks = 4096, kSelectCompactWideWorkgroups = 256;
 
 // selection entries of a workgroup
@@ -220,7 +224,7 @@ int launch_select_compact(int row_bytes, CompactArgs &a, int n_layers_slice, int
   a.rows_per_wg = how.rows_per_wg;
   const dim3 grid(how.groups, batch_slice * a.n_kv_heads, n_layers_slice), block(how.wide ? 1024 : kThreads);
 #define CKV_SELECT(NSEG) \
-  hipLaunchKernelGGL((how.wide ? select_compact_kernel<NSEG, 1024, 4> : how.chunks <= kThreads ? select_compact_kernel<NSEG, kThreads, 1> : select_compact_kernel<NSEG, kThreads, 4>), \
+  hipLaunchKernelGGL((how.wide ? select_compact_kernel<NSEG, 1024, 4> : how.chunks <= kSelectCompactFewChunks ? select_compact_kernel<NSEG, kThreads, 1> : select_compact_kernel<NSEG, kThreads, 4>), \
                      grid, block, 0, s, a, chunk_scores, score_cap)
   switch (row_bytes / 16) {
     case 8: CKV_SELECT(8); break;
@@ -245,7 +249,7 @@ SelectInGather select_in_gather(CompactArgs &a, int n_layers_slice, int batch_sl
   how.rows_per_wg = how.wide ? 160 : a.rows_per_wg;   // few workgroups, each wide and long
   if (how.wide) g = gather_groups(a, n_layers_slice, batch_slice, how.rows_per_wg);
   how.groups = g.most;
-  how.yes = g.total <= (how.wide ? kSelectCompactWideWorkgroups : kSelectCompactWorkgroups);
+  how.yes = g.total <= (how.wide ? kSelectCompactWideWorkgroups : how.chunks > kSelectCompactFewChunks ? kSelectCompactWorkgroups : kSelectCompactFewWorkgroups);
   return how;
 }
 

@@ -13,6 +13,8 @@ DEV = "cuda:0"
 CASES = [
     ([255], 1, 30, 2, 1), ([256], 1, 100, 2, 3), ([257], 1, 50, 1, 2), ([1024 * 3 - 1], 3, 20, 2, 1), ([1024 * 3 + 1], 3, 20, 2, 1),
     ([4095 * 2 + 1], 2, 10, 2, 1), ([4097 * 2 - 1], 2, 10, 2, 2), ([4096], 1, 90, 4, 1),      # many workgroups of a wide head
+    ([1030], 4, 50, 4, 25), ([1030], 4, 50, 4, 26),      # 1400 and 1456 workgroups of 258 chunks
+    ([1024], 4, 50, 16, 18),      # 4032 of 256
     ([7, 500, 33], 33, 30, 2, 2), ([1000, 10, 2000], 10, 0, 1, 1), ([999], 500, 60, 1, 1), ([0, 640], 16, 25, 2, 1),
     ([3000], 10, 30, 32, 33),      # more layers than one launch carries
 ]

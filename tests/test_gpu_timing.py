@@ -13,6 +13,10 @@ CASES = [
     ((500, 10, 2, 64, False), {STATS: 1, COLSUM: 1, COMPACT: 1}),                      # selects while it gathers
     ((500, 10, 2, 64, True), {COLSUM: 1, COMPACT: 1}),
     ((5000, 1, 2, 64, False), {STATS: 1, COLSUM: 1, SELECT: 1, COMPACT: 1}),           # too many chunks for that
+    ((2560, 10, 32, 64, False), {STATS: 1, COLSUM: 1, COMPACT: 1}),                    # 256 chunks, one per thread: 1152 workgroups
+    ((2570, 10, 27, 64, False), {STATS: 1, COLSUM: 1, COMPACT: 1}),                    # four per thread: 972 workgroups, ...
+    ((10240, 10, 10, 64, False), {STATS: 1, COLSUM: 1, COMPACT: 1}),                   # ... 1320 ...
+    ((10240, 10, 11, 64, False), {STATS: 1, COLSUM: 1, SELECT: 1, COMPACT: 1}),        # ... and 1452, where selecting apart is faster
     ((500, 10, 40, 64, False), {STATS: 1, COLSUM: 1, SELECT: 1, COMPACT: 2}),          # two launches' worth of layers
     ((700, 300, 1, 64, False), {STATS: 1, COLSUM: 1, CHUNK_SUMS: 1, COMPACT: 1}),
     ((3000, 10, 1, 128, False), {STATS: 1, COLSUM: 1, COMPACT: 1}),                    # single pass
