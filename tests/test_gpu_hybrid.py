@@ -110,23 +110,27 @@ def test_uniform_table_equals_plain_stack_call(lib):
 
 
 # One launch per kernel for groups of different sizes, where it can carry them (32 groups, chunks of at most 256 tokens), one run
-# after the other where it cannot: each group comes out as in the uniform call with its chunk size.  With the caller's
-# log-sum-exps nothing in a score depends on how the launch is cut, so it does to the bit; 17 sequences take two launches.
-@pytest.mark.parametrize("table,reuse,batch,dtype", [
-    ([5, 256, 1, 20, 33], 2, 3, "bf16"), ([10, 3, 10, 7], 1, 17, "f16"), ([20, 300, 5], 1, 2, "f32"),
-    ([3, 10, 1] * 11, 1, 1, "bf16"),       # 33 groups
+# after the other where it cannot: each group comes out as in the uniform call with its chunk size, to the bit.  With the
+# caller's log-sum-exps nothing in a score depends on how the launch is cut; without them the key ranges are those of the
+# uniform call, which has as many layers.  There and with 128 rows of 128 16-bit values, 5, 10 and 20 take the single pass, a
+# launch per size.  17 sequences take two launches.
+@pytest.mark.parametrize("table,reuse,batch,dtype,d,w,given", [
+    ([5, 256, 1, 20, 33], 2, 3, "bf16", 64, 16, True), ([10, 3, 10, 7], 1, 17, "f16", 64, 16, True), ([20, 300, 5], 1, 2, "f32", 64, 16, True),
+    ([3, 10, 1] * 11, 1, 1, "bf16", 64, 16, True),       # 33 groups
+    ([20, 5, 3, 10, 20, 256, 5], 2, 3, "bf16", 128, 64, False), ([7, 10, 5, 10], 1, 17, "f16", 128, 64, False),
+    ([5, 300, 10], 1, 2, "bf16", 128, 64, False), ([5, 20, 10], 1, 2, "f16", 128, 64, False), ([4, 20, 1], 1, 2, "f32", 128, 64, False),
 ])
-def test_groups_of_different_sizes_equal_uniform_calls(lib, table, reuse, batch, dtype):
+def test_groups_of_different_sizes_equal_uniform_calls(lib, table, reuse, batch, dtype, d, w, given):
     gen = torch.Generator(device=DEV).manual_seed(len(table))
     kind, dt = {"bf16": (torch.bfloat16, lib.BF16), "f16": (torch.float16, lib.F16), "f32": (torch.float32, lib.F32)}[dtype]
-    hq, hkv, d, w, lens = 4, 2, 64, 16, [700 + 37 * i for i in range(batch)]
+    hq, hkv, lens = 4, 2, [700 + 37 * i for i in range(batch)]
     n = len(table) * reuse
     total = sum(lens) * hkv * d
     base = [sum(lens[:i]) * hkv * d for i in range(batch)]
     k = [torch.randn(total, generator=gen, device=DEV).to(kind) for _ in range(n)]
     v = [torch.randn(total, generator=gen, device=DEV).to(kind) for _ in range(n)]
     q = [torch.randn((batch, hq, w, d), generator=gen, device=DEV).to(kind) for _ in range(n)]
-    lse = [torch.rand((batch, hq, w), generator=gen, device=DEV) + 6 for _ in range(n)]
+    lse = [torch.rand((batch, hq, w), generator=gen, device=DEV) + 6 for _ in range(n)] if given else None
     keep = [(m - w) // 5 for m in lens]
 
     def call(chunk):
@@ -141,7 +145,10 @@ def test_groups_of_different_sizes_equal_uniform_calls(lib, table, reuse, batch,
         vo = [torch.zeros_like(ko[0]) for _ in range(n)]
         if isinstance(chunk, int):
             ws = torch.empty(lib.chunkkv_workspace_bytes(prob, n, reuse), dtype=torch.uint8, device=DEV)
-            lib.chunkkv_compress_stack_lse(prob, reuse, q, k, v, lse, ko, vo, *sel, cnt, ws)
+            if given:
+                lib.chunkkv_compress_stack_lse(prob, reuse, q, k, v, lse, ko, vo, *sel, cnt, ws)
+            else:
+                lib.chunkkv_compress_stack(prob, reuse, q, k, v, ko, vo, *sel, cnt, ws)
         else:
             ws = torch.empty(lib.chunkkv_workspace_bytes_hybrid(prob, n, reuse, chunk), dtype=torch.uint8, device=DEV)
             lib.chunkkv_compress_stack_hybrid(prob, reuse, chunk, q, k, v, lse, ko, vo, *sel, cnt, ws)

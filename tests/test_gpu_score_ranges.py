@@ -1,6 +1,6 @@
 """Single-pass scoring where its kernel can go wrong: the ragged last period, a range that holds window keys alone, the
-largest window, workgroups that share the rows of a range, wavefronts without rows, and every compiled chunk size; scores
-against plain float64."""
+largest window, workgroups that share the rows of a range and ones that hold 256 of them, wavefronts without rows, and every
+compiled chunk size; scores against plain float64."""
 import math
 
 import pytest
@@ -28,6 +28,7 @@ def oracle_scores(q, k, w, c):
 
 # (prefix tokens, window, query heads per kv-head, chunk size): periods are 160 keys, ranges four of them or more
 CASES = [
+    (1, 64, 4, 20), (100, 64, 4, 10),        # 256 rows: a ragged first period
     (1, 32, 4, 5), (159, 32, 4, 10), (160, 32, 4, 20), (161, 64, 4, 5),
     (640, 96, 2, 10),        # four whole periods, then a range that holds window keys alone
     (639, 32, 7, 5), (641, 32, 7, 10), (2000, 32, 7, 20),   # 224 rows: the last wavefront of the second row group has none
@@ -53,14 +54,15 @@ def test_scores_match_float64(dtype, P, w, g, c):
     got = scores.cpu().double()[:, :want.shape[1]]
     # sums are stored with 12 mantissa bits, 2^-13 each, which up to 256 rows average out; fp32 around that is 1e-6
     assert float(((got - want).abs() / want).max()) < 1.3e-4
-    # a few layers in one launch (no shared rows) give the same scores as one alone
-    n = 5
-    many = ckv.Problem(hkv * g, hkv, d, w, c, dtype, [L] * n, [0] * n, [i * hkv * L * d for i in range(n)], L * d, d)
+    # the same head over and over, until the launch is too large for workgroups to share rows: the same scores
+    ranges = -(-(-(-L // 160)) // 4)      # of four periods: no case is long enough for longer ones
+    n = 128 // (ranges * hkv) + 1 if g * w > 128 else 5
+    assert ranges <= 32 and (g * w <= 128 or ranges * hkv <= 128 < ranges * hkv * n)
+    many = ckv.Problem(n * hkv * g, n * hkv, d, w, c, dtype, [L], [0], [0], L * d, d)
     ws = torch.full((ckv.chunkkv_workspace_bytes(many),), 0xFF, dtype=torch.uint8, device=DEV)
-    scores5 = torch.full((n, hkv, many.score_cap), float("nan"), device=DEV)
-    ckv.chunkkv_score(many, q.to(DEV).expand(n, -1, -1, -1).contiguous(), k.to(DEV).expand(n, -1, -1, -1).contiguous(), scores5, None, ws)
-    for i in range(n):
-        assert torch.equal(scores5[i, :, :want.shape[1]], scores[:, :want.shape[1]])
+    more = torch.full((n * hkv, many.score_cap), float("nan"), device=DEV)
+    ckv.chunkkv_score(many, q.to(DEV).repeat(n, 1, 1), k.to(DEV).repeat(n, 1, 1), more, None, ws)
+    assert torch.equal(more[:, :want.shape[1]], scores[:, :want.shape[1]].repeat(n, 1))
 
 
 # The row totals keep the bits of their ranges' sums: all prefix logits are X and scale * log2(e) is one, so the sums are whole
@@ -82,11 +84,12 @@ def test_row_totals_are_rounded_once(P, dtype):
 
 
 # Two passes, where pass 1 merges the row statistics of the ranges itself: one range, a whole number of loads of eight ranges
-# and one more, 63 ranges (the most), a batch whose sequences have different numbers of them, and the last and first sizes
+# and one more, 63 and 64 ranges (the most), a batch whose sequences have different numbers of them, and the last and first sizes
 # on either side of the line from which a kernel merges them.
 TWO_PASS = [
     (ckv.F32, 64, [40], 2, 2, 16, 3), (ckv.F32, 64, [8 * 64, 33], 2, 2, 16, 1), (ckv.BF16, 128, [9 * 64, 640, 65], 2, 4, 16, 8),
-    (ckv.F16, 64, [64 * 128 + 1, 500], 1, 4, 32, 16), (ckv.F32, 128, [16000], 4, 1, 16, 33), (ckv.BF16, 128, [20011], 1, 8, 32, 300),
+    (ckv.F16, 64, [64 * 128 + 1, 500], 1, 4, 32, 16), (ckv.F32, 128, [16000], 4, 1, 16, 33), (ckv.F32, 128, [16384], 4, 1, 16, 33),
+    (ckv.BF16, 128, [20011], 1, 8, 32, 300),
     (ckv.BF16, 128, [131072], 8, 1, 16, 10), (ckv.BF16, 128, [131073], 8, 1, 16, 10),
 ]
 
