@@ -1,4 +1,4 @@
-// Host side of libchunkkv: argument checks, workspace plan and launch sequence of the four C-ABI calls.
+// Host side of libchunkkv: argument checks, workspace plans and launch sequences of the C-ABI calls.
 #include <math.h>
 #include <string.h>
 
@@ -16,22 +16,23 @@ constexpr int kTargetWorkgroups = 4096;  // ~4 resident rounds of 2 workgroups o
 // 16000 tokens 34.3 -> 28.9 us a call, 19000 with 64 rows 66 -> 42, 120602 in fp32 288 -> 234.  Above it that kernel is a
 // percent or two and merging everywhere more (10 layers of 109334 tokens, 224 rows 906 us, 947 merged).
 constexpr int64_t kMergeTiles = 16384, kMergeWorkgroups = 1536;
-// So there are at most kMaxRanges ranges, and kGoodRanges as long as that asks for no more than kRangeTiles tiles in a row
-// and leaves no CU without a workgroup: 120602 tokens, 4 heads, fp32 in 32 / 63 / 236 ranges 147 / 81 / 90 us.
+// So there are at most kMaxRanges ranges, and kGoodRanges as long as those have no more tiles in a row than kRangeTiles or than
+// there are for each CU, whichever is more: 120602 tokens, 4 heads, fp32 in 32 / 63 / 236 ranges 147 / 81 / 90 us.  (Short
+// launches leave CUs without a workgroup for it: 16000 tokens and 4 heads are 128 of four tiles.)
 constexpr int kGoodRanges = 32, kMaxRanges = 64, kRangeTiles = 8;
 // Single-pass scoring with 256 rows: up to this many workgroups leave half the CUs empty, so two of them, with 128 rows each,
 // share a key range; K is read twice.  us of a call on one layer, split / not: 104 workgroups 26.9 / 30.0, 128 of them at 65536
 // tokens 59.6 / 69.8; 200 36.1 / 35.9, 256 at 20011 tokens 42.6 / 41.8, 256 at 131072 155 / 140.
 constexpr int64_t kRowSplitWorkgroups = 128;
 constexpr int kSinglePeriodKeys = 160;   // granule of the single-pass kernel's key ranges
-// Key tiles (16 KB) one scoring launch set should hold.  Measured on MI355X: every extra dependent launch
-// costs ~30 us of idle GPU, more than splitting the stack into sets wins back, so one set it is.
+// Key tiles (16 KB) one scoring launch set should hold.  Sets would let the gather of one run beside the scoring of the next on a
+// second stream, which takes longer (the 131072-token stack 2.17 ms in one set, 2.23 in two, 2.45 in eight), so one set it is.
 constexpr int64_t kTilesPerLaunch = 1 << 30;
 
 struct Plan {
   ScoreGeom geom;
   int n_leaders, rows_pad;
-  int batch_leaders;  // leader layers scored per launch set (the unit that overlaps with compaction)
+  int batch_leaders;  // leader layers scored per launch set
   int tpw0, max_split0;
   int merge0;         // two-pass scoring: pass 1 merges the row statistics itself
   int fuse_chunks;
@@ -157,8 +158,7 @@ int make_plan(const chunkkv_problem *p, int n_layers, int reuse, Plan *pl) {
   for (int b = 0; b < p->batch; ++b) {
     tiles0 += ceil_div(p->seqlen[b], TK);
   }
-  // leader layers per launch set: enough key tiles (~kTilesPerLaunch) to amortise workgroup start-up,
-  // few enough that compaction of one set overlaps scoring of the next; sets are balanced in size
+  // leader layers per launch set: about kTilesPerLaunch key tiles and what the pointer tables hold; sets are balanced in size
   int64_t per_leader = tiles0 * p->n_kv_heads;
   int gb = (int)((kTilesPerLaunch + per_leader - 1) / (per_leader > 0 ? per_leader : 1));
   if (gb < 1) gb = 1;
@@ -581,7 +581,7 @@ static int stack_entry(const chunkkv_problem *prob, int32_t n_layers, int32_t re
 // A stack whose groups' chunk sizes differ, each kernel launched over all groups it can take at once: the single-pass
 // kernels once per chunk size they are compiled for, pass 0 and pass 1 once for all other groups, selection and gather once
 // for all.  One run of groups after the other is a chain of four or five launches that do not fill the chip, per run: eight
-// sizes over 16 layers of 12345 tokens 355 us, together 212.  `pl` is the plan of the chunk size that needs the most
+// sizes over 16 layers of 12345 tokens 355 us, together with the same kernels 212.  `pl` is the plan of the chunk size that needs the most
 // workspace; the others fit its regions.
 static int stack_mixed(const chunkkv_problem *prob, const Plan &pl, int32_t n_layers, int32_t reuse, const int32_t *chunks,
                        const void *const *q_obs, const void *const *k, const void *const *v, const float *const *lse,
