@@ -267,7 +267,8 @@ int run_score(const chunkkv_problem *p, const Plan &pl, const void *const *q, co
     a.token_imp = token_imp; a.imp_pitch = imp_pitch;
     a.fuse_chunks = pl.fuse_chunks;
     if (!pl.fuse_chunks && !token_imp) { a.token_imp = (float *)(ws + pl.off_imp); a.imp_pitch = (int64_t)p->score_cap * p->chunk; }
-    int split0 = 1, split1 = 0;
+    int split1 = 0, ranges0 = 0;
+    for (int i = 1; i < kMaxBatchPerLaunch; ++i) a.first_range[i] = INT32_MAX;
     // Super-tiles: smaller ones where a launch would leave CUs without a workgroup (512 tokens in fp32, 4 workgroups 12 us,
     // 16 of them 8); the sums of a chunk are the same bits whatever super-tile it lies in.
     a.super_keys = kSuperKeys;
@@ -281,8 +282,8 @@ int run_score(const chunkkv_problem *p, const Plan &pl, const void *const *q, co
     }
     const int tpw1 = pass1_tiles_per_wg(units1 * p->n_kv_heads, pl.merge0);
     for (int i = 0; i < nb; ++i) {
-      const int s0 = ceil_div(ceil_div(a.seq.seqlen[i], TK), pl.tpw0);
-      split0 = s0 > split0 ? s0 : split0;
+      ranges0 += ceil_div(ceil_div(a.seq.seqlen[i], TK), pl.tpw0);
+      if (i + 1 < nb) a.first_range[i + 1] = ranges0;
       for (int z = 0; z < ng; ++z) {
         const int s1 = ceil_div(super_tiles(i, z), tpw1);
         split1 = s1 > split1 ? s1 : split1;
@@ -316,7 +317,7 @@ int run_score(const chunkkv_problem *p, const Plan &pl, const void *const *q, co
     }
     if (!lse) {
       a.tiles_per_wg = pl.tpw0;
-      { Timed t(kStats, s); rc = launch_score_pass(0, p->dtype, p->head_dim, pl.geom, a, dim3(split0, nb * p->n_kv_heads, ng), s); }
+      { Timed t(kStats, s); rc = launch_score_pass(0, p->dtype, p->head_dim, pl.geom, a, dim3(ranges0, p->n_kv_heads, ng), s); }
       if (rc) return rc;
       if (pl.merge0) {
         a.stats_tiles = pl.tpw0;

@@ -41,6 +41,11 @@ struct ScoreArgs {
   int64_t kv_stride_head, kv_stride_tok;
   float scale_log2e;       // softmax scale * log2(e)
   int32_t tiles_per_wg;    // pass 0: key tiles, pass 1: super-tiles each workgroup walks
+  // Pass 0: number of the first key range of every sequence (INT32_MAX past the last one).  Its grid has no empty workgroups:
+  // they go to the XCDs, and there to the shader engines, in turn, and with a row of the grid as long as the longest sequence
+  // has ranges some CUs got two of them and others none.  us of a call, then and now: five sequences of 3246 to 14215 tokens in
+  // fp32 191 / 159 (one range of two tiles each, 2564 of them: 183); six of 1000 to 40000 with 224 rows 84 / 60.
+  int32_t first_range[kMaxBatchPerLaunch];
   int32_t max_split;       // pitch of part_stats in splits
   int32_t rows_pad;        // g*w rounded up to 32
   float2 *part_stats;      // [problem][max_split][rows_pad]  (running max, sum) in log2 units

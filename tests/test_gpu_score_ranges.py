@@ -90,6 +90,7 @@ TWO_PASS = [
     (ckv.F32, 64, [40], 2, 2, 16, 3), (ckv.F32, 64, [8 * 64, 33], 2, 2, 16, 1), (ckv.BF16, 128, [9 * 64, 640, 65], 2, 4, 16, 8),
     (ckv.F16, 64, [64 * 128 + 1, 500], 1, 4, 32, 16), (ckv.F32, 128, [16000], 4, 1, 16, 33), (ckv.F32, 128, [16384], 4, 1, 16, 33),
     (ckv.BF16, 128, [20011], 1, 8, 32, 300),
+    (ckv.F16, 64, [33 + 97 * (i * 7 % 17) for i in range(17)], 2, 4, 32, 7),     # two launches of up to 16 sequences
     (ckv.BF16, 128, [131072], 8, 1, 16, 10), (ckv.BF16, 128, [131073], 8, 1, 16, 10),
 ]
 
