@@ -302,14 +302,14 @@ int run_score(const chunkkv_problem *p, const Plan &pl, const void *const *q, co
       a.row_stats = (float *)(ws + pl.off_part);
       a.max_split = pl.max_split_s;
       a.rows_pad = pl.rows_pad_s;
-      int splits = 1;
+      int ranges = 0;
       for (int i = 0; i < nb; ++i) {
         const int np = ceil_div(a.seq.seqlen[i], kSinglePeriodKeys);
-        const int sp = ceil_div(np, single_periods_per_range(np));
-        splits = sp > splits ? sp : splits;
+        a.first_range[i] = ranges;
+        ranges += ceil_div(np, single_periods_per_range(np));
       }
-      a.row_groups = pl.rows_pad_s == 256 && (int64_t)splits * nb * p->n_kv_heads * ng <= kRowSplitWorkgroups ? 2 : 1;
-      { Timed t(kStats, s); rc = launch_score_single(p->dtype, a, dim3(splits, nb * p->n_kv_heads, ng * a.row_groups), s); }
+      a.row_groups = pl.rows_pad_s == 256 && (int64_t)ranges * p->n_kv_heads * ng <= kRowSplitWorkgroups ? 2 : 1;
+      { Timed t(kStats, s); rc = launch_score_single(p->dtype, a, dim3(ranges, p->n_kv_heads, ng * a.row_groups), s); }
       if (rc) return rc;
       if (units1 > 0) { Timed t(kColsum, s); rc = launch_single_scores(a, ng, nb, s); }
       if (rc) return rc;

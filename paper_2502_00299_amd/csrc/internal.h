@@ -41,10 +41,12 @@ struct ScoreArgs {
   int64_t kv_stride_head, kv_stride_tok;
   float scale_log2e;       // softmax scale * log2(e)
   int32_t tiles_per_wg;    // pass 0: key tiles, pass 1: super-tiles each workgroup walks
-  // Pass 0: number of the first key range of every sequence (INT32_MAX past the last one).  Its grid has no empty workgroups:
-  // they go to the XCDs, and there to the shader engines, in turn, and with a row of the grid as long as the longest sequence
-  // has ranges some CUs got two of them and others none.  us of a call, then and now: five sequences of 3246 to 14215 tokens in
-  // fp32 191 / 159 (one range of two tiles each, 2564 of them: 183); six of 1000 to 40000 with 224 rows 84 / 60.
+  // Pass 0 and the single-pass kernels: number of the first key range (the reduction: group of periods) of every sequence,
+  // INT32_MAX past the last one.  The x of their grids counts those of all sequences, so there are no empty workgroups: these go to the
+  // XCDs, and there to the shader engines, in turn, and with a row of the grid as long as the longest sequence has ranges some
+  // CUs got two of them and others none.  us of a call, then and now: two passes, five sequences of 3246 to 14215 tokens in fp32
+  // 191 / 159, six of 1000 to 40000 with 224 rows 84 / 60; single pass, one of 20400
+  // and eleven of 300 116 / 40 (16 ranges for the long one instead of 32: 108), eight of up to 20300 at c = 20 61 / 49 (59).
   int32_t first_range[kMaxBatchPerLaunch];
   int32_t max_split;       // pitch of part_stats in splits
   int32_t rows_pad;        // g*w rounded up to 32
@@ -191,6 +193,16 @@ __device__ __forceinline__ float merge_row_stats(const float *sums, const float 
   return m + __builtin_log2f(l);
 }
 
+// Sequence of the x-th range (or group of periods) of a launch; x becomes its number within the sequence.
+__device__ __forceinline__ int find_sequence(const ScoreArgs &a, int &x) {
+  int seq = 0, first = 0;
+#pragma unroll
+  for (int i = 1; i < kMaxBatchPerLaunch; ++i)
+    if (x >= a.first_range[i]) { seq = i; first = a.first_range[i]; }
+  x -= first;
+  return seq;
+}
+
 // Geometry of the scoring kernels for one (dtype, head_dim, row count).
 struct ScoreGeom {
   int row_bytes;   // head_dim * sizeof(element)
@@ -210,7 +222,7 @@ int launch_chunk_sums(const ScoreArgs &a, int n_leaders_slice, int batch_slice, 
 int launch_score_single(int dtype, const ScoreArgs &a, dim3 grid, hipStream_t s);
 int launch_jaccard(const int32_t *sel_chunk, const int32_t *sel_len, const int32_t *sel_count, int sel_cap, int chunk,
                    int rows_per_group, int n_pairs, float *out, hipStream_t s);
-int launch_single_scores(const ScoreArgs &a, int n_leaders_slice, int batch_slice, hipStream_t s);
+int launch_single_scores(ScoreArgs &a, int n_leaders_slice, int batch_slice, hipStream_t s);
 bool single_pass_ok(int dtype, int head_dim, int rows, int chunk);
 int launch_topk(const TopkArgs &a, int n_groups, int batch_slice, hipStream_t s);
 int launch_decode_mfma(int dtype, int head_dim, const DecodeArgs &a, int batch_slice, hipStream_t s);

@@ -125,15 +125,7 @@ __global__ __launch_bounds__(kThreads, ((NQW >= 4 || (DT == CHUNKKV_F32 && HD ==
   const bool active = (4 / WQ == WK) ? true : (wk < WK);  // wavefronts beyond the key blocks only load
   const int z = blockIdx.z;
   int bl = blockIdx.y / a.n_kv_heads, h = blockIdx.y % a.n_kv_heads, split = blockIdx.x;
-  if constexpr (PASS == 0) {   // the grid's x counts the key ranges of all sequences, see first_range
-    int first = 0;
-    bl = 0;
-    h = blockIdx.y;
-#pragma unroll
-    for (int i = 1; i < kMaxBatchPerLaunch; ++i)
-      if ((int)blockIdx.x >= a.first_range[i]) { bl = i; first = a.first_range[i]; }
-    split -= first;
-  }
+  if constexpr (PASS == 0) { bl = find_sequence(a, split); h = blockIdx.y; }
   const int g = a.n_q_heads / a.n_kv_heads, w = a.window, c = PASS == 1 ? CKV_ARG(ScoreArgs, chunk_of, z) : 1;
   const int L = CKV_ARG(ScoreArgs, seq.seqlen, bl), P = L - w, nrows = g * w;
   const int64_t problem = ((int64_t)CKV_ARG(ScoreArgs, leader, z) * a.batch_total + (a.batch0 + bl)) * a.n_kv_heads + h;

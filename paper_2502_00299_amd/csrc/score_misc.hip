@@ -149,7 +149,7 @@ int launch_chunk_sums(const ScoreArgs &a, int n_leaders_slice, int batch_slice, 
 // 32 layers of 32768 tokens 93 -> 75 us, a ragged batch at c = 20 130 -> 90, one layer of 8192 tokens 8.8 -> 7.5 (16 layers
 // of 131072, at the memory's rate before and after: 222 -> 217).  Two groups of sums per task, which share the weights,
 // took 84 us on the first and 24 instead of 13 on one layer at c = 5; reads that are not streaming, 81.
-// grid: x = period group, y = (sequence, kv-head), z = leader.
+// grid: x = period group of any sequence, y = kv-head, z = leader.
 constexpr int kSinglePeriod = 160, kSingleHalf = 80;   // as in the single-pass scoring kernel
 constexpr int kScoresTargetWgs = 2048, kScoresMaxPeriods = 32;
 
@@ -178,13 +178,13 @@ __global__ __launch_bounds__(256) void single_scores_kernel(ScoreArgs a, int per
   typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wavefront-uniform, and known to be
-  const int bl = blockIdx.y / a.n_kv_heads, h = blockIdx.y % a.n_kv_heads, z = blockIdx.z;
+  int group = blockIdx.x;
+  const int bl = find_sequence(a, group), h = blockIdx.y, z = blockIdx.z;
   const int64_t problem = ((int64_t)CKV_ARG(ScoreArgs, leader, z) * a.batch_total + (a.batch0 + bl)) * a.n_kv_heads + h;
   const int L = CKV_ARG(ScoreArgs, seq.seqlen, bl), P = L - a.window, c = kSingleHalf / S;
   const int C = (P + c - 1) / c;
   const int np = (P + kSinglePeriod - 1) / kSinglePeriod;   // periods that hold prefix keys
-  const int p0 = blockIdx.x * periods_per_wg;
-  if (p0 >= np) return;
+  const int p0 = group * periods_per_wg;
   const int p1 = p0 + periods_per_wg < np ? p0 + periods_per_wg : np;
   const int nrows = (a.n_q_heads / a.n_kv_heads) * a.window;
   __shared__ float s_ref[256];
@@ -270,16 +270,11 @@ __global__ __launch_bounds__(256) void single_scores_kernel(ScoreArgs a, int per
   }
 }
 
-int launch_single_scores(const ScoreArgs &a, int n_leaders_slice, int batch_slice, hipStream_t s) {
-  int max_periods = 0;
+int launch_single_scores(ScoreArgs &a, int n_leaders_slice, int batch_slice, hipStream_t s) {
+  auto periods_of = [&](int b) { return (a.seq.seqlen[b] - a.window + kSinglePeriod - 1) / kSinglePeriod; };
   int64_t periods = 0;
-  for (int b = 0; b < batch_slice; ++b) {
-    const int P = a.seq.seqlen[b] - a.window;
-    const int np = (P + kSinglePeriod - 1) / kSinglePeriod;
-    max_periods = np > max_periods ? np : max_periods;
-    periods += np;
-  }
-  if (max_periods == 0 || n_leaders_slice <= 0) return CHUNKKV_OK;
+  for (int b = 0; b < batch_slice; ++b) periods += periods_of(b);
+  if (periods == 0 || n_leaders_slice <= 0) return CHUNKKV_OK;
   if (a.rows_pad != 128 && a.rows_pad != 256) return CHUNKKV_ERR_UNSUPPORTED;
   // at most about kScoresTargetWgs workgroups (eight per CU, one generation), with at least one task for each of their four
   // wavefronts; with 256 rows at least two periods, as 32 ranges of them are 64 KB of statistics for a period's 20 (32 calls
@@ -288,7 +283,12 @@ int launch_single_scores(const ScoreArgs &a, int n_leaders_slice, int batch_slic
   const int sums = kSingleHalf / a.chunk, least = sums == 16 && !wide ? 1 : 2;
   int64_t ppw = (periods * a.n_kv_heads * n_leaders_slice + kScoresTargetWgs - 1) / kScoresTargetWgs;
   ppw = ppw < least ? least : (ppw > kScoresMaxPeriods ? kScoresMaxPeriods : ppw);
-  dim3 grid((max_periods + (int)ppw - 1) / (int)ppw, batch_slice * a.n_kv_heads, n_leaders_slice);
+  int groups = 0;
+  for (int b = 0; b < batch_slice; ++b) {
+    a.first_range[b] = groups;
+    groups += (periods_of(b) + (int)ppw - 1) / (int)ppw;
+  }
+  dim3 grid(groups, a.n_kv_heads, n_leaders_slice);
   switch (sums) {
     case 4: hipLaunchKernelGGL((wide ? single_scores_kernel<4, 4> : single_scores_kernel<4, 2>), grid, dim3(256), 0, s, a, (int)ppw); break;
     case 8: hipLaunchKernelGGL((wide ? single_scores_kernel<8, 4> : single_scores_kernel<8, 2>), grid, dim3(256), 0, s, a, (int)ppw); break;

@@ -120,8 +120,9 @@ __global__ __launch_bounds__(kThreads, 2) void score_single_kernel(ScoreArgs a) 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wavefront-uniform, and known to be
   const int n = lane & 31, half = lane >> 5;
-  const int bl = blockIdx.y / a.n_kv_heads, h = blockIdx.y % a.n_kv_heads, z = blockIdx.z / a.row_groups;
-  const int split = blockIdx.x, row0 = (blockIdx.z % a.row_groups) * (128 * NQ);   // first window row of this workgroup
+  int split = blockIdx.x;
+  const int bl = find_sequence(a, split), h = blockIdx.y, z = blockIdx.z / a.row_groups;
+  const int row0 = (blockIdx.z % a.row_groups) * (128 * NQ);   // first window row of this workgroup
   const int g = a.n_q_heads / a.n_kv_heads, w = a.window;
   const int L = CKV_ARG(ScoreArgs, seq.seqlen, bl), P = L - w, nrows = g * w;
   const int64_t problem = ((int64_t)CKV_ARG(ScoreArgs, leader, z) * a.batch_total + (a.batch0 + bl)) * a.n_kv_heads + h;
@@ -130,7 +131,6 @@ __global__ __launch_bounds__(kThreads, 2) void score_single_kernel(ScoreArgs a) 
   const int ppr = single_periods_per_range(np_total);
   const int u0 = split * ppr;
   const int u1 = u0 + ppr < np_total ? u0 + ppr : np_total;
-  if (u0 >= np_total) return;
   const int np_prefix = (P + kSpPeriod - 1) / kSpPeriod;   // periods with keys before the window
   const int np = (u1 < np_prefix ? u1 : np_prefix) - u0;   // periods of this workgroup: none, if it has window keys alone
   const int range0 = u0 * kSpPeriod;    // its first key
