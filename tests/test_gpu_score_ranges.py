@@ -65,6 +65,32 @@ def test_scores_match_float64(dtype, P, w, g, c):
     assert torch.equal(more[:, :want.shape[1]], scores[:, :want.shape[1]].repeat(n, 1))
 
 
+# The grids count the ranges of all sequences: ragged batches, sequences without a prefix first, last and in between, 16 and 17
+# of them (two launches), with shared rows and without, against every sequence alone, to the bit.
+@pytest.mark.parametrize("prefixes,w,g,c,hkv", [
+    ([0, 700, 0, 0, 5121, 20, 0], 64, 4, 5, 2), ([20400] + [300] * 11, 64, 4, 20, 2), ([641, 1, 160, 2000], 32, 4, 10, 3),
+    ([100 * i for i in range(16)], 32, 7, 10, 2), ([161 * (i * 5 % 17) for i in range(17)], 64, 4, 20, 1), ([0, 0], 64, 4, 10, 2),
+])
+def test_ragged_batch_equals_sequences_alone(prefixes, w, g, c, hkv):
+    gen = torch.Generator(device=DEV).manual_seed(len(prefixes))
+    d, lens = 128, [p + w for p in prefixes]
+    k = torch.randn((max(lens), hkv, d), generator=gen, device=DEV).bfloat16()      # every sequence is a prefix of the same cache
+    q = torch.randn((len(lens), hkv * g, w, d), generator=gen, device=DEV).bfloat16()
+
+    def score(lens, q):
+        prob = ckv.Problem(hkv * g, hkv, d, w, c, ckv.BF16, lens, [0] * len(lens), [0] * len(lens), d, hkv * d)
+        ws = torch.full((ckv.chunkkv_workspace_bytes(prob),), 0xFF, dtype=torch.uint8, device=DEV)
+        scores = torch.full((len(lens), hkv, max(1, prob.score_cap)), -1.0, device=DEV)
+        ckv.chunkkv_score(prob, q, k, scores, None, ws)
+        return scores
+
+    got = score(lens, q)
+    for b, p in enumerate(prefixes):
+        n = (p + c - 1) // c
+        assert torch.equal(got[b, :, :n], score(lens[b:b + 1], q[b:b + 1].contiguous())[0, :, :n]), b
+        assert (got[b, :, n:] == -1.0).all()
+
+
 # The row totals keep the bits of their ranges' sums: all prefix logits are X and scale * log2(e) is one, so the sums are whole
 # numbers, every score is 65 c / P, and the only rounding is that of X + log2(P) at 2^13.. (its last bit is 2^-10).  A rounding
 # per range on top of it takes all of these prefixes past the bound.
