@@ -15,11 +15,18 @@ constexpr int kTargetWorkgroups = 4096;  // ~4 resident rounds of 2 workgroups o
 // itself while its first tiles travel.  A kernel in between took 5 us, and 9 to 49 for one layer of a hundred ranges or more:
 // 16000 tokens 34.3 -> 28.9 us a call, 19000 with 64 rows 66 -> 42, 120602 in fp32 288 -> 234.  Above it that kernel is a
 // percent or two and merging everywhere more (10 layers of 109334 tokens, 224 rows 906 us, 947 merged).
-constexpr int64_t kMergeTiles = 16384, kMergeWorkgroups = 1536;
-// So there are at most kMaxRanges ranges, and kGoodRanges as long as those have no more tiles in a row than kRangeTiles or than
-// there are for each CU, whichever is more: 120602 tokens, 4 heads, fp32 in 32 / 63 / 236 ranges 147 / 81 / 90 us.  (Short
-// launches leave CUs without a workgroup for it: 16000 tokens and 4 heads are 128 of four tiles.)
-constexpr int kGoodRanges = 32, kMaxRanges = 64, kRangeTiles = 8;
+constexpr int64_t kMergeTiles = 16384;
+// So there are at most kMaxRanges ranges.
+constexpr int kMaxRanges = 64;
+// How the two passes are cut into workgroups (units_per_workgroup in score_plan.h): whole rounds, as far as a launch has few.  What
+// a workgroup costs, in microseconds: a 32-key block against 32 rows with two workgroups on the CU; beside its tiles start, queries,
+// first tiles and end; in pass 1 the merge of eight ranges' statistics.  us of a call, and with about 32 ranges of eight tiles or
+// more and up to 1536 workgroups in pass 1 whatever the rounds are: 12345 tokens, three of eight groups in two passes 198 / 210;
+// 32 layers of 4270 tokens, 64 rows 112 / 133; 59567 tokens in fp32, 256 rows 328 / 358; 32 layers of five sequences of 1379 to 3768
+// tokens, d = 64 85 / 107.  In a launch of many rounds an empty place at the end costs little, and few long walks lose to uneven
+// ones (eight sequences of 7138 to 47085 tokens, 32 rows 248, in one round 266).
+constexpr double kBlockUs[2] = {0.6, 1.9}, kStartUs = 2.4, kMergeUs = 0.7, kHalfRound[2] = {0.7, 0.75};   // [0]: 16-bit types, [1]: fp32
+constexpr int kFewRounds = 4, kCUs = 256;
 // Single-pass scoring with 256 rows: up to this many workgroups leave half the CUs empty, so two of them, with 128 rows each,
 // share a key range; K is read twice.  us of a call on one layer, split / not: 104 workgroups 26.9 / 30.0, 128 of them at 65536
 // tokens 59.6 / 69.8; 200 36.1 / 35.9, 256 at 20011 tokens 42.6 / 41.8, 256 at 131072 155 / 140.
@@ -33,8 +40,7 @@ struct Plan {
   ScoreGeom geom;
   int n_leaders, rows_pad;
   int batch_leaders;  // leader layers scored per launch set
-  int tpw0, max_split0;
-  int merge0;         // two-pass scoring: pass 1 merges the row statistics itself
+  int tpw0, max_split0;   // two-pass scoring: least tiles of a key range, most ranges
   int fuse_chunks;
   // single-pass path: usable for this problem?  geometry and workspace
   int single_ok, n_periods_fit, rows_pad_s, n_periods, max_split_s;
@@ -138,13 +144,6 @@ bool takes_one_pass(const chunkkv_problem *p, const Plan &pl, int chunk) {
   return !(p->flags & CHUNKKV_FLAG_TWO_PASS) && pl.n_periods_fit && single_pass_ok(p->dtype, p->head_dim, (p->n_q_heads / p->n_kv_heads) * p->window, chunk);
 }
 
-// Super-tiles a workgroup of the importance pass takes, of `units` in the launch.  Where every workgroup merges the row
-// statistics, three rounds of them at most (120602 tokens, 63 ranges 92 us, with 1892 workgroups 106).
-int pass1_tiles_per_wg(int64_t units, bool merge) {
-  const int64_t wgs = merge ? kMergeWorkgroups : kTargetWorkgroups, n = (units + wgs - 1) / wgs;
-  return n < 1 ? 1 : (int)n;
-}
-
 // Workspace layout and key-range split; a pure function of (problem, n_layers, reuse).
 int make_plan(const chunkkv_problem *p, int n_layers, int reuse, Plan *pl) {
   if (n_layers < 1 || reuse < 1) return CHUNKKV_ERR_SHAPE;
@@ -170,19 +169,9 @@ int make_plan(const chunkkv_problem *p, int n_layers, int reuse, Plan *pl) {
   pl->tpw0 = (int)((tiles0 * heads + kTargetWorkgroups - 1) / kTargetWorkgroups);
   if (pl->tpw0 < 1) pl->tpw0 = 1;
   pl->max_split0 = 1;   // room for the ranges' pairs
-  int most0 = 1;        // tiles of the longest sequence
   for (int b = 0; b < p->batch; ++b) {
-    const int t = ceil_div(p->seqlen[b], TK), s = ceil_div(t, pl->tpw0);
+    const int s = ceil_div(ceil_div(p->seqlen[b], TK), pl->tpw0);
     if (s > pl->max_split0) pl->max_split0 = s;
-    if (t > most0) most0 = t;
-  }
-  pl->merge0 = tiles0 * heads <= kMergeTiles;
-  if (pl->merge0) {
-    const int64_t per_cu = (tiles0 * heads + 255) / 256;
-    int64_t least = per_cu > kRangeTiles ? per_cu : kRangeTiles;
-    if (least > ceil_div(most0, kGoodRanges)) least = ceil_div(most0, kGoodRanges);
-    if (least < ceil_div(most0, kMaxRanges)) least = ceil_div(most0, kMaxRanges);
-    if (pl->tpw0 < least) pl->tpw0 = (int)least;
   }
   // single-pass path
   pl->rows_pad_s = rows > 128 ? 256 : 128;
@@ -267,8 +256,7 @@ int run_score(const chunkkv_problem *p, const Plan &pl, const void *const *q, co
     a.token_imp = token_imp; a.imp_pitch = imp_pitch;
     a.fuse_chunks = pl.fuse_chunks;
     if (!pl.fuse_chunks && !token_imp) { a.token_imp = (float *)(ws + pl.off_imp); a.imp_pitch = (int64_t)p->score_cap * p->chunk; }
-    int split1 = 0, ranges0 = 0;
-    for (int i = 1; i < kMaxBatchPerLaunch; ++i) a.first_range[i] = INT32_MAX;
+    for (int i = 1; i <= kMaxBatchPerLaunch; ++i) a.first_range[i] = INT32_MAX;
     // Super-tiles: smaller ones where a launch would leave CUs without a workgroup (512 tokens in fp32, 4 workgroups 12 us,
     // 16 of them 8); the sums of a chunk are the same bits whatever super-tile it lies in.
     a.super_keys = kSuperKeys;
@@ -279,15 +267,6 @@ int run_score(const chunkkv_problem *p, const Plan &pl, const void *const *q, co
       for (int z = 0; z < ng; ++z)
         for (int i = 0; i < nb; ++i) units1 += super_tiles(i, z);
       if (!pl.fuse_chunks || units1 * p->n_kv_heads >= 256 || a.super_keys / 2 < TK || a.super_keys <= 64) break;
-    }
-    const int tpw1 = pass1_tiles_per_wg(units1 * p->n_kv_heads, pl.merge0);
-    for (int i = 0; i < nb; ++i) {
-      ranges0 += ceil_div(ceil_div(a.seq.seqlen[i], TK), pl.tpw0);
-      if (i + 1 < nb) a.first_range[i + 1] = ranges0;
-      for (int z = 0; z < ng; ++z) {
-        const int s1 = ceil_div(super_tiles(i, z), tpw1);
-        split1 = s1 > split1 ? s1 : split1;
-      }
     }
     int rc;
     if (lse) {
@@ -315,20 +294,70 @@ int run_score(const chunkkv_problem *p, const Plan &pl, const void *const *q, co
       if (rc) return rc;
       continue;
     }
+    const int slots = score_workgroups_per_cu(p->dtype, p->head_dim, pl.geom) * kCUs, f32 = p->dtype == CHUNKKV_F32 ? 1 : 0;
+    const double half = slots == kCUs ? 1.0 : kHalfRound[f32];
+    const int blocks = TK / 32, key_waves = 4 / pl.geom.wq < blocks ? 4 / pl.geom.wq : blocks;
+    const double tile_us = (double)(blocks / key_waves) * pl.geom.nqw * kBlockUs[f32];
+    double start1 = kStartUs / tile_us;
+    int64_t tiles = 0;
+    int most = 1, ranges = 0;   // tiles of the longest sequence, ranges of all
+    for (int i = 0; i < nb; ++i) {
+      const int t = ceil_div(a.seq.seqlen[i], TK);
+      tiles += t;
+      most = t > most ? t : most;
+    }
+    const bool short_launch = tiles * p->n_kv_heads * ng <= kMergeTiles;
+    // Neighbours are the heads of one range in short launches (one layer of 23344 tokens, 32 rows 37.9 us, the ranges of one head
+    // 43.0), the ranges of one head in longer ones (packed, 32 layers of 3812 and 12202 tokens, 8 heads of 16 rows 332, heads 359).
+    a.heads_first = short_launch;
+    const int per_range = short_launch ? 1 : p->n_kv_heads;   // entries of the grid's x or y for one range
+    auto grid = [&](int64_t n) { return short_launch ? dim3(p->n_kv_heads, (uint32_t)n, ng) : dim3((uint32_t)(n * p->n_kv_heads), 1, ng); };
+    const int rounds = short_launch ? kTargetWorkgroups / slots : kFewRounds;
     if (!lse) {
-      a.tiles_per_wg = pl.tpw0;
-      { Timed t(kStats, s); rc = launch_score_pass(0, p->dtype, p->head_dim, pl.geom, a, dim3(ranges0, p->n_kv_heads, ng), s); }
+      const bool merge = short_launch;   // pass 1 merges the row statistics itself
+      const int least = merge && pl.tpw0 < ceil_div(most, kMaxRanges) ? ceil_div(most, kMaxRanges) : pl.tpw0;
+      auto merging = [&](int t) { return merge ? kMergeUs / tile_us * ceil_div(ceil_div(most, t), 8) : 0.0; };
+      const int tpw0 = units_per_workgroup(least, most, slots, rounds, half, kStartUs / tile_us, [&](int t) {
+        int64_t n = 0;
+        for (int i = 0; i < nb; ++i) n += ceil_div(ceil_div(a.seq.seqlen[i], TK), t);
+        return n * p->n_kv_heads * ng;
+      }, merging);
+      for (int i = 0; i < nb; ++i) {
+        ranges += ceil_div(ceil_div(a.seq.seqlen[i], TK), tpw0);
+        a.first_range[i + 1] = ranges * per_range;
+      }
+      a.tiles_per_wg = tpw0;
+      { Timed t(kStats, s); rc = launch_score_pass(0, p->dtype, p->head_dim, pl.geom, a, grid(ranges), s); }
       if (rc) return rc;
-      if (pl.merge0) {
-        a.stats_tiles = pl.tpw0;
+      if (merge) {
+        a.stats_tiles = tpw0;
+        start1 += merging(tpw0);
       } else {
         { Timed t(kCombine, s); rc = launch_stats_combine(a, ng, nb, TK, s); }
         if (rc) return rc;
       }
     }
     if (units1 == 0) continue;   // no prefix: nothing to sum
-    a.tiles_per_wg = tpw1;
-    { Timed t(kColsum, s); rc = launch_score_pass(1, p->dtype, p->head_dim, pl.geom, a, dim3(split1, nb * p->n_kv_heads, ng), s); }
+    // super-tiles of a sequence: those of the layer with most, which differ where chunk sizes do
+    int most1 = 1, seq_units[kMaxBatchPerLaunch];
+    for (int i = 0; i < nb; ++i) {
+      seq_units[i] = 0;
+      for (int z = 0; z < ng; ++z) seq_units[i] = super_tiles(i, z) > seq_units[i] ? super_tiles(i, z) : seq_units[i];
+      most1 = seq_units[i] > most1 ? seq_units[i] : most1;
+    }
+    const int64_t all1 = units1 * p->n_kv_heads;
+    auto ranges1 = [&](int t) {
+      int64_t n = 0;
+      for (int i = 0; i < nb; ++i) n += ceil_div(seq_units[i], t);
+      return n;
+    };
+    a.tiles_per_wg = units_per_workgroup((int)((all1 + kTargetWorkgroups - 1) / kTargetWorkgroups), most1, slots, rounds, half, start1 * TK / a.super_keys,
+                                         [&](int t) { return ranges1(t) * p->n_kv_heads * ng; }, [](int) { return 0.0; });
+    for (int i = 0, n = 0; i < nb; ++i) {
+      n += ceil_div(seq_units[i], a.tiles_per_wg);
+      a.first_range[i + 1] = n * per_range;
+    }
+    { Timed t(kColsum, s); rc = launch_score_pass(1, p->dtype, p->head_dim, pl.geom, a, grid(ranges1(a.tiles_per_wg)), s); }
     if (rc) return rc;
     if (!pl.fuse_chunks) {
       { Timed t(kChunkSums, s); rc = launch_chunk_sums(a, ng, nb, s); }

@@ -41,13 +41,14 @@ struct ScoreArgs {
   int64_t kv_stride_head, kv_stride_tok;
   float scale_log2e;       // softmax scale * log2(e)
   int32_t tiles_per_wg;    // pass 0: key tiles, pass 1: super-tiles each workgroup walks
-  // Pass 0 and the single-pass kernels: number of the first key range (the reduction: group of periods) of every sequence,
-  // INT32_MAX past the last one.  The x of their grids counts those of all sequences, so there are no empty workgroups: these go to the
-  // XCDs, and there to the shader engines, in turn, and with a row of the grid as long as the longest sequence has ranges some
-  // CUs got two of them and others none.  us of a call, then and now: two passes, five sequences of 3246 to 14215 tokens in fp32
-  // 191 / 159, six of 1000 to 40000 with 224 rows 84 / 60; single pass, one of 20400
-  // and eleven of 300 116 / 40 (16 ranges for the long one instead of 32: 108), eight of up to 20300 at c = 20 61 / 49 (59).
-  int32_t first_range[kMaxBatchPerLaunch];
+  // Number of the first key range (the reduction: group of periods) of every sequence, INT32_MAX past the last one; two passes
+  // without heads_first: of its first workgroup.  The grids count the ranges of all sequences, so there are no empty workgroups:
+  // these go to the XCDs, and there to the shader engines, in turn, and with a row of the grid as long as the longest sequence
+  // has ranges some CUs got two of them and others none.  us of a call, so and with empty ones: two passes, five sequences of 3246 to
+  // 14215 tokens in fp32 159 / 191, six of 1000 to 40000 with 224 rows 60 / 84; single pass, one of 20400 and eleven of 300 40 / 116
+  // (16 ranges for the long one instead of 32: 108), eight of up to 20300 at c = 20 49 / 61 (59).
+  int32_t first_range[kMaxBatchPerLaunch + 1];   // two passes: and the end of the last one
+  int32_t heads_first;     // two passes: neighbouring workgroups are 1: heads of one range, 0: ranges of one head
   int32_t max_split;       // pitch of part_stats in splits
   int32_t rows_pad;        // g*w rounded up to 32
   float2 *part_stats;      // [problem][max_split][rows_pad]  (running max, sum) in log2 units
@@ -212,6 +213,7 @@ struct ScoreGeom {
   int wq;          // wavefronts splitting the rows (the other 4/wq split keys)
 };
 bool score_geometry(int dtype, int head_dim, int rows, ScoreGeom *g);
+int score_workgroups_per_cu(int dtype, int head_dim, const ScoreGeom &g);   // of the two passes
 
 // Launchers (each checks hipGetLastError and returns a chunkkv_status).
 int launch_score_pass(int pass, int dtype, int head_dim, const ScoreGeom &g, const ScoreArgs &a,

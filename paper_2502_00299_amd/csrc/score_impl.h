@@ -124,8 +124,14 @@ __global__ __launch_bounds__(kThreads, ((NQW >= 4 || (DT == CHUNKKV_F32 && HD ==
   const int wq = wave % WQ, wk = wave / WQ;
   const bool active = (4 / WQ == WK) ? true : (wk < WK);  // wavefronts beyond the key blocks only load
   const int z = blockIdx.z;
-  int bl = blockIdx.y / a.n_kv_heads, h = blockIdx.y % a.n_kv_heads, split = blockIdx.x;
-  if constexpr (PASS == 0) { bl = find_sequence(a, split); h = blockIdx.y; }
+  // short launches: grid x = head, y = range of any sequence; longer ones: x = range of any head of any sequence
+  int split = a.heads_first ? blockIdx.y : blockIdx.x, h = blockIdx.x;
+  const int bl = find_sequence(a, split);
+  if (!a.heads_first) {
+    const int next = CKV_ARG(ScoreArgs, first_range, bl + 1), ranges = (next - (int)(blockIdx.x - split)) / a.n_kv_heads;
+    h = split / ranges;
+    split -= h * ranges;
+  }
   const int g = a.n_q_heads / a.n_kv_heads, w = a.window, c = PASS == 1 ? CKV_ARG(ScoreArgs, chunk_of, z) : 1;
   const int L = CKV_ARG(ScoreArgs, seq.seqlen, bl), P = L - w, nrows = g * w;
   const int64_t problem = ((int64_t)CKV_ARG(ScoreArgs, leader, z) * a.batch_total + (a.batch0 + bl)) * a.n_kv_heads + h;

@@ -161,3 +161,26 @@ def test_infinite_key_that_rows_do_not_see(P, w, g, c, dtype, flags):
     ckv.chunkkv_score(prob, q.to(DEV), k.to(DEV), scores, None, ws)
     got = scores.cpu().double()[:, :want.shape[1]]
     assert float(((got - want).abs() / want).max()) < 1.3e-4   # as above; a NaN fails as well
+
+
+# Launches on either side of the line from which the ranges of a head are neighbours (16384 key tiles, of 128 keys here): a ragged batch
+# with sequences without a prefix, against every sequence alone.  Both are within 1e-6 of float64.
+@pytest.mark.parametrize("lens", [[90000, 16, 150000, 16, 17, 40000], [16, 90000, 60000], [40000, 16] * 9])
+def test_long_ragged_launches_equal_sequences_alone(lens):
+    hkv, g, w, d, c = 8, 2, 16, 64, 33
+    gen = torch.Generator(device=DEV).manual_seed(3)
+    k = torch.randn((max(lens), hkv, d), generator=gen, device=DEV).bfloat16()      # every sequence is a prefix of the same cache
+    q = torch.randn((len(lens), hkv * g, w, d), generator=gen, device=DEV).bfloat16()
+
+    def score(lens, q):
+        prob = ckv.Problem(hkv * g, hkv, d, w, c, ckv.BF16, lens, [0] * len(lens), [0] * len(lens), d, hkv * d)
+        ws = torch.full((ckv.chunkkv_workspace_bytes(prob),), 0xFF, dtype=torch.uint8, device=DEV)
+        scores = torch.full((len(lens), hkv, max(1, prob.score_cap)), -1.0, device=DEV)
+        ckv.chunkkv_score(prob, q, k, scores, None, ws)
+        return scores
+
+    got = score(lens, q)
+    for b, n in enumerate((L - w + c - 1) // c for L in lens):
+        alone = score(lens[b:b + 1], q[b:b + 1].contiguous())[0, :, :n]
+        assert n == 0 or float(((got[b, :, :n] - alone).abs() / alone).max()) < 2e-6, b
+        assert (got[b, :, n:] == -1.0).all()

@@ -1,5 +1,6 @@
 """Arithmetic of the scoring kernels (csrc/score_plan.h), on the host."""
 import os
+import random
 import subprocess
 
 import pytest
@@ -32,3 +33,30 @@ def test_super_tiles_do_not_grow_as_they_are_cut(ask):
         assert strides == sorted(strides, reverse=True), chunk
         for keys, n in zip((256, 128, 64), strides):
             assert n % chunk == 0 and (n == chunk or keys - chunk < n <= keys), (keys, chunk)
+
+
+def test_workgroups_fill_whole_rounds(ask):
+    """Units per workgroup: within the limits, the least ones for launches of many rounds, and never a longer launch by the rule's own
+    measure than one unit or one round would be."""
+    rng = random.Random(7)
+    cases = [(1, 1, [1]), (1, 0, [0, 0]), (3, 10, [10]), (1, 500, [500]), (4, 4096, [4096] * 16), (1, 513, [513]), (1, 257, [257, 1])]
+    cases += [(rng.choice([1, 2, 9]), None, [rng.randrange(0, 2000) for _ in range(rng.randrange(1, 17))]) for _ in range(200)]
+    lines, want = [], []
+    for lo, hi, units in cases:
+        hi, slots, rounds, half, start = max(units) if hi is None else hi, rng.choice([256, 512]), rng.choice([4, 8]), 0.7, rng.choice([0.5, 2.0, 6.0])
+        lines.append(f"{lo} {hi} {slots} {rounds} {half} {start} {len(units)} " + " ".join(map(str, units)))
+        want.append((lo, hi, slots, rounds, half, start, units))
+    for line, (lo, hi, slots, rounds, half, start, units) in zip(ask(lines, "units"), want):
+        def wgs(t):
+            return sum(-(-u // t) for u in units)
+
+        def cost(t):
+            full, rest = divmod(wgs(t), slots)
+            return t * (full + (0 if rest == 0 else half if 2 * rest <= slots else 1)) + start * (full + (rest != 0)) + 0.1 * t
+        t, n = map(int, line.split())
+        assert lo <= t <= max(lo, hi) and n == wgs(t)
+        if lo >= hi or wgs(lo) > rounds * slots:
+            assert t == lo
+        else:
+            one = next((x for x in range(lo, hi + 1) if wgs(x) <= slots), hi)
+            assert cost(t) <= cost(one) + 1e-9 and cost(t) <= cost(lo) * (1 + 1e-9) + 1e-9
