@@ -185,19 +185,40 @@ __global__ __launch_bounds__(kThreads, ((NQW >= 4 || (DT == CHUNKKV_F32 && HD ==
     else if (newer == 1) __builtin_amdgcn_s_waitcnt(vmcnt_imm(kLoadsPerWave));
     else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
   };
+  // The window queries, operand fragments that stay in registers, come through the last slots of the ring, 32 rows of every wavefront
+  // at a time and with the swizzle of the keys, beside the first tiles: read straight into fragments every load touches 32 lines.
+  // us of a call, so and read straight: 512 tokens in
+  // fp32, d = 64 16.9 / 18.1; one layer of 1955 tokens, 64 rows 16.7 / 18.3; 32 calls on 13078 tokens, 128 rows 889 / 941.  Rows of 512 bytes
+  // would fill the whole ring; they are read straight.
+  constexpr bool kStageQ = ROWB <= 256;
+  constexpr int kQBytes = 32 * ROWB;                                              // of one wavefront
+  constexpr int kFirstTiles = kStageQ ? (kRing * kTileBytes - 4 * kQBytes) / kTileBytes : kRing - 1;   // 2 or 3 beside them
+  static_assert(kFirstTiles >= 1 && kFirstTiles <= kRing - 1, "queries in the ring");
+  const int q_area = (kRing * kTileBytes - 4 * kQBytes) + __builtin_amdgcn_readfirstlane(wave) * kQBytes;
 #pragma unroll
-  for (int s = 0; s < kRing - 1; ++s)
+  for (int s = 0; s < kFirstTiles; ++s)
     if (s < nt) issue_tile(s);
-
-  // window queries: operand fragments, resident for the whole kernel
+  auto issue_queries = [&](int qi) __attribute__((always_inline)) {
+    const __amdgpu_buffer_rsrc_t qrsrc = __builtin_amdgcn_make_buffer_rsrc((void *)qbase, 0, nrows * ROWB, 0x00020000);   // rows past the last read as zero
+#pragma unroll
+    for (int j = 0; j < kQBytes / 1024; ++j) {
+      const int row = j * (1024 / ROWB) + lane / NSEG;
+      const uint32_t off = (uint32_t)(((wq * NQW + qi) * 32 + row) * ROWB + ((lane % NSEG) ^ (row & 7)) * 16);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(qrsrc, (__attribute__((address_space(3))) void *)(smem + q_area + j * 1024), 16, off, 0, 0, 0);
+    }
+  };
   u32x4 qf[NQW][NKS];
+  if constexpr (kStageQ) {
+    issue_queries(0);
+  } else {
 #pragma unroll
-  for (int qi = 0; qi < NQW; ++qi) {
-    const int row = (wq * NQW + qi) * 32 + n;
+    for (int qi = 0; qi < NQW; ++qi) {
+      const int row = (wq * NQW + qi) * 32 + n;
 #pragma unroll
-    for (int ks = 0; ks < NKS; ++ks) {
-      qf[qi][ks] = u32x4{0, 0, 0, 0};
-      if (row < nrows) qf[qi][ks] = *(const u32x4 *)(qbase + (int64_t)row * ROWB + (2 * ks + half) * 16);
+      for (int ks = 0; ks < NKS; ++ks) {
+        qf[qi][ks] = u32x4{0, 0, 0, 0};
+        if (row < nrows) qf[qi][ks] = *(const u32x4 *)(qbase + (int64_t)row * ROWB + (2 * ks + half) * 16);
+      }
     }
   }
 
@@ -375,8 +396,24 @@ __global__ __launch_bounds__(kThreads, ((NQW >= 4 || (DT == CHUNKKV_F32 && HD ==
     else step(b, cur, prev, std::true_type{}, std::false_type{});
   };
 
+  if constexpr (kStageQ) {
+#pragma unroll
+    for (int qi = 0; qi < NQW; ++qi) {
+      if (qi > 0) issue_queries(qi);
+      __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+#pragma unroll
+      for (int ks = 0; ks < NKS; ++ks) qf[qi][ks] = *frag_at((uint32_t)q_area, ks);
+      __builtin_amdgcn_s_waitcnt(0xC07F);   // the fragments are in registers: the area is free
+    }
+    if (kFirstTiles < kRing - 1) {
+      __builtin_amdgcn_s_barrier();         // for the other wavefronts' tiles too
+#pragma unroll
+      for (int s = kFirstTiles; s < kRing - 1; ++s)
+        if (s < nt) issue_tile(s);
+    }
+  }
   wait_tile(0);
-  lds_barrier();  // every wavefront's part of tile 0 and the start values are in LDS
+  lds_barrier();  // every wavefront's part of tile 0 and the start values are in LDS, its queries in registers
   if (kRing - 1 < nt) issue_tile(kRing - 1);
   if constexpr (PASS == 1 && kStartInRegs) {
 #pragma unroll
