@@ -210,8 +210,7 @@ int make_plan(const chunkkv_problem *p, int n_layers, int reuse, Plan *pl) {
   pl->off_ebuf = pl->off_mper = off;
   if (pl->single_ok) {
     const size_t cells = problems * (size_t)pl->n_periods * pl->rows_pad_s;   // (period, row)
-    const int sums = 80 / p->chunk;   // chunk sums per lane half and period: 20-bit floats in groups of eight, else 24-bit
-    pl->off_ebuf = off; off += align256(cells * (size_t)(sums == 4 ? 24 : 5 * sums));
+    pl->off_ebuf = off; off += align256(cells * (size_t)single_e_row_bytes(p->chunk));
     pl->off_mper = off; off += align256(cells * sizeof(float));
   }
   pl->total = off < 256 ? 256 : off;
@@ -229,8 +228,8 @@ void fill_seq(SeqTable *t, const chunkkv_problem *p, int b0, int nb) {
 }
 
 // Scores ng leader layers (pointer tables already gathered) for all sequences; leaders[i] is the index of the i-th, whose
-// problems of the workspace and scores are its own, chunks[i] its chunk size.  Chunk sizes differ only where two passes score
-// (pl and p are then those of any of them).
+// problems of the workspace and scores are its own, chunks[i] its chunk size.  Where they differ, pl and p are those of any of them,
+// pl with the workspace of the one that needs most, and either all of them or none take one pass.
 // lse == nullptr: the row normalisation is computed here; otherwise lse[i] is leader i's caller-supplied
 // [B][Hq][w] array and only the importance pass runs.
 int run_score(const chunkkv_problem *p, const Plan &pl, const void *const *q, const void *const *k,
@@ -280,6 +279,11 @@ int run_score(const chunkkv_problem *p, const Plan &pl, const void *const *q, co
       a.m_period = (float *)(ws + pl.off_mper);
       a.row_stats = (float *)(ws + pl.off_part);
       a.max_split = pl.max_split_s;
+      for (int i = 0; i < ng; ++i) {
+        const int bytes = single_e_row_bytes(chunks[i]);
+        a.e_row_bytes = bytes > a.e_row_bytes ? bytes : a.e_row_bytes;
+        a.mixed_chunks |= chunks[i] != chunks[0];
+      }
       a.rows_pad = pl.rows_pad_s;
       int ranges = 0;
       for (int i = 0; i < nb; ++i) {
@@ -609,9 +613,10 @@ static int stack_entry(const chunkkv_problem *prob, int32_t n_layers, int32_t re
 }  // extern "C"
 
 // A stack whose groups' chunk sizes differ, each kernel launched over all groups it can take at once: the single-pass
-// kernels once per chunk size they are compiled for, pass 0 and pass 1 once for all other groups, selection and gather once
+// kernels once for the chunk sizes they are compiled for, pass 0 and pass 1 once for all other groups, selection and gather once
 // for all.  One run of groups after the other is a chain of four or five launches that do not fill the chip, per run: eight
-// sizes over 16 layers of 12345 tokens 355 us, together with the same kernels 212.  `pl` is the plan of the chunk size that needs the most
+// sizes over 16 layers of 12345 tokens 171 us, with a single-pass launch and a reduction per size 199; 32 groups of seven sizes and
+// 400 tokens 37, 67.  `pl` is the plan of the chunk size that needs the most
 // workspace; the others fit its regions.
 static int stack_mixed(const chunkkv_problem *prob, const Plan &pl, int32_t n_layers, int32_t reuse, const int32_t *chunks,
                        const void *const *q_obs, const void *const *k, const void *const *v, const float *const *lse,
@@ -636,7 +641,7 @@ static int stack_mixed(const chunkkv_problem *prob, const Plan &pl, int32_t n_la
     int32_t leaders[kMaxLayersPerLaunch], cs[kMaxLayersPerLaunch];
     int ng = 0;
     for (int g = first; g < n_groups; ++g) {
-      if (done[g] || (one_pass(chunks[first]) ? chunks[g] != chunks[first] : one_pass(chunks[g]))) continue;
+      if (done[g] || one_pass(chunks[first]) != one_pass(chunks[g])) continue;
       done[g] = true;
       qs[ng] = q_obs[g * reuse]; ks[ng] = k[g * reuse]; ls[ng] = lse ? lse[g * reuse] : nullptr;
       leaders[ng] = g; cs[ng] = chunks[g];

@@ -34,10 +34,10 @@ struct ScoreArgs {
   const void *k[kMaxLayersPerLaunch];
   SeqTable seq;
   int32_t leader[kMaxLayersPerLaunch];    // leader index of every slice layer: whose problems of the workspace are its own
-  int32_t chunk_of[kMaxLayersPerLaunch];  // importance pass: chunk size of every slice layer
+  int32_t chunk_of[kMaxLayersPerLaunch];  // chunk size of every slice layer
   int32_t batch0;          // index of this slice's first sequence
   int32_t batch_total;
-  int32_t n_q_heads, n_kv_heads, window, chunk;   // chunk: of all slice layers, everywhere but in the importance pass
+  int32_t n_q_heads, n_kv_heads, window, chunk;   // chunk: of all slice layers, unless theirs may differ (importance pass, mixed_chunks)
   int64_t kv_stride_head, kv_stride_tok;
   float scale_log2e;       // softmax scale * log2(e)
   int32_t tiles_per_wg;    // pass 0: key tiles, pass 1: super-tiles each workgroup walks
@@ -69,6 +69,8 @@ struct ScoreArgs {
   float *m_period;         // [problem][n_periods][rows_pad]  reference those sums are relative to
   float *row_stats;        // [problem][max_split][rows_pad]  a row's sum over a key range, see merge_row_stats
   int32_t row_groups;      // workgroups that share the rows of a key range (1 or 2)
+  int32_t e_row_bytes;     // of e_buf, per period and row of a problem: the most of any layer
+  int32_t mixed_chunks;    // 1: the layers' chunk sizes differ
 };
 
 struct TopkArgs {
@@ -226,6 +228,8 @@ int launch_jaccard(const int32_t *sel_chunk, const int32_t *sel_len, const int32
                    int rows_per_group, int n_pairs, float *out, hipStream_t s);
 int launch_single_scores(ScoreArgs &a, int n_leaders_slice, int batch_slice, hipStream_t s);
 bool single_pass_ok(int dtype, int head_dim, int rows, int chunk);
+// bytes of e_buf per period and row: 20-bit floats in groups of eight, four per lane half as 24-bit ones
+inline int single_e_row_bytes(int chunk) { return 80 / chunk == 4 ? 24 : 5 * (80 / chunk); }
 int launch_topk(const TopkArgs &a, int n_groups, int batch_slice, hipStream_t s);
 int launch_decode_mfma(int dtype, int head_dim, const DecodeArgs &a, int batch_slice, hipStream_t s);
 int launch_decode(int dtype, int head_dim, bool matrix_cores, const DecodeArgs &a, int batch_slice, hipStream_t s);

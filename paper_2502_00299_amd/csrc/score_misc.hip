@@ -174,8 +174,8 @@ __device__ __forceinline__ float wave_sum_scatter(float (&v)[N]) {
   return x;
 }
 
-template <int S, int RB>   // chunks per lane half and period; 64-row blocks of rows_pad
-__global__ __launch_bounds__(256) void single_scores_kernel(ScoreArgs a, int periods_per_wg) {
+template <int S, int RB>   // chunks per lane half and period; 64-row blocks of rows_pad; a: the kernel's argument
+__device__ __forceinline__ void single_scores(const ScoreArgs &a, int periods_per_wg, float *s_ref) {
   typedef unsigned int u32x3 __attribute__((ext_vector_type(3)));
   typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
   const int tid = threadIdx.x, lane = tid & 63;
@@ -189,13 +189,12 @@ __global__ __launch_bounds__(256) void single_scores_kernel(ScoreArgs a, int per
   const int p0 = group * periods_per_wg;
   const int p1 = p0 + periods_per_wg < np ? p0 + periods_per_wg : np;
   const int nrows = (a.n_q_heads / a.n_kv_heads) * a.window;
-  __shared__ float s_ref[256];
 
   constexpr int G8 = S / 8, NV = S == 4 ? 4 : 8, combos = S == 4 ? 2 : 2 * G8;   // values and tasks per period
   constexpr int kRowBytes = S == 4 ? 24 : combos * 20;                           // E bytes per period and row
   const int64_t prow = (int64_t)a.rows_pad;
   const float *m_problem = a.m_period + problem * a.n_periods * prow;
-  const char *e_problem = (const char *)a.e_buf + problem * a.n_periods * prow * kRowBytes;
+  const char *e_problem = (const char *)a.e_buf + problem * a.n_periods * prow * a.e_row_bytes;
   float *scores = a.chunk_scores + problem * a.score_cap;
   const int n_tasks = (p1 - p0) * combos;
 
@@ -272,6 +271,22 @@ __global__ __launch_bounds__(256) void single_scores_kernel(ScoreArgs a, int per
   }
 }
 
+template <int S, int RB>
+__global__ __launch_bounds__(256) void single_scores_kernel(ScoreArgs a, int periods_per_wg) {
+  __shared__ float s_ref[256];
+  single_scores<S, RB>(a, periods_per_wg, s_ref);
+}
+
+// Layers of different chunk sizes in one launch.
+template <int RB>
+__global__ __launch_bounds__(256) void single_scores_mixed_kernel(ScoreArgs a, int periods_per_wg) {
+  __shared__ float s_ref[256];
+  const int c = CKV_ARG(ScoreArgs, chunk_of, blockIdx.z);
+  if (c == 5) single_scores<16, RB>(a, periods_per_wg, s_ref);
+  else if (c == 10) single_scores<8, RB>(a, periods_per_wg, s_ref);
+  else single_scores<4, RB>(a, periods_per_wg, s_ref);
+}
+
 int launch_single_scores(ScoreArgs &a, int n_leaders_slice, int batch_slice, hipStream_t s) {
   auto periods_of = [&](int b) { return (a.seq.seqlen[b] - a.window + kSinglePeriod - 1) / kSinglePeriod; };
   int64_t periods = 0;
@@ -282,7 +297,7 @@ int launch_single_scores(ScoreArgs &a, int n_leaders_slice, int batch_slice, hip
   // wavefronts; with 256 rows at least two periods, as 32 ranges of them are 64 KB of statistics for a period's 20 (32 calls
   // on 20011 tokens, 16 of them scored, c = 5: 927 us, with one period 968)
   const bool wide = a.rows_pad == 256;
-  const int sums = kSingleHalf / a.chunk, least = sums == 16 && !wide ? 1 : 2;
+  const int sums = kSingleHalf / a.chunk, least = sums == 16 && !wide && !a.mixed_chunks ? 1 : 2;
   int64_t ppw = (periods * a.n_kv_heads * n_leaders_slice + kScoresTargetWgs - 1) / kScoresTargetWgs;
   ppw = ppw < least ? least : (ppw > kScoresMaxPeriods ? kScoresMaxPeriods : ppw);
   int groups = 0;
@@ -291,7 +306,8 @@ int launch_single_scores(ScoreArgs &a, int n_leaders_slice, int batch_slice, hip
     groups += (periods_of(b) + (int)ppw - 1) / (int)ppw;
   }
   dim3 grid(groups, a.n_kv_heads, n_leaders_slice);
-  switch (sums) {
+  if (a.mixed_chunks) hipLaunchKernelGGL((wide ? single_scores_mixed_kernel<4> : single_scores_mixed_kernel<2>), grid, dim3(256), 0, s, a, (int)ppw);
+  else switch (sums) {
     case 4: hipLaunchKernelGGL((wide ? single_scores_kernel<4, 4> : single_scores_kernel<4, 2>), grid, dim3(256), 0, s, a, (int)ppw); break;
     case 8: hipLaunchKernelGGL((wide ? single_scores_kernel<8, 4> : single_scores_kernel<8, 2>), grid, dim3(256), 0, s, a, (int)ppw); break;
     case 16: hipLaunchKernelGGL((wide ? single_scores_kernel<16, 4> : single_scores_kernel<16, 2>), grid, dim3(256), 0, s, a, (int)ppw); break;

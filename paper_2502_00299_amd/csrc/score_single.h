@@ -106,16 +106,15 @@ __device__ __forceinline__ f32x16 mma0(const u32x4 &a, const u32x4 &b, const f32
     return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
 }
 
-// DT: chunkkv_dtype (16-bit), C: chunk size, NQ: 32-row blocks per wavefront (rows_pad = 128 * NQ)
+// DT: chunkkv_dtype (16-bit), C: chunk size, NQ: 32-row blocks per wavefront (rows_pad = 128 * NQ); smem: kSpRingBytes of LDS; a: the
+// kernel's argument
 template <int DT, int C, int NQ>
-__global__ __launch_bounds__(kThreads, 2) void score_single_kernel(ScoreArgs a) {
+__device__ __forceinline__ void score_single_range(const ScoreArgs &a, char *smem) {
   static_assert(is_16bit(DT), "the single-pass kernel takes bf16 or fp16 caches");
   static_assert(kSpHalf % C == 0 && (kSpHalf / C) % 4 == 0 && kSpHalf / C <= 16, "chunk size");
   static_assert(NQ == 1 || NQ == 2, "row blocks per wavefront");
   constexpr int S = kSpHalf / C;  // chunks per lane half and period
   constexpr int ROWB = 256, NKS = 8, ESZ = 2;
-
-  extern __shared__ __align__(16) char smem[];   // kSpRingBytes
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wavefront-uniform, and known to be
@@ -242,7 +241,7 @@ __global__ __launch_bounds__(kThreads, 2) void score_single_kernel(ScoreArgs a) 
   // vector instruction behind the store overwrote them before they were read.
   const uint32_t rp = (uint32_t)a.rows_pad;
   const __amdgpu_buffer_rsrc_t e_rsrc = __builtin_amdgcn_make_buffer_rsrc(
-      (char *)a.e_buf + problem * a.n_periods * a.rows_pad * kPeriodRowBytes, 0, (int)((uint32_t)a.n_periods * rp * (uint32_t)kPeriodRowBytes), 0x00020000);
+      (char *)a.e_buf + problem * a.n_periods * a.rows_pad * a.e_row_bytes, 0, (int)((uint32_t)a.n_periods * rp * (uint32_t)kPeriodRowBytes), 0x00020000);
   const __amdgpu_buffer_rsrc_t m_rsrc = __builtin_amdgcn_make_buffer_rsrc(
       (char *)a.m_period + problem * a.n_periods * a.rows_pad * 4, 0, (int)((uint32_t)a.n_periods * rp * 4u), 0x00020000);
   const uint32_t lane_row = (uint32_t)(row0 + wave * NQ * 32 + n);
@@ -522,10 +521,23 @@ __global__ __launch_bounds__(kThreads, 2) void score_single_kernel(ScoreArgs a) 
 }
 
 template <int DT, int C, int NQ>
-int launch_single_cfg(const ScoreArgs &a, dim3 grid, hipStream_t s) {
-  static std::once_flag once;
-  static hipError_t attr_rc = hipSuccess;
-  auto kern = score_single_kernel<DT, C, NQ>;
+__global__ __launch_bounds__(kThreads, 2) void score_single_kernel(ScoreArgs a) {
+  extern __shared__ __align__(16) char smem[];
+  score_single_range<DT, C, NQ>(a, smem);
+}
+
+// Layers of different chunk sizes in one launch: a workgroup runs the code of its layer's.
+template <int DT, int NQ>
+__global__ __launch_bounds__(kThreads, 2) void score_single_mixed_kernel(ScoreArgs a) {
+  extern __shared__ __align__(16) char smem[];
+  const int c = CKV_ARG(ScoreArgs, chunk_of, blockIdx.z / a.row_groups);
+  if (c == 5) score_single_range<DT, 5, NQ>(a, smem);
+  else if (c == 10) score_single_range<DT, 10, NQ>(a, smem);
+  else score_single_range<DT, 20, NQ>(a, smem);
+}
+
+template <typename Kernel>
+int launch_single(Kernel kern, std::once_flag &once, hipError_t &attr_rc, const ScoreArgs &a, dim3 grid, hipStream_t s) {
   std::call_once(once, [&] {
     attr_rc = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, kSpRingBytes);
   });
@@ -533,12 +545,25 @@ int launch_single_cfg(const ScoreArgs &a, dim3 grid, hipStream_t s) {
   hipLaunchKernelGGL(kern, grid, dim3(kThreads), kSpRingBytes, s, a);
   return hipGetLastError() == hipSuccess ? CHUNKKV_OK : CHUNKKV_ERR_LAUNCH;
 }
+template <int DT, int C, int NQ>
+int launch_single_cfg(const ScoreArgs &a, dim3 grid, hipStream_t s) {
+  static std::once_flag once;
+  static hipError_t attr_rc = hipSuccess;
+  return launch_single(score_single_kernel<DT, C, NQ>, once, attr_rc, a, grid, s);
+}
+template <int DT, int NQ>
+int launch_single_mixed(const ScoreArgs &a, dim3 grid, hipStream_t s) {
+  static std::once_flag once;
+  static hipError_t attr_rc = hipSuccess;
+  return launch_single(score_single_mixed_kernel<DT, NQ>, once, attr_rc, a, grid, s);
+}
 
 // every compiled geometry of one storage type: chunk size x row blocks per wavefront
 template <int DT>
 int launch_single_dt(const ScoreArgs &a, dim3 grid, hipStream_t s) {
   const int nq = a.rows_pad / (128 * a.row_groups);
   if (nq != 1 && nq != 2) return CHUNKKV_ERR_UNSUPPORTED;
+  if (a.mixed_chunks) return nq == 1 ? launch_single_mixed<DT, 1>(a, grid, s) : launch_single_mixed<DT, 2>(a, grid, s);
   switch (a.chunk) {
     case 5: return nq == 1 ? launch_single_cfg<DT, 5, 1>(a, grid, s) : launch_single_cfg<DT, 5, 2>(a, grid, s);
     case 10: return nq == 1 ? launch_single_cfg<DT, 10, 1>(a, grid, s) : launch_single_cfg<DT, 10, 2>(a, grid, s);

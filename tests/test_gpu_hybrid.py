@@ -21,6 +21,10 @@ CASES = {
     "ragged_f32_x6_R3": (W.get_workload("tiny").with_(n_layers=6), 3, [1, 4]),
     "ragged_bf16_x4_R2": (W.get_workload("ragged_b8").with_(seqlens=(1500, 640, 2304), n_spans=(7, 3, 11), n_layers=4,
                                                             keep_pct=30), 2, [33, 2]),
+    # all three single-pass sizes in one launch, 224 rows: ragged, then so few workgroups that two share the rows of a range
+    "ragged_bf16_x6_R1": (W.get_workload("ragged_b8").with_(seqlens=(1500, 640, 2304), n_spans=(7, 3, 11), n_layers=6,
+                                                            keep_pct=20), 1, [5, 20, 10, 5, 10, 20]),
+    "bf16_1k_x2_R1": (W.get_workload("llama8b_128k_stack").with_(seqlens=(1000,), n_spans=(5,), n_layers=2), 1, [20, 5]),
 }
 
 
