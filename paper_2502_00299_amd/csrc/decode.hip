@@ -106,16 +106,15 @@ __device__ __forceinline__ float dot16(const u32x4 &k, const u32x4 &q) {
   }
 }
 
-// DT: chunkkv_dtype, HD: head dim, G: query heads of the kv-head handled by one workgroup
-template <int DT, int HD, int G>
-__global__ __launch_bounds__(kThreads) void decode_kernel(DecodeArgs a) {
+// DT: chunkkv_dtype, HD: head dim, G: query heads of the kv-head handled by one workgroup, NW: its wavefronts
+template <int DT, int HD, int G, int NW>
+__global__ __launch_bounds__(NW * 64) void decode_kernel(DecodeArgs a) {
   constexpr int ESZ = DT == CHUNKKV_F32 ? 4 : 2;
   constexpr int ROWB = HD * ESZ;
   constexpr int LPR = ROWB / 16;   // lanes per row
   constexpr int RPW = 64 / LPR;    // rows per wavefront load
   constexpr int EPL = 16 / ESZ;    // elements per lane
   constexpr int U = kDecodeUnroll;
-  constexpr int NW = kThreads / 64;
 
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int grp = lane / LPR, seg = lane % LPR;
@@ -166,15 +165,27 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(DecodeArgs a) {
   const float c1 = a.scale_log2e;
 
   // rows r0 .. r1-1; a step of the workgroup covers NW * U * RPW consecutive rows
-  for (int base = r0 + wave * (U * RPW); base < r1; base += NW * U * RPW) {
-    u32x4 kr[U], vr[U];
+  constexpr bool kAhead = NW > 4;   // the rows of the next step are on their way while those of this one are worked on
+  u32x4 kr[U], vr[U], kn[U], vn[U];
+  auto load = [&](int base, u32x4 (&k)[U], u32x4 (&v)[U]) __attribute__((always_inline)) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int rowv = base + u * RPW + grp;           // V: register u holds row u
       const int rowk = base + (u ^ ub) * RPW + grp;    // K: register u holds row u ^ ub (ub = 0 without the swizzle)
       // every row is read once: streaming (non-temporal) loads
-      kr[u] = __builtin_nontemporal_load((const u32x4 *)(kbase + (int64_t)(rowk < r1 ? rowk : r1 - 1) * tok));  // r1 >= 1 inside the loop
-      vr[u] = __builtin_nontemporal_load((const u32x4 *)(vbase + (int64_t)(rowv < r1 ? rowv : r1 - 1) * tok));
+      k[u] = __builtin_nontemporal_load((const u32x4 *)(kbase + (int64_t)(rowk < r1 ? rowk : r1 - 1) * tok));  // r1 >= 1: there are rows
+      v[u] = __builtin_nontemporal_load((const u32x4 *)(vbase + (int64_t)(rowv < r1 ? rowv : r1 - 1) * tok));
+    }
+  };
+  const int base0 = r0 + wave * (U * RPW);
+  if (kAhead && base0 < r1) load(base0, kn, vn);
+  for (int base = base0; base < r1; base += NW * U * RPW) {
+    if constexpr (kAhead) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) { kr[u] = kn[u]; vr[u] = vn[u]; }
+      if (base + NW * U * RPW < r1) load(base + NW * U * RPW, kn, vn);
+    } else {
+      load(base, kr, vr);
     }
     if constexpr (kScatter) {
       float x[U][G];
@@ -318,6 +329,14 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(DecodeArgs a) {
 #pragma unroll
         for (int e = 0; e < EPL; ++e) acc[e] += s_o[w][j][sg][e] * f;
       }
+      if (a.cut.n_split == 1) {   // one range per head: no merge kernel follows
+        const int64_t hd = (int64_t)b * a.n_q_heads + (int64_t)h * g + j0 + j;
+        float *out = a.out + hd * HD + sg * EPL;
+#pragma unroll
+        for (int e = 0; e < EPL; ++e) out[e] = Lsum > 0.f ? acc[e] / Lsum : 0.f;
+        if (a.lse != nullptr && sg == 0) a.lse[hd] = Lsum > 0.f ? (M + __builtin_log2f(Lsum)) * 0.6931471805599453f : -__builtin_inff();
+        return;
+      }
       const int64_t slot = (int64_t)CKV_ARG(DecodeArgs, cut.first_split, bl) * a.n_q_heads + ((int64_t)h * g + j0 + j) * CKV_ARG(DecodeArgs, cut.splits, bl) + split;
       if (sg == 0) a.part_ml[slot] = make_float2(M, Lsum);
       float *po = a.part_o + slot * HD + sg * EPL;
@@ -400,16 +419,32 @@ __global__ __launch_bounds__(kCombineThreads) void decode_combine_kernel(DecodeA
 }
 
 // fp32 caches; for 16-bit caches only rows more than 64 MB apart come here, one head at a time
-template <int DT, int HD>
+template <int DT, int HD, int NW, bool FOUR = true>   // FOUR: compiled for four heads per workgroup
 int launch_decode_valu(const DecodeArgs &a, int batch_slice, int g, hipStream_t s) {
   const int G = DT == CHUNKKV_F32 ? decode_heads_per_wg(DT, g) : 1;
   const dim3 grid(a.cut.n_split, batch_slice * a.n_kv_heads, (g + G - 1) / G);
-  if (G == 1) hipLaunchKernelGGL((decode_kernel<DT, HD, 1>), grid, dim3(kThreads), 0, s, a);
+  if (G == 1) hipLaunchKernelGGL((decode_kernel<DT, HD, 1, NW>), grid, dim3(NW * 64), 0, s, a);
   else if constexpr (DT == CHUNKKV_F32) {
-    if (G == 2) hipLaunchKernelGGL((decode_kernel<DT, HD, 2>), grid, dim3(kThreads), 0, s, a);
-    else hipLaunchKernelGGL((decode_kernel<DT, HD, 4>), grid, dim3(kThreads), 0, s, a);
+    if (G == 2) hipLaunchKernelGGL((decode_kernel<DT, HD, 2, NW>), grid, dim3(NW * 64), 0, s, a);
+    else if constexpr (FOUR) hipLaunchKernelGGL((decode_kernel<DT, HD, 4, NW>), grid, dim3(NW * 64), 0, s, a);
+    else return CHUNKKV_ERR_UNSUPPORTED;
   }
   return hipGetLastError() == hipSuccess ? CHUNKKV_OK : CHUNKKV_ERR_LAUNCH;
+}
+
+// Ranges are 256 rows or more, as many as there are places for their partial results, and a step of four wavefronts is 32 rows of 512
+// bytes: few workgroups spent their time waiting for one step after the other.  So up to a workgroup per CU they have 16
+// wavefronts, at d = 128 up to two per CU 8 (8 from the start with four heads, where 16 leave no registers), and read a step ahead.
+// us of a layer, so and with four: 244 tokens of 8 kv-heads 8.3 / 25 (half of the rest is the merge launch, which one range
+// does without), 3350 tokens of 2 12 / 27, five sequences of 300 of 4 kv-heads, 4 heads each 14 / 28.  At d = 64 a step is 64 rows: five sequences of
+// 560 to 3200 tokens 13.2 with eight, 12.3 with four.
+template <int HD>
+int launch_decode_f32(const DecodeArgs &a, int batch_slice, int g, hipStream_t s) {
+  const int G = decode_heads_per_wg(CHUNKKV_F32, g);
+  const int64_t wgs = (int64_t)a.cut.n_split * batch_slice * a.n_kv_heads * ((g + G - 1) / G);
+  if (wgs <= kDecodeCUs && !(HD == 128 && G == 4)) return launch_decode_valu<CHUNKKV_F32, HD, 16, HD != 128>(a, batch_slice, g, s);
+  if (HD == 128 && wgs <= 2 * kDecodeCUs) return launch_decode_valu<CHUNKKV_F32, HD, 8>(a, batch_slice, g, s);
+  return launch_decode_valu<CHUNKKV_F32, HD, 4>(a, batch_slice, g, s);
 }
 
 template <int HD>
@@ -417,11 +452,11 @@ int launch_decode_hd(int dtype, bool matrix_cores, const DecodeArgs &a, int batc
   const int g = a.n_q_heads / a.n_kv_heads;
   int rc;
   if (matrix_cores) rc = launch_decode_mfma(dtype, HD, a, batch_slice, s);
-  else if (dtype == CHUNKKV_BF16) rc = launch_decode_valu<CHUNKKV_BF16, HD>(a, batch_slice, g, s);
-  else if (dtype == CHUNKKV_F16) rc = launch_decode_valu<CHUNKKV_F16, HD>(a, batch_slice, g, s);
-  else rc = launch_decode_valu<CHUNKKV_F32, HD>(a, batch_slice, g, s);
+  else if (dtype == CHUNKKV_BF16) rc = launch_decode_valu<CHUNKKV_BF16, HD, 4>(a, batch_slice, g, s);
+  else if (dtype == CHUNKKV_F16) rc = launch_decode_valu<CHUNKKV_F16, HD, 4>(a, batch_slice, g, s);
+  else rc = launch_decode_f32<HD>(a, batch_slice, g, s);
   if (rc) return rc;
-  if (matrix_cores && a.cut.n_split == 1) return CHUNKKV_OK;   // the range kernel wrote the outputs
+  if (a.cut.n_split == 1) return CHUNKKV_OK;   // the range kernel wrote the outputs
   hipLaunchKernelGGL((decode_combine_kernel<HD>), dim3(a.n_q_heads, batch_slice), dim3(kCombineThreads), 0, s, a);
   return hipGetLastError() == hipSuccess ? CHUNKKV_OK : CHUNKKV_ERR_LAUNCH;
 }
