@@ -23,8 +23,8 @@ constexpr int kMaxRanges = 64;
 // first tiles and end; in pass 1 the merge of eight ranges' statistics.  us of a call, and with about 32 ranges of eight tiles or
 // more and up to 1536 workgroups in pass 1 whatever the rounds are: 12345 tokens, three of eight groups in two passes 198 / 210;
 // 32 layers of 4270 tokens, 64 rows 112 / 133; 59567 tokens in fp32, 256 rows 328 / 358; 32 layers of five sequences of 1379 to 3768
-// tokens, d = 64 85 / 107.  In a launch of many rounds an empty place at the end costs little, and few long walks lose to uneven
-// ones (eight sequences of 7138 to 47085 tokens, 32 rows 248, in one round 266).
+// tokens, d = 64 85 / 107.  In a long launch that memory bounds few long walks lose (eight sequences of 7138 to 47085 tokens, 32 rows
+// 248, in one round 266): there only those of up to kFewRounds rounds are cut anew.
 constexpr double kBlockUs[2] = {0.6, 1.9}, kStartUs = 2.4, kMergeUs = 0.7, kHalfRound[2] = {0.7, 0.75};   // [0]: 16-bit types, [1]: fp32
 constexpr int kFewRounds = 4, kCUs = 256;
 // Single-pass scoring with 256 rows: up to this many workgroups leave half the CUs empty, so two of them, with 128 rows each,
@@ -316,12 +316,14 @@ int run_score(const chunkkv_problem *p, const Plan &pl, const void *const *q, co
     a.heads_first = short_launch;
     const int per_range = short_launch ? 1 : p->n_kv_heads;   // entries of the grid's x or y for one range
     auto grid = [&](int64_t n) { return short_launch ? dim3(p->n_kv_heads, (uint32_t)n, ng) : dim3((uint32_t)(n * p->n_kv_heads), 1, ng); };
-    const int rounds = short_launch ? kTargetWorkgroups / slots : kFewRounds;
+    // Long launches: two rounds or more, and where memory is not what bounds them (65536 tokens, 8 layers, 256 rows with log-sum-exps in 3 whole
+    // rounds 498 us a call, in 6.6 518).
+    const int rounds = short_launch || pl.geom.wq * pl.geom.nqw >= 4 ? kTargetWorkgroups / slots : kFewRounds, least_rounds = short_launch ? -3 : 2;
     if (!lse) {
       const bool merge = short_launch;   // pass 1 merges the row statistics itself
       const int least = merge && pl.tpw0 < ceil_div(most, kMaxRanges) ? ceil_div(most, kMaxRanges) : pl.tpw0;
       auto merging = [&](int t) { return merge ? kMergeUs / tile_us * ceil_div(ceil_div(most, t), 8) : 0.0; };
-      const int tpw0 = units_per_workgroup(least, most, slots, rounds, half, kStartUs / tile_us, [&](int t) {
+      const int tpw0 = units_per_workgroup(least, most, slots, least_rounds, rounds, half, kStartUs / tile_us, [&](int t) {
         int64_t n = 0;
         for (int i = 0; i < nb; ++i) n += ceil_div(ceil_div(a.seq.seqlen[i], TK), t);
         return n * p->n_kv_heads * ng;
@@ -355,7 +357,7 @@ int run_score(const chunkkv_problem *p, const Plan &pl, const void *const *q, co
       for (int i = 0; i < nb; ++i) n += ceil_div(seq_units[i], t);
       return n;
     };
-    a.tiles_per_wg = units_per_workgroup((int)((all1 + kTargetWorkgroups - 1) / kTargetWorkgroups), most1, slots, rounds, half, start1 * TK / a.super_keys,
+    a.tiles_per_wg = units_per_workgroup((int)((all1 + kTargetWorkgroups - 1) / kTargetWorkgroups), most1, slots, least_rounds, rounds, half, start1 * TK / a.super_keys,
                                          [&](int t) { return ranges1(t) * p->n_kv_heads * ng; }, [](int) { return 0.0; });
     for (int i = 0, n = 0; i < nb; ++i) {
       n += ceil_div(seq_units[i], a.tiles_per_wg);

@@ -29,15 +29,16 @@ CKV_HOST_DEVICE int super_stride(int keys, int chunk) { return chunk <= keys ? k
 // workgroups at once, if they run in rounds and a workgroup takes as long as its units and `start` more of them.  In a last round that
 // leaves every second place empty a unit takes `half` as long, as its workgroup has a CU for itself; the start, a chain of
 // latencies, does not.  wgs(t): workgroups of t units; extra(t): what else t costs, in units.  Looked at is the smallest t that
-// fits into an eighth of a round, a quarter and so on up to `rounds` of them; launches of more rounds keep `lo`.
+// fits into r rounds, for r from `least_rounds` (0: half a round, -1: a quarter and so on) to `rounds`; launches of more rounds keep
+// `lo`.
 // Workgroups do not take equally long, which many short ones even out: kUneven of a workgroup's units are lost at the end.
 constexpr double kUneven = 0.1;
 template <typename Count, typename Extra>
-inline int units_per_workgroup(int lo, int hi, int slots, int rounds, double half, double start, Count wgs, Extra extra) {
+inline int units_per_workgroup(int lo, int hi, int slots, int least_rounds, int rounds, double half, double start, Count wgs, Extra extra) {
   if (lo >= hi || wgs(lo) > (int64_t)rounds * slots) return lo;
   int best = lo;
   double least = 1e300;
-  for (int r = -3; r <= rounds; ++r) {
+  for (int r = least_rounds; r <= rounds; ++r) {
     const int64_t target = r <= 0 ? slots >> -r : (int64_t)slots * r;
     int a = lo, b = hi;
     while (a < b) {

@@ -1,4 +1,4 @@
-// With "units": reads "lo hi slots rounds half start n u1 .. un" lines, n sequences of so many units, and prints the units of a
+// With "units": reads "lo hi slots least_rounds rounds half start n u1 .. un" lines, n sequences of so many units, and prints the units of a
 // workgroup and how many workgroups that makes.  With "stride": reads "keys chunk" lines and prints the keys of a super-tile.  Otherwise:
 // walks the ring loads of the single-pass scoring kernel: reads "prefix pitch row_bytes" lines from stdin and, for every
 // period of the sequence and the ones behind it, those with prefix keys present and not, checks what the descriptor of that period lets
@@ -25,9 +25,9 @@ static const char *walk(int prefix, uint32_t pitch, uint32_t row_bytes) {
 }
 
 int main(int argc, char **argv) {
-  int keys, chunk, lo, hi, slots, rounds, n, units[16];
+  int keys, chunk, lo, hi, slots, least, rounds, n, units[16];
   double half, start;
-  while (argc > 1 && argv[1][0] == 'u' && std::scanf("%d %d %d %d %lf %lf %d", &lo, &hi, &slots, &rounds, &half, &start, &n) == 7 && n <= 16) {
+  while (argc > 1 && argv[1][0] == 'u' && std::scanf("%d %d %d %d %d %lf %lf %d", &lo, &hi, &slots, &least, &rounds, &half, &start, &n) == 8 && n <= 16) {
     for (int i = 0; i < n; ++i)
       if (std::scanf("%d", &units[i]) != 1) return 1;
     auto wgs = [&](int t) {
@@ -35,7 +35,7 @@ int main(int argc, char **argv) {
       for (int i = 0; i < n; ++i) w += (units[i] + t - 1) / t;
       return w;
     };
-    const int t = ckv::units_per_workgroup(lo, hi, slots, rounds, half, start, wgs, [](int) { return 0.0; });
+    const int t = ckv::units_per_workgroup(lo, hi, slots, least, rounds, half, start, wgs, [](int) { return 0.0; });
     std::printf("%d %lld\n", t, (long long)wgs(t));
   }
   while (argc > 1 && std::scanf("%d %d", &keys, &chunk) == 2) std::printf("%d\n", ckv::super_stride(keys, chunk));

@@ -43,10 +43,10 @@ def test_workgroups_fill_whole_rounds(ask):
     cases += [(rng.choice([1, 2, 9]), None, [rng.randrange(0, 2000) for _ in range(rng.randrange(1, 17))]) for _ in range(200)]
     lines, want = [], []
     for lo, hi, units in cases:
-        hi, slots, rounds, half, start = max(units) if hi is None else hi, rng.choice([256, 512]), rng.choice([4, 8]), 0.7, rng.choice([0.5, 2.0, 6.0])
-        lines.append(f"{lo} {hi} {slots} {rounds} {half} {start} {len(units)} " + " ".join(map(str, units)))
-        want.append((lo, hi, slots, rounds, half, start, units))
-    for line, (lo, hi, slots, rounds, half, start, units) in zip(ask(lines, "units"), want):
+        hi, slots, least, rounds, half, start = max(units) if hi is None else hi, rng.choice([256, 512]), rng.choice([-3, 2]), rng.choice([4, 8]), 0.7, rng.choice([0.5, 2.0, 6.0])
+        lines.append(f"{lo} {hi} {slots} {least} {rounds} {half} {start} {len(units)} " + " ".join(map(str, units)))
+        want.append((lo, hi, slots, least, rounds, half, start, units))
+    for line, (lo, hi, slots, least, rounds, half, start, units) in zip(ask(lines, "units"), want):
         def wgs(t):
             return sum(-(-u // t) for u in units)
 
@@ -58,5 +58,6 @@ def test_workgroups_fill_whole_rounds(ask):
         if lo >= hi or wgs(lo) > rounds * slots:
             assert t == lo
         else:
-            one = next((x for x in range(lo, hi + 1) if wgs(x) <= slots), hi)
-            assert cost(t) <= cost(one) + 1e-9 and cost(t) <= cost(lo) * (1 + 1e-9) + 1e-9
+            for r in range(max(1, least), rounds + 1):
+                fits = next((x for x in range(lo, hi + 1) if wgs(x) <= r * slots), hi)
+                assert cost(t) <= cost(fits) * (1 + 1e-9)
