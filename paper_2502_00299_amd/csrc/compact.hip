@@ -91,44 +91,58 @@ __global__ __launch_bounds__(kThreads) void compact_kernel(CompactArgs a) {
   const int64_t selrow = ((int64_t)group * a.batch_total + (a.batch0 + bl)) * a.n_kv_heads + h;
   const int32_t *sel_chunk = a.sel_chunk + selrow * a.sel_cap;
   const int32_t *sel_len = a.sel_len + selrow * a.sel_cap;
-  int count = n_keep > 0 ? a.sel_count[selrow] : 0;
-  count = count < 0 ? 0 : (count > a.sel_cap ? a.sel_cap : count);
   const int n_win = (w + c - 1) / c;
   const int e0 = blockIdx.x * ne;
+  // The number of entries, this workgroup's own and the lengths of those before them are read together: the arrays have room for
+  // sel_cap entries, and what lies past the last one is not used.
+  const int e = e0 + lane, own = e < a.sel_cap ? e : 0;
+  int count = n_keep > 0 ? a.sel_count[selrow] : 0;
+  int ch = 0, len = 0, dst = 0;
+  if (wave == 0) {
+    ch = sel_chunk[own];
+    len = sel_len[own];
+    if (a.sel_off != nullptr) dst = a.sel_off[selrow * a.sel_cap + own];
+  }
+  int before[4] = {0, 0, 0, 0};   // this thread's share of the first 4 * kThreads of them, if offsets are not at hand
+  const int most_before = e0 < a.sel_cap ? e0 : a.sel_cap;
+  if (a.sel_off == nullptr) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int i = j * kThreads + threadIdx.x;
+      before[j] = i < most_before ? sel_len[i] : 0;
+    }
+  }
+  count = count < 0 ? 0 : (count > a.sel_cap ? a.sel_cap : count);
   if (e0 >= count + n_win) return;
 
   __shared__ int s_src[kCompactEntries], s_dst[kCompactEntries], s_len[kCompactEntries];
   __shared__ int s_red[kThreads / 64];
   // Token offset of each entry inside the output: the stack call passes the offsets the selection kernel already
   // produced, otherwise the lengths are summed here.
-  int before = 0;   // kept tokens before entry min(e0, count)
+  int kept_before = 0;   // kept tokens before entry min(e0, count)
   if (a.sel_off == nullptr) {
     const int lim = e0 < count ? e0 : count;
-    for (int i0 = 0; i0 < lim; i0 += 4 * kThreads) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) kept_before += (int)(j * kThreads + threadIdx.x) < lim ? before[j] : 0;
+    for (int i0 = 4 * kThreads; i0 < lim; i0 += 4 * kThreads) {
       int x[4];
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const int i = i0 + j * kThreads + threadIdx.x;
         x[j] = i < lim ? sel_len[i] : 0;
       }
-      before += (x[0] + x[1]) + (x[2] + x[3]);
+      kept_before += (x[0] + x[1]) + (x[2] + x[3]);
     }
-    for (int o = 32; o > 0; o >>= 1) before += __shfl_xor(before, o);
-    if (lane == 0) s_red[wave] = before;
+    for (int o = 32; o > 0; o >>= 1) kept_before += __shfl_xor(kept_before, o);
+    if (lane == 0) s_red[wave] = kept_before;
     __syncthreads();
-    before = s_red[0] + s_red[1] + s_red[2] + s_red[3];
+    kept_before = s_red[0] + s_red[1] + s_red[2] + s_red[3];
   }
   if (wave == 0) {
-    const int e = e0 + lane;
     const bool mine = lane < ne && e < count + n_win, chosen = mine && e < count;
-    int ch = 0, len = 0, dst = 0;
-    if (chosen) {
-      ch = sel_chunk[e];
-      len = sel_len[e];
-    }
+    if (!chosen) ch = len = dst = 0;
     int kept = n_keep;   // where the window starts
     if (a.sel_off != nullptr) {
-      if (chosen) dst = a.sel_off[selrow * a.sel_cap + e];
       if (a.whole_chunks) kept = count > 0 ? a.sel_off[selrow * a.sel_cap + count - 1] + sel_len[count - 1] : 0;
     } else {
       int inc = len;
@@ -136,9 +150,9 @@ __global__ __launch_bounds__(kThreads) void compact_kernel(CompactArgs a) {
         const int y = __shfl_up(inc, o);
         if (lane >= o) inc += y;
       }
-      dst = before + inc - len;
+      dst = kept_before + inc - len;
       // a group that holds window entries has seen every selection entry by its last lane
-      if (a.whole_chunks) kept = before + __shfl(inc, 63);
+      if (a.whole_chunks) kept = kept_before + __shfl(inc, 63);
     }
     kept = kept < 0 ? 0 : (kept > n_keep ? n_keep : kept);
     int src = ch * c;
