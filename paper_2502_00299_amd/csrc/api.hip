@@ -36,6 +36,12 @@ constexpr int kSinglePeriodKeys = 160;   // granule of the single-pass kernel's 
 // second stream, which takes longer (the 131072-token stack 2.17 ms in one set, 2.23 in two, 2.45 in eight), so one set it is.
 constexpr int64_t kTilesPerLaunch = 1 << 30;
 
+// Streaming (non-temporal) loads leave the memory-side cache (256 MB) to others.  They are for calls whose K and V are larger than
+// it, where nothing a pass reads is still there for the next; smaller ones lose what they find there.  A per-layer call is one of many,
+// so a third of that.  us of a call, streaming and plain: 32 layers of 32768 tokens 679 / 696, 28 of 17734 97 / 101, 32 calls on 20011
+// 867 / 894; 16 layers of 1477 tokens 24.8 / 23.2, 7 of 47180 (170 MB, d = 64) 57.1 / 55.5, one of 8192 25.4 / 24.1.
+constexpr int64_t kStreamBytes = 192 << 20, kStreamLayerBytes = 64 << 20;
+
 struct Plan {
   ScoreGeom geom;
   int n_leaders, rows_pad;
@@ -144,6 +150,13 @@ bool takes_one_pass(const chunkkv_problem *p, const Plan &pl, int chunk) {
   return !(p->flags & CHUNKKV_FLAG_TWO_PASS) && pl.n_periods_fit && single_pass_ok(p->dtype, p->head_dim, (p->n_q_heads / p->n_kv_heads) * p->window, chunk);
 }
 
+// Are K and V of `layers` layers more than `limit` bytes?
+bool streams(const chunkkv_problem *p, int64_t layers, int64_t limit) {
+  int64_t tokens = 0;
+  for (int b = 0; b < p->batch; ++b) tokens += p->seqlen[b];
+  return 2 * layers * tokens * p->n_kv_heads * p->head_dim * elem_bytes(p->dtype) > limit;
+}
+
 // Workspace layout and key-range split; a pure function of (problem, n_layers, reuse).
 int make_plan(const chunkkv_problem *p, int n_layers, int reuse, Plan *pl) {
   if (n_layers < 1 || reuse < 1) return CHUNKKV_ERR_SHAPE;
@@ -234,7 +247,7 @@ void fill_seq(SeqTable *t, const chunkkv_problem *p, int b0, int nb) {
 // [B][Hq][w] array and only the importance pass runs.
 int run_score(const chunkkv_problem *p, const Plan &pl, const void *const *q, const void *const *k,
               const float *const *lse, int ng, const int32_t *leaders, const int32_t *chunks, float *chunk_scores, float *token_imp,
-              int64_t imp_pitch, char *ws, hipStream_t s) {
+              int64_t imp_pitch, bool stream, char *ws, hipStream_t s) {
   const int TK = pl.geom.tile_keys;
   for (int b0 = 0; b0 < p->batch; b0 += kMaxBatchPerLaunch) {
     const int nb = p->batch - b0 < kMaxBatchPerLaunch ? p->batch - b0 : kMaxBatchPerLaunch;
@@ -275,6 +288,7 @@ int run_score(const chunkkv_problem *p, const Plan &pl, const void *const *q, co
       // one pass over K: per-(chunk, row) sums and the references they are relative to; then the merge of the
       // range statistics and the weighted row sum in one small kernel
       a.n_periods = pl.n_periods;
+      a.stream_k = stream;
       a.e_buf = ws + pl.off_ebuf;
       a.m_period = (float *)(ws + pl.off_mper);
       a.row_stats = (float *)(ws + pl.off_part);
@@ -395,7 +409,7 @@ int run_topk(const chunkkv_problem *p, const int32_t *chunks, const float *chunk
 
 // Arguments of a gather: layers [l0, l0 + nl) and sequences [b0, b0 + nb), of the pointers' first layer on.  chunks[i]: chunk
 // size of the i-th reuse group from that of layer l_begin on.
-void fill_compact(CompactArgs *a, const chunkkv_problem *p, const int32_t *chunks, int l_begin, int l0, int nl, int b0, int nb, int reuse,
+void fill_compact(CompactArgs *a, const chunkkv_problem *p, const int32_t *chunks, int l_begin, int l0, int nl, int b0, int nb, int reuse, bool stream,
                   const void *const *k, const void *const *v, void *const *k_out, void *const *v_out, const int32_t *sel_chunk,
                   const int32_t *sel_len, const int32_t *sel_count, const int32_t *sel_off) {
   memset(a, 0, sizeof(*a));
@@ -411,9 +425,10 @@ void fill_compact(CompactArgs *a, const chunkkv_problem *p, const int32_t *chunk
   a->sel_chunk = sel_chunk; a->sel_len = sel_len; a->sel_count = sel_count; a->sel_off = sel_off;
   a->sel_cap = p->sel_cap;
   a->whole_chunks = (p->flags & CHUNKKV_FLAG_WHOLE_CHUNKS) ? 1 : 0;
+  a->stream = stream;
 }
 
-int run_compact(const chunkkv_problem *p, const int32_t *chunks, int l_begin, int n_layers, int reuse, const void *const *k, const void *const *v,
+int run_compact(const chunkkv_problem *p, const int32_t *chunks, int l_begin, int n_layers, int reuse, bool stream, const void *const *k, const void *const *v,
                 void *const *k_out, void *const *v_out, const int32_t *sel_chunk, const int32_t *sel_len,
                 const int32_t *sel_count, const int32_t *sel_off, hipStream_t s) {
   const int row_bytes = p->head_dim * elem_bytes(p->dtype);
@@ -422,7 +437,7 @@ int run_compact(const chunkkv_problem *p, const int32_t *chunks, int l_begin, in
     for (int b0 = 0; b0 < p->batch; b0 += kMaxBatchPerLaunch) {
       const int nb = p->batch - b0 < kMaxBatchPerLaunch ? p->batch - b0 : kMaxBatchPerLaunch;
       CompactArgs a;
-      fill_compact(&a, p, chunks, l_begin, l0, nl, b0, nb, reuse, k, v, k_out, v_out, sel_chunk, sel_len, sel_count, sel_off);
+      fill_compact(&a, p, chunks, l_begin, l0, nl, b0, nb, reuse, stream, k, v, k_out, v_out, sel_chunk, sel_len, sel_count, sel_off);
       int rc;
       { Timed t(kCompact, s); rc = launch_compact(row_bytes, a, nl, nb, s); }
       if (rc) return rc;
@@ -434,13 +449,13 @@ int run_compact(const chunkkv_problem *p, const int32_t *chunks, int l_begin, in
 // Selection of the reuse groups from that of layer l_begin on and gather of layers [l_begin, l_end) with it: in one launch
 // where one can carry them and that suits the problem.
 int run_selection(const chunkkv_problem *p, const int32_t *chunks, const float *chunk_scores, int group0, int n_groups, int l_begin, int l_end,
-                  int reuse, const void *const *k, const void *const *v, void *const *k_out, void *const *v_out, int32_t *sel_chunk,
+                  int reuse, bool stream, const void *const *k, const void *const *v, void *const *k_out, void *const *v_out, int32_t *sel_chunk,
                   int32_t *sel_len, int32_t *sel_count, int32_t *sel_off, hipStream_t s) {
   const int row_bytes = p->head_dim * elem_bytes(p->dtype), nl = l_end - l_begin;
   int rc;
   if (nl <= kMaxLayersPerLaunch && p->batch <= kMaxBatchPerLaunch) {
     CompactArgs a;
-    fill_compact(&a, p, chunks, l_begin, l_begin, nl, 0, p->batch, reuse, k, v, k_out, v_out, sel_chunk, sel_len, sel_count, sel_off);
+    fill_compact(&a, p, chunks, l_begin, l_begin, nl, 0, p->batch, reuse, stream, k, v, k_out, v_out, sel_chunk, sel_len, sel_count, sel_off);
     const SelectInGather how = select_in_gather(a, nl, p->batch);
     if (how.yes) {
       Timed t(kCompact, s);
@@ -453,7 +468,7 @@ int run_selection(const chunkkv_problem *p, const int32_t *chunks, const float *
   }
   rc = run_topk(p, chunks, chunk_scores, group0, n_groups, sel_chunk, sel_len, sel_count, sel_off, s);
   if (rc) return rc;
-  return run_compact(p, chunks, l_begin, l_end, reuse, k, v, k_out, v_out, sel_chunk, sel_len, sel_count, sel_off, s);
+  return run_compact(p, chunks, l_begin, l_end, reuse, stream, k, v, k_out, v_out, sel_chunk, sel_len, sel_count, sel_off, s);
 }
 
 }  // namespace
@@ -517,7 +532,7 @@ static int score_entry(const chunkkv_problem *prob, const void *q_obs, const voi
   if (!workspace || workspace_bytes < pl.total) return CHUNKKV_ERR_WORKSPACE;
   const int32_t leader = 0;
   return run_score(prob, pl, &q_obs, &k, with_lse ? &lse : nullptr, 1, &leader, &prob->chunk, chunk_scores, token_importance,
-                   (int64_t)prob->score_cap * prob->chunk, (char *)workspace, (hipStream_t)stream);
+                   (int64_t)prob->score_cap * prob->chunk, streams(prob, 1, kStreamBytes), (char *)workspace, (hipStream_t)stream);
 }
 
 int chunkkv_score(const chunkkv_problem *prob, const void *q_obs, const void *k, float *chunk_scores,
@@ -547,7 +562,7 @@ int chunkkv_compact(const chunkkv_problem *prob, const void *k, const void *v, c
   if (rc) return rc;
   if (!k || !v || !sel_chunk || !sel_len || !sel_count || !k_out || !v_out) return CHUNKKV_ERR_NULL;
   if (misaligned(k) || misaligned(v) || misaligned(k_out) || misaligned(v_out)) return CHUNKKV_ERR_SHAPE;
-  return run_compact(prob, &prob->chunk, 0, 1, 1, &k, &v, &k_out, &v_out, sel_chunk, sel_len, sel_count, nullptr,
+  return run_compact(prob, &prob->chunk, 0, 1, 1, streams(prob, 1, kStreamBytes), &k, &v, &k_out, &v_out, sel_chunk, sel_len, sel_count, nullptr,
                      (hipStream_t)stream);
 }
 
@@ -577,6 +592,7 @@ static int stack_groups(const chunkkv_problem *prob, const Plan &pl, int g_begin
                         int32_t *sel_chunk, int32_t *sel_len, int32_t *sel_count, char *ws, hipStream_t s) {
   float *scores = (float *)(ws + pl.off_scores);
   int32_t *sel_off = (int32_t *)(ws + pl.off_seloff);
+  const bool stream = streams(prob, n_layers, kStreamBytes);
   for (int g0 = g_begin; g0 < g_end; g0 += pl.batch_leaders) {
     const int ng = g_end - g0 < pl.batch_leaders ? g_end - g0 : pl.batch_leaders;
     const void *qs[kMaxLayersPerLaunch], *ks[kMaxLayersPerLaunch];
@@ -587,10 +603,10 @@ static int stack_groups(const chunkkv_problem *prob, const Plan &pl, int g_begin
       ls[i] = with_lse ? lse[(g0 + i) * reuse] : nullptr;
       leaders[i] = g0 + i; chunks[i] = prob->chunk;
     }
-    int rc = run_score(prob, pl, qs, ks, with_lse ? ls : nullptr, ng, leaders, chunks, scores, nullptr, 0, ws, s);
+    int rc = run_score(prob, pl, qs, ks, with_lse ? ls : nullptr, ng, leaders, chunks, scores, nullptr, 0, stream, ws, s);
     if (rc) return rc;
     const int l_begin = g0 * reuse, l_end = (g0 + ng) * reuse < n_layers ? (g0 + ng) * reuse : n_layers;
-    rc = run_selection(prob, chunks, scores, g0, ng, l_begin, l_end, reuse, k, v, k_out, v_out, sel_chunk, sel_len, sel_count, sel_off, s);
+    rc = run_selection(prob, chunks, scores, g0, ng, l_begin, l_end, reuse, stream, k, v, k_out, v_out, sel_chunk, sel_len, sel_count, sel_off, s);
     if (rc) return rc;
   }
   return CHUNKKV_OK;
@@ -627,6 +643,7 @@ static int stack_mixed(const chunkkv_problem *prob, const Plan &pl, int32_t n_la
   const int n_groups = pl.n_leaders;
   float *scores = (float *)(ws + pl.off_scores);
   int32_t *sel_off = (int32_t *)(ws + pl.off_seloff);
+  const bool stream = streams(prob, n_layers, kStreamBytes);
   bool done[kMaxLayersPerLaunch] = {};
   for (int first = 0; first < n_groups; ++first) {
     if (done[first]) continue;
@@ -649,10 +666,10 @@ static int stack_mixed(const chunkkv_problem *prob, const Plan &pl, int32_t n_la
       leaders[ng] = g; cs[ng] = chunks[g];
       ++ng;
     }
-    rc = run_score(&run, rp, qs, ks, lse ? ls : nullptr, ng, leaders, cs, scores, nullptr, 0, ws, s);
+    rc = run_score(&run, rp, qs, ks, lse ? ls : nullptr, ng, leaders, cs, scores, nullptr, 0, stream, ws, s);
     if (rc) return rc;
   }
-  return run_selection(prob, chunks, scores, 0, n_groups, 0, n_layers, reuse, k, v, k_out, v_out, sel_chunk, sel_len, sel_count, sel_off, s);
+  return run_selection(prob, chunks, scores, 0, n_groups, 0, n_layers, reuse, stream, k, v, k_out, v_out, sel_chunk, sel_len, sel_count, sel_off, s);
 }
 
 extern "C" {
@@ -750,15 +767,16 @@ int chunkkv_compress_layer(const chunkkv_problem *prob, int32_t layer, int32_t r
   hipStream_t s = (hipStream_t)stream;
   // the kernels see this layer's group as group 0 of arrays that start at the group's rows
   const int64_t row0 = (int64_t)(layer / reuse) * prob->batch * prob->n_kv_heads;
+  const bool stream_loads = streams(prob, 1, kStreamLayerBytes);
   int32_t *sc = sel_chunk + row0 * prob->sel_cap, *sl = sel_len + row0 * prob->sel_cap, *cnt = sel_count + row0;
   if (leader) {
     float *scores = (float *)(ws + pl.off_scores);
     const int32_t leader0 = 0;
-    rc = run_score(prob, pl, &q_obs, &k, lse ? &lse : nullptr, 1, &leader0, &prob->chunk, scores, nullptr, 0, ws, s);
+    rc = run_score(prob, pl, &q_obs, &k, lse ? &lse : nullptr, 1, &leader0, &prob->chunk, scores, nullptr, 0, stream_loads, ws, s);
     if (rc) return rc;
-    return run_selection(prob, &prob->chunk, scores, 0, 1, 0, 1, 1, &k, &v, &k_out, &v_out, sc, sl, cnt, nullptr, s);
+    return run_selection(prob, &prob->chunk, scores, 0, 1, 0, 1, 1, stream_loads, &k, &v, &k_out, &v_out, sc, sl, cnt, nullptr, s);
   }
-  return run_compact(prob, &prob->chunk, 0, 1, 1, &k, &v, &k_out, &v_out, sc, sl, cnt, nullptr, s);
+  return run_compact(prob, &prob->chunk, 0, 1, 1, stream_loads, &k, &v, &k_out, &v_out, sc, sl, cnt, nullptr, s);
 }
 
 int chunkkv_jaccard(const chunkkv_problem *prob, int32_t n_groups, const int32_t *sel_chunk, const int32_t *sel_len,

@@ -5,10 +5,14 @@
 // entries of up to `c` rows) and copies their rows as one flat list of 16-byte segments, K rows first, then V rows:
 // consecutive lanes copy consecutive segments whatever the chunk size is, five segments in flight per lane.  The
 // entries' chunk, length and offset are loaded once, by one wavefront, into LDS.
-// Over a stack the kernel is bound by HBM (copy speed) and a workgroup takes about 160 rows, over a single layer by
+// Stores are streaming (non-temporal): what is written is not read again here, and it would push what is still to be read out of
+// the memory-side cache.  Loads are where the call's caches are larger than that one (CompactArgs::stream).  us of a call, so and with
+// streaming loads, plain stores and 160 rows: 32 layers of 131072 tokens 1963 / 2029, the ragged batch at c = 20 1993 / 2074, 16 layers of 1477
+// tokens 23.2 / 24.5.
+// Over a stack the kernel is bound by HBM (copy speed) and a workgroup takes about 80 rows, over a single layer by
 // the latency of entry -> rows -> stores, and 40 rows (one round of loads) give four times the workgroups:
 // one layer of 20011 tokens, c = 5, keep 20 %, 13.8 -> 9.6 us; two layers of 12345 tokens, c = 1, 23.7 -> 11.3 us, c = 20,
-// 17.5 -> 10.2 us.  A 32-layer stack of 131072 tokens (3.45 GB) takes 626 us = 5.5 TB/s; a plain device
+// 17.5 -> 10.2 us.  A 32-layer stack of 131072 tokens (3.45 GB) took 626 us = 5.5 TB/s with plain stores; a plain device
 // copy of 1 to 4 GiB reaches 4.9 to 5.1.
 // Grid: x = group of entries, y = (sequence, kv-head), z = layer; all layers of the stack are one launch.
 #include "select.h"
@@ -36,7 +40,7 @@ __host__ __device__ inline int compact_entries(int rows, int chunk) {
 
 // Copies the rows of entries [0, n) of the lists (source token, destination token, length) of one layer, sequence and
 // kv-head; ne: entries a workgroup can have.
-template <int NSEG, int T>  // 16-byte segments per row, threads
+template <int NSEG, int T, bool STREAM>  // 16-byte segments per row, threads, streaming loads
 __device__ __forceinline__ void copy_entries(const CompactArgs &a, int layer, int bl, int h, int c, int ne, int n, const int *s_src, const int *s_dst, const int *s_len) {
   const int64_t esz = a.elem_bytes;
   const int64_t base = CKV_ARG(CompactArgs, seq.kv_base, bl), obase = CKV_ARG(CompactArgs, seq.out_base, bl);
@@ -69,18 +73,18 @@ __device__ __forceinline__ void copy_entries(const CompactArgs &a, int layer, in
       const int len = s_len[en];
       const bool live = i < len && u0 + j * T < total;
       i = i < len ? i : 0;
-      // every byte is read once: streaming (non-temporal) loads (measured 2.6 % faster; the same hint on the
-      // stores is 2 % slower)
-      r[j] = __builtin_nontemporal_load((const u32x4 *)((is_v ? vin : kin) + (int64_t)(s_src[en] + i) * in_tok + seg * 16));
+      const u32x4 *from = (const u32x4 *)((is_v ? vin : kin) + (int64_t)(s_src[en] + i) * in_tok + seg * 16);
+      if constexpr (STREAM) r[j] = __builtin_nontemporal_load(from);
+      else r[j] = *from;
       to[j] = live ? (is_v ? vout : kout) + (int64_t)(s_dst[en] + i) * out_tok + seg * 16 : nullptr;
     }
 #pragma unroll
     for (int j = 0; j < 5; ++j)
-      if (to[j] != nullptr) *(u32x4 *)to[j] = r[j];
+      if (to[j] != nullptr) __builtin_nontemporal_store(r[j], (u32x4 *)to[j]);
   }
 }
 
-template <int NSEG>  // 16-byte segments per row
+template <int NSEG, bool STREAM>  // 16-byte segments per row
 __global__ __launch_bounds__(kThreads) void compact_kernel(CompactArgs a) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int bl = blockIdx.y / a.n_kv_heads, h = blockIdx.y % a.n_kv_heads;
@@ -168,13 +172,13 @@ __global__ __launch_bounds__(kThreads) void compact_kernel(CompactArgs a) {
     if (lane < ne) { s_src[lane] = src; s_dst[lane] = dst; s_len[lane] = mine ? len : 0; }
   }
   __syncthreads();
-  copy_entries<NSEG, kThreads>(a, layer, bl, h, c, ne, count + n_win - e0 < ne ? count + n_win - e0 : ne, s_src, s_dst, s_len);
+  copy_entries<NSEG, kThreads, STREAM>(a, layer, bl, h, c, ne, count + n_win - e0 < ne ? count + n_win - e0 : ne, s_src, s_dst, s_len);
 }
 
 // Selection and gather in one launch: every workgroup selects the chunks of its head for itself and keeps the places that
 // are its own; one workgroup per head and reuse group writes the selection out.  For short launches over few chunks, where a
 // dependent launch costs more than the selection's 2 to 5 us.
-template <int NSEG, int T, int KR>
+template <int NSEG, int T, int KR, bool STREAM>
 __global__ __launch_bounds__(T) void select_compact_kernel(CompactArgs a, const float *chunk_scores, int score_cap) {
   const int bl = blockIdx.y / a.n_kv_heads, h = blockIdx.y % a.n_kv_heads, layer = blockIdx.z;
   const int n_keep = CKV_ARG(CompactArgs, seq.n_keep, bl), w = a.window, c = CKV_ARG(CompactArgs, chunk_of, layer);
@@ -199,7 +203,7 @@ __global__ __launch_bounds__(T) void select_compact_kernel(CompactArgs a, const 
   }
   __syncthreads();
   const int n = sel.count + n_win - e0;
-  if (n > 0) copy_entries<NSEG, T>(a, layer, bl, h, c, ne, n < ne ? n : ne, s_src, s_dst, s_len);
+  if (n > 0) copy_entries<NSEG, T, STREAM>(a, layer, bl, h, c, ne, n < ne ? n : ne, s_src, s_dst, s_len);
 }
 
 // Workgroups of a launch with `rows` rows each.
@@ -226,9 +230,9 @@ static GatherGroups gather_groups(const CompactArgs &a, int n_layers_slice, int 
 }
 // Sets the rows of a workgroup: fewer in a launch that would leave CUs without one.
 static GatherGroups choose_rows(CompactArgs &a, int n_layers_slice, int batch_slice) {
-  a.rows_per_wg = 160;
+  a.rows_per_wg = 80;
   GatherGroups g = gather_groups(a, n_layers_slice, batch_slice, a.rows_per_wg);
-  if (g.total >= 4096) return g;
+  if (g.total >= 8192) return g;
   a.rows_per_wg = 40;
   return gather_groups(a, n_layers_slice, batch_slice, a.rows_per_wg);
 }
@@ -237,9 +241,10 @@ int launch_select_compact(int row_bytes, CompactArgs &a, int n_layers_slice, int
                           const SelectInGather &how, hipStream_t s) {
   a.rows_per_wg = how.rows_per_wg;
   const dim3 grid(how.groups, batch_slice * a.n_kv_heads, n_layers_slice), block(how.wide ? 1024 : kThreads);
-#define CKV_SELECT(NSEG) \
-  hipLaunchKernelGGL((how.wide ? select_compact_kernel<NSEG, 1024, 4> : how.chunks <= kSelectCompactFewChunks ? select_compact_kernel<NSEG, kThreads, 1> : select_compact_kernel<NSEG, kThreads, 4>), \
+#define CKV_SELECT_AS(NSEG, STREAM) \
+  hipLaunchKernelGGL((how.wide ? select_compact_kernel<NSEG, 1024, 4, STREAM> : how.chunks <= kSelectCompactFewChunks ? select_compact_kernel<NSEG, kThreads, 1, STREAM> : select_compact_kernel<NSEG, kThreads, 4, STREAM>), \
                      grid, block, 0, s, a, chunk_scores, score_cap)
+#define CKV_SELECT(NSEG) do { if (a.stream) CKV_SELECT_AS(NSEG, true); else CKV_SELECT_AS(NSEG, false); } while (0)
   switch (row_bytes / 16) {
     case 8: CKV_SELECT(8); break;
     case 16: CKV_SELECT(16); break;
@@ -247,6 +252,7 @@ int launch_select_compact(int row_bytes, CompactArgs &a, int n_layers_slice, int
     default: return CHUNKKV_ERR_UNSUPPORTED;
   }
 #undef CKV_SELECT
+#undef CKV_SELECT_AS
   return hipGetLastError() == hipSuccess ? CHUNKKV_OK : CHUNKKV_ERR_LAUNCH;
 }
 
@@ -270,9 +276,9 @@ SelectInGather select_in_gather(CompactArgs &a, int n_layers_slice, int batch_sl
 int launch_compact(int row_bytes, CompactArgs &a, int n_layers_slice, int batch_slice, hipStream_t s) {
   const dim3 grid(choose_rows(a, n_layers_slice, batch_slice).most, batch_slice * a.n_kv_heads, n_layers_slice);
   switch (row_bytes / 16) {
-    case 8: hipLaunchKernelGGL(compact_kernel<8>, grid, dim3(kThreads), 0, s, a); break;
-    case 16: hipLaunchKernelGGL(compact_kernel<16>, grid, dim3(kThreads), 0, s, a); break;
-    case 32: hipLaunchKernelGGL(compact_kernel<32>, grid, dim3(kThreads), 0, s, a); break;
+    case 8: hipLaunchKernelGGL((a.stream ? compact_kernel<8, true> : compact_kernel<8, false>), grid, dim3(kThreads), 0, s, a); break;
+    case 16: hipLaunchKernelGGL((a.stream ? compact_kernel<16, true> : compact_kernel<16, false>), grid, dim3(kThreads), 0, s, a); break;
+    case 32: hipLaunchKernelGGL((a.stream ? compact_kernel<32, true> : compact_kernel<32, false>), grid, dim3(kThreads), 0, s, a); break;
     default: return CHUNKKV_ERR_UNSUPPORTED;
   }
   return hipGetLastError() == hipSuccess ? CHUNKKV_OK : CHUNKKV_ERR_LAUNCH;

@@ -71,6 +71,7 @@ struct ScoreArgs {
   int32_t row_groups;      // workgroups that share the rows of a key range (1 or 2)
   int32_t e_row_bytes;     // of e_buf, per period and row of a problem: the most of any layer
   int32_t mixed_chunks;    // 1: the layers' chunk sizes differ
+  int32_t stream_k;        // 1: K is read with streaming (non-temporal) loads
 };
 
 struct TopkArgs {
@@ -100,6 +101,7 @@ struct CompactArgs {
   int32_t sel_cap;
   int32_t rows_per_wg;        // chosen by the launcher: rows a workgroup copies, in whole entries
   int32_t whole_chunks;       // 1: the window follows the kept tokens directly (their count varies per head)
+  int32_t stream;             // 1: rows are read with streaming (non-temporal) loads
 };
 
 // Decode attention over one layer's cache (decode.hip).  Per-head partial results use the FULL batch index.

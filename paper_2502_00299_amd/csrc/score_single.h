@@ -106,9 +106,9 @@ __device__ __forceinline__ f32x16 mma0(const u32x4 &a, const u32x4 &b, const f32
     return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
 }
 
-// DT: chunkkv_dtype (16-bit), C: chunk size, NQ: 32-row blocks per wavefront (rows_pad = 128 * NQ); smem: kSpRingBytes of LDS; a: the
-// kernel's argument
-template <int DT, int C, int NQ>
+// DT: chunkkv_dtype (16-bit), C: chunk size, NQ: 32-row blocks per wavefront (rows_pad = 128 * NQ), STREAM: streaming loads of K; smem:
+// kSpRingBytes of LDS; a: the kernel's argument
+template <int DT, int C, int NQ, bool STREAM>
 __device__ __forceinline__ void score_single_range(const ScoreArgs &a, char *smem) {
   static_assert(is_16bit(DT), "the single-pass kernel takes bf16 or fp16 caches");
   static_assert(kSpHalf % C == 0 && (kSpHalf / C) % 4 == 0 && kSpHalf / C <= 16, "chunk size");
@@ -162,8 +162,8 @@ __device__ __forceinline__ void score_single_range(const ScoreArgs &a, char *sme
     const RingRows rows = ring_rows(range0 + prel * kSpPeriod, P, (uint32_t)ktok, ROWB, prel < np);  // wavefront-uniform
     const __amdgpu_buffer_rsrc_t krsrc = __builtin_amdgcn_make_buffer_rsrc((void *)kbase, 0, (int)rows.records, 0x00020000);
     char *dst = smem + (prel & 1) * kSpPeriodBytes + wave * 2048 + T * kSpStepBytes;
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(krsrc, (__attribute__((address_space(3))) void *)dst, 16, klane[T], rows.offset, 0, 0);
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(krsrc, (__attribute__((address_space(3))) void *)(dst + 1024), 16, klane[T] + kdelta, rows.offset, 0, 0);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(krsrc, (__attribute__((address_space(3))) void *)dst, 16, klane[T], rows.offset, 0, STREAM ? kNonTemporal : 0);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(krsrc, (__attribute__((address_space(3))) void *)(dst + 1024), 16, klane[T] + kdelta, rows.offset, 0, STREAM ? kNonTemporal : 0);
   };
   // The window queries come through the ring as well (a row block is 8 KB, like a step): read straight into operand
   // fragments, every load would touch 32 lines, 10 thousand cycles for 64 KB.  The first steps of K share the way.
@@ -520,20 +520,20 @@ __device__ __forceinline__ void score_single_range(const ScoreArgs &a, char *sme
   __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));   // the empty loads past the last step still write zeros into the ring
 }
 
-template <int DT, int C, int NQ>
+template <int DT, int C, int NQ, bool STREAM>
 __global__ __launch_bounds__(kThreads, 2) void score_single_kernel(ScoreArgs a) {
   extern __shared__ __align__(16) char smem[];
-  score_single_range<DT, C, NQ>(a, smem);
+  score_single_range<DT, C, NQ, STREAM>(a, smem);
 }
 
 // Layers of different chunk sizes in one launch: a workgroup runs the code of its layer's.
-template <int DT, int NQ>
+template <int DT, int NQ, bool STREAM>
 __global__ __launch_bounds__(kThreads, 2) void score_single_mixed_kernel(ScoreArgs a) {
   extern __shared__ __align__(16) char smem[];
   const int c = CKV_ARG(ScoreArgs, chunk_of, blockIdx.z / a.row_groups);
-  if (c == 5) score_single_range<DT, 5, NQ>(a, smem);
-  else if (c == 10) score_single_range<DT, 10, NQ>(a, smem);
-  else score_single_range<DT, 20, NQ>(a, smem);
+  if (c == 5) score_single_range<DT, 5, NQ, STREAM>(a, smem);
+  else if (c == 10) score_single_range<DT, 10, NQ, STREAM>(a, smem);
+  else score_single_range<DT, 20, NQ, STREAM>(a, smem);
 }
 
 template <typename Kernel>
@@ -545,31 +545,36 @@ int launch_single(Kernel kern, std::once_flag &once, hipError_t &attr_rc, const 
   hipLaunchKernelGGL(kern, grid, dim3(kThreads), kSpRingBytes, s, a);
   return hipGetLastError() == hipSuccess ? CHUNKKV_OK : CHUNKKV_ERR_LAUNCH;
 }
-template <int DT, int C, int NQ>
+template <int DT, int C, int NQ, bool STREAM>
 int launch_single_cfg(const ScoreArgs &a, dim3 grid, hipStream_t s) {
   static std::once_flag once;
   static hipError_t attr_rc = hipSuccess;
-  return launch_single(score_single_kernel<DT, C, NQ>, once, attr_rc, a, grid, s);
+  return launch_single(score_single_kernel<DT, C, NQ, STREAM>, once, attr_rc, a, grid, s);
 }
-template <int DT, int NQ>
+template <int DT, int NQ, bool STREAM>
 int launch_single_mixed(const ScoreArgs &a, dim3 grid, hipStream_t s) {
   static std::once_flag once;
   static hipError_t attr_rc = hipSuccess;
-  return launch_single(score_single_mixed_kernel<DT, NQ>, once, attr_rc, a, grid, s);
+  return launch_single(score_single_mixed_kernel<DT, NQ, STREAM>, once, attr_rc, a, grid, s);
 }
 
-// every compiled geometry of one storage type: chunk size x row blocks per wavefront
+// every compiled geometry of one storage type: chunk size x row blocks per wavefront x streaming loads
+template <int DT, int NQ, bool STREAM>
+int launch_single_chunk(const ScoreArgs &a, dim3 grid, hipStream_t s) {
+  if (a.mixed_chunks) return launch_single_mixed<DT, NQ, STREAM>(a, grid, s);
+  switch (a.chunk) {
+    case 5: return launch_single_cfg<DT, 5, NQ, STREAM>(a, grid, s);
+    case 10: return launch_single_cfg<DT, 10, NQ, STREAM>(a, grid, s);
+    case 20: return launch_single_cfg<DT, 20, NQ, STREAM>(a, grid, s);
+    default: return CHUNKKV_ERR_UNSUPPORTED;
+  }
+}
 template <int DT>
 int launch_single_dt(const ScoreArgs &a, dim3 grid, hipStream_t s) {
   const int nq = a.rows_pad / (128 * a.row_groups);
-  if (nq != 1 && nq != 2) return CHUNKKV_ERR_UNSUPPORTED;
-  if (a.mixed_chunks) return nq == 1 ? launch_single_mixed<DT, 1>(a, grid, s) : launch_single_mixed<DT, 2>(a, grid, s);
-  switch (a.chunk) {
-    case 5: return nq == 1 ? launch_single_cfg<DT, 5, 1>(a, grid, s) : launch_single_cfg<DT, 5, 2>(a, grid, s);
-    case 10: return nq == 1 ? launch_single_cfg<DT, 10, 1>(a, grid, s) : launch_single_cfg<DT, 10, 2>(a, grid, s);
-    case 20: return nq == 1 ? launch_single_cfg<DT, 20, 1>(a, grid, s) : launch_single_cfg<DT, 20, 2>(a, grid, s);
-    default: return CHUNKKV_ERR_UNSUPPORTED;
-  }
+  if (nq == 1) return a.stream_k ? launch_single_chunk<DT, 1, true>(a, grid, s) : launch_single_chunk<DT, 1, false>(a, grid, s);
+  if (nq == 2) return a.stream_k ? launch_single_chunk<DT, 2, true>(a, grid, s) : launch_single_chunk<DT, 2, false>(a, grid, s);
+  return CHUNKKV_ERR_UNSUPPORTED;
 }
 
 }  // namespace ckv
