@@ -12,8 +12,8 @@
 // Over a stack the kernel is bound by HBM (copy speed) and a workgroup takes about 80 rows, over a single layer by
 // the latency of entry -> rows -> stores, and 40 rows (one round of loads) give four times the workgroups:
 // one layer of 20011 tokens, c = 5, keep 20 %, 13.8 -> 9.6 us; two layers of 12345 tokens, c = 1, 23.7 -> 11.3 us, c = 20,
-// 17.5 -> 10.2 us.  A 32-layer stack of 131072 tokens (3.45 GB) took 626 us = 5.5 TB/s with plain stores; a plain device
-// copy of 1 to 4 GiB reaches 4.9 to 5.1.
+// 17.5 -> 10.2 us.  A 32-layer stack of 131072 tokens (3.45 GB) takes 599 us = 5.8 TB/s, with plain stores 626; a plain
+// device copy of 1 to 4 GiB reaches 4.9 to 5.1.
 // Grid: x = group of entries, y = (sequence, kv-head), z = layer; all layers of the stack are one launch.
 #include "select.h"
 
