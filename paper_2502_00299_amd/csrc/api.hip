@@ -10,14 +10,13 @@
 namespace ckv {
 namespace {
 
-constexpr int kTargetWorkgroups = 4096;  // ~4 resident rounds of 2 workgroups on each of 256 CUs
+constexpr int kTargetWorkgroups = 4096;  // eight rounds of 2 workgroups on each of 256 CUs
 // Two-pass scoring of up to this many key tiles: pass 1 merges the row statistics of the ranges itself, every workgroup for
 // itself while its first tiles travel.  A kernel in between took 5 us, and 9 to 49 for one layer of a hundred ranges or more:
 // 16000 tokens 34.3 -> 28.9 us a call, 19000 with 64 rows 66 -> 42, 120602 in fp32 288 -> 234.  Above it that kernel is a
-// percent or two and merging everywhere more (10 layers of 109334 tokens, 224 rows 906 us, 947 merged).
+// percent or two and merging everywhere more (10 layers of 109334 tokens, 224 rows 906 us, 947 merged).  A layer of up to so many
+// tiles has at most kMaxRanges ranges.
 constexpr int64_t kMergeTiles = 16384;
-// So there are at most kMaxRanges ranges.
-constexpr int kMaxRanges = 64;
 // How the two passes are cut into workgroups (units_per_workgroup in score_plan.h): whole rounds, as far as a launch has few.  What
 // a workgroup costs, in microseconds: a 32-key block against 32 rows with two workgroups on the CU; beside its tiles start, queries,
 // first tiles and end; in pass 1 the merge of eight ranges' statistics.  us of a call, and with about 32 ranges of eight tiles or
@@ -46,10 +45,10 @@ struct Plan {
   ScoreGeom geom;
   int n_leaders, rows_pad;
   int batch_leaders;  // leader layers scored per launch set
-  int tpw0, max_split0;   // two-pass scoring: least tiles of a key range, most ranges
   int fuse_chunks;
   // single-pass path: usable for this problem?  geometry and workspace
   int single_ok, n_periods_fit, rows_pad_s, n_periods, max_split_s;
+  size_t part_bytes;      // of the region at off_part
   size_t off_part, off_refs, off_scores, off_seloff, off_imp, off_ebuf, off_mper, total;
 };
 
@@ -157,7 +156,51 @@ bool streams(const chunkkv_problem *p, int64_t layers, int64_t limit) {
   return 2 * layers * tokens * p->n_kv_heads * p->head_dim * elem_bytes(p->dtype) > limit;
 }
 
-// Workspace layout and key-range split; a pure function of (problem, n_layers, reuse).
+// How a pass of the two is cut into workgroups.
+struct PassCut {
+  int slots;            // workgroups on the chip at once
+  int rounds, least_rounds;
+  double half, tile_us;   // of units_per_workgroup; what a workgroup's tile costs
+};
+PassCut pass_cut(const chunkkv_problem *p, const ScoreGeom &g, bool short_launch) {
+  const int f32 = p->dtype == CHUNKKV_F32 ? 1 : 0, blocks = g.tile_keys / 32, key_waves = 4 / g.wq < blocks ? 4 / g.wq : blocks;
+  PassCut c;
+  c.slots = score_workgroups_per_cu(p->dtype, p->head_dim, g) * kCUs;
+  // Long launches: two rounds or more, and where memory is not what bounds them (65536 tokens, 8 layers, 256 rows with log-sum-exps in 3 whole
+  // rounds 498 us a call, in 6.6 518).
+  c.rounds = short_launch || g.wq * g.nqw >= 4 ? kTargetWorkgroups / c.slots : kFewRounds;
+  c.least_rounds = short_launch ? -3 : 2;
+  c.half = c.slots == kCUs ? 1.0 : kHalfRound[f32];
+  c.tile_us = (double)(blocks / key_waves) * g.nqw * kBlockUs[f32];
+  return c;
+}
+
+// Key tiles of a range of pass 0 for the sequences b0 .. b0 + nb - 1: what cuts ONE layer of them best.  A function of the sequences and
+// the geometry, as the ranges of the single-pass kernel are, so that the row references, and with them every rounding of a score, do not
+// depend on how many layers share a launch: the stack call and the per-layer calls agree bit for bit.  In a launch of many layers a
+// workgroup walks several ranges, in whole rounds.  us of a call, so and with ranges chosen per launch, which saves statistics, their
+// merge and sets of layers: 32 layers of 20873 tokens, 4 heads 358 / 338; 3 of 40842 193 / 180; 6 of 6343 63.6 / 60.4; one layer the same.
+int stats_range_tiles(const chunkkv_problem *p, const ScoreGeom &g, int b0, int nb) {
+  int64_t all = 0, tiles = 0;
+  int most = 1;
+  for (int b = 0; b < p->batch; ++b) all += ceil_div(p->seqlen[b], g.tile_keys);
+  for (int b = b0; b < b0 + nb; ++b) {
+    const int t = ceil_div(p->seqlen[b], g.tile_keys);
+    tiles += t;
+    most = t > most ? t : most;
+  }
+  int least = (int)((all * p->n_kv_heads + kTargetWorkgroups - 1) / kTargetWorkgroups);
+  const bool merge = tiles * p->n_kv_heads <= kMergeTiles;
+  if (merge && least < ceil_div(most, kMaxRanges)) least = ceil_div(most, kMaxRanges);
+  const PassCut c = pass_cut(p, g, merge);
+  return units_per_workgroup(least, most, c.slots, c.least_rounds, c.rounds, c.half, kStartUs / c.tile_us, [&](int t) {
+    int64_t n = 0;
+    for (int b = b0; b < b0 + nb; ++b) n += ceil_div(ceil_div(p->seqlen[b], g.tile_keys), t);
+    return n * p->n_kv_heads;
+  }, [&](int t) { return merge ? kMergeUs / c.tile_us * ceil_div(ceil_div(most, t), 8) : 0.0; });
+}
+
+// Workspace layout; a pure function of (problem, n_layers, reuse).
 int make_plan(const chunkkv_problem *p, int n_layers, int reuse, Plan *pl) {
   if (n_layers < 1 || reuse < 1) return CHUNKKV_ERR_SHAPE;
   const int rows = (p->n_q_heads / p->n_kv_heads) * p->window;
@@ -179,12 +222,14 @@ int make_plan(const chunkkv_problem *p, int n_layers, int reuse, Plan *pl) {
   const int nsets = ceil_div(pl->n_leaders, gb);
   pl->batch_leaders = ceil_div(pl->n_leaders, nsets);
   const int64_t heads = (int64_t)pl->batch_leaders * p->n_kv_heads;
-  pl->tpw0 = (int)((tiles0 * heads + kTargetWorkgroups - 1) / kTargetWorkgroups);
-  if (pl->tpw0 < 1) pl->tpw0 = 1;
-  pl->max_split0 = 1;   // room for the ranges' pairs
+  // Room for the pairs of pass 0: about kTargetWorkgroups ranges of every set of layers, the longest sequence's number of them for every
+  // sequence.  That is room for the ranges of one layer at least (n times ceil(t / ceil(n x)) is no less than ceil(t / ceil(x)), and
+  // a layer's ranges have ceil(x) tiles or more), and pass 0 is launched over as many layers at a time as fit.
+  const int tiles_even = (int)((tiles0 * heads + kTargetWorkgroups - 1) / kTargetWorkgroups);
+  int max_split0 = 1;
   for (int b = 0; b < p->batch; ++b) {
-    const int s = ceil_div(ceil_div(p->seqlen[b], TK), pl->tpw0);
-    if (s > pl->max_split0) pl->max_split0 = s;
+    const int s = ceil_div(ceil_div(p->seqlen[b], TK), tiles_even);
+    if (s > max_split0) max_split0 = s;
   }
   // single-pass path
   pl->rows_pad_s = rows > 128 ? 256 : 128;
@@ -208,13 +253,13 @@ int make_plan(const chunkkv_problem *p, int n_layers, int reuse, Plan *pl) {
     }
   }
   const size_t problems = (size_t)pl->n_leaders * p->batch * p->n_kv_heads;
-  size_t part_bytes = problems * pl->max_split0 * pl->rows_pad * sizeof(float2);
+  pl->part_bytes = problems * max_split0 * pl->rows_pad * sizeof(float2);
   if (pl->single_ok) {
     const size_t pb = problems * room * pl->rows_pad_s * sizeof(float2);
-    part_bytes = pb > part_bytes ? pb : part_bytes;
+    pl->part_bytes = pb > pl->part_bytes ? pb : pl->part_bytes;
   }
   size_t off = 0;
-  pl->off_part = off;   off += align256(part_bytes);
+  pl->off_part = off;   off += align256(pl->part_bytes);
   pl->off_refs = off;   off += align256(problems * pl->rows_pad * sizeof(float));
   pl->off_scores = off; off += align256(problems * (size_t)p->score_cap * sizeof(float));
   pl->off_seloff = off; off += align256(problems * (size_t)p->sel_cap * sizeof(int32_t));
@@ -261,7 +306,7 @@ int run_score(const chunkkv_problem *p, const Plan &pl, const void *const *q, co
     a.kv_stride_head = p->kv_stride_head; a.kv_stride_tok = p->kv_stride_tok;
     const float scale = p->softmax_scale > 0.f ? p->softmax_scale : 1.0f / sqrtf((float)p->head_dim);
     a.scale_log2e = scale * 1.4426950408889634f;
-    a.max_split = pl.max_split0; a.rows_pad = pl.rows_pad;
+    a.rows_pad = pl.rows_pad;
     a.part_stats = (float2 *)(ws + pl.off_part);
     a.refs = (float *)(ws + pl.off_refs);
     a.chunk_scores = chunk_scores; a.score_cap = p->score_cap;
@@ -312,50 +357,54 @@ int run_score(const chunkkv_problem *p, const Plan &pl, const void *const *q, co
       if (rc) return rc;
       continue;
     }
-    const int slots = score_workgroups_per_cu(p->dtype, p->head_dim, pl.geom) * kCUs, f32 = p->dtype == CHUNKKV_F32 ? 1 : 0;
-    const double half = slots == kCUs ? 1.0 : kHalfRound[f32];
-    const int blocks = TK / 32, key_waves = 4 / pl.geom.wq < blocks ? 4 / pl.geom.wq : blocks;
-    const double tile_us = (double)(blocks / key_waves) * pl.geom.nqw * kBlockUs[f32];
-    double start1 = kStartUs / tile_us;
     int64_t tiles = 0;
-    int most = 1, ranges = 0;   // tiles of the longest sequence, ranges of all
+    int most = 1;   // tiles of the longest sequence
     for (int i = 0; i < nb; ++i) {
       const int t = ceil_div(a.seq.seqlen[i], TK);
       tiles += t;
       most = t > most ? t : most;
     }
     const bool short_launch = tiles * p->n_kv_heads * ng <= kMergeTiles;
+    const PassCut cut = pass_cut(p, pl.geom, short_launch);
+    double start1 = kStartUs / cut.tile_us;
     // Neighbours are the heads of one range in short launches (one layer of 23344 tokens, 32 rows 37.9 us, the ranges of one head
     // 43.0), the ranges of one head in longer ones (packed, 32 layers of 3812 and 12202 tokens, 8 heads of 16 rows 332, heads 359).
     a.heads_first = short_launch;
     const int per_range = short_launch ? 1 : p->n_kv_heads;   // entries of the grid's x or y for one range
-    auto grid = [&](int64_t n) { return short_launch ? dim3(p->n_kv_heads, (uint32_t)n, ng) : dim3((uint32_t)(n * p->n_kv_heads), 1, ng); };
-    // Long launches: two rounds or more, and where memory is not what bounds them (65536 tokens, 8 layers, 256 rows with log-sum-exps in 3 whole
-    // rounds 498 us a call, in 6.6 518).
-    const int rounds = short_launch || pl.geom.wq * pl.geom.nqw >= 4 ? kTargetWorkgroups / slots : kFewRounds, least_rounds = short_launch ? -3 : 2;
+    auto grid = [&](int64_t n, int layers) { return short_launch ? dim3(p->n_kv_heads, (uint32_t)n, layers) : dim3((uint32_t)(n * p->n_kv_heads), 1, layers); };
     if (!lse) {
-      const bool merge = short_launch;   // pass 1 merges the row statistics itself
-      const int least = merge && pl.tpw0 < ceil_div(most, kMaxRanges) ? ceil_div(most, kMaxRanges) : pl.tpw0;
-      auto merging = [&](int t) { return merge ? kMergeUs / tile_us * ceil_div(ceil_div(most, t), 8) : 0.0; };
-      const int tpw0 = units_per_workgroup(least, most, slots, least_rounds, rounds, half, kStartUs / tile_us, [&](int t) {
-        int64_t n = 0;
-        for (int i = 0; i < nb; ++i) n += ceil_div(ceil_div(a.seq.seqlen[i], TK), t);
-        return n * p->n_kv_heads * ng;
-      }, merging);
-      for (int i = 0; i < nb; ++i) {
-        ranges += ceil_div(ceil_div(a.seq.seqlen[i], TK), tpw0);
-        a.first_range[i + 1] = ranges * per_range;
-      }
-      a.tiles_per_wg = tpw0;
-      { Timed t(kStats, s); rc = launch_score_pass(0, p->dtype, p->head_dim, pl.geom, a, grid(ranges), s); }
-      if (rc) return rc;
-      if (merge) {
-        a.stats_tiles = tpw0;
-        start1 += merging(tpw0);
-      } else {
-        { Timed t(kCombine, s); rc = launch_stats_combine(a, ng, nb, TK, s); }
+      a.range_tiles = stats_range_tiles(p, pl.geom, b0, nb);
+      a.max_split = ceil_div(most, a.range_tiles);
+      a.batch_slice = nb;
+      // layers whose pairs fit the workspace
+      const int64_t fit = (int64_t)(pl.part_bytes / sizeof(float2)) / ((int64_t)nb * p->n_kv_heads * a.max_split * a.rows_pad);
+      if (fit < 1) return CHUNKKV_ERR_WORKSPACE;
+      const int sets = (int)((ng + fit - 1) / fit), per_set = ceil_div(ng, sets);
+      a.merge_stats = short_launch && sets == 1;   // else a kernel between the passes does, set by set
+      for (int z0 = 0; z0 < ng; z0 += per_set) {
+        const int nz = ng - z0 < per_set ? ng - z0 : per_set;
+        ScoreArgs set = a;
+        for (int i = 0; i < nz; ++i) { set.q[i] = a.q[z0 + i]; set.k[i] = a.k[z0 + i]; set.leader[i] = a.leader[z0 + i]; }
+        auto wgs = [&](int n) {   // of n ranges
+          int64_t all = 0;
+          for (int i = 0; i < nb; ++i) all += ceil_div(ceil_div(ceil_div(a.seq.seqlen[i], TK), a.range_tiles), n);
+          return all;
+        };
+        const int least = (int)((tiles * p->n_kv_heads * nz + kTargetWorkgroups - 1) / kTargetWorkgroups);
+        set.ranges_per_wg = units_per_workgroup(ceil_div(least, a.range_tiles), a.max_split, cut.slots, cut.least_rounds, cut.rounds, cut.half,
+                                                kStartUs / cut.tile_us / a.range_tiles, [&](int n) { return wgs(n) * p->n_kv_heads * nz; }, [](int) { return 0.0; });
+        for (int i = 0, n = 0; i < nb; ++i) {
+          n += ceil_div(ceil_div(ceil_div(a.seq.seqlen[i], TK), a.range_tiles), set.ranges_per_wg);
+          set.first_range[i + 1] = n * per_range;
+        }
+        { Timed t(kStats, s); rc = launch_score_pass(0, p->dtype, p->head_dim, pl.geom, set, grid(wgs(set.ranges_per_wg), nz), s); }
         if (rc) return rc;
+        if (!a.merge_stats) {
+          { Timed t(kCombine, s); rc = launch_stats_combine(set, nz, nb, TK, s); }
+          if (rc) return rc;
+        }
       }
+      if (a.merge_stats) start1 += kMergeUs / cut.tile_us * ceil_div(a.max_split, 8);
     }
     if (units1 == 0) continue;   // no prefix: nothing to sum
     // super-tiles of a sequence: those of the layer with most, which differ where chunk sizes do
@@ -371,13 +420,13 @@ int run_score(const chunkkv_problem *p, const Plan &pl, const void *const *q, co
       for (int i = 0; i < nb; ++i) n += ceil_div(seq_units[i], t);
       return n;
     };
-    a.tiles_per_wg = units_per_workgroup((int)((all1 + kTargetWorkgroups - 1) / kTargetWorkgroups), most1, slots, least_rounds, rounds, half, start1 * TK / a.super_keys,
+    a.tiles_per_wg = units_per_workgroup((int)((all1 + kTargetWorkgroups - 1) / kTargetWorkgroups), most1, cut.slots, cut.least_rounds, cut.rounds, cut.half, start1 * TK / a.super_keys,
                                          [&](int t) { return ranges1(t) * p->n_kv_heads * ng; }, [](int) { return 0.0; });
     for (int i = 0, n = 0; i < nb; ++i) {
       n += ceil_div(seq_units[i], a.tiles_per_wg);
       a.first_range[i + 1] = n * per_range;
     }
-    { Timed t(kColsum, s); rc = launch_score_pass(1, p->dtype, p->head_dim, pl.geom, a, grid(ranges1(a.tiles_per_wg)), s); }
+    { Timed t(kColsum, s); rc = launch_score_pass(1, p->dtype, p->head_dim, pl.geom, a, grid(ranges1(a.tiles_per_wg), ng), s); }
     if (rc) return rc;
     if (!pl.fuse_chunks) {
       { Timed t(kChunkSums, s); rc = launch_chunk_sums(a, ng, nb, s); }
@@ -652,7 +701,7 @@ static int stack_mixed(const chunkkv_problem *prob, const Plan &pl, int32_t n_la
     Plan rp;
     int rc = make_plan(&run, n_layers, reuse, &rp);
     if (rc) return rc;
-    rp.off_part = pl.off_part; rp.off_refs = pl.off_refs; rp.off_scores = pl.off_scores; rp.off_seloff = pl.off_seloff;
+    rp.part_bytes = pl.part_bytes; rp.off_part = pl.off_part; rp.off_refs = pl.off_refs; rp.off_scores = pl.off_scores; rp.off_seloff = pl.off_seloff;
     rp.off_imp = pl.off_imp; rp.off_ebuf = pl.off_ebuf; rp.off_mper = pl.off_mper;
     auto one_pass = [&](int c) { return !lse && takes_one_pass(prob, pl, c); };
     const void *qs[kMaxLayersPerLaunch], *ks[kMaxLayersPerLaunch];

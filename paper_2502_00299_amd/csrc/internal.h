@@ -17,6 +17,7 @@ constexpr int kTileBytes = 16384;        // one K tile staged in LDS (ring slot)
 constexpr int kSuperKeys = 256;        // most keys per importance / chunk-sum step of pass 1 (several tiles)
 constexpr int kThreads = 256;            // 4 wavefronts of 64
 constexpr int kMaxRows = 512;            // g * w limit
+constexpr int kMaxRanges = 64;           // two passes: most key ranges of a sequence whose statistics pass 1 merges
 constexpr int kCompactEntries = 64;      // most selection entries per compaction workgroup
 
 // Per-sequence metadata of one launch slice (<= kMaxBatchPerLaunch sequences).
@@ -40,7 +41,10 @@ struct ScoreArgs {
   int32_t n_q_heads, n_kv_heads, window, chunk;   // chunk: of all slice layers, unless theirs may differ (importance pass, mixed_chunks)
   int64_t kv_stride_head, kv_stride_tok;
   float scale_log2e;       // softmax scale * log2(e)
-  int32_t tiles_per_wg;    // pass 0: key tiles, pass 1: super-tiles each workgroup walks
+  int32_t tiles_per_wg;    // pass 1: super-tiles each workgroup walks
+  int32_t range_tiles;     // two passes: key tiles of a key range of pass 0
+  int32_t ranges_per_wg;   // pass 0: key ranges each workgroup walks
+  int32_t batch_slice;     // sequences of this slice
   // Number of the first key range (the reduction: group of periods) of every sequence, INT32_MAX past the last one; two passes
   // without heads_first: of its first workgroup.  The grids count the ranges of all sequences, so there are no empty workgroups:
   // these go to the XCDs, and there to the shader engines, in turn, and with a row of the grid as long as the longest sequence
@@ -49,9 +53,9 @@ struct ScoreArgs {
   // (16 ranges for the long one instead of 32: 108), eight of up to 20300 at c = 20 49 / 61 (59).
   int32_t first_range[kMaxBatchPerLaunch + 1];   // two passes: and the end of the last one
   int32_t heads_first;     // two passes: neighbouring workgroups are 1: heads of one range, 0: ranges of one head
-  int32_t max_split;       // pitch of part_stats in splits
+  int32_t max_split;       // pitch of part_stats and row_stats in ranges
   int32_t rows_pad;        // g*w rounded up to 32
-  float2 *part_stats;      // [problem][max_split][rows_pad]  (running max, sum) in log2 units
+  float2 *part_stats;      // [slice layer][slice sequence][Hkv][max_split][rows_pad]  (running max, sum) in log2 units
   float *refs;             // [problem][rows_pad]  max + log2(sum), where pass 1 does not merge; single pass: [problem][g * window]
                            // reference of the last key range's sum
   float *chunk_scores;     // [leader][batch_total][Hkv][score_cap]
@@ -60,7 +64,7 @@ struct ScoreArgs {
   int64_t imp_pitch;
   const float *lse[kMaxLayersPerLaunch];  // pass 1 with use_lse: per leader layer [batch_total][Hq][w], natural log
   int32_t use_lse;
-  int32_t stats_tiles;     // pass 1: > 0 = merge the pairs of pass 0 here; key tiles of one of its ranges
+  int32_t merge_stats;     // pass 1: 1 = merge the pairs of pass 0 here
   int32_t super_keys;      // pass 1: super-tiles of at most this many keys, or of one chunk
   int32_t fuse_chunks;     // pass 1: 1 = super-tiles hold whole chunks and chunk sums are written
   // single-pass path (score_single.h): key ranges are single_periods_per_range() whole periods of 160 keys
@@ -192,6 +196,35 @@ __device__ __forceinline__ float merge_row_stats(const float *sums, const float 
     for (int i = 0; i < kRowStatsAhead; ++i) {
       if (i % 4 == 0 && s0 + i >= n) break;
       l += s0 + i < n ? y[i] * __builtin_amdgcn_exp2f(x[i] - mm) : 0.f;
+    }
+    m = mm;
+  }
+  return m + __builtin_log2f(l);
+}
+
+// max + log2(sum) of a row's (max, sum) pairs, in range order, kPairsAhead loads in flight (16000 tokens, d = 64, 32 ranges 26.5 us a
+// call, with eight 27.6)
+constexpr int kPairsAhead = 16;
+__device__ __forceinline__ float merge_pairs(const float2 *ps, int n, int pitch) {
+  float m = -1.0e30f, l = 0.f;
+  for (int s0 = 0; s0 < n; s0 += kPairsAhead) {
+    float2 x[kPairsAhead];
+#pragma unroll
+    for (int i = 0; i < kPairsAhead; ++i) {
+      if (i % 4 == 0 && s0 + i >= n) break;
+      x[i] = ps[(int64_t)(s0 + i < n ? s0 + i : n - 1) * pitch];
+    }
+    float mm = m;
+#pragma unroll
+    for (int i = 0; i < kPairsAhead; ++i) {
+      if (i % 4 == 0 && s0 + i >= n) break;
+      mm = fmaxf(mm, x[i].x);
+    }
+    l *= __builtin_amdgcn_exp2f(m - mm);
+#pragma unroll
+    for (int i = 0; i < kPairsAhead; ++i) {
+      if (i % 4 == 0 && s0 + i >= n) break;
+      l += s0 + i < n ? x[i].y * __builtin_amdgcn_exp2f(x[i].x - mm) : 0.f;
     }
     m = mm;
   }

@@ -81,35 +81,6 @@ __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_s_barrier();
 }
 
-// max + log2(sum) of a row's (max, sum) pairs, in range order, kPairsAhead loads in flight (16000 tokens, d = 64, 32 ranges 26.5 us a
-// call, with eight 27.6)
-constexpr int kPairsAhead = 16;
-__device__ __forceinline__ float merge_pairs(const float2 *ps, int n, int pitch) {
-  float m = kNegBig, l = 0.f;
-  for (int s0 = 0; s0 < n; s0 += kPairsAhead) {
-    float2 x[kPairsAhead];
-#pragma unroll
-    for (int i = 0; i < kPairsAhead; ++i) {
-      if (i % 4 == 0 && s0 + i >= n) break;
-      x[i] = ps[(int64_t)(s0 + i < n ? s0 + i : n - 1) * pitch];
-    }
-    float mm = m;
-#pragma unroll
-    for (int i = 0; i < kPairsAhead; ++i) {
-      if (i % 4 == 0 && s0 + i >= n) break;
-      mm = fmaxf(mm, x[i].x);
-    }
-    l *= fast_exp2(m - mm);
-#pragma unroll
-    for (int i = 0; i < kPairsAhead; ++i) {
-      if (i % 4 == 0 && s0 + i >= n) break;
-      l += s0 + i < n ? x[i].y * fast_exp2(x[i].x - mm) : 0.f;
-    }
-    m = mm;
-  }
-  return m + __builtin_log2f(l);
-}
-
 // DT: chunkkv_dtype, HD: head dim, NQW: 32-row blocks per wavefront, WQ: wavefronts splitting the rows.
 // Two workgroups per CU, except where the operand fragments alone need more than half the register file
 // (four row blocks per wavefront; fp32 operands at head_dim 128).
@@ -146,6 +117,7 @@ __global__ __launch_bounds__(kThreads, ((NQW >= 4 || (DT == CHUNKKV_F32 && HD ==
   const int g = a.n_q_heads / a.n_kv_heads, w = a.window, c = PASS == 1 ? CKV_ARG(ScoreArgs, chunk_of, z) : 1;
   const int L = CKV_ARG(ScoreArgs, seq.seqlen, bl), P = L - w, nrows = g * w;
   const int64_t problem = ((int64_t)CKV_ARG(ScoreArgs, leader, z) * a.batch_total + (a.batch0 + bl)) * a.n_kv_heads + h;
+  float2 *pairs = a.part_stats + (((int64_t)z * a.batch_slice + bl) * a.n_kv_heads + h) * a.max_split * a.rows_pad;   // of this problem
 
   // Work units: pass 0 walks tiles of TK keys over [0, L); pass 1 walks super-tiles over [0, P), each
   // advancing `sstride` keys (a multiple of c when chunk sums are fused) and made of `spt` tiles.
@@ -153,8 +125,8 @@ __global__ __launch_bounds__(kThreads, ((NQW >= 4 || (DT == CHUNKKV_F32 && HD ==
   const int spt = (sstride + TK - 1) / TK;
   const int span = PASS == 0 ? L : P;
   const int nunits = (span + sstride - 1) / sstride;
-  const int u0 = split * a.tiles_per_wg;
-  const int u1 = u0 + a.tiles_per_wg < nunits ? u0 + a.tiles_per_wg : nunits;
+  const int units = PASS == 0 ? a.ranges_per_wg * a.range_tiles : a.tiles_per_wg, u0 = split * units;
+  const int u1 = u0 + units < nunits ? u0 + units : nunits;
   if (u0 >= nunits) return;
   // tiles of this workgroup, numbered 0..nt-1: tile i belongs to unit u0 + i/spt, position i%spt;
   // the last unit stops at the end of the span
@@ -233,7 +205,9 @@ __global__ __launch_bounds__(kThreads, ((NQW >= 4 || (DT == CHUNKKV_F32 && HD ==
     }
   }
 
-  // pass 0 state: running (max, sum) of the lane's row and the last key the row may see
+  // pass 0 state: running (max, sum) of the lane's row over the key range, the range, its tiles still to come, and the last key the
+  // row may see
+  int range = PASS == 0 ? split * a.ranges_per_wg : 0, range_left = a.range_tiles;
   float m_run[NQW], l_run[NQW];
   int lim[NQW];
 #pragma unroll
@@ -244,16 +218,16 @@ __global__ __launch_bounds__(kThreads, ((NQW >= 4 || (DT == CHUNKKV_F32 && HD ==
     lim[qi] = P + (row < nrows ? row % w : 0);
   }
   // pass 1: accumulator start values, so that acc*c1 = logit*c1 - ref (padding rows end at -1e30).  The reference is the
-  // caller's log-sum-exp, or (stats_tiles) merged from the key ranges' pairs while the first tiles travel, or what
+  // caller's log-sum-exp, or (merge_stats) merged from the key ranges' pairs while the first tiles travel, or what
   // stats_combine_kernel made of them
   if constexpr (PASS == 1) {
     const float *lse = a.use_lse ? CKV_ARG(ScoreArgs, lse, z) + ((int64_t)(a.batch0 + bl) * a.n_q_heads + (int64_t)h * g) * w : nullptr;
-    const int ranges = a.stats_tiles > 0 ? ((L + TK - 1) / TK + a.stats_tiles - 1) / a.stats_tiles : 0;
+    const int ranges = a.merge_stats ? ((L + TK - 1) / TK + a.range_tiles - 1) / a.range_tiles : 0;
     for (int r = tid; r < WQ * NQW * 32; r += kThreads) {
       float start = kNegBig;
       if (r < nrows) {
         if (lse != nullptr) start = -(lse[r] * 1.4426950408889634f);
-        else if (ranges > 0) start = -merge_pairs(a.part_stats + problem * a.max_split * a.rows_pad + r, ranges, a.rows_pad);
+        else if (ranges > 0) start = -merge_pairs(pairs + r, ranges, a.rows_pad);
         else start = -a.refs[problem * a.rows_pad + r];
       }
       s_start[r] = start / c1;
@@ -310,6 +284,42 @@ __global__ __launch_bounds__(kThreads, ((NQW >= 4 || (DT == CHUNKKV_F32 && HD ==
       colsum += __shfl_xor(colsum, 32);
       if (half == 0) s_part[wq * kSuperKeys + (i % spt) * TK + kb * 32 + n] = colsum;
     }
+  };
+
+  // pass 0, after the epilogue of the last key block of a key range: its pair of every row, and a fresh start
+  auto end_of_range = [&](int b) __attribute__((always_inline)) {
+    if ((b + 1) % KPW != 0 || (--range_left > 0 && b + 1 < nblk)) return;
+    // [4 wavefronts][32 rows] maxima, then sums, in turn: the barrier of the next range is behind every read of this one's.
+    // (As floats: before accesses as float2 the compiler waits for the tiles in flight.)
+    float *s_max = s_part + (range & 1) * 256, *s_sum = s_max + 128;
+#pragma unroll
+    for (int qi = 0; qi < NQW; ++qi) {
+      // merge the two lane halves (same row, different keys)
+      const float m_o = __shfl_xor(m_run[qi], 32), l_o = __shfl_xor(l_run[qi], 32);
+      float m = fmaxf(m_run[qi], m_o);
+      float l = l_run[qi] * fast_exp2(m_run[qi] - m) + l_o * fast_exp2(m_o - m);
+      m_run[qi] = kNegBig;
+      l_run[qi] = 0.f;
+      if constexpr (4 / WQ > 1) {
+        // NQW == 1 here: merge the wavefronts that split the keys (idle ones carry (-big, 0))
+        if (half == 0) {
+          s_max[wave * 32 + n] = m;
+          s_sum[wave * 32 + n] = l;
+        }
+        lds_barrier();
+        if (wk == 0) {
+          for (int o = 1; o < 4 / WQ; ++o) {
+            const float mo = s_max[(o * WQ + wq) * 32 + n], lo = s_sum[(o * WQ + wq) * 32 + n];
+            const float mm = fmaxf(m, mo);
+            l = l * fast_exp2(m - mm) + lo * fast_exp2(mo - mm);
+            m = mm;
+          }
+        }
+      }
+      if (wk == 0 && half == 0) pairs[(int64_t)range * a.rows_pad + (wq * NQW + qi) * 32 + n] = make_float2(m, l);
+    }
+    ++range;
+    range_left = a.range_tiles;
   };
 
   // pass 1, after the epilogue of the last key block of a super-tile: importance, then chunk sums
@@ -443,7 +453,11 @@ __global__ __launch_bounds__(kThreads, ((NQW >= 4 || (DT == CHUNKKV_F32 && HD ==
   step(0, accA, accB, std::false_type{}, std::false_type{});
   for (int b = 1; b < nblk; b += 2) {
     run_step(b, accB, accA);
-    if (b + 1 < nblk) run_step(b + 1, accA, accB);
+    if constexpr (PASS == 0) end_of_range(b - 1);
+    if (b + 1 < nblk) {
+      run_step(b + 1, accA, accB);
+      if constexpr (PASS == 0) end_of_range(b);
+    }
   }
   auto last_epilogue = [&](f32x16 (&last)[NQW]) {
     if (block_masked(nblk - 1)) epilogue(last, nblk - 1, std::true_type{});
@@ -453,35 +467,8 @@ __global__ __launch_bounds__(kThreads, ((NQW >= 4 || (DT == CHUNKKV_F32 && HD ==
     if ((nblk - 1) % 2 == 0) last_epilogue(accA);
     else last_epilogue(accB);
   }
-  flush_if_unit_done(nblk - 1);
-
-  if constexpr (PASS == 0) {
-    float2 *s_st = (float2 *)s_part;  // [4 wavefronts][32 rows]
-#pragma unroll
-    for (int qi = 0; qi < NQW; ++qi) {
-      // merge the two lane halves (same row, different keys)
-      const float m_o = __shfl_xor(m_run[qi], 32), l_o = __shfl_xor(l_run[qi], 32);
-      float m = fmaxf(m_run[qi], m_o);
-      float l = l_run[qi] * fast_exp2(m_run[qi] - m) + l_o * fast_exp2(m_o - m);
-      if constexpr (4 / WQ > 1) {
-        // NQW == 1 here: merge the wavefronts that split the keys (idle ones carry (-big, 0))
-        if (half == 0) s_st[wave * 32 + n] = make_float2(m, l);
-        __syncthreads();
-        if (wk == 0) {
-          for (int o = 1; o < 4 / WQ; ++o) {
-            const float2 x = s_st[(o * WQ + wq) * 32 + n];
-            const float mm = fmaxf(m, x.x);
-            l = l * fast_exp2(m - mm) + x.y * fast_exp2(x.x - mm);
-            m = mm;
-          }
-        }
-      }
-      if (wk == 0 && half == 0) {
-        const int row = (wq * NQW + qi) * 32 + n;
-        a.part_stats[(problem * a.max_split + split) * a.rows_pad + row] = make_float2(m, l);
-      }
-    }
-  }
+  if constexpr (PASS == 0) end_of_range(nblk - 1);
+  else flush_if_unit_done(nblk - 1);
 }
 
 template <int DT, int HD, int NQW, int WQ>

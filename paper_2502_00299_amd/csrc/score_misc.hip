@@ -50,10 +50,10 @@ int launch_score_single(int dtype, const ScoreArgs &a, dim3 grid, hipStream_t s)
   return CHUNKKV_ERR_UNSUPPORTED;
 }
 
-// ref_r = max_r + log2(sum_r) over all key ranges of a problem.  Four lanes share a row: each merges a
+// ref_r = max_r + log2(sum_r) over all key ranges of a problem.  Up to kMaxRanges ranges as the second pass does it where it merges the
+// pairs itself, in launches of fewer rounds of workgroups: the same bits.  More of them: four lanes share a row, each merges a
 // quarter of the ranges in one pass ((m, l) pairs merge associatively), then the four partial pairs are
-// merged with two shuffles, always in the same order, kCombineAhead pairs of a lane in flight.  For launches of several
-// rounds of workgroups: in shorter ones the second pass merges the pairs itself.
+// merged with two shuffles, always in the same order, kCombineAhead pairs of a lane in flight.
 // grid: x = (sequence, kv-head), y = leader, z = block of 64 rows; 256 threads.
 constexpr int kCombineAhead = 8;
 __global__ __launch_bounds__(256) void stats_combine_kernel(ScoreArgs a, int tile_keys) {
@@ -61,11 +61,15 @@ __global__ __launch_bounds__(256) void stats_combine_kernel(ScoreArgs a, int til
   const int64_t problem = ((int64_t)CKV_ARG(ScoreArgs, leader, z) * a.batch_total + (a.batch0 + bl)) * a.n_kv_heads + h;
   const int L = CKV_ARG(ScoreArgs, seq.seqlen, bl);
   const int ntiles = (L + tile_keys - 1) / tile_keys;
-  const int nsplit = (ntiles + a.tiles_per_wg - 1) / a.tiles_per_wg;
+  const int nsplit = (ntiles + a.range_tiles - 1) / a.range_tiles;
   const int part = threadIdx.x & 3;
   const int row = blockIdx.z * 64 + (threadIdx.x >> 2);  // rows_pad is a multiple of 32; rows past it are skipped below
   const bool live = row < a.rows_pad;
-  const float2 *ps = a.part_stats + problem * a.max_split * a.rows_pad + (live ? row : 0);
+  const float2 *ps = a.part_stats + (((int64_t)z * a.batch_slice + bl) * a.n_kv_heads + h) * a.max_split * a.rows_pad + (live ? row : 0);
+  if (nsplit <= kMaxRanges) {
+    if (live && part == 0) a.refs[problem * a.rows_pad + row] = merge_pairs(ps, nsplit, a.rows_pad);
+    return;
+  }
   float m = -1.0e30f, l = 0.f;
   for (int s0 = part; s0 < nsplit; s0 += 4 * kCombineAhead) {
     float2 x[kCombineAhead];
