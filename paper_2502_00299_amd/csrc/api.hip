@@ -162,10 +162,10 @@ struct PassCut {
   int rounds, least_rounds;
   double half, tile_us;   // of units_per_workgroup; what a workgroup's tile costs
 };
-PassCut pass_cut(const chunkkv_problem *p, const ScoreGeom &g, bool short_launch) {
+PassCut pass_cut(const chunkkv_problem *p, const ScoreGeom &g, int pass, bool short_launch) {
   const int f32 = p->dtype == CHUNKKV_F32 ? 1 : 0, blocks = g.tile_keys / 32, key_waves = 4 / g.wq < blocks ? 4 / g.wq : blocks;
   PassCut c;
-  c.slots = score_workgroups_per_cu(p->dtype, p->head_dim, g) * kCUs;
+  c.slots = score_workgroups_per_cu(p->dtype, p->head_dim, g.nqw, g.wq, pass) * kCUs;
   // Long launches: two rounds or more, and where memory is not what bounds them (65536 tokens, 8 layers, 256 rows with log-sum-exps in 3 whole
   // rounds 498 us a call, in 6.6 518).
   c.rounds = short_launch || g.wq * g.nqw >= 4 ? kTargetWorkgroups / c.slots : kFewRounds;
@@ -192,7 +192,7 @@ int stats_range_tiles(const chunkkv_problem *p, const ScoreGeom &g, int b0, int 
   int least = (int)((all * p->n_kv_heads + kTargetWorkgroups - 1) / kTargetWorkgroups);
   const bool merge = tiles * p->n_kv_heads <= kMergeTiles;
   if (merge && least < ceil_div(most, kMaxRanges)) least = ceil_div(most, kMaxRanges);
-  const PassCut c = pass_cut(p, g, merge);
+  const PassCut c = pass_cut(p, g, 0, merge);
   return units_per_workgroup(least, most, c.slots, c.least_rounds, c.rounds, c.half, kStartUs / c.tile_us, [&](int t) {
     int64_t n = 0;
     for (int b = b0; b < b0 + nb; ++b) n += ceil_div(ceil_div(p->seqlen[b], g.tile_keys), t);
@@ -365,8 +365,8 @@ int run_score(const chunkkv_problem *p, const Plan &pl, const void *const *q, co
       most = t > most ? t : most;
     }
     const bool short_launch = tiles * p->n_kv_heads * ng <= kMergeTiles;
-    const PassCut cut = pass_cut(p, pl.geom, short_launch);
-    double start1 = kStartUs / cut.tile_us;
+    const PassCut cut0 = pass_cut(p, pl.geom, 0, short_launch), cut1 = pass_cut(p, pl.geom, 1, short_launch);
+    double start1 = kStartUs / cut1.tile_us;
     // Neighbours are the heads of one range in short launches (one layer of 23344 tokens, 32 rows 37.9 us, the ranges of one head
     // 43.0), the ranges of one head in longer ones (packed, 32 layers of 3812 and 12202 tokens, 8 heads of 16 rows 332, heads 359).
     a.heads_first = short_launch;
@@ -391,8 +391,8 @@ int run_score(const chunkkv_problem *p, const Plan &pl, const void *const *q, co
           return all;
         };
         const int least = (int)((tiles * p->n_kv_heads * nz + kTargetWorkgroups - 1) / kTargetWorkgroups);
-        set.ranges_per_wg = units_per_workgroup(ceil_div(least, a.range_tiles), a.max_split, cut.slots, cut.least_rounds, cut.rounds, cut.half,
-                                                kStartUs / cut.tile_us / a.range_tiles, [&](int n) { return wgs(n) * p->n_kv_heads * nz; }, [](int) { return 0.0; });
+        set.ranges_per_wg = units_per_workgroup(ceil_div(least, a.range_tiles), a.max_split, cut0.slots, cut0.least_rounds, cut0.rounds, cut0.half,
+                                                kStartUs / cut0.tile_us / a.range_tiles, [&](int n) { return wgs(n) * p->n_kv_heads * nz; }, [](int) { return 0.0; });
         for (int i = 0, n = 0; i < nb; ++i) {
           n += ceil_div(ceil_div(ceil_div(a.seq.seqlen[i], TK), a.range_tiles), set.ranges_per_wg);
           set.first_range[i + 1] = n * per_range;
@@ -404,7 +404,7 @@ int run_score(const chunkkv_problem *p, const Plan &pl, const void *const *q, co
           if (rc) return rc;
         }
       }
-      if (a.merge_stats) start1 += kMergeUs / cut.tile_us * ceil_div(a.max_split, 8);
+      if (a.merge_stats) start1 += kMergeUs / cut1.tile_us * ceil_div(a.max_split, 8);
     }
     if (units1 == 0) continue;   // no prefix: nothing to sum
     // super-tiles of a sequence: those of the layer with most, which differ where chunk sizes do
@@ -420,7 +420,7 @@ int run_score(const chunkkv_problem *p, const Plan &pl, const void *const *q, co
       for (int i = 0; i < nb; ++i) n += ceil_div(seq_units[i], t);
       return n;
     };
-    a.tiles_per_wg = units_per_workgroup((int)((all1 + kTargetWorkgroups - 1) / kTargetWorkgroups), most1, cut.slots, cut.least_rounds, cut.rounds, cut.half, start1 * TK / a.super_keys,
+    a.tiles_per_wg = units_per_workgroup((int)((all1 + kTargetWorkgroups - 1) / kTargetWorkgroups), most1, cut1.slots, cut1.least_rounds, cut1.rounds, cut1.half, start1 * TK / a.super_keys,
                                          [&](int t) { return ranges1(t) * p->n_kv_heads * ng; }, [](int) { return 0.0; });
     for (int i = 0, n = 0; i < nb; ++i) {
       n += ceil_div(seq_units[i], a.tiles_per_wg);

@@ -250,7 +250,13 @@ struct ScoreGeom {
   int wq;          // wavefronts splitting the rows (the other 4/wq split keys)
 };
 bool score_geometry(int dtype, int head_dim, int rows, ScoreGeom *g);
-int score_workgroups_per_cu(int dtype, int head_dim, const ScoreGeom &g);   // of the two passes
+// Workgroups of a pass (0 or 1) of the two that a CU holds: what the kernels are compiled for, and what their launches are cut for.  Two
+// (73 KB of LDS each), except where half the register file does not do: four row blocks per wavefront, and fp32 operands at head_dim
+// 128 with two of them or, in pass 0, with up to 64 rows (60 bytes of scratch).
+constexpr int score_workgroups_per_cu(int dtype, int head_dim, int nqw, int wq, int pass) {
+  if (dtype == CHUNKKV_F32 && head_dim == 128) return nqw == 1 && (pass == 1 || wq == 4) ? 2 : 1;
+  return nqw >= 4 ? 1 : 2;
+}
 
 // Launchers (each checks hipGetLastError and returns a chunkkv_status).
 int launch_score_pass(int pass, int dtype, int head_dim, const ScoreGeom &g, const ScoreArgs &a,

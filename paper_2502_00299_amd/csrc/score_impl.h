@@ -82,10 +82,8 @@ __device__ __forceinline__ void lds_barrier() {
 }
 
 // DT: chunkkv_dtype, HD: head dim, NQW: 32-row blocks per wavefront, WQ: wavefronts splitting the rows.
-// Two workgroups per CU, except where the operand fragments alone need more than half the register file
-// (four row blocks per wavefront; fp32 operands at head_dim 128).
 template <int DT, int HD, int NQW, int WQ, int PASS>
-__global__ __launch_bounds__(kThreads, ((NQW >= 4 || (DT == CHUNKKV_F32 && HD == 128)) ? 1 : 2)) void score_kernel(ScoreArgs a) {
+__global__ __launch_bounds__(kThreads, score_workgroups_per_cu(DT, HD, NQW, WQ, PASS)) void score_kernel(ScoreArgs a) {
   constexpr int ESZ = is_16bit(DT) ? 2 : 4;
   constexpr int ROWB = HD * ESZ;
   constexpr int NSEG = ROWB / 16;

@@ -26,8 +26,6 @@ bool score_geometry(int dtype, int head_dim, int rows, ScoreGeom *g) {
   return true;
 }
 
-int score_workgroups_per_cu(int dtype, int head_dim, const ScoreGeom &g) { return g.nqw >= 4 || (dtype == CHUNKKV_F32 && head_dim == 128) ? 1 : 2; }
-
 int launch_score_pass(int pass, int dtype, int head_dim, const ScoreGeom &g, const ScoreArgs &a, dim3 grid,
                       hipStream_t s) {
   if (grid.x == 0 || grid.y == 0 || grid.z == 0) return CHUNKKV_OK;
