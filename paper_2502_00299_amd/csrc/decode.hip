@@ -118,8 +118,10 @@ __global__ __launch_bounds__(NW * 64) void decode_kernel(DecodeArgs a) {
 
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int grp = lane / LPR, seg = lane % LPR;
-  const int bl = blockIdx.y / a.n_kv_heads, h = blockIdx.y % a.n_kv_heads;
-  const int split = blockIdx.x;
+  const int h = blockIdx.y;
+  int bl = 0, split = blockIdx.x;   // range of any sequence: no workgroups beyond the ranges of a short one
+  while (bl + 1 < kMaxBatchPerLaunch && (int)blockIdx.x >= CKV_ARG(DecodeArgs, cut.first_split, bl + 1)) ++bl;
+  if (bl > 0) split -= CKV_ARG(DecodeArgs, cut.first_split, bl);
   const int g = a.n_q_heads / a.n_kv_heads;
   const int j0 = blockIdx.z * G;  // first query head (within the kv-head's group) of this workgroup
   const int b = a.batch0 + bl;
@@ -300,7 +302,7 @@ __global__ __launch_bounds__(NW * 64) void decode_kernel(DecodeArgs a) {
       m[j] = M;
     }
   }
-  // merge the wavefronts through LDS: thread (j, seg) folds the four states in wavefront order
+  // merge the wavefronts through LDS: thread (j, seg) folds the states in wavefront order
   __shared__ float s_m[NW][G][LPR], s_l[NW][G][LPR], s_o[NW][G][LPR][EPL];
   if (grp == 0) {
 #pragma unroll
@@ -422,7 +424,7 @@ __global__ __launch_bounds__(kCombineThreads) void decode_combine_kernel(DecodeA
 template <int DT, int HD, int NW, bool FOUR = true>   // FOUR: compiled for four heads per workgroup
 int launch_decode_valu(const DecodeArgs &a, int batch_slice, int g, hipStream_t s) {
   const int G = DT == CHUNKKV_F32 ? decode_heads_per_wg(DT, g) : 1;
-  const dim3 grid(a.cut.n_split, batch_slice * a.n_kv_heads, (g + G - 1) / G);
+  const dim3 grid(a.cut.first_split[batch_slice - 1] + a.cut.splits[batch_slice - 1], a.n_kv_heads, (g + G - 1) / G);
   if (G == 1) hipLaunchKernelGGL((decode_kernel<DT, HD, 1, NW>), grid, dim3(NW * 64), 0, s, a);
   else if constexpr (DT == CHUNKKV_F32) {
     if (G == 2) hipLaunchKernelGGL((decode_kernel<DT, HD, 2, NW>), grid, dim3(NW * 64), 0, s, a);
@@ -432,18 +434,12 @@ int launch_decode_valu(const DecodeArgs &a, int batch_slice, int g, hipStream_t 
   return hipGetLastError() == hipSuccess ? CHUNKKV_OK : CHUNKKV_ERR_LAUNCH;
 }
 
-// Ranges are 256 rows or more, as many as there are places for their partial results, and a step of four wavefronts is 32 rows of 512
-// bytes: few workgroups spent their time waiting for one step after the other.  So up to a workgroup per CU they have 16
-// wavefronts, at d = 128 up to two per CU 8 (8 from the start with four heads, where 16 leave no registers), and read a step ahead.
-// us of a layer, so and with four: 244 tokens of 8 kv-heads 8.3 / 25 (half of the rest is the merge launch, which one range
-// does without), 3350 tokens of 2 12 / 27, five sequences of 300 of 4 kv-heads, 4 heads each 14 / 28.  At d = 64 a step is 64 rows: five sequences of
-// 560 to 3200 tokens 13.2 with eight, 12.3 with four.
 template <int HD>
 int launch_decode_f32(const DecodeArgs &a, int batch_slice, int g, hipStream_t s) {
-  const int G = decode_heads_per_wg(CHUNKKV_F32, g);
-  const int64_t wgs = (int64_t)a.cut.n_split * batch_slice * a.n_kv_heads * ((g + G - 1) / G);
-  if (wgs <= kDecodeCUs && !(HD == 128 && G == 4)) return launch_decode_valu<CHUNKKV_F32, HD, 16, HD != 128>(a, batch_slice, g, s);
-  if (HD == 128 && wgs <= 2 * kDecodeCUs) return launch_decode_valu<CHUNKKV_F32, HD, 8>(a, batch_slice, g, s);
+  const int waves = decode_f32_waves(HD, g, a.n_kv_heads, batch_slice, a.cut);
+  if (waves == 16) return launch_decode_valu<CHUNKKV_F32, HD, 16, HD != 128>(a, batch_slice, g, s);
+  if constexpr (HD == 128)
+    if (waves == 8) return launch_decode_valu<CHUNKKV_F32, HD, 8>(a, batch_slice, g, s);
   return launch_decode_valu<CHUNKKV_F32, HD, 4>(a, batch_slice, g, s);
 }
 

@@ -24,7 +24,7 @@ inline int decode_heads_per_wg(int dtype, int g) {
 struct DecodeCut {
   int32_t rows_per_split[kMaxBatchPerLaunch];  // rows of one key range of the sequence
   int32_t splits[kMaxBatchPerLaunch];          // key ranges of the sequence
-  int32_t first_split[kMaxBatchPerLaunch];     // key ranges of the slice's sequences before it
+  int32_t first_split[kMaxBatchPerLaunch];     // key ranges of the slice's sequences before it, INT32_MAX past the last one
   int32_t n_split;                             // most key ranges of a sequence; 1: every head is one range and no merge follows
 };
 
@@ -148,6 +148,23 @@ inline void decode_cut(const chunkkv_problem *p, bool compacted, int b0, int nb,
     first += a->splits[i];
     a->n_split = a->splits[i] > a->n_split ? a->splits[i] : a->n_split;
   }
+  for (int i = nb; i < kMaxBatchPerLaunch; ++i) a->first_split[i] = INT32_MAX;
+}
+// Wavefronts of a workgroup over fp32 caches, for the sequences of one launch.  Ranges are 256 rows or more, as many as there are places for
+// their partial results, and a step of four wavefronts is 32 rows of 512 bytes: few workgroups spent their time waiting for one step after
+// the other.  So up to a workgroup per CU (the grid counts the ranges of all sequences) they have 16
+// wavefronts, at d = 128 up to two per CU 8 (8 from the start with four heads, where 16 leave no registers), and read a step ahead.
+// us of a layer, so and with four: 244 tokens of 8 kv-heads 8.3 / 25 (half of the rest is the merge launch, which one range
+// does without), 3350 tokens of 2 12 / 27, five sequences of 300 of 4 kv-heads, 4 heads each 14 / 28.  At d = 64 a step is 64 rows: five sequences of
+// 560 to 3200 tokens 13.2 with eight, 12.3 with four.  One sequence of 8000 tokens and seven of 300, 4 kv-heads, 4 heads each 15.6; in a
+// grid with a row as long as the longest sequence's for each, all of it counted, 55; counted by the workgroups with rows, 44.
+inline int decode_f32_waves(int head_dim, int g, int n_kv_heads, int nb, const DecodeCut &cut) {
+  const int G = decode_heads_per_wg(CHUNKKV_F32, g);
+  int64_t wgs = 0;
+  for (int i = 0; i < nb; ++i) wgs += cut.splits[i];
+  wgs *= (int64_t)n_kv_heads * ((g + G - 1) / G);
+  if (wgs <= kDecodeCUs && !(head_dim == 128 && G == 4)) return 16;
+  return head_dim == 128 && wgs <= 2 * kDecodeCUs ? 8 : 4;
 }
 inline void decode_plan(const chunkkv_problem *p, bool compacted, DecodePlan *pl) {
   const size_t places = (size_t)p->batch * p->n_q_heads * (size_t)decode_even_splits(p, compacted);

@@ -17,9 +17,11 @@ def cut(tmp_path_factory):
     subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-I", os.path.join(ROOT, "include"), "-I",
                     os.path.join(ROOT, "paper_2502_00299_amd", "csrc"), "-o", exe, os.path.join(ROOT, "tests", "decode_plan_main.cpp")], check=True)
 
-    def ask(problems):
+    def ask(problems, *mode):
         text = "".join(f"{dt} {hq} {hkv} {d} {pitch} {len(n)} {' '.join(map(str, n))}\n" for dt, hq, hkv, d, pitch, n in problems)
-        out = subprocess.run([exe], input=text, capture_output=True, text=True, check=True, timeout=120).stdout.splitlines()
+        out = subprocess.run([exe, *mode], input=text, capture_output=True, text=True, check=True, timeout=120).stdout.splitlines()
+        if mode:
+            return [list(map(int, line.split())) for line in out]
         answers = []
         for line in out:
             total, *launches = line.split(" | ")
@@ -92,3 +94,22 @@ def test_no_range_is_far_longer_than_a_cu_s_share(cut):
         dt, hq, hkv, d, pitch, n = prob
         share = -(-sum(n) * workgroups_per_range(dt, hq, hkv) // 256)
         assert max(rows for rows, _, _ in seqs) <= max(2 * share + 31, 512), prob
+
+
+def test_fp32_wavefronts_count_workgroups_that_have_rows(cut):
+    """16, 8 or 4 wavefronts by the workgroups with rows: a long sequence among short ones does not count for all of them."""
+    rng = random.Random(8)
+    problems = [(F32, 16, 4, 64, 256, [8000] + [300] * 7), (F32, 8, 4, 128, 512, [8000] + [300] * 7), (F32, 16, 4, 128, 512, [8000] + [300] * 7)]
+    problems += [(F32, *p[1:]) for p in (drawn(rng) for _ in range(2000)) if p[4] < 1 << 25]
+    answers = cut(problems, "waves")
+    assert answers[:3] == [[16], [16], [8]]
+    seen = set()
+    for prob, launches, (_, cuts) in zip(problems, answers, cut(problems)):
+        dt, hq, hkv, d, pitch, n = prob
+        for waves, (_, seqs) in zip(launches, cuts):
+            wgs = sum(ranges for _, ranges, _ in seqs) * workgroups_per_range(dt, hq, hkv)
+            four_heads = hq // hkv > 2
+            want = 16 if wgs <= 256 and not (d == 128 and four_heads) else 8 if d == 128 and wgs <= 512 else 4
+            assert waves == want, prob
+            seen.add((d, waves))
+    assert seen == {(64, 16), (64, 4), (128, 16), (128, 8), (128, 4)}

@@ -19,15 +19,28 @@ def reference(q, k, v):
     return out.reshape(q.shape), torch.logsumexp(s, 2).reshape(-1)
 
 
-# rows of the sequences, kv-heads, heads per kv-head: ranges are 256 rows or more
+def workgroups(lens, hkv, g):
+    """Workgroups that have rows: ranges of one length, about 1024 of them, 256 rows or more."""
+    batches = -(-g // 4) if g > 2 else 1
+    rows = -(-(sum(lens) * hkv * batches) // 1024)
+    rows = 256 if rows < 256 else -(-rows // 128) * 128
+    return sum(-(-n // rows) for n in lens) * hkv * batches
+
+
+# rows of the sequences, kv-heads, heads per kv-head, workgroups
 @pytest.mark.parametrize("d", [64, 128])
-@pytest.mark.parametrize("lens,hkv,g", [
-    ([1], 1, 1), ([31], 2, 2), ([129, 256, 64], 2, 4), ([255], 8, 3),             # one range per head
-    ([257], 2, 1), ([513, 1, 256], 2, 4), ([3000], 8, 2), ([2049, 700], 4, 5),    # up to a workgroup per CU
-    ([12000], 8, 2), ([9000, 3001], 8, 4),                                        # up to two
-    ([20000], 8, 1), ([20000, 13], 8, 4),
+@pytest.mark.parametrize("lens,hkv,g,wgs", [
+    ([1], 1, 1, 1), ([31], 2, 2, 2), ([129, 256, 64], 2, 4, 6), ([255], 8, 3, 8),                   # one range per head
+    # up to a workgroup per CU: 16 wavefronts (d = 128 and three heads or more: 8)
+    ([257], 2, 1, 4), ([513, 1, 256], 2, 4, 10), ([3000], 8, 2, 96), ([2049, 700], 4, 5, 96), ([8192], 8, 1, 256),
+    ([8000] + [300] * 7, 4, 2, 184), ([8000] + [300] * 7, 4, 4, 184), ([300, 1, 700] * 6, 2, 2, 72),
+    # up to two: 8 at d = 128, 4 at d = 64
+    ([8193], 8, 1, 264), ([12000], 8, 2, 376), ([9000, 3001], 8, 4, 384), ([16384], 8, 1, 512),
+    # more: 4
+    ([16385], 8, 1, 520), ([20000], 8, 1, 632), ([20000, 13], 8, 4, 640),
 ])
-def test_matches_float64(d, lens, hkv, g):
+def test_matches_float64(d, lens, hkv, g, wgs):
+    assert workgroups(lens, hkv, g) == wgs
     gen = torch.Generator().manual_seed(sum(lens) + g)
     B, hq, total = len(lens), hkv * g, sum(lens)
     k, v = (torch.randn((total, hkv, d), generator=gen) for _ in range(2))
