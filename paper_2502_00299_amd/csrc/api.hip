@@ -35,11 +35,20 @@ constexpr int kSinglePeriodKeys = 160;   // granule of the single-pass kernel's 
 // second stream, which takes longer (the 131072-token stack 2.17 ms in one set, 2.23 in two, 2.45 in eight), so one set it is.
 constexpr int64_t kTilesPerLaunch = 1 << 30;
 
-// Streaming (non-temporal) loads leave the memory-side cache (256 MB) to others.  They are for calls whose K and V are larger than
-// it, where nothing a pass reads is still there for the next; smaller ones lose what they find there.  A per-layer call is one of many,
-// so a third of that.  us of a call, streaming and plain: 32 layers of 32768 tokens 679 / 696, 28 of 17734 97 / 101, 32 calls on 20011
-// 867 / 894; 16 layers of 1477 tokens 24.8 / 23.2, 7 of 47180 (170 MB, d = 64) 57.1 / 55.5, one of 8192 25.4 / 24.1.
+// Streaming (non-temporal) loads leave the memory-side cache (256 MB) to others.  They are for calls whose K and V fill most of
+// it: nothing a pass reads is still there for the next, while smaller ones lose what they find there.  us of a call, streaming and
+// plain: 32 layers of 32768 tokens 679 / 696, 28 of 17734 97 / 101; 16 layers of 1477 tokens 24.8 / 23.2, 7 of 47180 (170 MB, d = 64)
+// 57.1 / 55.5.  A per-layer call is one of many, so a third of that: 16 calls one after the other on layers of 67 MB 360 / 375, 101 MB 424 / 441,
+// 201 MB 677 / 703, 268 MB 828 / 863, but a call right behind a kernel that wrote its K and V 67 MB 26.2 / 25.7, 101 MB 30.7 / 29.8, 201 MB 45.8 / 46.2,
+// 268 MB 55.6 / 57.5, and behind one that read them the same within 3 %.  Below the line the same call again on the same layer of 34 MB takes
+// 25.4 / 24.1, calls on one layer after the other 259 / 269.
 constexpr int64_t kStreamBytes = 192 << 20, kStreamLayerBytes = 64 << 20;
+// Streaming stores of the gather, too, where K' and V' are more than that cache holds (a per-layer call, one of many: a thirty-second of
+// it).  Smaller ones are still there for the decoding step that reads them next.  us of compressing and of one such step over 32 layers,
+// so and with plain stores: 31 MB written 284 / 254, 111 MB 443 / 422, 218 MB 564 / 528, 325 MB 537 / 530, 433 MB 770 / 763, 1291 MB
+// 1165 / 1201 (compressing alone: 48 / 47, 136 / 130, 242 / 253, 206 / 216, 434 / 451, 733 / 777); layer by layer 7 MB each
+// 1009 / 1004, 14 MB 1165 / 1160, 30 MB 1393 / 1422.
+constexpr int64_t kStreamOutBytes = 256 << 20, kStreamOutLayerBytes = 8 << 20;
 
 struct Plan {
   ScoreGeom geom;
@@ -149,11 +158,15 @@ bool takes_one_pass(const chunkkv_problem *p, const Plan &pl, int chunk) {
   return !(p->flags & CHUNKKV_FLAG_TWO_PASS) && pl.n_periods_fit && single_pass_ok(p->dtype, p->head_dim, (p->n_q_heads / p->n_kv_heads) * p->window, chunk);
 }
 
-// Are K and V of `layers` layers more than `limit` bytes?
-bool streams(const chunkkv_problem *p, int64_t layers, int64_t limit) {
-  int64_t tokens = 0;
-  for (int b = 0; b < p->batch; ++b) tokens += p->seqlen[b];
-  return 2 * layers * tokens * p->n_kv_heads * p->head_dim * elem_bytes(p->dtype) > limit;
+// Which accesses of a call over `layers` layers are streaming, by the bytes of K and V, and of K' and V'.
+Stream streams(const chunkkv_problem *p, int64_t layers, int64_t most, int64_t most_out) {
+  int64_t tokens = 0, kept = 0;
+  for (int b = 0; b < p->batch; ++b) {
+    tokens += p->seqlen[b];
+    kept += p->n_keep[b] + p->window;
+  }
+  const int64_t token_bytes = 2 * layers * p->n_kv_heads * p->head_dim * elem_bytes(p->dtype);
+  return tokens * token_bytes <= most ? Stream::kNone : kept * token_bytes <= most_out ? Stream::kLoads : Stream::kAll;
 }
 
 // How a pass of the two is cut into workgroups.
@@ -292,7 +305,7 @@ void fill_seq(SeqTable *t, const chunkkv_problem *p, int b0, int nb) {
 // [B][Hq][w] array and only the importance pass runs.
 int run_score(const chunkkv_problem *p, const Plan &pl, const void *const *q, const void *const *k,
               const float *const *lse, int ng, const int32_t *leaders, const int32_t *chunks, float *chunk_scores, float *token_imp,
-              int64_t imp_pitch, bool stream, char *ws, hipStream_t s) {
+              int64_t imp_pitch, Stream stream, char *ws, hipStream_t s) {
   const int TK = pl.geom.tile_keys;
   for (int b0 = 0; b0 < p->batch; b0 += kMaxBatchPerLaunch) {
     const int nb = p->batch - b0 < kMaxBatchPerLaunch ? p->batch - b0 : kMaxBatchPerLaunch;
@@ -333,7 +346,7 @@ int run_score(const chunkkv_problem *p, const Plan &pl, const void *const *q, co
       // one pass over K: per-(chunk, row) sums and the references they are relative to; then the merge of the
       // range statistics and the weighted row sum in one small kernel
       a.n_periods = pl.n_periods;
-      a.stream_k = stream;
+      a.stream_k = stream != Stream::kNone;
       a.e_buf = ws + pl.off_ebuf;
       a.m_period = (float *)(ws + pl.off_mper);
       a.row_stats = (float *)(ws + pl.off_part);
@@ -458,7 +471,7 @@ int run_topk(const chunkkv_problem *p, const int32_t *chunks, const float *chunk
 
 // Arguments of a gather: layers [l0, l0 + nl) and sequences [b0, b0 + nb), of the pointers' first layer on.  chunks[i]: chunk
 // size of the i-th reuse group from that of layer l_begin on.
-void fill_compact(CompactArgs *a, const chunkkv_problem *p, const int32_t *chunks, int l_begin, int l0, int nl, int b0, int nb, int reuse, bool stream,
+void fill_compact(CompactArgs *a, const chunkkv_problem *p, const int32_t *chunks, int l_begin, int l0, int nl, int b0, int nb, int reuse, Stream stream,
                   const void *const *k, const void *const *v, void *const *k_out, void *const *v_out, const int32_t *sel_chunk,
                   const int32_t *sel_len, const int32_t *sel_count, const int32_t *sel_off) {
   memset(a, 0, sizeof(*a));
@@ -477,7 +490,7 @@ void fill_compact(CompactArgs *a, const chunkkv_problem *p, const int32_t *chunk
   a->stream = stream;
 }
 
-int run_compact(const chunkkv_problem *p, const int32_t *chunks, int l_begin, int n_layers, int reuse, bool stream, const void *const *k, const void *const *v,
+int run_compact(const chunkkv_problem *p, const int32_t *chunks, int l_begin, int n_layers, int reuse, Stream stream, const void *const *k, const void *const *v,
                 void *const *k_out, void *const *v_out, const int32_t *sel_chunk, const int32_t *sel_len,
                 const int32_t *sel_count, const int32_t *sel_off, hipStream_t s) {
   const int row_bytes = p->head_dim * elem_bytes(p->dtype);
@@ -498,7 +511,7 @@ int run_compact(const chunkkv_problem *p, const int32_t *chunks, int l_begin, in
 // Selection of the reuse groups from that of layer l_begin on and gather of layers [l_begin, l_end) with it: in one launch
 // where one can carry them and that suits the problem.
 int run_selection(const chunkkv_problem *p, const int32_t *chunks, const float *chunk_scores, int group0, int n_groups, int l_begin, int l_end,
-                  int reuse, bool stream, const void *const *k, const void *const *v, void *const *k_out, void *const *v_out, int32_t *sel_chunk,
+                  int reuse, Stream stream, const void *const *k, const void *const *v, void *const *k_out, void *const *v_out, int32_t *sel_chunk,
                   int32_t *sel_len, int32_t *sel_count, int32_t *sel_off, hipStream_t s) {
   const int row_bytes = p->head_dim * elem_bytes(p->dtype), nl = l_end - l_begin;
   int rc;
@@ -581,7 +594,7 @@ static int score_entry(const chunkkv_problem *prob, const void *q_obs, const voi
   if (!workspace || workspace_bytes < pl.total) return CHUNKKV_ERR_WORKSPACE;
   const int32_t leader = 0;
   return run_score(prob, pl, &q_obs, &k, with_lse ? &lse : nullptr, 1, &leader, &prob->chunk, chunk_scores, token_importance,
-                   (int64_t)prob->score_cap * prob->chunk, streams(prob, 1, kStreamBytes), (char *)workspace, (hipStream_t)stream);
+                   (int64_t)prob->score_cap * prob->chunk, streams(prob, 1, kStreamBytes, kStreamOutBytes), (char *)workspace, (hipStream_t)stream);
 }
 
 int chunkkv_score(const chunkkv_problem *prob, const void *q_obs, const void *k, float *chunk_scores,
@@ -611,7 +624,7 @@ int chunkkv_compact(const chunkkv_problem *prob, const void *k, const void *v, c
   if (rc) return rc;
   if (!k || !v || !sel_chunk || !sel_len || !sel_count || !k_out || !v_out) return CHUNKKV_ERR_NULL;
   if (misaligned(k) || misaligned(v) || misaligned(k_out) || misaligned(v_out)) return CHUNKKV_ERR_SHAPE;
-  return run_compact(prob, &prob->chunk, 0, 1, 1, streams(prob, 1, kStreamBytes), &k, &v, &k_out, &v_out, sel_chunk, sel_len, sel_count, nullptr,
+  return run_compact(prob, &prob->chunk, 0, 1, 1, streams(prob, 1, kStreamBytes, kStreamOutBytes), &k, &v, &k_out, &v_out, sel_chunk, sel_len, sel_count, nullptr,
                      (hipStream_t)stream);
 }
 
@@ -641,7 +654,7 @@ static int stack_groups(const chunkkv_problem *prob, const Plan &pl, int g_begin
                         int32_t *sel_chunk, int32_t *sel_len, int32_t *sel_count, char *ws, hipStream_t s) {
   float *scores = (float *)(ws + pl.off_scores);
   int32_t *sel_off = (int32_t *)(ws + pl.off_seloff);
-  const bool stream = streams(prob, n_layers, kStreamBytes);
+  const Stream stream = streams(prob, n_layers, kStreamBytes, kStreamOutBytes);
   for (int g0 = g_begin; g0 < g_end; g0 += pl.batch_leaders) {
     const int ng = g_end - g0 < pl.batch_leaders ? g_end - g0 : pl.batch_leaders;
     const void *qs[kMaxLayersPerLaunch], *ks[kMaxLayersPerLaunch];
@@ -692,7 +705,7 @@ static int stack_mixed(const chunkkv_problem *prob, const Plan &pl, int32_t n_la
   const int n_groups = pl.n_leaders;
   float *scores = (float *)(ws + pl.off_scores);
   int32_t *sel_off = (int32_t *)(ws + pl.off_seloff);
-  const bool stream = streams(prob, n_layers, kStreamBytes);
+  const Stream stream = streams(prob, n_layers, kStreamBytes, kStreamOutBytes);
   bool done[kMaxLayersPerLaunch] = {};
   for (int first = 0; first < n_groups; ++first) {
     if (done[first]) continue;
@@ -816,16 +829,16 @@ int chunkkv_compress_layer(const chunkkv_problem *prob, int32_t layer, int32_t r
   hipStream_t s = (hipStream_t)stream;
   // the kernels see this layer's group as group 0 of arrays that start at the group's rows
   const int64_t row0 = (int64_t)(layer / reuse) * prob->batch * prob->n_kv_heads;
-  const bool stream_loads = streams(prob, 1, kStreamLayerBytes);
+  const Stream how = streams(prob, 1, kStreamLayerBytes, kStreamOutLayerBytes);
   int32_t *sc = sel_chunk + row0 * prob->sel_cap, *sl = sel_len + row0 * prob->sel_cap, *cnt = sel_count + row0;
   if (leader) {
     float *scores = (float *)(ws + pl.off_scores);
     const int32_t leader0 = 0;
-    rc = run_score(prob, pl, &q_obs, &k, lse ? &lse : nullptr, 1, &leader0, &prob->chunk, scores, nullptr, 0, stream_loads, ws, s);
+    rc = run_score(prob, pl, &q_obs, &k, lse ? &lse : nullptr, 1, &leader0, &prob->chunk, scores, nullptr, 0, how, ws, s);
     if (rc) return rc;
-    return run_selection(prob, &prob->chunk, scores, 0, 1, 0, 1, 1, stream_loads, &k, &v, &k_out, &v_out, sc, sl, cnt, nullptr, s);
+    return run_selection(prob, &prob->chunk, scores, 0, 1, 0, 1, 1, how, &k, &v, &k_out, &v_out, sc, sl, cnt, nullptr, s);
   }
-  return run_compact(prob, &prob->chunk, 0, 1, 1, stream_loads, &k, &v, &k_out, &v_out, sc, sl, cnt, nullptr, s);
+  return run_compact(prob, &prob->chunk, 0, 1, 1, how, &k, &v, &k_out, &v_out, sc, sl, cnt, nullptr, s);
 }
 
 int chunkkv_jaccard(const chunkkv_problem *prob, int32_t n_groups, const int32_t *sel_chunk, const int32_t *sel_len,

@@ -5,10 +5,9 @@
 // entries of up to `c` rows) and copies their rows as one flat list of 16-byte segments, K rows first, then V rows:
 // consecutive lanes copy consecutive segments whatever the chunk size is, five segments in flight per lane.  The
 // entries' chunk, length and offset are loaded once, by one wavefront, into LDS.
-// Stores are streaming (non-temporal): what is written is not read again here, and it would push what is still to be read out of
-// the memory-side cache.  Loads are where the call's caches are larger than that one (CompactArgs::stream).  us of a call, so and with
-// streaming loads, plain stores and 160 rows: 32 layers of 131072 tokens 1963 / 2029, the ragged batch at c = 20 1993 / 2074, 16 layers of 1477
-// tokens 23.2 / 24.5.
+// Streaming (non-temporal) loads where the call's caches are larger than the memory-side one, streaming stores where what is written is,
+// too (the lines, with both sides measured, are in api.hip): smaller ones are found there by the next call.  An instance per kind, as a branch
+// around the accesses parts them from their addresses: 32 layers of 131072 tokens 1978 us, as a branch 2045, the ragged batch at c = 20 1965 and 2075.
 // Over a stack the kernel is bound by HBM (copy speed) and a workgroup takes about 80 rows, over a single layer by
 // the latency of entry -> rows -> stores, and 40 rows (one round of loads) give four times the workgroups:
 // one layer of 20011 tokens, c = 5, keep 20 %, 13.8 -> 9.6 us; two layers of 12345 tokens, c = 1, 23.7 -> 11.3 us, c = 20,
@@ -40,7 +39,7 @@ __host__ __device__ inline int compact_entries(int rows, int chunk) {
 
 // Copies the rows of entries [0, n) of the lists (source token, destination token, length) of one layer, sequence and
 // kv-head; ne: entries a workgroup can have.
-template <int NSEG, int T, bool STREAM>  // 16-byte segments per row, threads, streaming loads
+template <int NSEG, int T, Stream STREAM>  // 16-byte segments per row, threads
 __device__ __forceinline__ void copy_entries(const CompactArgs &a, int layer, int bl, int h, int c, int ne, int n, const int *s_src, const int *s_dst, const int *s_len) {
   const int64_t esz = a.elem_bytes;
   const int64_t base = CKV_ARG(CompactArgs, seq.kv_base, bl), obase = CKV_ARG(CompactArgs, seq.out_base, bl);
@@ -74,17 +73,20 @@ __device__ __forceinline__ void copy_entries(const CompactArgs &a, int layer, in
       const bool live = i < len && u0 + j * T < total;
       i = i < len ? i : 0;
       const u32x4 *from = (const u32x4 *)((is_v ? vin : kin) + (int64_t)(s_src[en] + i) * in_tok + seg * 16);
-      if constexpr (STREAM) r[j] = __builtin_nontemporal_load(from);
+      if constexpr (STREAM != Stream::kNone) r[j] = __builtin_nontemporal_load(from);
       else r[j] = *from;
       to[j] = live ? (is_v ? vout : kout) + (int64_t)(s_dst[en] + i) * out_tok + seg * 16 : nullptr;
     }
 #pragma unroll
     for (int j = 0; j < 5; ++j)
-      if (to[j] != nullptr) __builtin_nontemporal_store(r[j], (u32x4 *)to[j]);
+      if (to[j] != nullptr) {
+        if constexpr (STREAM == Stream::kAll) __builtin_nontemporal_store(r[j], (u32x4 *)to[j]);
+        else *(u32x4 *)to[j] = r[j];
+      }
   }
 }
 
-template <int NSEG, bool STREAM>  // 16-byte segments per row
+template <int NSEG, Stream STREAM>  // 16-byte segments per row
 __global__ __launch_bounds__(kThreads) void compact_kernel(CompactArgs a) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int bl = blockIdx.y / a.n_kv_heads, h = blockIdx.y % a.n_kv_heads;
@@ -177,8 +179,8 @@ __global__ __launch_bounds__(kThreads) void compact_kernel(CompactArgs a) {
 
 // Selection and gather in one launch: every workgroup selects the chunks of its head for itself and keeps the places that
 // are its own; one workgroup per head and reuse group writes the selection out.  For short launches over few chunks, where a
-// dependent launch costs more than the selection's 2 to 5 us.
-template <int NSEG, int T, int KR, bool STREAM>
+// dependent launch costs more than the selection's 2 to 5 us; what they write is hardly ever more than the memory-side cache holds (plain stores).
+template <int NSEG, int T, int KR, Stream STREAM>
 __global__ __launch_bounds__(T) void select_compact_kernel(CompactArgs a, const float *chunk_scores, int score_cap) {
   const int bl = blockIdx.y / a.n_kv_heads, h = blockIdx.y % a.n_kv_heads, layer = blockIdx.z;
   const int n_keep = CKV_ARG(CompactArgs, seq.n_keep, bl), w = a.window, c = CKV_ARG(CompactArgs, chunk_of, layer);
@@ -244,7 +246,7 @@ int launch_select_compact(int row_bytes, CompactArgs &a, int n_layers_slice, int
 #define CKV_SELECT_AS(NSEG, STREAM) \
   hipLaunchKernelGGL((how.wide ? select_compact_kernel<NSEG, 1024, 4, STREAM> : how.chunks <= kSelectCompactFewChunks ? select_compact_kernel<NSEG, kThreads, 1, STREAM> : select_compact_kernel<NSEG, kThreads, 4, STREAM>), \
                      grid, block, 0, s, a, chunk_scores, score_cap)
-#define CKV_SELECT(NSEG) do { if (a.stream) CKV_SELECT_AS(NSEG, true); else CKV_SELECT_AS(NSEG, false); } while (0)
+#define CKV_SELECT(NSEG) do { if (a.stream != Stream::kNone) CKV_SELECT_AS(NSEG, Stream::kLoads); else CKV_SELECT_AS(NSEG, Stream::kNone); } while (0)
   switch (row_bytes / 16) {
     case 8: CKV_SELECT(8); break;
     case 16: CKV_SELECT(16); break;
@@ -275,12 +277,16 @@ SelectInGather select_in_gather(CompactArgs &a, int n_layers_slice, int batch_sl
 
 int launch_compact(int row_bytes, CompactArgs &a, int n_layers_slice, int batch_slice, hipStream_t s) {
   const dim3 grid(choose_rows(a, n_layers_slice, batch_slice).most, batch_slice * a.n_kv_heads, n_layers_slice);
+#define CKV_COMPACT(NSEG) \
+  hipLaunchKernelGGL((a.stream == Stream::kAll ? compact_kernel<NSEG, Stream::kAll> : a.stream == Stream::kLoads ? compact_kernel<NSEG, Stream::kLoads> : compact_kernel<NSEG, Stream::kNone>), \
+                     grid, dim3(kThreads), 0, s, a)
   switch (row_bytes / 16) {
-    case 8: hipLaunchKernelGGL((a.stream ? compact_kernel<8, true> : compact_kernel<8, false>), grid, dim3(kThreads), 0, s, a); break;
-    case 16: hipLaunchKernelGGL((a.stream ? compact_kernel<16, true> : compact_kernel<16, false>), grid, dim3(kThreads), 0, s, a); break;
-    case 32: hipLaunchKernelGGL((a.stream ? compact_kernel<32, true> : compact_kernel<32, false>), grid, dim3(kThreads), 0, s, a); break;
+    case 8: CKV_COMPACT(8); break;
+    case 16: CKV_COMPACT(16); break;
+    case 32: CKV_COMPACT(32); break;
     default: return CHUNKKV_ERR_UNSUPPORTED;
   }
+#undef CKV_COMPACT
   return hipGetLastError() == hipSuccess ? CHUNKKV_OK : CHUNKKV_ERR_LAUNCH;
 }
 

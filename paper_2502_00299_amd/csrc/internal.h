@@ -90,6 +90,9 @@ struct TopkArgs {
   int32_t whole_chunks;       // 1: Algorithm 3 as printed: floor(n_keep / c) whole chunks, nothing is cut
 };
 
+// Which accesses to K, V, K' and V' are streaming (non-temporal): none, the loads, the gather's stores too.
+enum class Stream : int32_t { kNone, kLoads, kAll };
+
 struct CompactArgs {
   const void *k[kMaxLayersPerLaunch];
   const void *v[kMaxLayersPerLaunch];
@@ -105,7 +108,7 @@ struct CompactArgs {
   int32_t sel_cap;
   int32_t rows_per_wg;        // chosen by the launcher: rows a workgroup copies, in whole entries
   int32_t whole_chunks;       // 1: the window follows the kept tokens directly (their count varies per head)
-  int32_t stream;             // 1: rows are read with streaming (non-temporal) loads
+  Stream stream;
 };
 
 // Decode attention over one layer's cache (decode.hip).  Per-head partial results use the FULL batch index.

@@ -1,5 +1,6 @@
-"""Calls on either side of the lines from which K and V are read with streaming loads: the stack call (192 MB) and the per-layer
-call (64 MB) give the same selections and the same gathered bytes, which are rows of the caches."""
+"""Calls on either side of the lines from which K and V are read, and K' and V' written, with streaming accesses, for rows of 128, 256
+and 512 bytes: the stack call (192 MB of K and V, 256 MB of K' and V') and the per-layer call (64 MB, 8 MB) give the same selections and
+the same gathered bytes, which are rows of the caches."""
 import pytest
 import torch
 
@@ -7,17 +8,27 @@ import paper_2502_00299_amd as ckv
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
+TOKEN = 4096   # bytes of K and V of a token in a layer, in every case
+KIND = {ckv.BF16: torch.bfloat16, ckv.F16: torch.float16, ckv.F32: torch.float32}
 
 
-@pytest.mark.parametrize("chunk,window,dtype", [(10, 64, ckv.BF16), (20, 32, ckv.F16), (5, 64, ckv.F16), (7, 32, ckv.BF16)])
-@pytest.mark.parametrize("n", [8191, 8193, 24575, 24577])   # 8 kv-heads of 128: 32 MB and 96 MB of K and V a layer, and a little more
-def test_stack_equals_layers(n, chunk, window, dtype):
-    hkv, g, d, N = 8, 4, 128, 2
-    kind = {ckv.BF16: torch.bfloat16, ckv.F16: torch.float16}[dtype]
+@pytest.mark.parametrize("chunk,window,dtype,d", [(10, 64, ckv.BF16, 128), (20, 32, ckv.F16, 128), (5, 64, ckv.F16, 128), (7, 32, ckv.BF16, 128),
+                                                  (16, 32, ckv.BF16, 64), (9, 32, ckv.F32, 128)])
+@pytest.mark.parametrize("n,kept", [(16383, 1702), (16385, 1702),      # two layers of 64 MB: the per-layer call's loads
+                                    (16385, 2048), (16385, 2049),      # 8 MB of K' and V': its stores
+                                    (24575, 2521), (24577, 2521),      # two layers of 96 MB: the stack call's loads
+                                    (33001, 32768), (33001, 32769)])   # 256 MB of K' and V': its stores
+def test_stack_equals_layers(n, kept, chunk, window, dtype, d):
+    kind = KIND[dtype]
+    g, N, hkv = 4, 2, TOKEN // (2 * d * torch.empty(0, dtype=kind).element_size())
+    mb = 1 << 20
+    edges = [n * TOKEN > 64 * mb, kept * TOKEN > 8 * mb, N * n * TOKEN > 192 * mb, N * kept * TOKEN > 256 * mb]
+    assert edges == {16383: [False, False, False, False], 16385: [True, kept == 2049, False, False], 24575: [True, True, False, False],
+                     24577: [True, True, True, False], 33001: [True, True, True, kept == 32769]}[n]
     gen = torch.Generator(device=DEV).manual_seed(n)
     k, v = ([torch.randn((hkv, n, d), generator=gen, device=DEV).to(kind) for _ in range(N)] for _ in range(2))
     q = torch.randn((1, hkv * g, window, d), generator=gen, device=DEV).to(kind)
-    keep = (n - window) // 10
+    keep = kept - window
     prob = ckv.Problem(hkv * g, hkv, d, window, chunk, dtype, [n], [keep], [0], n * d, d)
 
     def fresh():
@@ -35,11 +46,12 @@ def test_stack_equals_layers(n, chunk, window, dtype):
     assert torch.equal(sel[2], sel1[2])
     for h in range(hkv):
         m = int(count[h])
-        chunks, lens = sel[0][0, 0, h, :m], sel[1][0, 0, h, :m]
-        assert torch.equal(chunks, sel1[0][0, 0, h, :m]) and torch.equal(lens, sel1[1][0, 0, h, :m]) and int(lens.sum()) == keep
-        rows = torch.cat([torch.arange(int(c) * chunk, int(c) * chunk + int(m_), device=DEV) for c, m_ in zip(chunks.cpu(), lens.cpu())] +
-                         [torch.arange(n - window, n, device=DEV)])
+        chunks, lens = sel[0][0, 0, h, :m].long(), sel[1][0, 0, h, :m].long()
+        assert torch.equal(chunks, sel1[0][0, 0, h, :m].long()) and torch.equal(lens, sel1[1][0, 0, h, :m].long()) and int(lens.sum()) == keep
+        first = torch.cumsum(lens, 0) - lens   # place of every entry's first row
+        rows = torch.repeat_interleave(chunks * chunk - first, lens) + torch.arange(keep, device=DEV)
+        rows = torch.cat([rows, torch.arange(n - window, n, device=DEV)])
         for x, src in zip(out, k + v):
-            assert torch.equal(x.view(hkv, keep + window, d)[h], src[h][rows])
+            assert torch.equal(x.view(hkv, kept, d)[h], src[h][rows])
     for a, b in zip(out, out1):
         assert torch.equal(a, b)
