@@ -43,12 +43,14 @@ constexpr int64_t kTilesPerLaunch = 1 << 30;
 // 268 MB 55.6 / 57.5, and behind one that read them the same within 3 %.  Below the line the same call again on the same layer of 34 MB takes
 // 25.4 / 24.1, calls on one layer after the other 259 / 269.
 constexpr int64_t kStreamBytes = 192 << 20, kStreamLayerBytes = 64 << 20;
-// Streaming stores of the gather, too, where K' and V' are more than that cache holds (a per-layer call, one of many: a thirty-second of
-// it).  Smaller ones are still there for the decoding step that reads them next.  us of compressing and of one such step over 32 layers,
-// so and with plain stores: 31 MB written 284 / 254, 111 MB 443 / 422, 218 MB 564 / 528, 325 MB 537 / 530, 433 MB 770 / 763, 1291 MB
-// 1165 / 1201 (compressing alone: 48 / 47, 136 / 130, 242 / 253, 206 / 216, 434 / 451, 733 / 777); layer by layer 7 MB each
-// 1009 / 1004, 14 MB 1165 / 1160, 30 MB 1393 / 1422.
-constexpr int64_t kStreamOutBytes = 256 << 20, kStreamOutLayerBytes = 8 << 20;
+// Stores of the gather, and then the loads too, where K' and V' are more than half of that cache (a per-layer call, one of many: a
+// thirty-second of that).  Smaller ones are still there for the decoding step that reads them next.  us of compressing and of one such step
+// over 32 layers, streaming and plain: 31 MB written 284 / 254, 57 MB 373 / 318, 111 MB 443 / 422, two passes 29 MB 288 / 262, 111 MB 505 / 486.
+// Above, what is still there and what the next call has to write back for it even out: 218 MB 564 / 528, 163 MB in eight chunk sizes 334 / 340, 433 MB
+// 770 / 763, 1291 MB 1165 / 1201, and compressing alone, call after call, 4 to 8 % slower with plain stores (48 / 47, 83 / 82, 136 / 130 below the
+// line, two passes 52 / 56, 179 / 190; above 242 / 253, 168 / 179, 434 / 451, 733 / 777).  Layer by layer 3 MB each 874 / 851 (4096 tokens at 20 %, two passes 778 / 770), 7 MB 1009 / 1004,
+// 10 MB 917 / 922, 14 MB 547 / 556, 30 MB 1393 / 1422.
+constexpr int64_t kStreamOutBytes = 128 << 20, kStreamOutLayerBytes = 4 << 20;
 
 struct Plan {
   ScoreGeom geom;
@@ -166,7 +168,7 @@ Stream streams(const chunkkv_problem *p, int64_t layers, int64_t most, int64_t m
     kept += p->n_keep[b] + p->window;
   }
   const int64_t token_bytes = 2 * layers * p->n_kv_heads * p->head_dim * elem_bytes(p->dtype);
-  return tokens * token_bytes <= most ? Stream::kNone : kept * token_bytes <= most_out ? Stream::kLoads : Stream::kAll;
+  return kept * token_bytes > most_out ? Stream::kAll : tokens * token_bytes > most ? Stream::kLoads : Stream::kNone;
 }
 
 // How a pass of the two is cut into workgroups.

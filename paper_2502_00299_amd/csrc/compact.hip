@@ -5,8 +5,8 @@
 // entries of up to `c` rows) and copies their rows as one flat list of 16-byte segments, K rows first, then V rows:
 // consecutive lanes copy consecutive segments whatever the chunk size is, five segments in flight per lane.  The
 // entries' chunk, length and offset are loaded once, by one wavefront, into LDS.
-// Streaming (non-temporal) loads where the call's caches are larger than the memory-side one, streaming stores where what is written is,
-// too (the lines, with both sides measured, are in api.hip): smaller ones are found there by the next call.  An instance per kind, as a branch
+// Streaming (non-temporal) loads where the call's caches fill most of the memory-side one, streaming stores where what is written is more than half
+// of it (the lines, with both sides measured, are in api.hip): smaller ones are found there by the next call.  An instance per kind, as a branch
 // around the accesses parts them from their addresses: 32 layers of 131072 tokens 1978 us, as a branch 2045, the ragged batch at c = 20 1965 and 2075.
 // Over a stack the kernel is bound by HBM (copy speed) and a workgroup takes about 80 rows, over a single layer by
 // the latency of entry -> rows -> stores, and 40 rows (one round of loads) give four times the workgroups:
@@ -179,7 +179,7 @@ __global__ __launch_bounds__(kThreads) void compact_kernel(CompactArgs a) {
 
 // Selection and gather in one launch: every workgroup selects the chunks of its head for itself and keeps the places that
 // are its own; one workgroup per head and reuse group writes the selection out.  For short launches over few chunks, where a
-// dependent launch costs more than the selection's 2 to 5 us; what they write is hardly ever more than the memory-side cache holds (plain stores).
+// dependent launch costs more than the selection's 2 to 5 us.
 template <int NSEG, int T, int KR, Stream STREAM>
 __global__ __launch_bounds__(T) void select_compact_kernel(CompactArgs a, const float *chunk_scores, int score_cap) {
   const int bl = blockIdx.y / a.n_kv_heads, h = blockIdx.y % a.n_kv_heads, layer = blockIdx.z;
@@ -246,7 +246,12 @@ int launch_select_compact(int row_bytes, CompactArgs &a, int n_layers_slice, int
 #define CKV_SELECT_AS(NSEG, STREAM) \
   hipLaunchKernelGGL((how.wide ? select_compact_kernel<NSEG, 1024, 4, STREAM> : how.chunks <= kSelectCompactFewChunks ? select_compact_kernel<NSEG, kThreads, 1, STREAM> : select_compact_kernel<NSEG, kThreads, 4, STREAM>), \
                      grid, block, 0, s, a, chunk_scores, score_cap)
-#define CKV_SELECT(NSEG) do { if (a.stream != Stream::kNone) CKV_SELECT_AS(NSEG, Stream::kLoads); else CKV_SELECT_AS(NSEG, Stream::kNone); } while (0)
+#define CKV_SELECT(NSEG) \
+  do { \
+    if (a.stream == Stream::kAll) CKV_SELECT_AS(NSEG, Stream::kAll); \
+    else if (a.stream == Stream::kLoads) CKV_SELECT_AS(NSEG, Stream::kLoads); \
+    else CKV_SELECT_AS(NSEG, Stream::kNone); \
+  } while (0)
   switch (row_bytes / 16) {
     case 8: CKV_SELECT(8); break;
     case 16: CKV_SELECT(16); break;

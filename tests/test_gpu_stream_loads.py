@@ -1,5 +1,5 @@
 """Calls on either side of the lines from which K and V are read, and K' and V' written, with streaming accesses, for rows of 128, 256
-and 512 bytes: the stack call (192 MB of K and V, 256 MB of K' and V') and the per-layer call (64 MB, 8 MB) give the same selections and
+and 512 bytes: the stack call (192 MB of K and V, 128 MB of K' and V') and the per-layer call (64 MB, 4 MB) give the same selections and
 the same gathered bytes, which are rows of the caches."""
 import pytest
 import torch
@@ -14,17 +14,17 @@ KIND = {ckv.BF16: torch.bfloat16, ckv.F16: torch.float16, ckv.F32: torch.float32
 
 @pytest.mark.parametrize("chunk,window,dtype,d", [(10, 64, ckv.BF16, 128), (20, 32, ckv.F16, 128), (5, 64, ckv.F16, 128), (7, 32, ckv.BF16, 128),
                                                   (16, 32, ckv.BF16, 64), (9, 32, ckv.F32, 128)])
-@pytest.mark.parametrize("n,kept", [(16383, 1702), (16385, 1702),      # two layers of 64 MB: the per-layer call's loads
-                                    (16385, 2048), (16385, 2049),      # 8 MB of K' and V': its stores
+@pytest.mark.parametrize("n,kept", [(16383, 1001), (16385, 1001),      # two layers of 64 MB: the per-layer call's loads
+                                    (9001, 1024), (9001, 1025),        # 4 MB of K' and V': its stores
                                     (24575, 2521), (24577, 2521),      # two layers of 96 MB: the stack call's loads
-                                    (33001, 32768), (33001, 32769)])   # 256 MB of K' and V': its stores
+                                    (17001, 16384), (17001, 16385)])   # 128 MB of K' and V': its stores
 def test_stack_equals_layers(n, kept, chunk, window, dtype, d):
     kind = KIND[dtype]
     g, N, hkv = 4, 2, TOKEN // (2 * d * torch.empty(0, dtype=kind).element_size())
     mb = 1 << 20
-    edges = [n * TOKEN > 64 * mb, kept * TOKEN > 8 * mb, N * n * TOKEN > 192 * mb, N * kept * TOKEN > 256 * mb]
-    assert edges == {16383: [False, False, False, False], 16385: [True, kept == 2049, False, False], 24575: [True, True, False, False],
-                     24577: [True, True, True, False], 33001: [True, True, True, kept == 32769]}[n]
+    edges = [n * TOKEN > 64 * mb, kept * TOKEN > 4 * mb, N * n * TOKEN > 192 * mb, N * kept * TOKEN > 128 * mb]
+    assert edges == {16383: [False, False, False, False], 16385: [True, False, False, False], 9001: [False, kept == 1025, False, False],
+                     24575: [True, True, False, False], 24577: [True, True, True, False], 17001: [True, True, False, kept == 16385]}[n]
     gen = torch.Generator(device=DEV).manual_seed(n)
     k, v = ([torch.randn((hkv, n, d), generator=gen, device=DEV).to(kind) for _ in range(N)] for _ in range(2))
     q = torch.randn((1, hkv * g, window, d), generator=gen, device=DEV).to(kind)
