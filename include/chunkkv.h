@@ -174,8 +174,8 @@ int chunkkv_compress_layer(const chunkkv_problem *prob, int32_t layer, int32_t r
 /* Algorithm 2 with a chunk size per reuse group (the hybrid setting among the chunk-size ablations of
  * Section 4.6; chunk size 1 in a group is token-level selection there).  Group G = l / reuse scores, selects
  * and gathers with chunk_per_group[G]; prob->chunk is ignored; the budget n_keep[b] is the same token count in
- * every group.  Implemented as chunkkv_compress_stack over each run of consecutive groups with one chunk size,
- * so the results of a group are those of chunkkv_compress_stack with that chunk size.
+ * every group.  Groups of different sizes share their launches (more than 32 groups, or chunks of more than 256
+ * tokens, run by run of one size); the results of a group are those of chunkkv_compress_stack with that chunk size.
  *   chunk_per_group  HOST int32 [ceil(n_layers / reuse)], every entry >= 1
  *   lse              NULL, or as in chunkkv_compress_stack_lse
  *   sel_chunk, sel_len, sel_count   as in chunkkv_compress_stack; group G's entries count chunks of

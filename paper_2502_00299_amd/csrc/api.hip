@@ -19,8 +19,8 @@ constexpr int kTargetWorkgroups = 4096;  // eight rounds of 2 workgroups on each
 constexpr int64_t kMergeTiles = 16384;
 // How the two passes are cut into workgroups (units_per_workgroup in score_plan.h): whole rounds, as far as a launch has few.  What
 // a workgroup costs, in microseconds: a 32-key block against 32 rows with two workgroups on the CU; beside its tiles start, queries,
-// first tiles and end; in pass 1 the merge of eight ranges' statistics.  us of a call, and with about 32 ranges of eight tiles or
-// more and up to 1536 workgroups in pass 1 whatever the rounds are: 12345 tokens, three of eight groups in two passes 198 / 210;
+// first tiles and end; in pass 1 the merge of eight ranges' statistics.  us of a call (ranges of pass 0 chosen per launch, too), and with about
+// 32 ranges of eight tiles or more and up to 1536 workgroups in pass 1 whatever the rounds are: 12345 tokens, three of eight groups in two passes 198 / 210;
 // 32 layers of 4270 tokens, 64 rows 112 / 133; 59567 tokens in fp32, 256 rows 328 / 358; 32 layers of five sequences of 1379 to 3768
 // tokens, d = 64 85 / 107.  In a long launch that memory bounds few long walks lose (eight sequences of 7138 to 47085 tokens, 32 rows
 // 248, in one round 266): there only those of up to kFewRounds rounds are cut anew.
@@ -182,7 +182,7 @@ PassCut pass_cut(const chunkkv_problem *p, const ScoreGeom &g, int pass, bool sh
   PassCut c;
   c.slots = score_workgroups_per_cu(p->dtype, p->head_dim, g.nqw, g.wq, pass) * kCUs;
   // Long launches: two rounds or more, and where memory is not what bounds them (65536 tokens, 8 layers, 256 rows with log-sum-exps in 3 whole
-  // rounds 498 us a call, in 6.6 518).
+  // rounds 482 us a call, in 6.6 499).
   c.rounds = short_launch || g.wq * g.nqw >= 4 ? kTargetWorkgroups / c.slots : kFewRounds;
   c.least_rounds = short_launch ? -3 : 2;
   c.half = c.slots == kCUs ? 1.0 : kHalfRound[f32];

@@ -18,6 +18,7 @@ KIND = {ckv.F32: torch.float32, ckv.BF16: torch.bfloat16, ckv.F16: torch.float16
     ([513], 16, 2, 2, 16, 64, 5, ckv.F32),
     ([6000], 8, 4, 4, 32, 128, 6, ckv.F32),
     ([3000, 700, 65, 1900, 5000], 8, 4, 7, 32, 64, 11, ckv.BF16),
+    ([700, 130, 2500] * 6, 6, 2, 2, 32, 128, 7, ckv.BF16),   # more sequences than a launch takes
     ([20011], 32, 16, 1, 32, 64, 33, ckv.BF16),              # sets of layers
     ([9000, 400], 40, 8, 8, 64, 128, 3, ckv.F16),            # 512 rows, more layers than a launch takes
     ([70001], 2, 32, 1, 16, 128, 13, ckv.BF16),              # more ranges than the second pass merges
