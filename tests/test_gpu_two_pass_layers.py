@@ -21,7 +21,8 @@ KIND = {ckv.F32: torch.float32, ckv.BF16: torch.bfloat16, ckv.F16: torch.float16
     ([700, 130, 2500] * 6, 6, 2, 2, 32, 128, 7, ckv.BF16),   # more sequences than a launch takes
     ([20011], 32, 16, 1, 32, 64, 33, ckv.BF16),              # sets of layers
     ([9000, 400], 40, 8, 8, 64, 128, 3, ckv.F16),            # 512 rows, more layers than a launch takes
-    ([70001], 2, 32, 1, 16, 128, 13, ckv.BF16),              # more ranges than the second pass merges
+    ([70001], 2, 32, 1, 16, 128, 13, ckv.BF16),              # the kernel merges in the layer call, too
+    ([140001], 2, 8, 1, 16, 128, 13, ckv.BF16),              # 122 ranges, more than the second pass merges
 ])
 def test_layers_equal_stack(lens, layers, hkv, g, window, d, chunk, dtype):
     gen = torch.Generator(device=DEV).manual_seed(sum(lens) + layers)
